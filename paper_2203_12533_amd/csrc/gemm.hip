@@ -18,7 +18,7 @@
 // contiguous range of tiles, and within the range tiles are walked in groups of 8 tile-rows so that
 // concurrently resident workgroups share A and B panels through that XCD's L2.
 //
-// fp32 path: a plain LDS-tiled ALU kernel; it serves the small fp32 configuration only.
+// fp32 problems go to gemm_f32.hip.
 #include "common.hpp"
 #include <algorithm>
 #include <cmath>
@@ -254,66 +254,6 @@ static hipError_t launch_bf16_tile(hipStream_t s, const GemmBf16Params& p, bool 
 }
 
 // ======================================================================================================
-// fp32 ALU kernel: 64x64 tile, 256 threads, 4x4 outputs per thread, BK = 16.  Any M, N, K.
-// ======================================================================================================
-struct GemmF32Params {
-  const float* A;
-  const float* B;
-  int64_t M, N, K;
-  int64_t sam, sak, sbn, sbk;   // element strides: A(m,k) = A[m*sam + k*sak], B(k,n) = B[n*sbn + k*sbk]
-  EpiParams epi;
-};
-
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Params p) {
-  __shared__ float As[16][64 + 4];
-  __shared__ float Bs[16][64 + 4];
-  const int64_t m0 = (int64_t)blockIdx.y * 64, n0 = (int64_t)blockIdx.x * 64;
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  float acc[4][4] = {};
-  for (int64_t k0 = 0; k0 < p.K; k0 += 16) {
-    for (int idx = threadIdx.x; idx < 16 * 64; idx += 256) {
-      // consecutive threads walk the dimension that is contiguous in memory
-      int r, k;
-      if (p.sak == 1) { k = idx & 15; r = idx >> 4; } else { r = idx & 63; k = idx >> 6; }
-      const int64_t m = m0 + r, kk = k0 + k;
-      As[k][r] = (m < p.M && kk < p.K) ? p.A[m * p.sam + kk * p.sak] : 0.f;
-    }
-    for (int idx = threadIdx.x; idx < 16 * 64; idx += 256) {
-      int r, k;
-      if (p.sbk == 1) { k = idx & 15; r = idx >> 4; } else { r = idx & 63; k = idx >> 6; }
-      const int64_t n = n0 + r, kk = k0 + k;
-      Bs[k][r] = (n < p.N && kk < p.K) ? p.B[n * p.sbn + kk * p.sbk] : 0.f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      const float4 a = *reinterpret_cast<const float4*>(&As[k][ty * 4]);
-      const float4 b = *reinterpret_cast<const float4*>(&Bs[k][tx * 4]);
-      const float av[4] = {a.x, a.y, a.z, a.w}, bv[4] = {b.x, b.y, b.z, b.w};
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] += av[i] * bv[j];
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int64_t m = m0 + ty * 4 + i;
-    if (m >= p.M) continue;
-    const int64_t n = n0 + tx * 4;
-    const bool vec_ok = n + 3 < p.N && (p.epi.ldc & 3) == 0;
-    if (vec_ok) {
-      epilogue4<false>(p.epi, m, n, acc[i][0], acc[i][1], acc[i][2], acc[i][3]);
-    } else {
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        if (n + j < p.N) epilogue1<false>(p.epi, m, n + j, acc[i][j]);
-    }
-  }
-}
-
-// ======================================================================================================
 // host side
 // ======================================================================================================
 namespace {
@@ -538,17 +478,8 @@ static hipError_t launch_gemm_impl(hipStream_t s, const GemmArgs& a) {
     return gemm_xent_fusable(a) ? launch_gemm_ring(s, bf16_params_of(a, 256), false, true) : hipErrorInvalidValue;
 
   if (a.dtype == kF32) {
-    GemmF32Params p;
-    p.A = (const float*)a.A;
-    p.B = (const float*)a.B;
-    p.M = a.M; p.N = a.N; p.K = a.K;
-    p.sam = a.a_kmajor ? 1 : a.lda; p.sak = a.a_kmajor ? a.lda : 1;
-    p.sbn = a.b_kmajor ? 1 : a.ldb; p.sbk = a.b_kmajor ? a.ldb : 1;
-    p.epi = epi_of(a);
-    dim3 grid((unsigned)((a.N + 63) / 64), (unsigned)((a.M + 63) / 64));
-    if (grid.y > 65535) return hipErrorInvalidValue;
-    gemm_f32_kernel<<<grid, 256, 0, s>>>(p);
-    return hipGetLastError();
+    if ((a.M + 63) / 64 > 65535) return hipErrorInvalidValue;
+    return launch_gemm_f32(s, a, epi_of(a));
   }
   // Full tiles whose last round would occupy at most half the chip (384 tiles: a round of 256, then 128), A
   // row-major: the columns of that last round become a problem of their own, which takes the 128 x 256 tiles below.

@@ -434,6 +434,8 @@ __device__ __forceinline__ void gemm_epilogue_staged(bf16* smem, Acc& acc, const
   }
 }
 
+// fp32 operands (gemm_f32.hip); arguments already checked.
+hipError_t launch_gemm_f32(hipStream_t s, const GemmArgs& a, const EpiParams& epi);
 // Ring-buffered variant for full tiles (gemm_ring.hip).
 bool gemm_ring_supported(int64_t M, int64_t N, int64_t K);
 hipError_t launch_gemm_ring(hipStream_t s, const GemmBf16Params& p, bool a_kmajor, bool b_kmajor);

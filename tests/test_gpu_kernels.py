@@ -114,6 +114,25 @@ def test_gemm_fused_epilogues(ctx, orc, bf16, shape):
     assert_close(host(du), orc.gelu_bwd(prev, nobias), tol)
 
 
+# tiles of 32 x 32 and (from 256 tiles of 64 x 64 on) 64 x 64; fewer rows than a fragment piece, one past a tile, k not a
+# multiple of the 16-deep step and shorter than the four slices of it; rows of odd length (no alignment anywhere)
+@pytest.mark.parametrize("a_k,b_k", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("M,N,K", [(1, 3, 5), (33, 65, 16), (31, 32, 130), (1025, 1021, 67), (3, 20000, 33)])
+def test_gemm_fp32_edges_in_every_layout(ctx, M, N, K, a_k, b_k):
+    a, b = _rand(21, (K, M + 1) if a_k else (M, K + 3)), _rand(22, (K, N + 1) if b_k else (N, K + 5))
+    ad, bd, out = dev_f32(a), dev_f32(b), torch.full((M, N + 3), 7.0, device="cuda")
+    ctx.gemm(dtype=pwb.PW_F32, a_kmajor=a_k, b_kmajor=b_k, M=M, N=N, K=K, lda=a.shape[1], ldb=b.shape[1], ldc=N + 3,
+             epilogue=pwb.PW_EPI_STORE, out_dtype=pwb.PW_F32, accumulate=0, A=ptr(ad), B=ptr(bd), C=ptr(out))
+    ctx.synchronize()
+    a, b = a.astype(np.float64), b.astype(np.float64)
+    ref = (a[:, :M].T if a_k else a[:, :K]) @ (b[:, :N] if b_k else b[:, :K].T)
+    got = host(out)
+    # fp32 sums of at most K products: K * 2^-24 relative to the sum of magnitudes bounds any order
+    bound = (K + 4) * 2.0 ** -24 * ((np.abs(a[:, :M].T) if a_k else np.abs(a[:, :K])) @ (np.abs(b[:, :N]) if b_k else np.abs(b[:, :K].T)))
+    assert (np.abs(got[:, :N] - ref) <= bound).all()
+    assert (got[:, N:] == 7.0).all()
+
+
 @pytest.mark.parametrize("bf16", [False, True])
 def test_gemm_pair_small_problems_and_rejection(ctx, orc, bf16):
     """Two problems that do not qualify for a shared launch still give both results; one bad argument set
