@@ -486,6 +486,49 @@ def test_general_attention_rejects_bad_arguments(ctx):
 
 # ---- softmax cross-entropy ----------------------------------------------------------------------------
 
+# one tile of 16 positions and one to either side, several tiles per wave; what a query may not see (or a key is not
+# seen by) must not matter even where it is not a number
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("T", [2, 15, 16, 17, 83])
+def test_fp32_causal_attention_ignores_what_is_masked(ctx, T, hd):
+    B, H, d = 2, 2, 2 * hd
+    qkv, dout = _rand(41, (B, T, 3 * d)), _rand(42, (B, T, d))
+
+    def run(qkv, dout):
+        qd, gd = dev_f32(qkv), dev_f32(dout)
+        o, g, lse, delta = torch.empty_like(gd), torch.empty_like(qd), torch.empty((B, H, T), device="cuda"), torch.empty((B, H, T), device="cuda")
+        ctx.op("attention_fwd", pwb.PW_F32, ptr(qd), ptr(o), ptr(lse), B, T, H, hd)
+        ctx.op("attention_bwd", pwb.PW_F32, ptr(qd), ptr(o), ptr(gd), ptr(lse), ptr(delta), ptr(g), B, T, H, hd)
+        ctx.synchronize()
+        return host(o), host(g)
+
+    q, k, v = (np.moveaxis(t.reshape(B, T, H, hd), 2, 1).astype(np.float64) for t in np.split(qkv, 3, axis=2))
+    go = np.moveaxis(dout.reshape(B, T, H, hd), 2, 1).astype(np.float64)
+    s = np.where(np.tril(np.ones((T, T), bool)), q @ k.swapaxes(2, 3) / np.sqrt(hd), -np.inf)
+    p = np.exp(s - s.max(-1, keepdims=True))
+    p /= p.sum(-1, keepdims=True)
+    ro = p @ v
+    ds = p * (go @ v.swapaxes(2, 3) - (go * ro).sum(-1, keepdims=True)) / np.sqrt(hd)
+    flat = lambda t: np.moveaxis(t, 1, 2).reshape(B, T, d)  # noqa: E731
+    ro, rq, rk, rv = flat(ro), flat(ds @ k), flat(ds.swapaxes(2, 3) @ q), flat(p.swapaxes(2, 3) @ go)
+    o, g = run(qkv, dout)
+    for got, ref in ((o, ro), (g[..., :d], rq), (g[..., d:2 * d], rk), (g[..., 2 * d:], rv)):
+        assert_close(got, ref, 1e-5)
+    bad = qkv.copy()
+    bad[:, -1, d:] = np.nan                     # the last key and value: no earlier query sees them
+    bad[:, -1, 2 * d:] = np.inf
+    o, g = run(bad, dout)
+    assert_close(o[:, :-1], ro[:, :-1], 1e-5)
+    if T > 2:
+        assert_close(g[:, 1:-1, :d], rq[:, 1:-1], 1e-5)
+    bad, bad_g = qkv.copy(), dout.copy()
+    bad[:, 0, :d] = np.nan                      # the first query and its output gradient: no later key is seen by it
+    bad_g[:, 0] = np.inf
+    o, g = run(bad, bad_g)
+    assert_close(g[:, 1:, d:2 * d], rk[:, 1:], 1e-5)
+    assert_close(g[:, 1:, 2 * d:], rv[:, 1:], 1e-5)
+
+
 @pytest.mark.parametrize("bf16", [False, True])
 @pytest.mark.parametrize("B,T,V", [(3, 5, 1024), (2, 7, 4096), (1, 3, 32768), (2, 2, 8)])
 def test_softmax_xent(ctx, orc, B, T, V, bf16):
