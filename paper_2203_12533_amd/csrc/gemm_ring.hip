@@ -33,9 +33,7 @@ constexpr int kRBK = 64;            // k per stage
 constexpr int kRStages = 2;
 constexpr int kRingHM = 2;          // 16-row blocks of A per unit of the main loop (see ring_tile); 4 spills registers
 constexpr int kROperand = kRT * kRBK;            // elements per full operand tile (32 KiB)
-// Elements per stage: an A tile of TM rows (256, or 128 for problems that would otherwise leave half the chip
-// idle) and a B tile of 256 rows.
-template <int TM> constexpr int ring_stage() { return (TM + kRT) * kRBK; }
+constexpr int kRStage = 2 * kROperand;           // elements per stage: an A tile and a B tile
 
 typedef __attribute__((address_space(3))) void* lds_ptr;
 typedef const __attribute__((address_space(1))) void* gbl_ptr;
@@ -93,26 +91,23 @@ __device__ __forceinline__ bf16x8 read_fragment(const bf16* lds_tile, int frag_r
   }
 }
 
-// One TM x 256 output tile of problem p (TM = 256, or 128 for problems of few tiles); pid: index of the tile's
-// workgroup among the problem's own.  Waves form a 2 x NW grid: NW = 4 -> 8 waves with (TM / 2) x 64 wave tiles.  The products are 16 x 16 x 32 MFMAs: on
+// One 256 x 256 output tile of problem p; pid: index of the tile's
+// workgroup among the problem's own.  Waves form a 2 x NW grid: NW = 4 -> 8 waves with 128 x 64 wave tiles.  The products are 16 x 16 x 32 MFMAs: on
 // operands with random mantissas the chip runs into its board power limit, and per flop that shape draws less
 // than the 32 x 32 x 16 one (same loop, same LDS bytes: 2.06 against 1.82 PFLOP/s sustained).
-template <bool A_KMAJOR, bool B_KMAJOR, int NW, int TM, int EPISET = kEpiSetGeneral>
+template <bool A_KMAJOR, bool B_KMAJOR, int NW, int EPISET = kEpiSetGeneral>
 __device__ __forceinline__ void ring_tile(const GemmBf16Params& p, int pid, bf16* smem) {
-  static_assert(TM == kRT || (TM == 128 && !A_KMAJOR), "the half-height tile exists for row-major A only");
-  constexpr int kRStage = ring_stage<TM>();
-  constexpr int kAOperand = TM * kRBK;                // elements of the A tile
   int tm, tn;
   tile_of_block(pid, p.tiles_m * p.tiles_n, p.tiles_m, p.tiles_n, tm, tn);
-  const int64_t m0 = (int64_t)tm * TM, n0 = (int64_t)tn * kRT;
+  const int64_t m0 = (int64_t)tm * kRT, n0 = (int64_t)tn * kRT;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int wm = wave / NW, wn = wave % NW;
   constexpr int kWaveN = kRT / NW;                    // columns of a wave tile
-  constexpr int kWaveM = TM / 2;                      // rows of a wave tile
+  constexpr int kWaveM = kRT / 2;                     // rows of a wave tile
   constexpr int FM = kWaveM / 16, FN = kWaveN / 16;   // 16 x 16 accumulator blocks of the wave tile
   constexpr int HM = kRingHM;                         // a unit of work: HM row blocks x FN column blocks, one 32-deep k-step
   constexpr int UPS = FM / HM;                        // units per k-step
-  constexpr int PER_A = TM / 8 / (2 * NW);            // direct-load instructions (1 KiB each) per A tile and wave
+  constexpr int PER_A = kRT / 8 / (2 * NW);           // direct-load instructions (1 KiB each) per A tile and wave
   constexpr int PER_B = kRT / 8 / (2 * NW);           // ... per B tile and wave
   constexpr int PER = PER_A + PER_B;
   static_assert(HM * FN >= PER, "one direct load at most goes out behind each MFMA of the last unit");
@@ -151,7 +146,7 @@ __device__ __forceinline__ void ring_tile(const GemmBf16Params& p, int pid, bf16
   auto issue_idx = [&](int kt, int idx) {
     const uint32_t stage = smem_off + (uint32_t)(kt % kRStages) * (kRStage * 2);
     if (idx < PER_A) issue_one<A_KMAJOR, PER_A>(p.A, p.lda, m0, (int64_t)kt * kRBK, stage, wave_s, lane, idx);
-    else issue_one<B_KMAJOR, PER_B>(p.B, p.ldb, n0, (int64_t)kt * kRBK, stage + kAOperand * 2, wave_s, lane, idx - PER_A);
+    else issue_one<B_KMAJOR, PER_B>(p.B, p.ldb, n0, (int64_t)kt * kRBK, stage + kROperand * 2, wave_s, lane, idx - PER_A);
   };
   // A unit u of a k-tile: k-step u / UPS (32 deep), row blocks HM (u % UPS) .. + HM - 1 of the wave tile.
   auto load_a = [&](int stage, int u, bf16x8* af) {
@@ -160,7 +155,7 @@ __device__ __forceinline__ void ring_tile(const GemmBf16Params& p, int pid, bf16
     for (int i = 0; i < HM; ++i) af[i] = read_fragment<A_KMAJOR>(a_tile, wm * kWaveM + ((u % UPS) * HM + i) * 16, u / UPS, lane);
   };
   auto load_b = [&](int stage, int ks, bf16x8* bfr) {
-    const bf16* b_tile = smem + stage * kRStage + kAOperand;
+    const bf16* b_tile = smem + stage * kRStage + kROperand;
 #pragma unroll
     for (int j = 0; j < FN; ++j) bfr[j] = read_fragment<B_KMAJOR>(b_tile, wn * kWaveN + j * 16, ks, lane);
   };
@@ -266,10 +261,10 @@ __device__ __forceinline__ void ring_tile(const GemmBf16Params& p, int pid, bf16
   gemm_epilogue_staged<kWaveM / 32, kWaveN / 32, false, EPISET>(smem, acc, p, m0 + wm * kWaveM, n0 + wn * kWaveN, wave, lane);
 }
 
-template <bool A_KMAJOR, bool B_KMAJOR, int NW, int TM, int EPISET = kEpiSetGeneral>
+template <bool A_KMAJOR, bool B_KMAJOR, int NW, int EPISET = kEpiSetGeneral>
 __global__ __launch_bounds__(2 * NW * 64) void gemm_ring_kernel(GemmBf16Params p) {
   extern __shared__ __attribute__((aligned(16))) bf16 smem[];
-  ring_tile<A_KMAJOR, B_KMAJOR, NW, TM, EPISET>(p, blockIdx.x, smem);
+  ring_tile<A_KMAJOR, B_KMAJOR, NW, EPISET>(p, blockIdx.x, smem);
 }
 
 // Up to three independent problems of the same operand layout in one launch: workgroups [first[i], first[i+1])
@@ -280,12 +275,11 @@ __global__ __launch_bounds__(2 * NW * 64) void gemm_ring_group_kernel(GemmRingGr
   const int bid = (int)blockIdx.x;
   const int which = bid < g.first[1] ? 0 : (bid < g.first[2] ? 1 : 2);
   const GemmBf16Params p = which == 0 ? g.p[0] : (which == 1 ? g.p[1] : g.p[2]);
-  ring_tile<A_KMAJOR, B_KMAJOR, NW, kRT, EPISET>(p, bid - g.first[which], smem);
+  ring_tile<A_KMAJOR, B_KMAJOR, NW, EPISET>(p, bid - g.first[which], smem);
 }
 
-template <int TM> constexpr size_t ring_smem_bytes() { return (size_t)kRStages * ring_stage<TM>() * sizeof(bf16); }
-constexpr size_t kRSmemBytes = ring_smem_bytes<kRT>();   // 128 KiB (96 KiB with the half-height A tile)
-static_assert(ring_smem_bytes<128>() >= 8 * 32 * 68 * 4, "epilogue staging must fit");
+constexpr size_t kRSmemBytes = (size_t)kRStages * kRStage * sizeof(bf16);   // 128 KiB
+static_assert(kRSmemBytes >= 8 * 32 * 68 * 4, "epilogue staging must fit");
 
 // Waves along n.  4 (8 waves, 128 x 64 wave tiles) is what runs; 2 (4 waves, 128 x 128 wave tiles, accumulators in
 // AGPRs, a third fewer LDS fragment reads per MFMA) measured the same within noise with 32 x 32 MFMA blocks on every
@@ -296,24 +290,19 @@ template <bool AK, bool BK_, int NW>
 hipError_t prepare_ring_variant() {
   static bool attr_done = false;
   if (attr_done) return hipSuccess;
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_ring_kernel<AK, BK_, NW, kRT>),
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_ring_kernel<AK, BK_, NW>),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRSmemBytes);
   if (e == hipSuccess)
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_ring_group_kernel<AK, BK_, NW>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRSmemBytes);
-  if constexpr (!AK) {
-    if (e == hipSuccess)
-      e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_ring_kernel<AK, BK_, NW, 128>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)ring_smem_bytes<128>());
-  }
   if constexpr (!AK && BK_) {   // the forward layout also carries the LM head's loss epilogues
     if (e == hipSuccess)
-      e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_ring_kernel<AK, BK_, NW, kRT, kEpiSetXent>),
+      e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_ring_kernel<AK, BK_, NW, kEpiSetXent>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRSmemBytes);
   }
   if constexpr (AK && BK_) {    // the weight-gradient layout also carries the Adam epilogue
     if (e == hipSuccess)
-      e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_ring_kernel<AK, BK_, NW, kRT, kEpiSetAdam>),
+      e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_ring_kernel<AK, BK_, NW, kEpiSetAdam>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRSmemBytes);
     if (e == hipSuccess)
       e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_ring_group_kernel<AK, BK_, NW, kEpiSetAdam>),
@@ -341,7 +330,7 @@ hipError_t launch_ring_variant(hipStream_t s, const GemmBf16Params* p, int n) {
   if (set == kEpiSetXent) {
     if constexpr (!AK && BK_) {
       if (n != 1) return hipErrorInvalidValue;
-      gemm_ring_kernel<AK, BK_, NW, kRT, kEpiSetXent><<<p[0].tiles_m * p[0].tiles_n, 2 * NW * 64, kRSmemBytes, s>>>(p[0]);
+      gemm_ring_kernel<AK, BK_, NW, kEpiSetXent><<<p[0].tiles_m * p[0].tiles_n, 2 * NW * 64, kRSmemBytes, s>>>(p[0]);
       return hipGetLastError();
     } else {
       return hipErrorInvalidValue;
@@ -353,11 +342,11 @@ hipError_t launch_ring_variant(hipStream_t s, const GemmBf16Params* p, int n) {
   if (n == 1) {
     if constexpr (AK && BK_) {
       if (set == kEpiSetAdam) {
-        gemm_ring_kernel<AK, BK_, NW, kRT, kEpiSetAdam><<<p[0].tiles_m * p[0].tiles_n, 2 * NW * 64, kRSmemBytes, s>>>(p[0]);
+        gemm_ring_kernel<AK, BK_, NW, kEpiSetAdam><<<p[0].tiles_m * p[0].tiles_n, 2 * NW * 64, kRSmemBytes, s>>>(p[0]);
         return hipGetLastError();
       }
     }
-    gemm_ring_kernel<AK, BK_, NW, kRT><<<p[0].tiles_m * p[0].tiles_n, 2 * NW * 64, kRSmemBytes, s>>>(p[0]);
+    gemm_ring_kernel<AK, BK_, NW><<<p[0].tiles_m * p[0].tiles_n, 2 * NW * 64, kRSmemBytes, s>>>(p[0]);
   } else {
     GemmRingGroup g{};
     int total = 0;
@@ -380,14 +369,6 @@ hipError_t launch_ring_variant(hipStream_t s, const GemmBf16Params* p, int n) {
   return hipGetLastError();
 }
 
-template <bool BK_, int NW>
-hipError_t launch_ring_half(hipStream_t s, const GemmBf16Params& p) {
-  hipError_t e = prepare_ring_variant<false, BK_, NW>();
-  if (e != hipSuccess) return e;
-  gemm_ring_kernel<false, BK_, NW, 128><<<p.tiles_m * p.tiles_n, 2 * NW * 64, ring_smem_bytes<128>(), s>>>(p);
-  return hipGetLastError();
-}
-
 template <int NW>
 hipError_t launch_ring_nw(hipStream_t s, const GemmBf16Params* p, int n, bool ak, bool bk) {
   if (!ak && !bk) return launch_ring_variant<false, false, NW>(s, p, n);
@@ -404,11 +385,6 @@ hipError_t launch_gemm_ring(hipStream_t s, const GemmBf16Params& p, bool ak, boo
 hipError_t launch_gemm_ring_group(hipStream_t s, const GemmBf16Params* p, int n, bool ak, bool bk) {
   if (n < 1 || n > kRingGroupMax) return hipErrorInvalidValue;
   return launch_ring_nw<kRingNW>(s, p, n, ak, bk);
-}
-
-// 128 x 256 tiles (p.tiles_m counts 128-row tiles), A row-major.
-hipError_t launch_gemm_ring_half(hipStream_t s, const GemmBf16Params& p, bool bk) {
-  return bk ? launch_ring_half<true, kRingNW>(s, p) : launch_ring_half<false, kRingNW>(s, p);
 }
 
 bool gemm_ring_supported(int64_t M, int64_t N, int64_t K) { return M % kRT == 0 && N % kRT == 0 && K % kRBK == 0 && K >= kRBK; }

@@ -47,7 +47,7 @@ def test_forward_gemms_at_cfg3_shape(ctx, orc, name, n_out, k_in):
 
 def test_gemms_of_a_pipeline_stage_micro_batch_at_cfg4_shape(ctx, orc):
     """cfg4's micro-batches of 2048 tokens give the GEMMs that write d_model = 4096 columns only 128 full tiles;
-    they run on 128 x 256 tiles.  FFN2 forward (K = 16384) with the residual epilogue and the FFN1 data gradient
+    they run on 128 x 128 tiles.  FFN2 forward (K = 16384) with the residual epilogue and the FFN1 data gradient
     (both operands k-contiguous) at full shape, sampled rows against the oracle."""
     c4 = I.workload("cfg4")
     n, d, f = c4.n_tokens, c4.d_model, c4.d_ff
@@ -361,7 +361,7 @@ def test_one_layer_step_with_fused_update_and_fused_head_loss(one_layer, fused_u
 def test_one_layer_step_at_cfg5_width_matches_oracle(orc):
     """The wide-layer workload's width end to end against the oracle: one layer with d_model 8192 and 64 heads of 128
     (LayerNorm's block-per-row path, contraction length 8192 in the ring-buffered GEMM, 3072-tile weight gradients,
-    the 128 x 256-tile kernel for the out-projection), 2 x 256 tokens; FFN width and vocabulary are cut (4096, 2048)
+    the 128 x 128-tile kernel for the out-projection), 2 x 256 tokens; FFN width and vocabulary are cut (4096, 2048)
     so that the fp64 oracle's 0.37 G parameters fit the host and its step takes tens of seconds.  Loss and every
     gradient tensor are compared, weights drawn with the workload's own standard deviation."""
     c5 = I.workload("cfg5")

@@ -26,9 +26,7 @@ def _rand(seed, shape, std=1.0):
 # ---- GEMM ---------------------------------------------------------------------------------------------
 
 # (4096, 4096, K): 256 full 256x256 tiles, the ring-buffered kernel, with 1, 2 and 3 k-tiles of 64;
-# (1024, 4096, K): 64 full tiles, which the ring-buffered kernel takes as 128 tiles of 128 x 256;
-# (2048, 12288, K): 384 full tiles = one round of 256 and a last round of 128, whose columns are computed on
-# 128 x 256 tiles by a second launch
+# (1024, 4096, K): 64 full tiles, (2048, 12288, K): 384 - rounds that leave much of the chip idle, on 128 x 128 tiles
 GEMM_SHAPES = [(300, 200, 136), (512, 384, 256), (130, 72, 8), (4096, 4096, 128), (4072, 4088, 200), (4096, 4096, 64),
                (4096, 4096, 192), (1024, 4096, 192), (1024, 4096, 64), (2048, 12288, 128)]
 
@@ -80,7 +78,7 @@ def test_gemm_dgrad_and_wgrad_layouts(ctx, orc, shape, bf16):
     assert_close(host(dx), rdx, 4e-3 if bf16 else 2e-6)
 
 
-# ragged (register-staged kernel), 64 full tiles (ring kernel on 128 x 256 tiles), 256 full tiles (ring kernel)
+# ragged, 64 full tiles (both on the any-shape kernel), 256 full tiles (ring kernel)
 @pytest.mark.parametrize("bf16", [False, True])
 @pytest.mark.parametrize("shape", [(264, 328, 192), (1024, 4096, 128), (4096, 4096, 128), (2048, 12288, 64)])
 def test_gemm_fused_epilogues(ctx, orc, bf16, shape):
@@ -130,6 +128,36 @@ def test_gemm_fp32_edges_in_every_layout(ctx, M, N, K, a_k, b_k):
     # fp32 sums of at most K products: K * 2^-24 relative to the sum of magnitudes bounds any order
     bound = (K + 4) * 2.0 ** -24 * ((np.abs(a[:, :M].T) if a_k else np.abs(a[:, :K])) @ (np.abs(b[:, :N]) if b_k else np.abs(b[:, :K].T)))
     assert (np.abs(got[:, :N] - ref) <= bound).all()
+    assert (got[:, N:] == 7.0).all()
+
+
+# one size per tile shape of the any-shape kernel (64 x 64 and 128 x 64 tiles with k split over waves, 128 x 128 in both
+# loop forms), ragged in every dimension, k from one partial step on; what lies behind the last k of a row is no number, and
+# the last size has rows too far apart for 32-bit offsets
+@pytest.mark.parametrize("a_k,b_k", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("M,N,K,pad", [(8, 8, 8, 8), (1000, 776, 328, 8), (72, 40, 1288, 8), (1160, 1032, 72, 8), (1672, 1800, 200, 8),
+                                       (2312, 2440, 136, 8), (2312, 2440, 2120, 8), (16, 24, 72, 1 << 23)])
+def test_gemm_bf16_any_shape_in_every_layout(ctx, M, N, K, pad, a_k, b_k):
+    if pad > 8 and (a_k or b_k):
+        pytest.skip("72 rows of that length")
+
+    def operand(seed, rows, cols):
+        t = torch.full((rows, cols + pad), float("nan"), dtype=torch.bfloat16, device="cuda")
+        v = I.round_to_bf16(_rand(seed, (rows, cols)))
+        t[:, :cols] = torch.from_numpy(v).cuda().to(torch.bfloat16)
+        return t, v.astype(np.float64)
+
+    a, av = operand(23, K, M) if a_k else operand(23, M, K)
+    b, bv = operand(24, K, N) if b_k else operand(24, N, K)
+    ldc = (N + 7) // 8 * 8 + 8
+    out = torch.full((M, ldc), 7.0, device="cuda")
+    ctx.gemm(dtype=pwb.PW_BF16, a_kmajor=a_k, b_kmajor=b_k, M=M, N=N, K=K, lda=a.shape[1], ldb=b.shape[1], ldc=ldc,
+             epilogue=pwb.PW_EPI_STORE, out_dtype=pwb.PW_F32, accumulate=0, A=ptr(a), B=ptr(b), C=ptr(out))
+    ctx.synchronize()
+    av, bv = av.T if a_k else av, bv if b_k else bv.T
+    got = host(out)
+    # the products are exact in fp32; fp32 sums of K of them, in any order
+    assert (np.abs(got[:, :N] - av @ bv) <= (K + 4) * 2.0 ** -24 * (np.abs(av) @ np.abs(bv))).all()
     assert (got[:, N:] == 7.0).all()
 
 
