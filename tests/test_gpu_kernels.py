@@ -624,6 +624,47 @@ def test_embedding_backward_handles_one_id_everywhere(ctx, orc):
 
 # ---- column sums and optimisers -----------------------------------------------------------------------
 
+# positions that fit an id's row of dwte and that do not (4 columns hold three), more of them than the list of one pass
+# (2048), rows of one to eight pieces per thread, the smallest and a large table
+@pytest.mark.parametrize("B,T,d,V", [(1, 1, 4, 1), (4, 1024, 4, 1), (2, 700, 8, 3), (3, 50, 1028, 40), (2, 300, 2048, 60),
+                                     (1, 40, 4100, 7), (2, 33, 8192, 9), (2, 600, 64, 9000), (1, 1500, 260, 100)])
+def test_embedding_backward_adds_rows_in_order_of_position(ctx, B, T, d, V):
+    tok = I.tokens(7, 5, (B, T + 1), V)
+    dx = _rand(51, (B, T, d))
+    td, xd = dev_i32(tok), dev_f32(dx)
+    dwte, dwpe = torch.full((V, d), 3.0, device="cuda"), torch.full((T, d), 3.0, device="cuda")
+    ctx.op("embedding_bwd", ptr(td), ptr(xd), ptr(dwte), ptr(dwpe), B, T, d, V)
+    ctx.synchronize()
+    want, wpe = np.zeros((V, d), np.float32), np.zeros((T, d), np.float32)
+    for b in range(B):
+        for t in range(T):                     # fp32 additions one after the other: the same bits
+            want[tok[b, t]] += dx[b, t]
+        wpe += dx[b]
+    assert np.array_equal(dwte.cpu().numpy(), want)
+    assert np.array_equal(dwpe.cpu().numpy(), wpe)
+
+
+# rows held in registers in 1, 2, 4 and 8 pieces per thread, one column past each, and rows read twice
+@pytest.mark.parametrize("bf16,V", [(True, 4096), (True, 4104), (True, 8200), (True, 16392), (True, 32776), (False, 2052),
+                                    (False, 4100), (False, 8196), (False, 16388)])
+def test_softmax_xent_at_every_row_length(ctx, orc, bf16, V):
+    B, T = 2, 3
+    z, zv = dev_act(_rand(61, (B * T, V), 2.0), bf16)
+    tok = I.tokens(8, 6, (B, T + 1), V)
+    tok[0, 1], tok[1, 3] = V - 1, 0
+    td, loss, rows = dev_i32(tok), torch.empty(1, device="cuda"), torch.empty(B * T, device="cuda")
+    ctx.op("softmax_xent", DT[bf16], ptr(z), ptr(td), ptr(loss), ptr(rows), B, T, V)
+    ctx.synchronize()
+    tgt = tok[:, 1:].reshape(-1)
+    lse = np.log(np.exp(zv - zv.max(1, keepdims=True)).sum(1)) + zv.max(1)
+    want = lse - zv[np.arange(B * T), tgt]
+    dz = np.exp(zv - lse[:, None])
+    dz[np.arange(B * T), tgt] -= 1.0
+    assert np.abs(host(rows) - want).max() < 1e-5 * np.abs(want).max()
+    assert abs(host(loss)[0] - want.mean()) < 1e-5 * want.mean()
+    assert_close(host(z), dz / (B * T), 4e-3 if bf16 else 1e-5)
+
+
 @pytest.mark.parametrize("bf16", [False, True])
 @pytest.mark.parametrize("rows,cols", [(513, 768), (8, 64), (2048, 8192), (1, 12)])
 def test_colsum(ctx, rows, cols, bf16):
