@@ -3,12 +3,11 @@
 // self-attention over packed [Q|K|V] rows, an encoder's unmasked self-attention and a decoder's attention over
 // the encoder output.
 //
-// Three families:
+// Two families:
 //  * fp32 kernels (here): every product on the fp32 matrix pipe.  They serve the fp32 configuration (small, latency
 //    bound) and whatever the bf16 kernels do not cover.
-//  * bf16 MFMA kernels with direct global->LDS loads for head_dim 128 (attention_dma.hip): every layout and
-//    mask - the ones that matter for throughput.
-//  * bf16 MFMA kernels for packed causal self-attention at head_dim 64 (attention_mfma.hip).
+//  * bf16 MFMA kernels with direct global->LDS loads (attention_dma.hip): every layout and mask, both head widths -
+//    the ones that matter for throughput.
 // Scores and probabilities never touch HBM in any family: the forward keeps a running (max, sum)
 // per row and writes only O and the row log-sum-exp; the backward recomputes P from Q, K and that
 // log-sum-exp.  All reductions run in a fixed order: results are the same bits on every run.
@@ -21,14 +20,12 @@
 
 namespace pw {
 
-hipError_t launch_attention_fwd_mfma(hipStream_t s, const void* qkv, void* o, float* lse, int B, int T, int H, int hd);
-hipError_t launch_attention_bwd_mfma(hipStream_t s, const void* qkv, const void* o, const void* dout, const float* lse,
-                                     float* delta, void* dqkv, int B, int T, int H, int hd);
-bool attention_mfma_supported(int T, int hd);
 bool mha_dma_supported(const MhaArgs& a);
-hipError_t launch_mha_fwd_dma(hipStream_t s, const MhaArgs& a, void* o, void* o_lo, float* lse);
+bool mha_dma_outputs_aligned(const void* dq, int64_t lddq, const void* dk, const void* dv, int64_t lddkv);
+hipError_t launch_mha_fwd_dma(hipStream_t s, const MhaArgs& a, void* o, void* o_lo, float* lse, bool exact);
 hipError_t launch_mha_dq_dkv_dma(hipStream_t s, const MhaArgs& a, const void* o, const void* o_lo, const void* dout,
-                                 const float* lse, float* delta, void* dq, int64_t lddq, void* dk, void* dv, int64_t lddkv);
+                                 const float* lse, float* delta, void* dq, int64_t lddq, void* dk, void* dv, int64_t lddkv,
+                                 bool exact);
 
 // ---- the fp32 matrix-core family -----------------------------------------------------------------------
 // v_mfma_f32_16x16x4_f32: A lane l = row l%16, k-slot l/16; B lane l = column l%16, the same k-slot; D lane l = column
@@ -453,7 +450,7 @@ static bool mha_args_ok(const MhaArgs& a) {
   return true;
 }
 
-// head_dim 128 in bf16 runs the kernels of attention_dma.hip unless PW_ATTN_DMA=0 (A/B switch for measurements).
+// bf16 runs the kernels of attention_dma.hip unless PW_ATTN_DMA=0 (A/B switch for measurements).
 static bool use_dma_kernels() {
   static int v = -1;
   if (v < 0) {
@@ -463,7 +460,8 @@ static bool use_dma_kernels() {
   return v != 0;
 }
 
-// Packed causal self-attention: what the kernels of attention_mfma.hip are written for.
+// Packed causal self-attention: at head_dim 64 the one form whose probabilities are rounded to bf16 for the second
+// products (as at head_dim 128 throughout); the others keep them exact.
 static bool is_packed_causal(const MhaArgs& a) {
   const int64_t d = (int64_t)a.H * a.hd;
   const size_t es = a.dtype == kBF16 ? 2 : 4;
@@ -473,15 +471,10 @@ static bool is_packed_causal(const MhaArgs& a) {
 
 hipError_t launch_mha_fwd(hipStream_t s, const MhaArgs& a, void* o, void* o_lo, float* lse) {
   if (!mha_args_ok(a) || !o || !lse) return hipErrorInvalidValue;
-  if (use_dma_kernels() && mha_dma_supported(a) && !(((uintptr_t)o | (uintptr_t)o_lo) & 15)) return launch_mha_fwd_dma(s, a, o, o_lo, lse);
-  if (a.dtype == kBF16 && is_packed_causal(a) && attention_mfma_supported(a.Tq, a.hd)) {
-    if (o_lo) {   // these kernels keep no remainder: an all-zero one says so to the backward pass
-      const int64_t n = (int64_t)a.B * a.Tq * a.H * a.hd;   // bf16 elements, an even number
-      const hipError_t e = launch_fill_f32(s, (float*)o_lo, n / 2, 0.f);
-      if (e != hipSuccess) return e;
-    }
-    return launch_attention_fwd_mfma(s, a.q, o, lse, a.B, a.Tq, a.H, a.hd);
-  }
+  const bool packed64 = a.dtype == kBF16 && a.hd == 64 && is_packed_causal(a);
+  if (packed64 && (((uintptr_t)a.q | (uintptr_t)o) & 15)) return hipErrorInvalidValue;
+  if (use_dma_kernels() && mha_dma_supported(a) && !(((uintptr_t)o | (uintptr_t)o_lo) & 15))
+    return launch_mha_fwd_dma(s, a, o, o_lo, lse, !packed64);
   if (a.dtype == kF32) return a.hd == 64 ? fwd_f32<float, 64>(s, a, o, o_lo, lse) : fwd_f32<float, 128>(s, a, o, o_lo, lse);
   return a.hd == 64 ? fwd_f32<bf16, 64>(s, a, o, o_lo, lse) : fwd_f32<bf16, 128>(s, a, o, o_lo, lse);
 }
@@ -491,13 +484,13 @@ hipError_t launch_mha_bwd(hipStream_t s, const MhaArgs& a, const void* o, const 
   if (!mha_args_ok(a) || !o || !dout || !lse || !delta || !dq || !dk || !dv) return hipErrorInvalidValue;
   const int64_t d = (int64_t)a.H * a.hd;
   if (lddq < d || lddkv < d) return hipErrorInvalidValue;
-  if (use_dma_kernels() && mha_dma_supported(a) && !(((uintptr_t)o | (uintptr_t)o_lo | (uintptr_t)dout) & 15)) {
-    return launch_mha_dq_dkv_dma(s, a, o, o_lo, dout, lse, delta, dq, lddq, dk, dv, lddkv);   // (delta comes from the dQ kernel)
-  }
   const size_t es = a.dtype == kBF16 ? 2 : 4;
   const bool packed_out = lddq == 3 * d && lddkv == 3 * d && (char*)dk == (char*)dq + d * es && (char*)dv == (char*)dq + 2 * d * es;
-  if (a.dtype == kBF16 && is_packed_causal(a) && packed_out && attention_mfma_supported(a.Tq, a.hd))
-    return launch_attention_bwd_mfma(s, a.q, o, dout, lse, delta, dq, a.B, a.Tq, a.H, a.hd);   // (its forward left o_lo zero)
+  const bool packed64 = a.dtype == kBF16 && a.hd == 64 && is_packed_causal(a) && packed_out;
+  if (packed64 && (((uintptr_t)a.q | (uintptr_t)o | (uintptr_t)dout | (uintptr_t)dq) & 15)) return hipErrorInvalidValue;
+  if (use_dma_kernels() && mha_dma_supported(a) && !(((uintptr_t)o | (uintptr_t)o_lo | (uintptr_t)dout) & 15) &&
+      (a.hd == 128 || mha_dma_outputs_aligned(dq, lddq, dk, dv, lddkv)))
+    return launch_mha_dq_dkv_dma(s, a, o, o_lo, dout, lse, delta, dq, lddq, dk, dv, lddkv, !packed64);
   if (a.dtype == kF32)
     return a.hd == 64 ? bwd_f32<float, 64>(s, a, o, o_lo, dout, lse, delta, dq, lddq, dk, dv, lddkv)
                       : bwd_f32<float, 128>(s, a, o, o_lo, dout, lse, delta, dq, lddq, dk, dv, lddkv);

@@ -1,4 +1,4 @@
-// Helpers shared by the MFMA attention kernels (register-layout bookkeeping; see attention_mfma.hip).
+// Helpers shared by the attention kernels (register-layout bookkeeping; see attention_dma.hip).
 #pragma once
 #include "common.hpp"
 

@@ -1,10 +1,15 @@
-// bf16 MFMA attention for head_dim 128 with direct global->LDS loads and transposing LDS reads.
+// bf16 MFMA attention (head_dim 64 and 128) with direct global->LDS loads and transposing LDS reads.
 //
-// Same register-layout scheme as attention_mfma.hip (softmax row on the lane; first product's A rows read
-// permuted so that P / dS feed the second product from the accumulator registers).  What changes is how
-// operands travel:
-//  * every tile (K, V, or Q, dO) is brought into LDS once, in its natural [row][128] layout, by
-//    global_load_lds_dwordx4 (each wave instruction deposits 4 rows = 1 KiB; no staging registers, no LDS
+// Register layout of v_mfma_f32_32x32x16_bf16 (D = A.B): A lane l supplies row l%32, k-slots 8 (l/32) .. +7; B lane l
+// column l%32, the same k-slots; D lane l holds column l%32, register r row 8 (r/4) + 4 (l/32) + r%4.  The softmax row sits
+// on the D column, i.e. on the lane (forward, dQ: S^T = K . Q^T; dK/dV: S = Q . K^T), so row statistics are one value per
+// lane; the A tile of the first product is read with permuted rows, perm = [0-3, 8-11, 4-7, 12-15] within every 16, so that
+// register r of half h stands for tile row 16 (r/8) + 8 h + r%8 and P (or dS) is the second product's B operand as it is.
+// No atomics: dQ is summed by the block that owns the queries, dK/dV by the block that owns the keys, S recomputed in both.
+//
+// How operands travel:
+//  * every tile (K, V, or Q, dO) is brought into LDS once, in its natural [row][head_dim] layout, by
+//    global_load_lds_dwordx4 (each wave instruction deposits 1 KiB; no staging registers, no LDS
 //    store instructions), double-buffered so the next tile is in flight while one is consumed;
 //  * the second product needs the tile as [feature][row]; instead of keeping a transposed copy it is read
 //    with ds_read_b64_tr_b16 (lane L of each 16-lane group points at [k0 + L/4][c0 + 4*(L%4)], lane i
@@ -12,7 +17,13 @@
 // LDS swizzle, one rule for both access patterns: chunk c (8 features = 16 bytes) of row r sits at
 // position c ^ (((r & 3) << 2) | ((r >> 2) & 3)).  16 consecutive (or permuted-within-16) rows of one chunk
 // then hit 16 distinct 16-byte bank groups, and the 4 rows touched by one transposing read fall into 4
-// different 64-byte windows.
+// different 64-byte windows.  At head_dim 64 a row is half of the 256 bytes all banks hold and its parity picks the half:
+// c ^ ((((r >> 1) & 1) << 2) | ((r >> 2) & 3)) does the same.
+// SPLIT (head_dim 64, all but packed causal self-attention): probabilities and dS enter the second products as two bf16
+// values each, what the first one's rounding left over in the second, i.e. as exactly as in fp32 - these calls have always
+// been computed in fp32.  Measured (us, forward and backward): 4 x 333 queries over 520 keys, 8 heads: 116 on the fp32
+// matrix pipe -> 53; 2 x 2014 over 1092, 9 heads: 189.  Packed causal, 4 x 1000, 12 heads: 131 with tiles staged through
+// registers and a transposed copy in LDS -> 85.
 // Rows past the end of a sequence are fetched from its last valid row (always in bounds); every use of such
 // a row is masked (causality, or the explicit key-index mask of the unmasked variant) or multiplied by an exact
 // zero (P = exp2(-inf)).
@@ -29,9 +40,7 @@ namespace pw {
 
 namespace {
 
-constexpr int HD = 128;
 constexpr int kNT = 256;                 // 4 waves
-constexpr int kRowBytes = HD * 2;        // 256
 typedef __attribute__((address_space(3))) void* lds_ptr;
 typedef short short4v __attribute__((ext_vector_type(4)));
 
@@ -42,7 +51,9 @@ struct MhaDev {
   int Tq, Tk, H;
 };
 
-__device__ __forceinline__ int swz(int r) { return ((r & 3) << 2) | ((r >> 2) & 3); }
+template <int HD> __device__ __forceinline__ int swz(int r) {
+  return HD == 128 ? ((r & 3) << 2) | ((r >> 2) & 3) : (((r >> 1) & 1) << 2) | ((r >> 2) & 3);
+}
 
 __device__ __forceinline__ void dma16(const bf16* g, uint32_t lds_off) {
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(g), "s"(lds_off) : "memory", "m0");
@@ -58,28 +69,29 @@ __device__ __forceinline__ void dma16_s(const bf16* base, uint32_t voff, uint32_
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(voff), "s"(base), "s"(lds_off) : "memory", "m0");
 }
 
-// Direct loads of a ROWS x 128 tile, ROWS/16 instructions of 1 KiB per wave (4 waves).  Instruction j of wave w
-// covers tile rows 4 (w ROWS/16 + j) .. +3; lane l fetches chunk (l%16) ^ swz(row) of row l/16 of those.
+// Direct loads of a ROWS x HD tile, instructions of 1 KiB (512 / HD rows), ROWS * HD / 2048 per wave (4 waves).  Lane l
+// fetches chunk (l % (HD/8)) ^ swz<HD>(row) of row l / (HD/8) of an instruction's rows.
 // TileOffsets holds this lane's byte offsets inside a tile whose first row is row 0 (they do not depend on the
 // tile), so a tile that lies fully inside the sequence costs no vector arithmetic: base + rows*ld is scalar.
-template <int ROWS>
+template <int HD> constexpr int kRowsPerInstr = 512 / HD;
+template <int ROWS, int HD>
 struct TileOffsets {
-  static constexpr int kPerWave = ROWS / 16;
+  static constexpr int kPerWave = ROWS * HD / 2048;
   uint32_t off[kPerWave];
   __device__ __forceinline__ void init(int64_t ld, int wave, int lane) {
 #pragma unroll
     for (int j = 0; j < kPerWave; ++j) {
-      const int r = (wave * kPerWave + j) * 4 + (lane >> 4);
-      off[j] = (uint32_t)((r * ld + (((lane & 15) ^ swz(r)) << 3)) * 2);
+      const int r = (wave * kPerWave + j) * kRowsPerInstr<HD> + lane / (HD / 8);
+      off[j] = (uint32_t)((r * ld + (((lane % (HD / 8)) ^ swz<HD>(r)) << 3)) * 2);
     }
   }
 };
 // src: element (row 0 of the sequence, feature 0); tile rows row0 .. row0+ROWS-1; rows past `last` are fetched
 // from row `last` (the slow path, only for the one tile that straddles the end of the sequence).
-template <int ROWS>
+template <int ROWS, int HD>
 __device__ __forceinline__ void issue_tile(const bf16* __restrict__ src, int64_t ld, int row0, int last,
-                                           const TileOffsets<ROWS>& to, uint32_t lds_off, int wave, int lane) {
-  constexpr int kPerWave = ROWS / 16;
+                                           const TileOffsets<ROWS, HD>& to, uint32_t lds_off, int wave, int lane) {
+  constexpr int kPerWave = TileOffsets<ROWS, HD>::kPerWave;
   if (row0 + ROWS - 1 <= last) {
     const bf16* base = src + (int64_t)row0 * ld;
 #pragma unroll
@@ -88,8 +100,8 @@ __device__ __forceinline__ void issue_tile(const bf16* __restrict__ src, int64_t
 #pragma unroll
     for (int j = 0; j < kPerWave; ++j) {
       const int instr = wave * kPerWave + j;
-      const int r = instr * 4 + (lane >> 4);
-      const int c = (lane & 15) ^ swz(r);
+      const int r = instr * kRowsPerInstr<HD> + lane / (HD / 8);
+      const int c = (lane % (HD / 8)) ^ swz<HD>(r);
       const int row = min(row0 + r, last);
       dma16(src + (int64_t)row * ld + c * 8, lds_off + instr * 1024);
     }
@@ -99,11 +111,12 @@ __device__ __forceinline__ void issue_tile(const bf16* __restrict__ src, int64_t
 // 32x32 block of a first product: A rows (permuted) from a swizzled natural LDS tile, B from register fragments.
 // The A fragments are fetched kDepth MFMAs ahead of their use (left alone the compiler fetches each one right
 // before the MFMA that needs it, and every MFMA of the chain then waits out a full LDS round trip).
+template <int HD>
 __device__ __forceinline__ f32x16 first_product(const bf16* __restrict__ tile, int row_base, const bf16x8* bfrag) {
   constexpr int kDepth = 3, KK = HD / 16;   // 2 and 4 measured the same
   const int lane = threadIdx.x & 63;
   const int row = row_base + perm_row(lane & 31);
-  const int t = (lane >> 5) ^ swz(row);                 // chunk (2 kk + half) ^ swz = (2 kk) ^ t
+  const int t = (lane >> 5) ^ swz<HD>(row);                 // chunk (2 kk + half) ^ swz = (2 kk) ^ t
   const bf16* a = tile + row * HD;
   f32x16 acc;
 #pragma unroll
@@ -121,8 +134,29 @@ __device__ __forceinline__ f32x16 first_product(const bf16* __restrict__ tile, i
   return acc;
 }
 
+// The second operand of a second product: 8 probabilities (or dS) per lane in bf16, and - SPLIT - what their rounding left
+// over, so that the product is as exact as with fp32 probabilities (2^-17).
+template <bool SPLIT> struct Frag { bf16x8 hi, lo; };
+template <> struct Frag<false> { bf16x8 hi; };
+template <bool SPLIT>
+__device__ __forceinline__ Frag<SPLIT> pack_frag(const f32x16& v, int first) {
+  Frag<SPLIT> f;
+  f.hi = pack8(v, first);
+  if constexpr (SPLIT) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) f.lo[e] = (bf16)(v[first + e] - (float)f.hi[e]);
+  }
+  return f;
+}
+template <bool SPLIT>
+__device__ __forceinline__ void mfma_frag(const bf16x8& a, const Frag<SPLIT>& b, f32x16& acc) {
+  if constexpr (SPLIT) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b.lo, acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b.hi, acc, 0, 0, 0);
+}
+
 // acc[cb] += Tile^T[features cb*32 ..][rows row_base .. row_base+15] . frag, the tile read transposed.
-__device__ __forceinline__ void second_product(const bf16* __restrict__ tile, int row_base, const bf16x8& frag, f32x16* acc) {
+template <int HD, bool SPLIT>
+__device__ __forceinline__ void second_product(const bf16* __restrict__ tile, int row_base, const Frag<SPLIT>& frag, f32x16* acc) {
   const int lane = threadIdx.x & 63;
   const int grp = lane >> 4, L = lane & 15;
   const int row0 = row_base + 8 * (grp >> 1) + (L >> 2);          // tile row this lane points at for t = 0
@@ -134,10 +168,10 @@ __device__ __forceinline__ void second_product(const bf16* __restrict__ tile, in
     for (int t = 0; t < 2; ++t) {
       const int row = row0 + 4 * t;
       const int chunk = (cb * 32 + f0) >> 3;
-      const bf16* p = tile + row * HD + ((chunk ^ swz(row)) << 3) + (f0 & 7);
+      const bf16* p = tile + row * HD + ((chunk ^ swz<HD>(row)) << 3) + (f0 & 7);
       u.h[t] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4v*)p);
     }
-    acc[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(u.v, frag, acc[cb], 0, 0, 0);
+    mfma_frag<SPLIT>(u.v, frag, acc[cb]);
   }
 }
 
@@ -150,12 +184,12 @@ __device__ __forceinline__ void wait_and_sync() {
 // ===================================================================================================
 // forward: block = 128 queries of one (batch, head); wave = 32 queries; key/value tiles of 64
 // ===================================================================================================
-template <bool CAUSAL>
+template <int HD, bool CAUSAL, bool SPLIT>
 __global__ __launch_bounds__(kNT, 2) void attn_fwd_dma_kernel(MhaDev a, bf16* __restrict__ o, bf16* __restrict__ o_lo,
                                                               float* __restrict__ lse) {
   constexpr int BKV = 64;
   constexpr int kTile = BKV * HD;                       // elements per K (or V) tile
-  extern __shared__ __attribute__((aligned(1024))) bf16 smem[];         // [stage][K | V], 64 KiB
+  extern __shared__ __attribute__((aligned(1024))) bf16 smem[];         // [stage][K | V]
   const int Tq = a.Tq, Tk = a.Tk, H = a.H;
   const int d = H * HD;
   const int64_t ld = a.ldkv;
@@ -184,12 +218,12 @@ __global__ __launch_bounds__(kNT, 2) void attn_fwd_dma_kernel(MhaDev a, bf16* __
 
   const int last_q = min(Tq, (qblk + 1) * 128) - 1;
   const int n_tiles = CAUSAL ? last_q / BKV + 1 : (Tk + BKV - 1) / BKV;
-  TileOffsets<BKV> to;
+  TileOffsets<BKV, HD> to;
   to.init(ld, wave, lane);
   auto issue = [&](int t) {
     const uint32_t st = smem_off + (uint32_t)(t & 1) * (2 * kTile * 2);
-    issue_tile<BKV>(kbase, ld, t * BKV, Tk - 1, to, st, wave, lane);
-    issue_tile<BKV>(vbase, ld, t * BKV, Tk - 1, to, st + kTile * 2, wave, lane);
+    issue_tile<BKV, HD>(kbase, ld, t * BKV, Tk - 1, to, st, wave, lane);
+    issue_tile<BKV, HD>(vbase, ld, t * BKV, Tk - 1, to, st + kTile * 2, wave, lane);
   };
   issue(0);
   for (int t = 0; t < n_tiles; ++t) {
@@ -201,7 +235,7 @@ __global__ __launch_bounds__(kNT, 2) void attn_fwd_dma_kernel(MhaDev a, bf16* __
     const bf16* Vs = Ks + kTile;
     f32x16 s[2];
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb) s[kb] = first_product(Ks, kb * 32, qf);
+    for (int kb = 0; kb < 2; ++kb) s[kb] = first_product<HD>(Ks, kb * 32, qf);
     // last visible key of this lane's query: itself (causal), else the last key there is
     const int last_key = CAUSAL ? query : Tk - 1;
     if (CAUSAL ? j0 + BKV - 1 > q0 : j0 + BKV > Tk) {   // the tile straddles the diagonal / the end of the keys
@@ -217,7 +251,8 @@ __global__ __launch_bounds__(kNT, 2) void attn_fwd_dma_kernel(MhaDev a, bf16* __
     mx = max3(mx, s[1][15], s[1][15]);
     const float other = __shfl_xor(mx, 32, 64);
     mx = max3(mx, other, other) * c2;
-    // lazy rescaling: the reference m only has to bound the exponents (see attention_mfma.hip)
+    // Lazy rescaling: the running reference m only has to bound the exponents, not equal the maximum.  It is moved (and the
+    // accumulators rescaled) only when some row's maximum grew by more than 2^8; otherwise exp2(s - m) <= 256.
     if (__builtin_amdgcn_ballot_w64(mx > m + 8.f) != 0) {
       const float m_new = fmaxf(m, mx);
       const float alpha = __builtin_amdgcn_exp2f(m - m_new);
@@ -241,7 +276,7 @@ __global__ __launch_bounds__(kNT, 2) void attn_fwd_dma_kernel(MhaDev a, bf16* __
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-      for (int b2 = 0; b2 < 2; ++b2) second_product(Vs, kb * 32 + b2 * 16, pack8(s[kb], b2 * 8), acc);
+      for (int b2 = 0; b2 < 2; ++b2) second_product<HD, SPLIT>(Vs, kb * 32 + b2 * 16, pack_frag<SPLIT>(s[kb], b2 * 8), acc);
   }
   l += __shfl_xor(l, 32, 64);
   if (query < Tq) {
@@ -260,7 +295,7 @@ __global__ __launch_bounds__(kNT, 2) void attn_fwd_dma_kernel(MhaDev a, bf16* __
 // It also produces delta_i = sum_c dO_ic O_ic for its queries (each wave has the dO fragments of its 32 rows in
 // registers anyway; O, plus the optional rounding remainder o_lo, is read the same way once) and leaves it in
 // `delta` for the dK/dV kernel, which is launched behind this one.
-template <bool CAUSAL>
+template <int HD, bool CAUSAL, bool SPLIT>
 __global__ __launch_bounds__(kNT, 2) void attn_dq_dma_kernel(MhaDev a, const bf16* __restrict__ o, const bf16* __restrict__ o_lo,
                                                              const bf16* __restrict__ dout, const float* __restrict__ lse,
                                                              float* __restrict__ delta, bf16* __restrict__ dq, int64_t lddq) {
@@ -293,21 +328,24 @@ __global__ __launch_bounds__(kNT, 2) void attn_dq_dma_kernel(MhaDev a, const bf1
   {
     bf16x8 of[HD / 16];
     load_row_frags<HD>(o + (int64_t)b * Tq * d + h * HD, d, q0, Tq, of);
-    float part = 0.f;
+    // The diagonal of O . dO^T, from the same instructions as dP: where a query sees one key only, O is V and dP - delta
+    // comes out as the exact zero that it is.
+    f32x16 od;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) od[r] = 0.f;
+#pragma unroll
+    for (int kk = 0; kk < HD / 16; ++kk) od = __builtin_amdgcn_mfma_f32_32x32x16_bf16(of[kk], gf[kk], od, 0, 0, 0);
     if (o_lo) {
-      bf16x8 lf[HD / 16];
-      load_row_frags<HD>(o_lo + (int64_t)b * Tq * d + h * HD, d, q0, Tq, lf);
+      load_row_frags<HD>(o_lo + (int64_t)b * Tq * d + h * HD, d, q0, Tq, of);
 #pragma unroll
-      for (int kk = 0; kk < HD / 16; ++kk)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) part += ((float)of[kk][e] + (float)lf[kk][e]) * (float)gf[kk][e];
-    } else {
-#pragma unroll
-      for (int kk = 0; kk < HD / 16; ++kk)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) part += (float)of[kk][e] * (float)gf[kk][e];
+      for (int kk = 0; kk < HD / 16; ++kk) od = __builtin_amdgcn_mfma_f32_32x32x16_bf16(of[kk], gf[kk], od, 0, 0, 0);
     }
-    dl = part + __shfl_xor(part, 32, 64);            // the two halves of the row's features
+    // register r of half h holds row 8 (r/4) + 4 h + r%4: this column's own row is i = lane % 32
+    const int i = lane & 31, reg = 4 * (i >> 3) + (i & 3);
+    dl = od[0];
+#pragma unroll
+    for (int r = 1; r < 16; ++r) dl = reg == r ? od[r] : dl;
+    dl = __shfl(dl, i + 32 * ((i >> 2) & 1), 64);
     if (half == 0 && query < Tq) delta[(int64_t)bh * Tq + query] = dl;
   }
   f32x16 acc[HD / 32];
@@ -319,12 +357,12 @@ __global__ __launch_bounds__(kNT, 2) void attn_dq_dma_kernel(MhaDev a, const bf1
   const int last_q = min(Tq, (qblk + 1) * 128) - 1;
   const int n_tiles = CAUSAL ? last_q / BKV + 1 : (Tk + BKV - 1) / BKV;
   const int last_key = CAUSAL ? query : Tk - 1;
-  TileOffsets<BKV> to;
+  TileOffsets<BKV, HD> to;
   to.init(ld, wave, lane);
   auto issue = [&](int t) {
     const uint32_t st = smem_off + (uint32_t)(t & 1) * (2 * kTile * 2);
-    issue_tile<BKV>(kbase, ld, t * BKV, Tk - 1, to, st, wave, lane);
-    issue_tile<BKV>(vbase, ld, t * BKV, Tk - 1, to, st + kTile * 2, wave, lane);
+    issue_tile<BKV, HD>(kbase, ld, t * BKV, Tk - 1, to, st, wave, lane);
+    issue_tile<BKV, HD>(vbase, ld, t * BKV, Tk - 1, to, st + kTile * 2, wave, lane);
   };
   issue(0);
   for (int t = 0; t < n_tiles; ++t) {
@@ -337,8 +375,8 @@ __global__ __launch_bounds__(kNT, 2) void attn_dq_dma_kernel(MhaDev a, const bf1
     const bool diag = CAUSAL ? j0 + BKV - 1 > q0 : j0 + BKV > Tk;
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb) {
-      f32x16 s = first_product(Ks, kb * 32, qf);      // S^T
-      f32x16 dp = first_product(Vs, kb * 32, gf);     // dP^T = V . dO^T
+      f32x16 s = first_product<HD>(Ks, kb * 32, qf);      // S^T
+      f32x16 dp = first_product<HD>(Vs, kb * 32, gf);     // dP^T = V . dO^T
       if (diag) {
 #pragma unroll
         for (int r = 0; r < 16; ++r)
@@ -347,7 +385,7 @@ __global__ __launch_bounds__(kNT, 2) void attn_dq_dma_kernel(MhaDev a, const bf1
 #pragma unroll
       for (int r = 0; r < 16; ++r) s[r] = __builtin_amdgcn_exp2f(fmaf(s[r], c2, -lse2)) * (dp[r] - dl);
 #pragma unroll
-      for (int b2 = 0; b2 < 2; ++b2) second_product(Ks, kb * 32 + b2 * 16, pack8(s, b2 * 8), acc);   // dQ^T += K^T . dS^T
+      for (int b2 = 0; b2 < 2; ++b2) second_product<HD, SPLIT>(Ks, kb * 32 + b2 * 16, pack_frag<SPLIT>(s, b2 * 8), acc);   // dQ^T += K^T . dS^T
     }
   }
   if (query < Tq) store_row<HD>(dq + ((int64_t)b * Tq + query) * lddq + h * HD, acc, scale);
@@ -386,14 +424,14 @@ __device__ __forceinline__ void load_stats(const float* Ls, const float* Ds, int
 // First products of block `next` (sn = S, dpn = dP against the tile rows rbn .. rbn+31 of Qn / Gn), with - when
 // HAVE_CUR - the arithmetic of block `cur` between the MFMAs: s becomes P = exp2(S c2 - lse), ds = P (dP - delta).
 // (Masked scores are handled through the statistics: a log-sum-exp of +inf makes P an exact zero.)
-template <bool HAVE_NEXT, bool HAVE_CUR>
+template <int HD, bool SPLIT, bool HAVE_NEXT, bool HAVE_CUR>
 __device__ __forceinline__ void dkv_front(const bf16* __restrict__ Qn, const bf16* __restrict__ Gn, int rbn,
                                           const bf16x8* kf, const bf16x8* vf, f32x16& sn, f32x16& dpn, f32x16& s,
-                                          const f32x16& dp, const DkvStats& st, float c2, bf16x8* pf, bf16x8* dsf) {
-  constexpr int kDepth = 3, KK = HD / 16;
+                                          const f32x16& dp, const DkvStats& st, float c2, Frag<SPLIT>* pf, Frag<SPLIT>* dsf) {
+  constexpr int kDepth = 3, KK = HD / 16, kElems = 16 / (2 * KK);   // score elements per MFMA
   const int lane = threadIdx.x & 63;
   const int row = rbn + perm_row(lane & 31);
-  const int t = (lane >> 5) ^ swz(row);
+  const int t = (lane >> 5) ^ swz<HD>(row);
   const bf16* aq = Qn + row * HD;
   const bf16* ag = Gn + row * HD;
   bf16x8 fq[kDepth], fg[kDepth];
@@ -421,35 +459,38 @@ __device__ __forceinline__ void dkv_front(const bf16* __restrict__ Qn, const bf1
       sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fq[kk % kDepth], kf[kk], sn, 0, 0, 0);
       if (kk + kDepth < KK) fq[kk % kDepth] = *reinterpret_cast<const bf16x8*>(aq + ((2 * (kk + kDepth)) ^ t) * 8);
     }
-    element(2 * kk);
+#pragma unroll
+    for (int e = 0; e < kElems; ++e) element(2 * kk * kElems + e);
     __builtin_amdgcn_sched_barrier(0);
     if (HAVE_NEXT) {
       dpn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fg[kk % kDepth], vf[kk], dpn, 0, 0, 0);
       if (kk + kDepth < KK) fg[kk % kDepth] = *reinterpret_cast<const bf16x8*>(ag + ((2 * (kk + kDepth)) ^ t) * 8);
     }
-    element(2 * kk + 1);
+#pragma unroll
+    for (int e = 0; e < kElems; ++e) element((2 * kk + 1) * kElems + e);
     __builtin_amdgcn_sched_barrier(0);
   }
   if (HAVE_CUR) {
 #pragma unroll
     for (int b2 = 0; b2 < 2; ++b2) {
-      pf[b2] = pack8(s, b2 * 8);
-      dsf[b2] = pack8(ds, b2 * 8);
+      pf[b2] = pack_frag<SPLIT>(s, b2 * 8);
+      dsf[b2] = pack_frag<SPLIT>(ds, b2 * 8);
     }
   }
 }
 
 // Second products of a block: dv += Gs^T . P and dk += Qs^T . dS over the 32 queries at tile rows rb .. rb+31,
-// 16 MFMAs whose transposed operand reads run kAhead steps ahead.
-__device__ __forceinline__ void dkv_back(const bf16* __restrict__ Qs, const bf16* __restrict__ Gs, int rb, const bf16x8* pf,
-                                         const bf16x8* dsf, f32x16* dk, f32x16* dv) {
-  constexpr int kAhead = 2, kSteps = 16;
+// HD / 8 MFMAs (twice as many with SPLIT) whose transposed operand reads run kAhead steps ahead.
+template <int HD, bool SPLIT>
+__device__ __forceinline__ void dkv_back(const bf16* __restrict__ Qs, const bf16* __restrict__ Gs, int rb, const Frag<SPLIT>* pf,
+                                         const Frag<SPLIT>* dsf, f32x16* dk, f32x16* dv) {
+  constexpr int kAhead = 2, kBlocks = HD / 32, kSteps = 4 * kBlocks;
   const int lane = threadIdx.x & 63;
   const int grp = lane >> 4, L = lane & 15;
   const int f0 = 16 * (grp & 1) + 4 * (L & 3);
-  // step j: b2 = j / 8 (16-query half of the block), mat = (j / 4) % 2 (0: dO -> dV, 1: Q -> dK), cb = j % 4
+  // step j: b2 = 16-query half of the block, mat (0: dO -> dV, 1: Q -> dK), cb = 32-feature block
   auto read = [&](int j) {
-    const int b2 = j >> 3, mat = (j >> 2) & 1, cb = j & 3;
+    const int b2 = j / (2 * kBlocks), mat = (j / kBlocks) & 1, cb = j % kBlocks;
     const bf16* tile = mat ? Qs : Gs;
     const int row0 = rb + b2 * 16 + 8 * (grp >> 1) + (L >> 2);
     union { bf16x8 v; short4v h[2]; } u;
@@ -457,7 +498,7 @@ __device__ __forceinline__ void dkv_back(const bf16* __restrict__ Qs, const bf16
     for (int t = 0; t < 2; ++t) {
       const int row = row0 + 4 * t;
       const int chunk = (cb * 32 + f0) >> 3;
-      const bf16* p = tile + row * HD + ((chunk ^ swz(row)) << 3) + (f0 & 7);
+      const bf16* p = tile + row * HD + ((chunk ^ swz<HD>(row)) << 3) + (f0 & 7);
       u.h[t] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4v*)p);
     }
     return u.v;
@@ -469,15 +510,14 @@ __device__ __forceinline__ void dkv_back(const bf16* __restrict__ Qs, const bf16
 #pragma unroll
   for (int j = 0; j < kSteps; ++j) {
     if (j + kAhead < kSteps) fr[(j + kAhead) % (kAhead + 1)] = read(j + kAhead);
-    const int b2 = j >> 3, mat = (j >> 2) & 1, cb = j & 3;
-    if (mat) dk[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[j % (kAhead + 1)], dsf[b2], dk[cb], 0, 0, 0);
-    else dv[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[j % (kAhead + 1)], pf[b2], dv[cb], 0, 0, 0);
+    const int b2 = j / (2 * kBlocks), mat = (j / kBlocks) & 1, cb = j % kBlocks;
+    mfma_frag<SPLIT>(fr[j % (kAhead + 1)], mat ? dsf[b2] : pf[b2], mat ? dk[cb] : dv[cb]);
     __builtin_amdgcn_sched_barrier(0);
   }
 }
 
-template <bool CAUSAL>
-__global__ __launch_bounds__(kNT) void attn_dkv_dma_kernel(MhaDev a, const bf16* __restrict__ dout,
+template <int HD, bool CAUSAL, bool SPLIT>
+__global__ __launch_bounds__(kNT, HD == 64 ? 2 : 1) void attn_dkv_dma_kernel(MhaDev a, const bf16* __restrict__ dout,
                                                             const float* __restrict__ lse, const float* __restrict__ delta,
                                                             bf16* __restrict__ dk_out, bf16* __restrict__ dv_out, int64_t lddkv) {
   constexpr int BQ = 64, kStages = 3;
@@ -500,7 +540,7 @@ __global__ __launch_bounds__(kNT) void attn_dkv_dma_kernel(MhaDev a, const bf16*
   const float c2 = kLog2e * scale;
   const uint32_t smem_off = (uint32_t)(uintptr_t)(lds_ptr)smem;
 
-  TileOffsets<BQ> to_q, to_g;
+  TileOffsets<BQ, HD> to_q, to_g;
   to_q.init(ld, wave, lane);
   to_g.init(d, wave, lane);
   bf16x8 kf[HD / 16], vf[HD / 16];
@@ -526,8 +566,8 @@ __global__ __launch_bounds__(kNT) void attn_dkv_dma_kernel(MhaDev a, const bf16*
   const uint32_t stats_off = smem_off + kStages * 2 * kTile * 2;
   auto issue = [&](int t) {
     const uint32_t st = smem_off + (uint32_t)(t % kStages) * (2 * kTile * 2);
-    issue_tile<BQ>(qbase, ld, t * BQ, T - 1, to_q, st, wave, lane);
-    issue_tile<BQ>(gbase, d, t * BQ, T - 1, to_g, st + kTile * 2, wave, lane);
+    issue_tile<BQ, HD>(qbase, ld, t * BQ, T - 1, to_q, st, wave, lane);
+    issue_tile<BQ, HD>(gbase, d, t * BQ, T - 1, to_g, st + kTile * 2, wave, lane);
     if (wave == 0) {
       const int i = min(t * BQ + lane, T - 1);
       dma4(lse_bh + i, stats_off + (uint32_t)(t % kStages) * (BQ * 4));
@@ -551,9 +591,10 @@ __global__ __launch_bounds__(kNT) void attn_dkv_dma_kernel(MhaDev a, const bf16*
   issue(first_tile);
   if (first_tile + 1 < n_tiles) {
     issue(first_tile + 1);
-    // all but the second tile: 2 x 4 direct loads per wave, two more (the statistics) in wave 0
-    if (wave == 0) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * (BQ / 16) + 2) : "memory");
-    else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * (BQ / 16)) : "memory");
+    // all but the second tile: its direct loads per wave, two more (the statistics) in wave 0
+    constexpr int kLoads = 2 * TileOffsets<BQ, HD>::kPerWave;
+    if (wave == 0) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kLoads + 2) : "memory");
+    else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kLoads) : "memory");
   } else {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   }
@@ -563,7 +604,7 @@ __global__ __launch_bounds__(kNT) void attn_dkv_dma_kernel(MhaDev a, const bf16*
   // Two sets of score registers: the even block of a tile lives in (s0, dp0), the odd one in (s1, dp1), so nothing is
   // ever copied from "next" to "current".
   f32x16 s0, dp0, s1, dp1;
-  bf16x8 pf[2], dsf[2];
+  Frag<SPLIT> pf[2], dsf[2];
   DkvStats st;
   // One step of the pipeline: the arithmetic of block n (scores in s, dp) between the first products of block n + 1
   // (into sn, dpn; NEXT: there is one), then the second products of block n.
@@ -594,17 +635,19 @@ __global__ __launch_bounds__(kNT) void attn_dkv_dma_kernel(MhaDev a, const bf16*
         asm volatile("" : "+v"(st.lq[r]));
       }
     }
-    dkv_front<NEXT, true>(Qn, Qn + kTile, (hb ^ 1) * 32, kf, vf, sn, dpn, s, dp, st, c2, pf, dsf);
+    dkv_front<HD, SPLIT, NEXT, true>(Qn, Qn + kTile, (hb ^ 1) * 32, kf, vf, sn, dpn, s, dp, st, c2, pf, dsf);
     // the next block's statistics travel to registers under the second products (its tile is resident: see advance)
     if (NEXT) load_stats(Ls[((n + 1) >> 1) % kStages], Ds[((n + 1) >> 1) % kStages], hb ^ 1, half, st);
-    dkv_back(Qs, Qs + kTile, hb * 32, pf, dsf, dk, dv);
+    dkv_back<HD, SPLIT>(Qs, Qs + kTile, hb * 32, pf, dsf, dk, dv);
     // Register classes: the output accumulators and the K / V fragments are only ever touched by MFMAs and live in
     // the accumulation registers; the scores are worked on by the vector ALU and stay in ordinary registers, so no
     // MFMA result has to be copied across (with the wait states that costs).
 #pragma unroll
-    for (int cb = 0; cb < HD / 32; ++cb) asm volatile("" : "+a"(dk[cb]), "+a"(dv[cb]));
+    for (int cb = 0; cb < HD / 32; ++cb)
+      if (HD == 128) asm volatile("" : "+a"(dk[cb]), "+a"(dv[cb]));
 #pragma unroll
-    for (int kk = 0; kk < HD / 16; ++kk) asm volatile("" : "+v"(kf[kk]), "+v"(vf[kk]));
+    for (int kk = 0; kk < HD / 16; ++kk)
+      if (HD == 128) asm volatile("" : "+v"(kf[kk]), "+v"(vf[kk]));
   };
   using yes = std::integral_constant<bool, true>;
   using no = std::integral_constant<bool, false>;
@@ -617,7 +660,7 @@ __global__ __launch_bounds__(kNT) void attn_dkv_dma_kernel(MhaDev a, const bf16*
   }
   if (any) {
     load_stats(Ls[t0 % kStages], Ds[t0 % kStages], 0, half, st);
-    dkv_front<true, false>(tile_q(2 * t0), tile_q(2 * t0) + kTile, 0, kf, vf, s0, dp0, s0, dp0, st, c2, pf, dsf);
+    dkv_front<HD, SPLIT, true, false>(tile_q(2 * t0), tile_q(2 * t0) + kTile, 0, kf, vf, s0, dp0, s0, dp0, st, c2, pf, dsf);
     for (int t = t0; t + 1 < n_tiles; ++t) {
       step(2 * t, yes{}, s0, dp0, s1, dp1);
       advance(t);
@@ -635,65 +678,85 @@ __global__ __launch_bounds__(kNT) void attn_dkv_dma_kernel(MhaDev a, const bf16*
 
 }  // namespace
 
-constexpr int kSmemTiles = 2 * 2 * 64 * HD * 2;          // two stages of two 64 x 128 bf16 tiles: 64 KiB
-constexpr int kSmemDkv = 3 * 2 * 64 * HD * 2 + 6 * 64 * 4;   // dK/dV: three stages and their statistics: 97.5 KiB
+// Dynamic LDS: two stages of two 64-row tiles (64 KiB at head_dim 128); dK/dV three stages and their statistics (97.5 KiB).
+template <int HD> constexpr int kSmemTiles = 2 * 2 * 64 * HD * 2;
+template <int HD> constexpr int kSmemDkv = 3 * 2 * 64 * HD * 2 + 6 * 64 * 4;
+
+template <int HD, bool CAUSAL, bool SPLIT>
+static hipError_t prepare_dma() {
+  const struct { const void* fn; int bytes; } all[] = {
+      {reinterpret_cast<const void*>(attn_fwd_dma_kernel<HD, CAUSAL, SPLIT>), kSmemTiles<HD>},
+      {reinterpret_cast<const void*>(attn_dq_dma_kernel<HD, CAUSAL, SPLIT>), kSmemTiles<HD>},
+      {reinterpret_cast<const void*>(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT>), kSmemDkv<HD>}};
+  for (const auto& k : all) {
+    const hipError_t e = hipFuncSetAttribute(k.fn, hipFuncAttributeMaxDynamicSharedMemorySize, k.bytes);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
 
 // Raises the dynamic-LDS limit of the kernels (once; called at context creation, never inside a capture).
 hipError_t attention_dma_init() {
   static bool done = false;
   if (done) return hipSuccess;
-  const struct { const void* fn; int bytes; } all[] = {
-      {reinterpret_cast<const void*>(attn_fwd_dma_kernel<true>), kSmemTiles},
-      {reinterpret_cast<const void*>(attn_fwd_dma_kernel<false>), kSmemTiles},
-      {reinterpret_cast<const void*>(attn_dq_dma_kernel<true>), kSmemTiles},
-      {reinterpret_cast<const void*>(attn_dq_dma_kernel<false>), kSmemTiles},
-      {reinterpret_cast<const void*>(attn_dkv_dma_kernel<true>), kSmemDkv},
-      {reinterpret_cast<const void*>(attn_dkv_dma_kernel<false>), kSmemDkv}};
-  for (const auto& k : all) {
-    const hipError_t e = hipFuncSetAttribute(k.fn, hipFuncAttributeMaxDynamicSharedMemorySize, k.bytes);
-    if (e != hipSuccess) return e;
-  }
-  done = true;
-  return hipSuccess;
+  hipError_t e = prepare_dma<128, true, false>();
+  if (e == hipSuccess) e = prepare_dma<128, false, false>();
+  if (e == hipSuccess) e = prepare_dma<64, true, false>();
+  if (e == hipSuccess) e = prepare_dma<64, true, true>();
+  if (e == hipSuccess) e = prepare_dma<64, false, true>();
+  if (e == hipSuccess) done = true;
+  return e;
 }
 
 static MhaDev dev_of(const MhaArgs& a) {
   return MhaDev{(const bf16*)a.q, (const bf16*)a.k, (const bf16*)a.v, a.ldq, a.ldkv, a.Tq, a.Tk, a.H};
 }
 
-// Whether the kernels of this file take the problem: bf16, head_dim 128, 16-byte aligned rows.
+// Whether the kernels of this file take the problem: bf16, 16-byte aligned rows.
 bool mha_dma_supported(const MhaArgs& a) {
-  if (a.dtype != kBF16 || a.hd != HD) return false;
+  if (a.dtype != kBF16 || (a.hd != 128 && a.hd != 64)) return false;
   if (((uintptr_t)a.q | (uintptr_t)a.k | (uintptr_t)a.v) & 15) return false;
   return a.ldq % 8 == 0 && a.ldkv % 8 == 0;
 }
 
-hipError_t launch_mha_fwd_dma(hipStream_t s, const MhaArgs& a, void* o, void* o_lo, float* lse) {
-  hipError_t e = attention_dma_init();
-  if (e != hipSuccess) return e;
+template <int HD, bool CAUSAL, bool SPLIT>
+static hipError_t fwd_dma(hipStream_t s, const MhaArgs& a, void* o, void* o_lo, float* lse) {
   const int grid = ((a.Tq + 127) / 128) * a.B * a.H;          // (problem, block) pairs, see xcd_block_map
-  if (a.causal)
-    attn_fwd_dma_kernel<true><<<grid, kNT, kSmemTiles, s>>>(dev_of(a), (bf16*)o, (bf16*)o_lo, lse);
-  else
-    attn_fwd_dma_kernel<false><<<grid, kNT, kSmemTiles, s>>>(dev_of(a), (bf16*)o, (bf16*)o_lo, lse);
+  attn_fwd_dma_kernel<HD, CAUSAL, SPLIT><<<grid, kNT, kSmemTiles<HD>, s>>>(dev_of(a), (bf16*)o, (bf16*)o_lo, lse);
   return hipGetLastError();
 }
-
-hipError_t launch_mha_dq_dkv_dma(hipStream_t s, const MhaArgs& a, const void* o, const void* o_lo, const void* dout,
-                                 const float* lse, float* delta, void* dq, int64_t lddq, void* dk, void* dv, int64_t lddkv) {
-  hipError_t e = attention_dma_init();
+// exact: probabilities enter the products with V, K, Q and dO as fp32 would (head_dim 64 only).
+hipError_t launch_mha_fwd_dma(hipStream_t s, const MhaArgs& a, void* o, void* o_lo, float* lse, bool exact) {
+  const hipError_t e = attention_dma_init();
   if (e != hipSuccess) return e;
-  if ((((uintptr_t)dq | (uintptr_t)dk | (uintptr_t)dv) & 7) || lddq % 4 || lddkv % 4) return hipErrorInvalidValue;
+  if (a.hd == 128) return a.causal ? fwd_dma<128, true, false>(s, a, o, o_lo, lse) : fwd_dma<128, false, false>(s, a, o, o_lo, lse);
+  if (!a.causal) return fwd_dma<64, false, true>(s, a, o, o_lo, lse);
+  return exact ? fwd_dma<64, true, true>(s, a, o, o_lo, lse) : fwd_dma<64, true, false>(s, a, o, o_lo, lse);
+}
+
+struct MhaGrads { const void *o, *o_lo, *dout; const float* lse; float* delta; void* dq; int64_t lddq; void *dk, *dv; int64_t lddkv; };
+template <int HD, bool CAUSAL, bool SPLIT>
+static hipError_t bwd_dma(hipStream_t s, const MhaArgs& a, const MhaGrads& g) {
   const int grid_q = ((a.Tq + 127) / 128) * a.B * a.H, grid_k = ((a.Tk + 127) / 128) * a.B * a.H;
-  const MhaDev dv_ = dev_of(a);
-  if (a.causal) {
-    attn_dq_dma_kernel<true><<<grid_q, kNT, kSmemTiles, s>>>(dv_, (const bf16*)o, (const bf16*)o_lo, (const bf16*)dout, lse, delta, (bf16*)dq, lddq);
-    attn_dkv_dma_kernel<true><<<grid_k, kNT, kSmemDkv, s>>>(dv_, (const bf16*)dout, lse, delta, (bf16*)dk, (bf16*)dv, lddkv);
-  } else {
-    attn_dq_dma_kernel<false><<<grid_q, kNT, kSmemTiles, s>>>(dv_, (const bf16*)o, (const bf16*)o_lo, (const bf16*)dout, lse, delta, (bf16*)dq, lddq);
-    attn_dkv_dma_kernel<false><<<grid_k, kNT, kSmemDkv, s>>>(dv_, (const bf16*)dout, lse, delta, (bf16*)dk, (bf16*)dv, lddkv);
-  }
+  attn_dq_dma_kernel<HD, CAUSAL, SPLIT><<<grid_q, kNT, kSmemTiles<HD>, s>>>(
+      dev_of(a), (const bf16*)g.o, (const bf16*)g.o_lo, (const bf16*)g.dout, g.lse, g.delta, (bf16*)g.dq, g.lddq);
+  attn_dkv_dma_kernel<HD, CAUSAL, SPLIT><<<grid_k, kNT, kSmemDkv<HD>, s>>>(
+      dev_of(a), (const bf16*)g.dout, g.lse, g.delta, (bf16*)g.dk, (bf16*)g.dv, g.lddkv);
   return hipGetLastError();
+}
+bool mha_dma_outputs_aligned(const void* dq, int64_t lddq, const void* dk, const void* dv, int64_t lddkv) {
+  return !((((uintptr_t)dq | (uintptr_t)dk | (uintptr_t)dv) & 7) || lddq % 4 || lddkv % 4);
+}
+hipError_t launch_mha_dq_dkv_dma(hipStream_t s, const MhaArgs& a, const void* o, const void* o_lo, const void* dout,
+                                 const float* lse, float* delta, void* dq, int64_t lddq, void* dk, void* dv, int64_t lddkv,
+                                 bool exact) {
+  const hipError_t e = attention_dma_init();
+  if (e != hipSuccess) return e;
+  if (!mha_dma_outputs_aligned(dq, lddq, dk, dv, lddkv)) return hipErrorInvalidValue;
+  const MhaGrads g{o, o_lo, dout, lse, delta, dq, lddq, dk, dv, lddkv};
+  if (a.hd == 128) return a.causal ? bwd_dma<128, true, false>(s, a, g) : bwd_dma<128, false, false>(s, a, g);
+  if (!a.causal) return bwd_dma<64, false, true>(s, a, g);
+  return exact ? bwd_dma<64, true, true>(s, a, g) : bwd_dma<64, true, false>(s, a, g);
 }
 
 }  // namespace pw

@@ -514,6 +514,43 @@ def test_general_attention_rejects_bad_arguments(ctx):
 
 # ---- softmax cross-entropy ----------------------------------------------------------------------------
 
+# query blocks of 128, key tiles of 64, 32-row MFMA blocks and one to either side of each; probabilities enter the products
+# exactly at this head width, so what is left is the rounding of the stored results (2^-9, uniform: 1.7e-3 in the norm)
+@pytest.mark.parametrize("Tq,Tk,causal", [(1, 1, 0), (31, 65, 0), (32, 64, 0), (33, 63, 0), (129, 127, 0), (128, 257, 0), (96, 96, 1),
+                                          (161, 161, 1)])
+def test_bf16_attention_at_head_width_64_is_exact_up_to_its_storage(ctx, Tq, Tk, causal):
+    B, H, hd = 2, 3, 64
+    d = H * hd
+    (q, qv), (kv, kvv), (go, gov) = (dev_act(_rand(s, shp), True) for s, shp in
+                                     ((71, (B * Tq, d)), (72, (B * Tk, 2 * d)), (73, (B * Tq, d))))
+    o, o_lo, dq, dkv = (empty_act(shp, True) for shp in ((B * Tq, d), (B * Tq, d), (B * Tq, d), (B * Tk, 2 * d)))
+    lse, delta = torch.empty((B, H, Tq), device="cuda"), torch.empty((B, H, Tq), device="cuda")
+    a = pwb.MhaArgs(pwb.PW_BF16, ptr(q), ptr(kv), ptr(kv) + 2 * d, d, 2 * d, B, Tq, Tk, H, hd, causal)
+    ctx.mha_fwd(a, ptr(o), ptr(lse), ptr(o_lo))
+    ctx.mha_bwd(a, ptr(o), ptr(go), ptr(lse), ptr(delta), ptr(dq), d, ptr(dkv), ptr(dkv) + 2 * d, 2 * d, ptr(o_lo))
+    ctx.synchronize()
+    heads = lambda t, T: np.moveaxis(t.reshape(B, T, H, hd), 2, 1)  # noqa: E731
+    q_, k_, v_, g_ = heads(qv, Tq), heads(kvv[:, :d], Tk), heads(kvv[:, d:], Tk), heads(gov, Tq)
+    s = q_ @ k_.swapaxes(2, 3) / 8.0
+    if causal:
+        s = np.where(np.tril(np.ones((Tq, Tk), bool)), s, -np.inf)
+    m = s.max(-1, keepdims=True)
+    p = np.exp(s - m)
+    l = p.sum(-1, keepdims=True)
+    p /= l
+    ro = p @ v_
+    ds = p * (g_ @ v_.swapaxes(2, 3) - (g_ * ro).sum(-1, keepdims=True)) / 8.0
+    flat = lambda t: np.moveaxis(t, 1, 2).reshape(-1, d)  # noqa: E731
+    assert np.abs(host(lse) - (m + np.log(l))[..., 0]).max() < 1e-5
+    rk = flat(ds.swapaxes(2, 3) @ q_)
+    for got, ref in ((host(o), flat(ro)), (host(dq), flat(ds @ k_)), (host(dkv)[:, :d], rk), (host(dkv)[:, d:], flat(p.swapaxes(2, 3) @ g_))):
+        if Tk == 1 and ref is not None and not np.abs(ref).max() > 1e-12:
+            assert np.abs(got).max() == 0.0      # one key: the score gradients are zero, exactly
+        else:
+            assert rel_l2(got, ref) < 2e-3
+    assert rel_l2(host(o) + host(o_lo), flat(ro)) < 2e-5
+
+
 # one tile of 16 positions and one to either side, several tiles per wave; what a query may not see (or a key is not
 # seen by) must not matter even where it is not a number
 @pytest.mark.parametrize("hd", [64, 128])
