@@ -1,7 +1,7 @@
 // LayerNorm forward / backward and column sums (bias gradients).  HBM-bound: every row is read once
 // from memory with 16-byte accesses, held in registers, and reduced with wave64 shuffles.  Rows of up to
 // 2048 columns are handled by ONE wave each (no block-wide synchronisation at all, several rows in flight per
-// compute unit); wider rows by one 256-thread block each.
+// compute unit; the backward up to 512); wider rows by a block.
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -177,68 +177,155 @@ int64_t layernorm_bwd_ws_floats(int N, int d) { return 3LL * ln_bwd_blocks(N) * 
 
 __device__ __forceinline__ void add4(float4& a, const float4& b) { a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w; }
 
-// Wide rows (d > 2048): block b handles rows b, b+G, ...; two block sums per row.
-template <class T>
-__global__ __launch_bounds__(kLnThreads) void layernorm_bwd_kernel(const T* __restrict__ dy, const float* __restrict__ x,
-                                                                   const float* __restrict__ g,
-                                                                   const float* __restrict__ mean,
-                                                                   const float* __restrict__ rstd,
-                                                                   const float* __restrict__ dres, float* __restrict__ dx,
-                                                                   T* __restrict__ dx_lp, float* __restrict__ ws, int N,
-                                                                   int d, int want_dsum) {
-  __shared__ float red[kLnThreads / 64];
-  const int d4 = d >> 2;
-  float4 accg[kLnMaxVec], accb[kLnMaxVec], accd[kLnMaxVec];
+// Rows of more than 512 columns: a block takes ROWS rows at a time, thread t owning float4 columns t, t + NT, ... (VEC of
+// them) of each.  HBM-bound, and bound by what a compute unit has in flight: with a wave per row the three running sums
+// alone are 96 registers at 2048 columns and a wave's next row has no room; spread over four waves they are 24, and the
+// next ROWS rows are requested before the current ones are reduced.  The 2 ROWS row sums are reduced together: every
+// exchange halves how many values a lane still carries, then the waves meet in LDS, once per step.
+// Measured with the reduction behind it (us; before: a wave per row up to 2048 columns, a block per row beyond), bf16:
+// 8192 x 2048 (268 MB) 68 -> 59, 8192 x 1024 37.5 -> 32.7, 2048 x 4096 41 -> 29, 4096 x 8192 136 -> 110, 64 x 8192 13.7 -> 11.4.
+template <class T> struct Lp4;                  // four elements as they are stored
+template <> struct Lp4<float> { typedef float4 type; };
+template <> struct Lp4<bf16> { typedef bf16x4 type; };
+__device__ __forceinline__ float4 widen(float4 v) { return v; }
+__device__ __forceinline__ float4 widen(bf16x4 v) { return make_float4((float)v[0], (float)v[1], (float)v[2], (float)v[3]); }
+
+template <class T, int NT, int VEC, int ROWS>
+__global__ __launch_bounds__(NT, NT == 256 ? 2 : 1) void layernorm_bwd_kernel(const T* __restrict__ dy, const float* __restrict__ x,
+                                                                      const float* __restrict__ g,
+                                                                      const float* __restrict__ mean,
+                                                                      const float* __restrict__ rstd,
+                                                                      const float* __restrict__ dres, float* __restrict__ dx,
+                                                                      T* __restrict__ dx_lp, float* __restrict__ ws, int N,
+                                                                      int d, int want_dsum) {
+  constexpr int kSums = 2 * ROWS, kWaves = NT / 64;
+  __shared__ __attribute__((aligned(16))) float red[2][kSums][kWaves];
+  typedef typename Lp4<T>::type lp4;
+  const int d4 = d >> 2, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int step = gridDim.x * ROWS;
+  const float inv_d = 1.f / (float)d;
+  bool own[VEC];
+  float4 gv[VEC], acc[3][VEC];
 #pragma unroll
-  for (int i = 0; i < kLnMaxVec; ++i) accg[i] = accb[i] = accd[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int n = blockIdx.x; n < N; n += gridDim.x) {
-    const float mu = mean[n], rs = rstd[n];
-    float4 xh[kLnMaxVec], gg[kLnMaxVec];
-    float s1 = 0.f, s2 = 0.f;
+  for (int i = 0; i < VEC; ++i) {
+    const int c = threadIdx.x + i * NT;
+    own[i] = c < d4;
+    gv[i] = own[i] ? reinterpret_cast<const float4*>(g)[c] : make_float4(0.f, 0.f, 0.f, 0.f);
+    acc[0][i] = acc[1][i] = acc[2][i] = make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+  float4 xv[ROWS][VEC], rv[ROWS][VEC];
+  lp4 dv[ROWS][VEC];
+  float mu[ROWS], rs[ROWS];
+  auto fetch = [&](int n0) {
 #pragma unroll
-    for (int i = 0; i < kLnMaxVec; ++i) {
-      const int c4 = threadIdx.x + i * kLnThreads;
-      if (c4 < d4) {
-        const float4 xv = reinterpret_cast<const float4*>(x + (size_t)n * d)[c4];
-        const float4 dv = load4<T>(dy + (size_t)n * d + 4 * c4);
-        const float4 gv = reinterpret_cast<const float4*>(g)[c4];
-        xh[i] = make_float4((xv.x - mu) * rs, (xv.y - mu) * rs, (xv.z - mu) * rs, (xv.w - mu) * rs);
-        gg[i] = make_float4(dv.x * gv.x, dv.y * gv.y, dv.z * gv.z, dv.w * gv.w);
-        s1 += (gg[i].x + gg[i].y) + (gg[i].z + gg[i].w);
-        s2 += (gg[i].x * xh[i].x + gg[i].y * xh[i].y) + (gg[i].z * xh[i].z + gg[i].w * xh[i].w);
-        accg[i].x += dv.x * xh[i].x; accg[i].y += dv.y * xh[i].y; accg[i].z += dv.z * xh[i].z; accg[i].w += dv.w * xh[i].w;
-        add4(accb[i], dv);
+    for (int r = 0; r < ROWS; ++r) {
+      const int n = n0 + r;
+      if (n >= N) break;                        // uniform
+      mu[r] = mean[n];
+      rs[r] = rstd[n];
+#pragma unroll
+      for (int i = 0; i < VEC; ++i)
+        if (own[i]) {
+          const size_t at = (size_t)n * d4 + threadIdx.x + i * NT;
+          xv[r][i] = reinterpret_cast<const float4*>(x)[at];
+          dv[r][i] = reinterpret_cast<const lp4*>(dy)[at];
+          if (dres) rv[r][i] = reinterpret_cast<const float4*>(dres)[at];
+        }
+    }
+  };
+  int n0 = blockIdx.x * ROWS, phase = 0;
+  if (n0 < N) fetch(n0);
+  for (; n0 < N; n0 += step, phase ^= 1) {
+    float4 xh[ROWS][VEC], dr[ROWS][VEC];        // normalised input; residual gradient
+    lp4 dw[ROWS][VEC];
+    float sums[kSums], rr[ROWS];
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {
+      const bool live = n0 + r < N;
+      float s1 = 0.f, s2 = 0.f;
+      rr[r] = rs[r];
+#pragma unroll
+      for (int i = 0; i < VEC; ++i) {
+        xh[r][i] = dr[r][i] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (own[i] && live) {
+          const float4 v = xv[r][i], dyv = widen(dv[r][i]);
+          dw[r][i] = dv[r][i];
+          if (dres) dr[r][i] = rv[r][i];
+          xh[r][i] = make_float4((v.x - mu[r]) * rs[r], (v.y - mu[r]) * rs[r], (v.z - mu[r]) * rs[r], (v.w - mu[r]) * rs[r]);
+          const float4 gg = make_float4(dyv.x * gv[i].x, dyv.y * gv[i].y, dyv.z * gv[i].z, dyv.w * gv[i].w);
+          s1 += (gg.x + gg.y) + (gg.z + gg.w);
+          s2 += (gg.x * xh[r][i].x + gg.y * xh[r][i].y) + (gg.z * xh[r][i].z + gg.w * xh[r][i].w);
+          acc[0][i].x += dyv.x * xh[r][i].x; acc[0][i].y += dyv.y * xh[r][i].y;
+          acc[0][i].z += dyv.z * xh[r][i].z; acc[0][i].w += dyv.w * xh[r][i].w;
+          add4(acc[1][i], dyv);
+        }
+      }
+      sums[2 * r] = s1;
+      sums[2 * r + 1] = s2;
+    }
+    if (n0 + step < N) fetch(n0 + step);        // the next rows travel while these are reduced and stored
+    // Lane l ends up with value l % kSums of this wave: exchange m (distance m) leaves each lane the half of its values
+    // whose index agrees with its own bit.
+    int left = kSums;
+#pragma unroll
+    for (int m = 1; m < 64; m <<= 1) {
+      if (left > 1) {
+        left >>= 1;
+        const bool up = (lane & m) != 0;
+#pragma unroll
+        for (int k = 0; k < kSums / 2; ++k)
+          if (k < left) {
+            const float keep = up ? sums[2 * k + 1] : sums[2 * k], give = up ? sums[2 * k] : sums[2 * k + 1];
+            sums[k] = keep + __shfl_xor(give, m, 64);
+          }
+      } else {
+        sums[0] += __shfl_xor(sums[0], m, 64);
       }
     }
-    const float m1 = block_sum(s1, red) / (float)d;
-    const float m2 = block_sum(s2, red) / (float)d;
+    if (lane < kSums) red[phase][lane][wave] = sums[0];
+    __syncthreads();                            // (the other phase's values were read before the previous one)
 #pragma unroll
-    for (int i = 0; i < kLnMaxVec; ++i) {
-      const int c4 = threadIdx.x + i * kLnThreads;
-      if (c4 < d4) {
-        float4 o = make_float4(rs * (gg[i].x - m1 - xh[i].x * m2), rs * (gg[i].y - m1 - xh[i].y * m2),
-                               rs * (gg[i].z - m1 - xh[i].z * m2), rs * (gg[i].w - m1 - xh[i].w * m2));
-        if (dres) add4(o, reinterpret_cast<const float4*>(dres + (size_t)n * d)[c4]);
-        reinterpret_cast<float4*>(dx + (size_t)n * d)[c4] = o;
-        if (dx_lp) store4<T>(dx_lp + (size_t)n * d + 4 * c4, o.x, o.y, o.z, o.w);
-        add4(accd[i], o);
-      }
+    for (int r = 0; r < ROWS; ++r) {
+      const int n = n0 + r;
+      if (n >= N) break;
+      auto total = [&](const float* p) {
+        float t = 0.f;
+#pragma unroll
+        for (int w = 0; w < kWaves; w += 4) {
+          const float4 q = *reinterpret_cast<const float4*>(p + w);
+          t += (q.x + q.y) + (q.z + q.w);
+        }
+        return t;
+      };
+      const float m1 = total(red[phase][2 * r]) * inv_d, m2 = total(red[phase][2 * r + 1]) * inv_d;
+#pragma unroll
+      for (int i = 0; i < VEC; ++i)
+        if (own[i]) {
+          const float4 dyv = widen(dw[r][i]);
+          float4 o = make_float4(rr[r] * (dyv.x * gv[i].x - m1 - xh[r][i].x * m2), rr[r] * (dyv.y * gv[i].y - m1 - xh[r][i].y * m2),
+                                 rr[r] * (dyv.z * gv[i].z - m1 - xh[r][i].z * m2), rr[r] * (dyv.w * gv[i].w - m1 - xh[r][i].w * m2));
+          add4(o, dr[r][i]);
+          const size_t at = (size_t)n * d4 + threadIdx.x + i * NT;
+          reinterpret_cast<float4*>(dx)[at] = o;
+          if (dx_lp) store4<T>(dx_lp + 4 * at, o.x, o.y, o.z, o.w);
+          add4(acc[2][i], o);
+        }
     }
   }
   float* w0 = ws + (size_t)blockIdx.x * d;
   const size_t set = (size_t)gridDim.x * d;
 #pragma unroll
-  for (int i = 0; i < kLnMaxVec; ++i) {
-    const int c4 = threadIdx.x + i * kLnThreads;
-    if (c4 < d4) {
-      reinterpret_cast<float4*>(w0)[c4] = accg[i];
-      reinterpret_cast<float4*>(w0 + set)[c4] = accb[i];
-      if (want_dsum) reinterpret_cast<float4*>(w0 + 2 * set)[c4] = accd[i];
+  for (int i = 0; i < VEC; ++i) {
+    const int c = threadIdx.x + i * NT;
+    if (own[i]) {
+      reinterpret_cast<float4*>(w0)[c] = acc[0][i];
+      reinterpret_cast<float4*>(w0 + set)[c] = acc[1][i];
+      if (want_dsum) reinterpret_cast<float4*>(w0 + 2 * set)[c] = acc[2][i];
     }
   }
 }
 
-// Rows of up to 2048 columns: one wave per row (wave w of the grid handles rows w, w + W, ...), lane l owns
+// Rows of up to 512 columns: one wave per row (wave w of the grid handles rows w, w + W, ...), lane l owns
 // float4 columns l, l + 64, ...  At the end the four waves of a block add their sums through LDS in wave order.
 template <class T, int VEC>
 __global__ __launch_bounds__(kLnThreads) void layernorm_bwd_wave_kernel(const T* __restrict__ dy, const float* __restrict__ x,
@@ -323,11 +410,22 @@ template <class T>
 static void launch_ln_bwd_wave(hipStream_t s, int G, const T* dy, const float* x, const float* g, const float* mean,
                                const float* rstd, const float* dres, float* dx, T* dx_lp, float* ws, int N, int d, int want) {
   if (d <= 256) layernorm_bwd_wave_kernel<T, 1><<<G, kLnThreads, 0, s>>>(dy, x, g, mean, rstd, dres, dx, dx_lp, ws, N, d, want);
-  else if (d <= 512) layernorm_bwd_wave_kernel<T, 2><<<G, kLnThreads, 0, s>>>(dy, x, g, mean, rstd, dres, dx, dx_lp, ws, N, d, want);
-  else if (d <= 1024) layernorm_bwd_wave_kernel<T, 4><<<G, kLnThreads, 0, s>>>(dy, x, g, mean, rstd, dres, dx, dx_lp, ws, N, d, want);
-  else layernorm_bwd_wave_kernel<T, 8><<<G, kLnThreads, 0, s>>>(dy, x, g, mean, rstd, dres, dx, dx_lp, ws, N, d, want);
+  else layernorm_bwd_wave_kernel<T, 2><<<G, kLnThreads, 0, s>>>(dy, x, g, mean, rstd, dres, dx, dx_lp, ws, N, d, want);
 }
-
+constexpr int kLnBwdWaveMaxD = 512;
+// Rows that a block of the kernel for width d takes at a time: what its registers hold twice over.
+template <class T> constexpr int ln_bwd_rows(int d) { return d <= 1024 ? 4 : d > 4096 ? 1 : sizeof(T) == 2 ? 4 : 2; }
+template <class T>
+static void launch_ln_bwd_block(hipStream_t s, int G, const T* dy, const float* x, const float* g, const float* mean,
+                                const float* rstd, const float* dres, float* dx, T* dx_lp, float* ws, int N, int d, int want) {
+#define PW_LN_BWD(NT, VEC, ROWS) layernorm_bwd_kernel<T, NT, VEC, ROWS><<<G, NT, 0, s>>>(dy, x, g, mean, rstd, dres, dx, dx_lp, ws, N, d, want)
+  constexpr int R = ln_bwd_rows<T>(2048);
+  if (d <= 1024) PW_LN_BWD(256, 1, 4);
+  else if (d <= 2048) PW_LN_BWD(256, 2, R);
+  else if (d <= 4096) PW_LN_BWD(512, 2, R);
+  else PW_LN_BWD(1024, 2, 1);
+#undef PW_LN_BWD
+}
 // out[c] (=|+=) sum_{p < parts} ws[p*stride + c].  Block = 32 columns x 32 part-groups: group j adds parts
 // j, j+32, ... in order, then the 32 group sums are added in group order: a fixed tree, same bits every run.
 constexpr int kRpCols = 32, kRpGroups = 32;
@@ -389,17 +487,19 @@ hipError_t launch_layernorm_bwd(hipStream_t s, int dtype, const void* dy, const 
   const int want = dsum != nullptr;
   int G = ln_bwd_blocks(N);
   if (N > 0) {
-    if (d <= kLnWaveMaxD) {
-      const int by_rows = (N + kLnThreads / 64 - 1) / (kLnThreads / 64);
-      if (by_rows < G) G = by_rows;
+    const int per_block = dtype == kF32 ? ln_bwd_rows<float>(d) : ln_bwd_rows<bf16>(d);
+    const int by_rows = (N + per_block - 1) / per_block;
+    if (by_rows < G) G = by_rows;
+    if (d > 2048 && G > kLnBwdMaxBlocks / 2) G = kLnBwdMaxBlocks / 2;   // one of the larger blocks per compute unit
+    if (d <= kLnBwdWaveMaxD) {
       if (dtype == kF32)
         launch_ln_bwd_wave<float>(s, G, (const float*)dy, x, g, mean, rstd, dres, dx, (float*)dx_lp, ws, N, d, want);
       else
         launch_ln_bwd_wave<bf16>(s, G, (const bf16*)dy, x, g, mean, rstd, dres, dx, (bf16*)dx_lp, ws, N, d, want);
     } else if (dtype == kF32) {
-      layernorm_bwd_kernel<float><<<G, kLnThreads, 0, s>>>((const float*)dy, x, g, mean, rstd, dres, dx, (float*)dx_lp, ws, N, d, want);
+      launch_ln_bwd_block<float>(s, G, (const float*)dy, x, g, mean, rstd, dres, dx, (float*)dx_lp, ws, N, d, want);
     } else {
-      layernorm_bwd_kernel<bf16><<<G, kLnThreads, 0, s>>>((const bf16*)dy, x, g, mean, rstd, dres, dx, (bf16*)dx_lp, ws, N, d, want);
+      launch_ln_bwd_block<bf16>(s, G, (const bf16*)dy, x, g, mean, rstd, dres, dx, (bf16*)dx_lp, ws, N, d, want);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

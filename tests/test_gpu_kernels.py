@@ -379,6 +379,36 @@ def test_layernorm_forward_backward(ctx, orc, N, d, bf16):
 
 # ---- attention ----------------------------------------------------------------------------------------
 
+# the block kernel's widths (256, 512 and 1024 threads, one and two pieces each), one column group past each, and row counts
+# that make a block go round twice and end inside its last group of rows; every optional argument left out as well
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("N,d", [(1, 516), (2051, 1024), (2050, 1028), (6, 2052), (1031, 4096), (300, 4100), (2, 8188)])
+def test_layernorm_backward_in_blocks_of_rows(ctx, bf16, N, d):
+    x, g = _rand(81, (N, d)) + 0.3, 1.0 + _rand(82, (d,), 0.2)
+    (dy, dyv), dres = dev_act(_rand(83, (N, d)), bf16), _rand(84, (N, d))
+    xd, gd, rd = dev_f32(x), dev_f32(g), dev_f32(dres)
+    mu = x.astype(np.float64).mean(1)
+    rs = 1.0 / np.sqrt(x.astype(np.float64).var(1) + 1e-5)
+    md, sd = dev_f32(mu), dev_f32(rs)
+    ws = torch.empty(pwb.lib().pw_layernorm_bwd_ws_floats(N, d), device="cuda")
+    xh = (x - mu[:, None]) * rs[:, None]
+    gg = dyv * g
+    base = rs[:, None] * (gg - gg.mean(1, keepdims=True) - xh * (gg * xh).mean(1, keepdims=True))
+    for full in (True, False):
+        dx, lp = torch.empty((N, d), device="cuda"), empty_act((N, d), bf16)
+        dg, db, ds = (torch.full((d,), 2.0, device="cuda") for _ in range(3))
+        ctx.op("layernorm_bwd", DT[bf16], ptr(dy), ptr(xd), ptr(gd), ptr(md), ptr(sd), ptr(rd) if full else None, ptr(dx),
+               ptr(lp) if full else None, ptr(dg), ptr(db), ptr(ds) if full else None, ptr(ws), N, d, int(full))
+        ctx.synchronize()
+        want = base + dres if full else base
+        assert_close(host(dx), want, 2e-6 * (1 + np.sqrt(d) / 64))
+        assert_close(host(dg), (dyv * xh).sum(0) + 2.0 * full, 1e-5)
+        assert_close(host(db), dyv.sum(0) + 2.0 * full, 1e-5)
+        if full:
+            assert_close(host(lp), want, 4e-3 if bf16 else 1e-5)
+            assert_close(host(ds), want.sum(0) + 2.0, 1e-5)
+
+
 @pytest.mark.parametrize("bf16", [False, True])
 @pytest.mark.parametrize("B,T,H,hd", [(2, 200, 2, 64), (1, 130, 3, 128), (2, 1, 1, 64), (1, 384, 2, 128)])
 def test_attention_forward_backward(ctx, orc, B, T, H, hd, bf16):
