@@ -101,9 +101,11 @@ typedef struct {
 } pw_stage_params;
 
 typedef enum {
-  PW_STREAM = 0,      /* enqueue every function of the chain at once on the executor stream */
+  PW_STREAM = 0,      /* enqueue every function of the chain at once on the executor stream; functions that are plain
+                         arithmetic with a constant (PW_FN_ADD_CONST .. PW_FN_DIV_CONST) and follow one another share
+                         a launch, each rounding its result as on its own */
   PW_GRAPH = 1,       /* the same launches, captured once into a HIP graph and replayed (chains of fewer than 8
-                         single-kernel functions are enqueued as stream launches: a graph launch costs more) */
+                         launches of single-kernel functions are enqueued on the stream: a graph launch costs more) */
   PW_SEQUENTIAL = 2   /* wait for each function to complete before enqueuing the next: the
                          sequential-dispatch baseline of Section 5.1, for comparison only.  Its inputs must not
                          depend on an unresolved pending future: PW_ERR_NOT_READY, nothing enqueued */

@@ -60,6 +60,14 @@ struct GemmArgs {
 hipError_t launch_scalar_fn(hipStream_t s, int kind, const float* x, float* y, int64_t n, float c, float busy_us, int reps,
                             uint32_t* done = nullptr, uint32_t token = 0);
 bool scalar_fn_one_block(int64_t n);
+// The functions of a chain that are plain arithmetic with a constant (kinds 1 to 3 above), several to a launch.
+constexpr int kScalarOps = 128;
+struct ScalarOps {
+  struct { float c; int32_t kind; } op[kScalarOps];
+  int n;
+};
+hipError_t launch_scalar_chain(hipStream_t s, const ScalarOps& ops, const float* x, float* y, int64_t n,
+                               uint32_t* done = nullptr, uint32_t token = 0);
 hipError_t launch_add2(hipStream_t s, const float* a, const float* b, float* y, int64_t n);
 hipError_t launch_fill_f32(hipStream_t s, float* p, int64_t n, float v);
 hipError_t launch_f32_to_bf16(hipStream_t s, const float* src, void* dst, int64_t n);

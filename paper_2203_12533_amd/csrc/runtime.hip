@@ -142,6 +142,7 @@ void future_drop(pw_ctx* c, pw_future h) {
 
 
 bool is_scalar_kind(int k) { return k >= PW_FN_ADD_CONST && k <= PW_FN_BUSY_CHAIN; }   // one fp32 input, one output
+bool is_arithmetic_kind(int k) { return k >= PW_FN_ADD_CONST && k <= PW_FN_DIV_CONST; }   // ... and nothing but arithmetic
 
 // Launch the body of one function on the executor stream.  in/out are device pointers.
 // Whether a launch of fn can carry a completion word (see FutureRec::done).
@@ -602,12 +603,23 @@ pw_status pw_chain(pw_ctx* c, const pw_fn* fns, int n_fns, const pw_future* in, 
     if (!fin[i]) return fail(c, PW_ERR_INVALID, "input %d is not a live future", i);
     specs[i] = fin[i]->spec;
   }
-  // A HIP-graph launch has a fixed cost worth about eight stream launches of a trivial kernel: shorter chains of
-  // single-kernel functions are enqueued as stream launches (same launches, same results).
-  if (mode == PW_GRAPH && n_fns < 8) {
+  // Functions that are plain arithmetic with a constant, one behind the other, share a launch (up to kScalarOps of them):
+  // the intermediate values of a chain are never seen.  run_len(i): how many start at link i.  The sequential baseline
+  // keeps a launch per function.
+  auto run_len = [&](int i) {
+    int n = 1;
+    if (mode != PW_SEQUENTIAL && is_arithmetic_kind(recs[i]->desc.kind))
+      while (i + n < n_fns && n < kScalarOps && is_arithmetic_kind(recs[i + n]->desc.kind)) ++n;
+    return n;
+  };
+  // A HIP-graph launch has a fixed cost worth about eight stream launches of a trivial kernel: chains that come to fewer
+  // launches of single-kernel functions are enqueued as stream launches (same launches, same results).
+  if (mode == PW_GRAPH) {
     bool single_kernels = true;
-    for (int i = 0; i < n_fns; ++i) single_kernels = single_kernels && (is_scalar_kind(recs[i]->desc.kind) || recs[i]->desc.kind == PW_FN_ADD2);
-    if (single_kernels) mode = PW_STREAM;
+    int launches = 0;
+    for (int i = 0; i < n_fns && single_kernels && launches < 8; i += run_len(i), ++launches)
+      single_kernels = is_scalar_kind(recs[i]->desc.kind) || recs[i]->desc.kind == PW_FN_ADD2;
+    if (single_kernels && launches < 8) mode = PW_STREAM;
   }
   if (mode == PW_SEQUENTIAL) {
     // This baseline waits on the host for every link.  An input that hangs on an unresolved pending future would
@@ -671,9 +683,21 @@ pw_status pw_chain(pw_ctx* c, const pw_fn* fns, int n_fns, const pw_future* in, 
     void* obuf[8];
     for (int j = 0; j < n_in; ++j) ibuf[j] = fin[j]->buf;
     for (int i = 0; i < n_fns; ++i) {
+      const int run = run_len(i), first = i;
+      i += run - 1;                                    // the run's last link: its buffer receives the result
       for (size_t j = 0; j < plan_bufs[i].size(); ++j) obuf[j] = plan_bufs[i][j].p;
       const bool last = i + 1 == n_fns && done;
-      pw_status s2 = fn_launch(c, recs[i], ibuf, obuf, last ? done->words : nullptr, last ? done_token : 0);
+      pw_status s2 = PW_OK;
+      if (run > 1) {
+        ScalarOps ops;
+        ops.n = run;
+        for (int k = 0; k < run; ++k) ops.op[k] = {recs[first + k]->cst, recs[first + k]->desc.kind};
+        const hipError_t e = launch_scalar_chain(c->exec, ops, (const float*)ibuf[0], (float*)obuf[0], spec_numel(recs[i]->desc.in[0]),
+                                                 last ? done->words : nullptr, last ? done_token : 0);
+        if (e != hipSuccess) s2 = fail(c, PW_ERR_DEVICE, "scalar chain launch: %s", hipGetErrorString(e));
+      } else {
+        s2 = fn_launch(c, recs[i], ibuf, obuf, last ? done->words : nullptr, last ? done_token : 0);
+      }
       if (s2 != PW_OK) return s2;
       if (sync_each && hipStreamSynchronize(c->exec) != hipSuccess) return fail(c, PW_ERR_DEVICE, "stream synchronize failed");
       for (size_t j = 0; j < plan_bufs[i].size(); ++j) ibuf[j] = obuf[j];

@@ -139,6 +139,38 @@ def test_op_by_op_equals_chained(ctx, orc):
     ctx.future_release(f)
 
 
+# runs of arithmetic functions that share a launch: one, as many as one launch takes and one more, broken by a function of
+# another kind, in one and in several blocks; infinities, zeros, values that overflow and underflow on the way
+@pytest.mark.parametrize("mode", [pwb.PW_STREAM, pwb.PW_GRAPH])
+@pytest.mark.parametrize("n", [1, 128, 1000])
+@pytest.mark.parametrize("lengths", [(1, 2), (128,), (129,), (3, 1, 300), (20,) * 9])
+def test_chain_of_mixed_arithmetic_equals_its_functions_one_by_one(ctx, mode, n, lengths):
+    x = I.normal(5, 9, n, 1.0)
+    x[:min(n, 4)] = np.array([np.inf, 3e38, 1e-38, -0.0], np.float32)[:min(n, 4)]
+    fns = {k: [ctx.compile_scalar_fn(k, n, c) for c in (1.1, 3.0, 0.3)] for k in
+           (pwb.PW_FN_ADD_CONST, pwb.PW_FN_MUL_CONST, pwb.PW_FN_DIV_CONST)}
+    busy = ctx.compile_scalar_fn(pwb.PW_FN_BUSY, n, 0.5, busy_us=0.0)
+    chain = []
+    for r, length in enumerate(lengths):
+        kinds = [(j * 7 + r) % 9 for j in range(length)]
+        chain += ([busy] if r else []) + [fns[1 + k // 3][k % 3] for k in kinds]
+    f_in = f = ctx.future_from_host(x)
+    for fn in chain:
+        (g,) = ctx.run_fn(fn, [f])
+        if f != f_in:
+            ctx.future_release(f)
+        f = g
+    want = ctx.await_(f)
+    for _ in range(2):
+        (out,) = ctx.chain(chain, [f_in], 1, mode)
+        assert np.array_equal(ctx.await_(out).view(np.uint32), want.view(np.uint32))
+        ctx.future_release(out)
+    ctx.future_release(f)
+    ctx.future_release(f_in)
+    for fn in [busy] + sum(fns.values(), []):
+        ctx.fn_release(fn)
+
+
 def test_figure2_program_with_fan_out(ctx):
     rows = {}
     for line in open(os.path.join(GOLD, "fig2_example.txt")):
