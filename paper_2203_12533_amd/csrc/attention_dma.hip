@@ -24,6 +24,10 @@
 // been computed in fp32.  Measured (us, forward and backward): 4 x 333 queries over 520 keys, 8 heads: 116 on the fp32
 // matrix pipe -> 53; 2 x 2014 over 1092, 9 heads: 189.  Packed causal, 4 x 1000, 12 heads: 131 with tiles staged through
 // registers and a transposed copy in LDS -> 85.
+// PARTS = 2, for few blocks: a wave alone takes 1.2 to 1.5 us per step whatever else the chip does (products, softmax and
+// barrier one behind the other), so a launch that leaves units idle, or whose causal mask gives one block twice the average,
+// lasts as long as its longest chain of steps.  Blocks of 64 rows then, two waves to 32 of them that take the halves of every
+// tile in turn and add up through LDS at the end: half the steps, in the same fp32 sums.  The two above: 53 -> 43.5, 85 -> 73.8.
 // Rows past the end of a sequence are fetched from its last valid row (always in bounds); every use of such
 // a row is masked (causality, or the explicit key-index mask of the unmasked variant) or multiplied by an exact
 // zero (P = exp2(-inf)).
@@ -181,25 +185,52 @@ __device__ __forceinline__ void wait_and_sync() {
   asm volatile("" ::: "memory");
 }
 
+// Where two waves hold partial sums of the same rows (PARTS = 2): the second one's go through LDS to the first.
+// box: this lane's word of a [HD / 2][64] array that both waves of a pair share.
+template <int HD>
+__device__ __forceinline__ void put_acc(float* box, const f32x16* acc) {
+#pragma unroll
+  for (int cb = 0; cb < HD / 32; ++cb)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) box[(cb * 16 + r) * 64] = acc[cb][r];
+}
+// acc of part 0 += acc of part 1; true in the waves that hold the result.  Called by the whole workgroup.
+template <int HD>
+__device__ __forceinline__ bool sum_parts(float* box, int part, f32x16* acc) {
+  __syncthreads();
+  if (part == 1) put_acc<HD>(box, acc);
+  __syncthreads();
+  if (part == 1) return false;
+#pragma unroll
+  for (int cb = 0; cb < HD / 32; ++cb)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[cb][r] += box[(cb * 16 + r) * 64];
+  return true;
+}
+
+// Tile rows per wave and iteration in the forward and dQ kernels.
+template <int HD, int PARTS> constexpr int kSubRows = HD == 128 && PARTS == 2 ? 32 : 64;
+
 // ===================================================================================================
 // forward: block = 128 queries of one (batch, head); wave = 32 queries; key/value tiles of 64
 // ===================================================================================================
-template <int HD, bool CAUSAL, bool SPLIT>
+template <int HD, bool CAUSAL, bool SPLIT, int PARTS>
 __global__ __launch_bounds__(kNT, 2) void attn_fwd_dma_kernel(MhaDev a, bf16* __restrict__ o, bf16* __restrict__ o_lo,
                                                               float* __restrict__ lse) {
-  constexpr int BKV = 64;
+  constexpr int kSub = kSubRows<HD, PARTS>, BKV = kSub * PARTS, kRows = 128 / PARTS;
   constexpr int kTile = BKV * HD;                       // elements per K (or V) tile
   extern __shared__ __attribute__((aligned(1024))) bf16 smem[];         // [stage][K | V]
   const int Tq = a.Tq, Tk = a.Tk, H = a.H;
   const int d = H * HD;
   const int64_t ld = a.ldkv;
-  const int nq = (Tq + 127) / 128;
+  const int nq = (Tq + kRows - 1) / kRows;
   int bh, qi;
   xcd_block_map(blockIdx.x, gridDim.x, nq, CAUSAL ? causal_group(nq, 64) : 1, bh, qi);
   const int b = bh / H, h = bh - b * H;
   const int qblk = CAUSAL ? nq - 1 - qi : qi;           // causal: longest blocks of a problem first
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, half = lane >> 5;
-  const int q0 = qblk * 128 + wave * 32;
+  const int part = PARTS == 1 ? 0 : wave >> 1;         // which kSub rows of every tile are this wave's
+  const int q0 = qblk * kRows + (PARTS == 1 ? wave : wave & 1) * 32;
   const int query = q0 + (lane & 31);
   const bf16* qbase = a.q + (int64_t)b * Tq * a.ldq + h * HD;
   const bf16* kbase = a.k + (int64_t)b * Tk * ld + h * HD;
@@ -216,7 +247,7 @@ __global__ __launch_bounds__(kNT, 2) void attn_fwd_dma_kernel(MhaDev a, bf16* __
     for (int r = 0; r < 16; ++r) acc[cb][r] = 0.f;
   float m = -INFINITY, l = 0.f;
 
-  const int last_q = min(Tq, (qblk + 1) * 128) - 1;
+  const int last_q = min(Tq, (qblk + 1) * kRows) - 1;
   const int n_tiles = CAUSAL ? last_q / BKV + 1 : (Tk + BKV - 1) / BKV;
   TileOffsets<BKV, HD> to;
   to.init(ld, wave, lane);
@@ -227,35 +258,39 @@ __global__ __launch_bounds__(kNT, 2) void attn_fwd_dma_kernel(MhaDev a, bf16* __
   };
   issue(0);
   for (int t = 0; t < n_tiles; ++t) {
-    const int j0 = t * BKV;
+    const int j0 = t * BKV + part * kSub;
     wait_and_sync();
     if (t + 1 < n_tiles) issue(t + 1);
-    if (CAUSAL && j0 > q0 + 31) continue;   // every key of the tile lies in this wave's future
-    const bf16* Ks = smem + (t & 1) * (2 * kTile);
+    if (CAUSAL ? j0 > q0 + 31 : PARTS > 1 && j0 >= Tk) continue;   // no key of the tile is this wave's to see
+    const bf16* Ks = smem + (t & 1) * (2 * kTile) + part * (kSub * HD);
     const bf16* Vs = Ks + kTile;
-    f32x16 s[2];
+    f32x16 s[kSub / 32];
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb) s[kb] = first_product<HD>(Ks, kb * 32, qf);
+    for (int kb = 0; kb < kSub / 32; ++kb) s[kb] = first_product<HD>(Ks, kb * 32, qf);
     // last visible key of this lane's query: itself (causal), else the last key there is
     const int last_key = CAUSAL ? query : Tk - 1;
-    if (CAUSAL ? j0 + BKV - 1 > q0 : j0 + BKV > Tk) {   // the tile straddles the diagonal / the end of the keys
+    if (CAUSAL ? j0 + kSub - 1 > q0 : j0 + kSub > Tk) {   // the tile straddles the diagonal / the end of the keys
 #pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
+      for (int kb = 0; kb < kSub / 32; ++kb)
 #pragma unroll
         for (int r = 0; r < 16; ++r)
           if (j0 + kb * 32 + reg_row(r, half) > last_key) s[kb][r] = -INFINITY;
     }
-    float mx = max3(s[0][0], s[1][0], s[0][1]);
+    float mx = max3(s[0][0], s[0][1], s[0][2]);
 #pragma unroll
-    for (int r = 1; r < 15; ++r) mx = max3(mx, s[1][r], s[0][r + 1]);
-    mx = max3(mx, s[1][15], s[1][15]);
+    for (int r = 3; r < 15; r += 2) mx = max3(mx, s[0][r], s[0][r + 1]);
+    if constexpr (kSub == 64) {
+#pragma unroll
+      for (int r = 0; r < 16; r += 2) mx = max3(mx, s[1][r], s[1][r + 1]);
+    }
+    mx = max3(mx, s[0][15], s[0][15]);
     const float other = __shfl_xor(mx, 32, 64);
     mx = max3(mx, other, other) * c2;
     // Lazy rescaling: the running reference m only has to bound the exponents, not equal the maximum.  It is moved (and the
     // accumulators rescaled) only when some row's maximum grew by more than 2^8; otherwise exp2(s - m) <= 256.
     if (__builtin_amdgcn_ballot_w64(mx > m + 8.f) != 0) {
       const float m_new = fmaxf(m, mx);
-      const float alpha = __builtin_amdgcn_exp2f(m - m_new);
+      const float alpha = PARTS > 1 && m == m_new ? 1.f : __builtin_amdgcn_exp2f(m - m_new);   // (both -inf: see ref)
       m = m_new;
       l *= alpha;
 #pragma unroll
@@ -263,22 +298,43 @@ __global__ __launch_bounds__(kNT, 2) void attn_fwd_dma_kernel(MhaDev a, bf16* __
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[cb][r] *= alpha;
     }
+    // (a part that has met nothing but -inf so far takes its zeros to the other part)
+    const float ref = PARTS > 1 && m == -INFINITY ? 0.f : m;
     float sum = 0.f;
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
+    for (int kb = 0; kb < kSub / 32; ++kb)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const float p = __builtin_amdgcn_exp2f(fmaf(s[kb][r], c2, -m));
+        const float p = __builtin_amdgcn_exp2f(fmaf(s[kb][r], c2, -ref));
         s[kb][r] = p;
         sum += p;
       }
     l += sum;
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
+    for (int kb = 0; kb < kSub / 32; ++kb)
 #pragma unroll
       for (int b2 = 0; b2 < 2; ++b2) second_product<HD, SPLIT>(Vs, kb * 32 + b2 * 16, pack_frag<SPLIT>(s[kb], b2 * 8), acc);
   }
   l += __shfl_xor(l, 32, 64);
+  if constexpr (PARTS > 1) {   // the second part hands its reference, sum and accumulators over through LDS
+    float* const box = reinterpret_cast<float*>(smem) + (wave & 1) * ((HD / 2 + 2) * 64) + lane;
+    __syncthreads();
+    if (part == 1) {
+      put_acc<HD>(box, acc);
+      box[(HD / 2) * 64] = m;
+      box[(HD / 2 + 1) * 64] = l;
+    }
+    __syncthreads();
+    if (part == 1) return;
+    const float m1 = box[(HD / 2) * 64], top = fmaxf(m, m1);
+    const float w0 = m == top ? 1.f : __builtin_amdgcn_exp2f(m - top), w1 = m1 == top ? 1.f : __builtin_amdgcn_exp2f(m1 - top);
+    m = top;
+    l = l * w0 + box[(HD / 2 + 1) * 64] * w1;
+#pragma unroll
+    for (int cb = 0; cb < HD / 32; ++cb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[cb][r] = acc[cb][r] * w0 + box[(cb * 16 + r) * 64] * w1;
+  }
   if (query < Tq) {
     const int64_t row = ((int64_t)b * Tq + query) * d + h * HD;
     if (o_lo)
@@ -295,23 +351,24 @@ __global__ __launch_bounds__(kNT, 2) void attn_fwd_dma_kernel(MhaDev a, bf16* __
 // It also produces delta_i = sum_c dO_ic O_ic for its queries (each wave has the dO fragments of its 32 rows in
 // registers anyway; O, plus the optional rounding remainder o_lo, is read the same way once) and leaves it in
 // `delta` for the dK/dV kernel, which is launched behind this one.
-template <int HD, bool CAUSAL, bool SPLIT>
+template <int HD, bool CAUSAL, bool SPLIT, int PARTS>
 __global__ __launch_bounds__(kNT, 2) void attn_dq_dma_kernel(MhaDev a, const bf16* __restrict__ o, const bf16* __restrict__ o_lo,
                                                              const bf16* __restrict__ dout, const float* __restrict__ lse,
                                                              float* __restrict__ delta, bf16* __restrict__ dq, int64_t lddq) {
-  constexpr int BKV = 64;
+  constexpr int kSub = kSubRows<HD, PARTS>, BKV = kSub * PARTS, kRows = 128 / PARTS;
   constexpr int kTile = BKV * HD;
   extern __shared__ __attribute__((aligned(1024))) bf16 smem[];
   const int Tq = a.Tq, Tk = a.Tk, H = a.H;
   const int d = H * HD;
   const int64_t ld = a.ldkv;
-  const int nq = (Tq + 127) / 128;
+  const int nq = (Tq + kRows - 1) / kRows;
   int bh, qi;
   xcd_block_map(blockIdx.x, gridDim.x, nq, CAUSAL ? causal_group(nq, 64) : 1, bh, qi);
   const int b = bh / H, h = bh - b * H;
   const int qblk = CAUSAL ? nq - 1 - qi : qi;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, half = lane >> 5;
-  const int q0 = qblk * 128 + wave * 32;
+  const int part = PARTS == 1 ? 0 : wave >> 1;         // which kSub rows of every tile are this wave's
+  const int q0 = qblk * kRows + (PARTS == 1 ? wave : wave & 1) * 32;
   const int query = q0 + (lane & 31);
   const bf16* qbase = a.q + (int64_t)b * Tq * a.ldq + h * HD;
   const bf16* kbase = a.k + (int64_t)b * Tk * ld + h * HD;
@@ -346,7 +403,7 @@ __global__ __launch_bounds__(kNT, 2) void attn_dq_dma_kernel(MhaDev a, const bf1
 #pragma unroll
     for (int r = 1; r < 16; ++r) dl = reg == r ? od[r] : dl;
     dl = __shfl(dl, i + 32 * ((i >> 2) & 1), 64);
-    if (half == 0 && query < Tq) delta[(int64_t)bh * Tq + query] = dl;
+    if (half == 0 && part == 0 && query < Tq) delta[(int64_t)bh * Tq + query] = dl;
   }
   f32x16 acc[HD / 32];
 #pragma unroll
@@ -354,7 +411,7 @@ __global__ __launch_bounds__(kNT, 2) void attn_dq_dma_kernel(MhaDev a, const bf1
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[cb][r] = 0.f;
 
-  const int last_q = min(Tq, (qblk + 1) * 128) - 1;
+  const int last_q = min(Tq, (qblk + 1) * kRows) - 1;
   const int n_tiles = CAUSAL ? last_q / BKV + 1 : (Tk + BKV - 1) / BKV;
   const int last_key = CAUSAL ? query : Tk - 1;
   TileOffsets<BKV, HD> to;
@@ -366,15 +423,15 @@ __global__ __launch_bounds__(kNT, 2) void attn_dq_dma_kernel(MhaDev a, const bf1
   };
   issue(0);
   for (int t = 0; t < n_tiles; ++t) {
-    const int j0 = t * BKV;
+    const int j0 = t * BKV + part * kSub;
     wait_and_sync();
     if (t + 1 < n_tiles) issue(t + 1);
-    if (CAUSAL && j0 > q0 + 31) continue;
-    const bf16* Ks = smem + (t & 1) * (2 * kTile);
+    if (CAUSAL ? j0 > q0 + 31 : PARTS > 1 && j0 >= Tk) continue;
+    const bf16* Ks = smem + (t & 1) * (2 * kTile) + part * (kSub * HD);
     const bf16* Vs = Ks + kTile;
-    const bool diag = CAUSAL ? j0 + BKV - 1 > q0 : j0 + BKV > Tk;
+    const bool diag = CAUSAL ? j0 + kSub - 1 > q0 : j0 + kSub > Tk;
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
+    for (int kb = 0; kb < kSub / 32; ++kb) {
       f32x16 s = first_product<HD>(Ks, kb * 32, qf);      // S^T
       f32x16 dp = first_product<HD>(Vs, kb * 32, gf);     // dP^T = V . dO^T
       if (diag) {
@@ -388,6 +445,8 @@ __global__ __launch_bounds__(kNT, 2) void attn_dq_dma_kernel(MhaDev a, const bf1
       for (int b2 = 0; b2 < 2; ++b2) second_product<HD, SPLIT>(Ks, kb * 32 + b2 * 16, pack_frag<SPLIT>(s, b2 * 8), acc);   // dQ^T += K^T . dS^T
     }
   }
+  if constexpr (PARTS > 1)
+    if (!sum_parts<HD>(reinterpret_cast<float*>(smem) + (wave & 1) * (HD / 2 * 64) + lane, part, acc)) return;
   if (query < Tq) store_row<HD>(dq + ((int64_t)b * Tq + query) * lddq + h * HD, acc, scale);
 }
 
@@ -516,11 +575,11 @@ __device__ __forceinline__ void dkv_back(const bf16* __restrict__ Qs, const bf16
   }
 }
 
-template <int HD, bool CAUSAL, bool SPLIT>
+template <int HD, bool CAUSAL, bool SPLIT, int PARTS>
 __global__ __launch_bounds__(kNT, HD == 64 ? 2 : 1) void attn_dkv_dma_kernel(MhaDev a, const bf16* __restrict__ dout,
                                                             const float* __restrict__ lse, const float* __restrict__ delta,
                                                             bf16* __restrict__ dk_out, bf16* __restrict__ dv_out, int64_t lddkv) {
-  constexpr int BQ = 64, kStages = 3;
+  constexpr int BQ = 64, kStages = 3, kRows = 128 / PARTS;
   constexpr int kTile = BQ * HD;
   extern __shared__ __attribute__((aligned(1024))) bf16 smem[];          // [stage][Q | dO], then the statistics
   float (*Ls)[BQ] = reinterpret_cast<float (*)[BQ]>(smem + kStages * 2 * kTile);
@@ -529,10 +588,12 @@ __global__ __launch_bounds__(kNT, HD == 64 ? 2 : 1) void attn_dkv_dma_kernel(Mha
   const int d = H * HD;
   const int64_t ld = a.ldq;
   int bh, kblk;                                         // causal: first key blocks see the most queries, they come first
-  xcd_block_map(blockIdx.x, gridDim.x, (Tk + 127) / 128, CAUSAL ? causal_group((Tk + 127) / 128, 32) : 1, bh, kblk);
+  const int nk = (Tk + kRows - 1) / kRows;
+  xcd_block_map(blockIdx.x, gridDim.x, nk, CAUSAL ? causal_group(nk, 32) : 1, bh, kblk);
   const int b = bh / H, h = bh - b * H;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, half = lane >> 5;
-  const int k0 = kblk * 128 + wave * 32;
+  const int part = PARTS == 1 ? 0 : wave >> 1;          // which 32 rows of every tile are this wave's (PARTS = 1: all 64)
+  const int k0 = kblk * kRows + (PARTS == 1 ? wave : wave & 1) * 32;
   const int key = k0 + (lane & 31);
   const bf16* qbase = a.q + (int64_t)b * T * ld + h * HD;
   const bf16* gbase = dout + (int64_t)b * T * d + h * HD;
@@ -555,7 +616,7 @@ __global__ __launch_bounds__(kNT, HD == 64 ? 2 : 1) void attn_dkv_dma_kernel(Mha
       dv[cb][r] = 0.f;
     }
 
-  const int first_tile = CAUSAL ? (kblk * 128) / BQ : 0;
+  const int first_tile = CAUSAL ? (kblk * kRows) / BQ : 0;
   const int n_tiles = (T + BQ - 1) / BQ;
   // A tile = 64 rows of Q and of dO plus the 64 queries' log-sum-exp and delta; all of it travels global -> LDS
   // directly (no destination registers: the compiler then has no pending load to wait for in the middle of the
@@ -608,11 +669,12 @@ __global__ __launch_bounds__(kNT, HD == 64 ? 2 : 1) void attn_dkv_dma_kernel(Mha
   DkvStats st;
   // One step of the pipeline: the arithmetic of block n (scores in s, dp) between the first products of block n + 1
   // (into sn, dpn; NEXT: there is one), then the second products of block n.
+  // The block behind block n of this wave is n + 1, or, where the other part has that one, n + 2.
   auto step = [&](int n, auto next, f32x16& s, f32x16& dp, f32x16& sn, f32x16& dpn) {
     constexpr bool NEXT = decltype(next)::value;
-    const int hb = n & 1, t = n >> 1;
+    const int hb = n & 1, nn = n + PARTS;
     const bf16* Qs = tile_q(n);
-    const bf16* Qn = tile_q(n + 1);
+    const bf16* Qn = tile_q(nn);
     // st holds the block's raw statistics, read from LDS during the previous step
 #pragma unroll
     for (int r = 0; r < 16; ++r) st.lq[r] *= kLog2e;
@@ -635,9 +697,9 @@ __global__ __launch_bounds__(kNT, HD == 64 ? 2 : 1) void attn_dkv_dma_kernel(Mha
         asm volatile("" : "+v"(st.lq[r]));
       }
     }
-    dkv_front<HD, SPLIT, NEXT, true>(Qn, Qn + kTile, (hb ^ 1) * 32, kf, vf, sn, dpn, s, dp, st, c2, pf, dsf);
+    dkv_front<HD, SPLIT, NEXT, true>(Qn, Qn + kTile, (nn & 1) * 32, kf, vf, sn, dpn, s, dp, st, c2, pf, dsf);
     // the next block's statistics travel to registers under the second products (its tile is resident: see advance)
-    if (NEXT) load_stats(Ls[((n + 1) >> 1) % kStages], Ds[((n + 1) >> 1) % kStages], hb ^ 1, half, st);
+    if (NEXT) load_stats(Ls[(nn >> 1) % kStages], Ds[(nn >> 1) % kStages], nn & 1, half, st);
     dkv_back<HD, SPLIT>(Qs, Qs + kTile, hb * 32, pf, dsf, dk, dv);
     // Register classes: the output accumulators and the K / V fragments are only ever touched by MFMAs and live in
     // the accumulation registers; the scores are worked on by the vector ALU and stay in ordinary registers, so no
@@ -651,23 +713,46 @@ __global__ __launch_bounds__(kNT, HD == 64 ? 2 : 1) void attn_dkv_dma_kernel(Mha
   };
   using yes = std::integral_constant<bool, true>;
   using no = std::integral_constant<bool, false>;
-  int t0 = first_tile;
-  bool any = true;
-  if (CAUSAL && wave >= 2) {             // this wave's first tile is the next one
-    any = first_tile + 1 < n_tiles;
-    if (any) advance(first_tile);
-    t0 = first_tile + 1;
-  }
-  if (any) {
-    load_stats(Ls[t0 % kStages], Ds[t0 % kStages], 0, half, st);
-    dkv_front<HD, SPLIT, true, false>(tile_q(2 * t0), tile_q(2 * t0) + kTile, 0, kf, vf, s0, dp0, s0, dp0, st, c2, pf, dsf);
-    for (int t = t0; t + 1 < n_tiles; ++t) {
-      step(2 * t, yes{}, s0, dp0, s1, dp1);
-      advance(t);
-      step(2 * t + 1, yes{}, s1, dp1, s0, dp0);
+  if constexpr (PARTS == 1) {
+    int t0 = first_tile;
+    bool any = true;
+    if (CAUSAL && wave >= 2) {             // this wave's first tile is the next one
+      any = first_tile + 1 < n_tiles;
+      if (any) advance(first_tile);
+      t0 = first_tile + 1;
     }
-    step(2 * (n_tiles - 1), yes{}, s0, dp0, s1, dp1);
-    step(2 * (n_tiles - 1) + 1, no{}, s1, dp1, s0, dp0);
+    if (any) {
+      load_stats(Ls[t0 % kStages], Ds[t0 % kStages], 0, half, st);
+      dkv_front<HD, SPLIT, true, false>(tile_q(2 * t0), tile_q(2 * t0) + kTile, 0, kf, vf, s0, dp0, s0, dp0, st, c2, pf, dsf);
+      for (int t = t0; t + 1 < n_tiles; ++t) {
+        step(2 * t, yes{}, s0, dp0, s1, dp1);
+        advance(t);
+        step(2 * t + 1, yes{}, s1, dp1, s0, dp0);
+      }
+      step(2 * (n_tiles - 1), yes{}, s0, dp0, s1, dp1);
+      step(2 * (n_tiles - 1) + 1, no{}, s1, dp1, s0, dp0);
+    }
+  } else {
+    // One block per tile and wave, the next one in the next tile: every step is led by the wait for it.
+    load_stats(Ls[first_tile % kStages], Ds[first_tile % kStages], part, half, st);
+    dkv_front<HD, SPLIT, true, false>(tile_q(2 * first_tile), tile_q(2 * first_tile) + kTile, part * 32, kf, vf, s0, dp0, s0, dp0, st, c2, pf, dsf);
+    int t = first_tile;
+    for (; t + 2 < n_tiles; t += 2) {
+      advance(t);
+      step(2 * t + part, yes{}, s0, dp0, s1, dp1);
+      advance(t + 1);
+      step(2 * t + 2 + part, yes{}, s1, dp1, s0, dp0);
+    }
+    if (t + 1 < n_tiles) {
+      advance(t);
+      step(2 * t + part, yes{}, s0, dp0, s1, dp1);
+      step(2 * t + 2 + part, no{}, s1, dp1, s0, dp0);
+    } else {
+      step(2 * t + part, no{}, s0, dp0, s1, dp1);
+    }
+    float* const box = reinterpret_cast<float*>(smem) + (wave & 1) * (HD / 2 * 64) + lane;
+    (void)sum_parts<HD>(box, part, dk);
+    if (!sum_parts<HD>(box, part, dv)) return;
   }
   if (key < Tk) {
     const int64_t row = ((int64_t)b * Tk + key) * lddkv + h * HD;
@@ -679,31 +764,36 @@ __global__ __launch_bounds__(kNT, HD == 64 ? 2 : 1) void attn_dkv_dma_kernel(Mha
 }  // namespace
 
 // Dynamic LDS: two stages of two 64-row tiles (64 KiB at head_dim 128); dK/dV three stages and their statistics (97.5 KiB).
-template <int HD> constexpr int kSmemTiles = 2 * 2 * 64 * HD * 2;
+template <int HD, int PARTS> constexpr int kSmemTiles = 2 * 2 * kSubRows<HD, PARTS> * PARTS * HD * 2;
 template <int HD> constexpr int kSmemDkv = 3 * 2 * 64 * HD * 2 + 6 * 64 * 4;
 
-template <int HD, bool CAUSAL, bool SPLIT>
+template <int HD, bool CAUSAL, bool SPLIT, int PARTS>
 static hipError_t prepare_dma() {
   const struct { const void* fn; int bytes; } all[] = {
-      {reinterpret_cast<const void*>(attn_fwd_dma_kernel<HD, CAUSAL, SPLIT>), kSmemTiles<HD>},
-      {reinterpret_cast<const void*>(attn_dq_dma_kernel<HD, CAUSAL, SPLIT>), kSmemTiles<HD>},
-      {reinterpret_cast<const void*>(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT>), kSmemDkv<HD>}};
+      {reinterpret_cast<const void*>(attn_fwd_dma_kernel<HD, CAUSAL, SPLIT, PARTS>), kSmemTiles<HD, PARTS>},
+      {reinterpret_cast<const void*>(attn_dq_dma_kernel<HD, CAUSAL, SPLIT, PARTS>), kSmemTiles<HD, PARTS>},
+      {reinterpret_cast<const void*>(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, PARTS>), kSmemDkv<HD>}};
   for (const auto& k : all) {
     const hipError_t e = hipFuncSetAttribute(k.fn, hipFuncAttributeMaxDynamicSharedMemorySize, k.bytes);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
 }
+template <int HD, bool CAUSAL, bool SPLIT>
+static hipError_t prepare_parts() {
+  const hipError_t e = prepare_dma<HD, CAUSAL, SPLIT, 1>();
+  return e != hipSuccess ? e : prepare_dma<HD, CAUSAL, SPLIT, 2>();
+}
 
 // Raises the dynamic-LDS limit of the kernels (once; called at context creation, never inside a capture).
 hipError_t attention_dma_init() {
   static bool done = false;
   if (done) return hipSuccess;
-  hipError_t e = prepare_dma<128, true, false>();
-  if (e == hipSuccess) e = prepare_dma<128, false, false>();
-  if (e == hipSuccess) e = prepare_dma<64, true, false>();
-  if (e == hipSuccess) e = prepare_dma<64, true, true>();
-  if (e == hipSuccess) e = prepare_dma<64, false, true>();
+  hipError_t e = prepare_parts<128, true, false>();
+  if (e == hipSuccess) e = prepare_parts<128, false, false>();
+  if (e == hipSuccess) e = prepare_parts<64, true, false>();
+  if (e == hipSuccess) e = prepare_parts<64, true, true>();
+  if (e == hipSuccess) e = prepare_parts<64, false, true>();
   if (e == hipSuccess) done = true;
   return e;
 }
@@ -719,10 +809,29 @@ bool mha_dma_supported(const MhaArgs& a) {
   return a.ldq % 8 == 0 && a.ldkv % 8 == 0;
 }
 
+// (problem, block) pairs, see xcd_block_map
+template <int PARTS> static int blocks_of(int rows, const MhaArgs& a) { return (rows + 128 / PARTS - 1) / (128 / PARTS) * a.B * a.H; }
+// Whether two waves share 32 rows (PARTS = 2: blocks of 64 rows, half the steps each, every tile loaded twice as often).
+// It pays where the blocks of 128 leave compute units idle (twice as many still find one each: 128 of them), and under the
+// causal mask also up to a block per unit (two at head_dim 64, where units hold several), since the longest blocks, twice the
+// average, then decide - if those are long.  Both ways in us:
+//   forward: causal 2 x 1024, 16 x 128 28.4 -> 24.8; 4 x 1000, 12 x 64 23.8 -> 20.4; 4 x 2048, 8 x 64 42.1 -> 34.5; but 8 x 1000, 12 x 64
+//     (768 blocks) 31 -> 35, 16 x 256, 16 x 64 11.9 -> 14.6, 8 x 1024, 16 x 128 58 -> 74.  Unmasked, 4 x 1024, 8 x 64 (256) 26.9 -> 23.2, 4 x
+//     333 over 520 15.7 -> 11.0; but 16 x 512 (512) 25.3 -> 25.5, 4 x 1024, 16 x 64 40.2 -> 41.7.
+//   dQ (with dK/dV): causal 2 x 1024, 16 x 128 70.6 -> 66.0, 2 x 1024, 16 x 64 59.7 -> 54.7; 32 x 128, 12 x 64 23.5 -> 27.2.  Unmasked, 1 x 1000 over
+//     2000, 16 x 128 (128) 93 -> 81; 4 x 700 over 500, 8 x 128 (192) 50.0 -> 51.9.
+//   dK/dV (with dQ): causal 4 x 1000, 12 x 64 62.6 -> 53.4, 1 x 1024, 8 x 128 65.9 -> 53.9; 3 x 700, 12 x 128 (216) 53.8 -> 59.6.  Unmasked, 1 x 2048 over
+//     256, 16 x 128 (32) 83 -> 60.6, 4 x 700 over 500 (128) 50.0 -> 43.9; 4 x 333 over 520, 8 x 64 (160) 37.9 -> 39.8.
+static bool two_parts(const MhaArgs& a, int rows, int other, int unmasked_limit, int causal_limit) {
+  const int blocks = blocks_of<1>(rows, a);
+  return blocks <= (a.causal ? (other >= 384 ? causal_limit : 128) : unmasked_limit);
+}
+
 template <int HD, bool CAUSAL, bool SPLIT>
 static hipError_t fwd_dma(hipStream_t s, const MhaArgs& a, void* o, void* o_lo, float* lse) {
-  const int grid = ((a.Tq + 127) / 128) * a.B * a.H;          // (problem, block) pairs, see xcd_block_map
-  attn_fwd_dma_kernel<HD, CAUSAL, SPLIT><<<grid, kNT, kSmemTiles<HD>, s>>>(dev_of(a), (bf16*)o, (bf16*)o_lo, lse);
+  auto run = [&](auto kernel, int grid, int lds) { kernel<<<grid, kNT, lds, s>>>(dev_of(a), (bf16*)o, (bf16*)o_lo, lse); };
+  if (two_parts(a, a.Tq, a.Tk, 256, HD == 64 ? 512 : 256)) run(attn_fwd_dma_kernel<HD, CAUSAL, SPLIT, 2>, blocks_of<2>(a.Tq, a), kSmemTiles<HD, 2>);
+  else run(attn_fwd_dma_kernel<HD, CAUSAL, SPLIT, 1>, blocks_of<1>(a.Tq, a), kSmemTiles<HD, 1>);
   return hipGetLastError();
 }
 // exact: probabilities enter the products with V, K, Q and dO as fp32 would (head_dim 64 only).
@@ -737,11 +846,16 @@ hipError_t launch_mha_fwd_dma(hipStream_t s, const MhaArgs& a, void* o, void* o_
 struct MhaGrads { const void *o, *o_lo, *dout; const float* lse; float* delta; void* dq; int64_t lddq; void *dk, *dv; int64_t lddkv; };
 template <int HD, bool CAUSAL, bool SPLIT>
 static hipError_t bwd_dma(hipStream_t s, const MhaArgs& a, const MhaGrads& g) {
-  const int grid_q = ((a.Tq + 127) / 128) * a.B * a.H, grid_k = ((a.Tk + 127) / 128) * a.B * a.H;
-  attn_dq_dma_kernel<HD, CAUSAL, SPLIT><<<grid_q, kNT, kSmemTiles<HD>, s>>>(
-      dev_of(a), (const bf16*)g.o, (const bf16*)g.o_lo, (const bf16*)g.dout, g.lse, g.delta, (bf16*)g.dq, g.lddq);
-  attn_dkv_dma_kernel<HD, CAUSAL, SPLIT><<<grid_k, kNT, kSmemDkv<HD>, s>>>(
-      dev_of(a), (const bf16*)g.dout, g.lse, g.delta, (bf16*)g.dk, (bf16*)g.dv, g.lddkv);
+  auto run_q = [&](auto kernel, int grid, int lds) {
+    kernel<<<grid, kNT, lds, s>>>(dev_of(a), (const bf16*)g.o, (const bf16*)g.o_lo, (const bf16*)g.dout, g.lse, g.delta, (bf16*)g.dq, g.lddq);
+  };
+  if (two_parts(a, a.Tq, a.Tk, 128, HD == 64 ? 512 : 256)) run_q(attn_dq_dma_kernel<HD, CAUSAL, SPLIT, 2>, blocks_of<2>(a.Tq, a), kSmemTiles<HD, 2>);
+  else run_q(attn_dq_dma_kernel<HD, CAUSAL, SPLIT, 1>, blocks_of<1>(a.Tq, a), kSmemTiles<HD, 1>);
+  auto run_kv = [&](auto kernel, int grid) {
+    kernel<<<grid, kNT, kSmemDkv<HD>, s>>>(dev_of(a), (const bf16*)g.dout, g.lse, g.delta, (bf16*)g.dk, (bf16*)g.dv, g.lddkv);
+  };
+  if (two_parts(a, a.Tk, a.Tq, 128, HD == 64 ? 512 : 128)) run_kv(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, 2>, blocks_of<2>(a.Tk, a));
+  else run_kv(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, 1>, blocks_of<1>(a.Tk, a));
   return hipGetLastError();
 }
 bool mha_dma_outputs_aligned(const void* dq, int64_t lddq, const void* dk, const void* dv, int64_t lddkv) {

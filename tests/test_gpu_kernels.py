@@ -581,6 +581,33 @@ def test_bf16_attention_at_head_width_64_is_exact_up_to_its_storage(ctx, Tq, Tk,
     assert rel_l2(host(o) + host(o_lo), flat(ro)) < 2e-5
 
 
+# bf16 blocks of 64 rows whose tiles two waves share (few blocks), and of 128 (many): one row to either side of a block, a
+# tile and a wave's part of it; a second wave with nothing to do
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("B,Tq,Tk,H,causal", [(1, 64, 32, 1, 0), (1, 63, 65, 2, 0), (1, 65, 128, 2, 0), (2, 129, 193, 1, 0), (1, 33, 33, 1, 1),
+                                              (1, 65, 65, 2, 1), (2, 128, 128, 1, 1), (1, 193, 193, 2, 1), (3, 400, 400, 8, 1),
+                                              (40, 70, 100, 4, 0), (17, 130, 130, 8, 1), (33, 70, 130, 8, 0), (33, 65, 65, 8, 1)])
+def test_bf16_attention_blocks_of_64_and_of_128_rows(ctx, orc, B, Tq, Tk, H, hd, causal):
+    _mha_case(ctx, orc, True, B, Tq, Tk, H, hd, causal, packed_kv=True)
+
+
+# keys that no query attends to (scores of -inf) in every tile of one wave's part, and all but the first of the other's
+@pytest.mark.parametrize("hd", [64, 128])
+def test_bf16_attention_with_scores_of_minus_infinity(ctx, orc, hd):
+    B, Tq, Tk, H = 1, 50, 160, 1
+    q, k, v = _rand(81, (Tq, hd), 1.0), _rand(82, (Tk, hd), 1.0), _rand(83, (Tk, hd), 1.0)
+    q[:, 0], off = 1.0, np.arange(Tk) // 32 % 4 != 0
+    (qt, qv), (kt, kv), (vt, vv) = (dev_act(x, True) for x in (q, k, v))
+    kt[torch.as_tensor(off, device="cuda")] = 0.0
+    kt[torch.as_tensor(off, device="cuda"), 0] = -torch.inf
+    o, lse = empty_act((Tq, hd), True), torch.empty((B, H, Tq), device="cuda")
+    torch.cuda.synchronize()
+    ctx.mha_fwd(pwb.MhaArgs(pwb.PW_BF16, ptr(qt), ptr(kt), ptr(vt), hd, hd, B, Tq, Tk, H, hd, 0), ptr(o), ptr(lse))
+    ctx.synchronize()
+    ro = orc.mha_fwd(qv, np.ascontiguousarray(kv[~off]), np.ascontiguousarray(vv[~off]), B, Tq, int((~off).sum()), H, hd, causal=False)
+    assert_close(host(o), ro, 6e-3)
+
+
 # one tile of 16 positions and one to either side, several tiles per wave; what a query may not see (or a key is not
 # seen by) must not matter even where it is not a number
 @pytest.mark.parametrize("hd", [64, 128])
