@@ -176,14 +176,14 @@ hipError_t layers_forward(Model* m, Model::Slot& s) {
   return hipSuccess;
 }
 
-// On entry m->dx_a holds the gradient w.r.t. the stack output (fp32) and, in bf16 mode, m->dx_lp its bf16
-// copy.  On exit m->dx_a holds the gradient w.r.t. the stack input.
+// dx_top: the gradient w.r.t. the stack output (fp32; m->dx_a, or the caller's own array, read in place); in bf16 mode
+// m->dx_lp (deferred: the top layer's g_y2) holds its bf16 copy.  On exit m->dx_a holds the gradient w.r.t. the stack input.
 // The bias gradients of the two projections that write the residual stream (b2, bo) are column sums of the
 // stream's gradient; the LayerNorm backward that produces that gradient delivers them.  top_b2_done says
 // whether the caller's producer of dx_a already did so for the last layer's b2.
 // defer: with deferred weight gradients (see lm.hpp) the four gradients that feed them go to this micro-batch's own
 // storage instead of the shared scratch, and the weight-gradient GEMMs are left to flush_wgrads.
-hipError_t layers_backward(Model* m, Model::Slot& s, int accumulate, bool top_b2_done, bool defer) {
+hipError_t layers_backward(Model* m, Model::Slot& s, const float* dx_top, int accumulate, bool top_b2_done, bool defer) {
   const pw_lm_config& c = m->cfg;
   const int N = m->N(), d = c.d_model, F = c.d_ff;
   const int dt = m->act_dtype();
@@ -193,6 +193,7 @@ hipError_t layers_backward(Model* m, Model::Slot& s, int accumulate, bool top_b2
   for (int l = c.n_layer - 1; l >= 0; --l) {
     auto& A = s.layer[l];
     const size_t e = layer_base(m, l);
+    const float* const dx_out = l == c.n_layer - 1 ? dx_top : m->dx_a;
     void* const d_big = defer ? A.g_u : m->d_big;
     void* const d_qkv = defer ? A.g_qkv : m->d_qkv;
     void* const lp_mid = defer ? A.g_yo : m->dx_lp2;                                   // bf16 copy of dx_b
@@ -203,22 +204,22 @@ hipError_t layers_backward(Model* m, Model::Slot& s, int accumulate, bool top_b2
     const bool odd = ((c.n_layer - 1 - l) & 1) != 0;
     void* const lp_in = late && odd ? m->dx_lp3 : m->dx_lp;
     void* const lp_below = defer && l > 0 ? s.layer[l - 1].g_y2 : (late && !odd ? m->dx_lp3 : m->dx_lp);   // bf16 copy of the new dx_a
-    const void* dx_op = c.bf16 ? (defer ? (const void*)A.g_y2 : (const void*)lp_in) : (const void*)m->dx_a;
+    const void* dx_op = c.bf16 ? (defer ? (const void*)A.g_y2 : (const void*)lp_in) : (const void*)dx_out;
     const void* const dx_in = dx_op;
     // Every data gradient comes BEFORE the weight gradient of the same layer: a weight gradient whose epilogue
     // applies the optimizer (fused update) rewrites the weight its data gradient still has to read.
     // FFN2: x_out = x_mid + h W2 + b2
     if (l == c.n_layer - 1 && !top_b2_done)
-      PW_TRY(launch_colsum(m->stream, kF32, m->dx_a, g + P(m, e + 11).offset, m->ws, N, d, accumulate), "b2 grad");
+      PW_TRY(launch_colsum(m->stream, kF32, dx_out, g + P(m, e + 11).offset, m->ws, N, d, accumulate), "b2 grad");
     PW_TRY(gemm_dgrad(m, dx_op, e + 10, N, F, d, kEpiGeluBwd, A.u, d_big, dt, 0), "ffn2 dgrad + gelu'");
     // FFN1: u = m W1 + b1
     // (b1 gradient = column sums of d_big: delivered by the weight-gradient GEMM where that is free)
     PW_TRY(gemm_dgrad(m, d_big, e + 8, N, d, F, kEpiStore, nullptr, m->d_small, dt, 0), "ffn1 dgrad");
-    // LN2 and the residual branch: dx_b = dx_a + LN2'(d_small).  The chain FFN2 data gradient -> FFN1 data gradient ->
+    // LN2 and the residual branch: dx_b = dx_out + LN2'(d_small).  The chain FFN2 data gradient -> FFN1 data gradient ->
     // LN2 backward runs without the two weight-gradient GEMMs in between, which need nothing of it: those GEMMs (and,
     // fused, the optimizer traffic of their epilogues) would otherwise push d_big, d_small and the residual gradient
     // out of the caches before their one reader gets to them.
-    PW_TRY(launch_layernorm_bwd(m->stream, dt, m->d_small, A.x_mid, m->w + P(m, e + 6).offset, A.mean2, A.rstd2, m->dx_a,
+    PW_TRY(launch_layernorm_bwd(m->stream, dt, m->d_small, A.x_mid, m->w + P(m, e + 6).offset, A.mean2, A.rstd2, dx_out,
                                 m->dx_b, c.bf16 ? lp_mid : nullptr, g + P(m, e + 6).offset, g + P(m, e + 7).offset,
                                 g + P(m, e + 5).offset /* bo */, m->ws, N, d, accumulate), "ln2 bwd");
     auto ffn_wgrads = [&]() -> hipError_t {
@@ -432,7 +433,7 @@ hipError_t model_train_step(Model* m, const int32_t* tokens, float* loss) {
   PW_TRY(launch_layernorm_bwd(m->stream, dt, m->d_small, s.x_out, m->w + P(m, tail).offset, m->meanf, m->rstdf, nullptr, m->dx_a,
                               c.bf16 ? m->dx_lp : nullptr, m->g + P(m, tail).offset, m->g + P(m, tail + 1).offset,
                               c.n_layer > 0 ? m->g + P(m, layer_base(m, c.n_layer - 1) + 11).offset : nullptr, m->ws, N, d, 0), "lnf bwd");
-  e = layers_backward(m, s, 0, true, false);
+  e = layers_backward(m, s, m->dx_a, 0, true, false);
   if (e != hipSuccess) return e;
   PW_TRY(launch_embedding_bwd(m->stream, tokens, m->dx_a, m->g + P(m, 0).offset, m->g + P(m, 1).offset, c.batch, c.seq, d, V), "embedding bwd");
   return model_apply_optimizer(m);
@@ -485,10 +486,13 @@ hipError_t model_stage_bwd(Model* m, int mb, const float* dy, float* dx) {
   }
   const bool defer = m->defer_wgrad && !capturing;
   const int64_t n = (int64_t)m->N() * c.d_model;
-  PW_TRY(launch_copy_bytes(m->stream, dy, m->dx_a, n * 4), "stage grad-output copy");
+  if (!dy || ((uintptr_t)dy & 15)) {   // read in place, 16 bytes at a time
+    m->error = "stage_bwd: the output gradient has to be 16-byte aligned";
+    return hipErrorInvalidValue;
+  }
   if (c.bf16)
     PW_TRY(launch_f32_to_bf16(m->stream, dy, defer ? s.layer[c.n_layer - 1].g_y2 : m->dx_lp, n), "stage grad-output to bf16");
-  hipError_t e = layers_backward(m, s, 1, false, defer);
+  hipError_t e = layers_backward(m, s, dy, 1, false, defer);
   if (e != hipSuccess) return e;
   if (defer) m->pending[mb] = 1;
   else m->wgrads_zero = false;
