@@ -428,6 +428,8 @@ static void launch_ln_bwd_block(hipStream_t s, int G, const T* dy, const float* 
 }
 // out[c] (=|+=) sum_{p < parts} ws[p*stride + c].  Block = 32 columns x 32 part-groups: group j adds parts
 // j, j+32, ... in order, then the 32 group sums are added in group order: a fixed tree, same bits every run.
+// Bound by the trips to memory of one thread's chain of up to 16 loads: 8 of them are requested at a time (512 parts of three
+// rows of 2048: 6.8 -> 4.7 us).
 constexpr int kRpCols = 32, kRpGroups = 32;
 __global__ __launch_bounds__(kRpCols * kRpGroups) void reduce_parts_kernel(const float* __restrict__ ws,
                                                                            float* __restrict__ out, int parts,
@@ -437,6 +439,7 @@ __global__ __launch_bounds__(kRpCols * kRpGroups) void reduce_parts_kernel(const
   const int64_t c = (int64_t)blockIdx.x * kRpCols + tx;
   float s = 0.f;
   if (c < cols)
+#pragma unroll 8
     for (int p = ty; p < parts; p += kRpGroups) s += ws[(size_t)p * stride + c];
   part[ty][tx] = s;
   __syncthreads();
@@ -459,6 +462,7 @@ __global__ __launch_bounds__(kRpCols * kRpGroups) void reduce_parts_multi_kernel
   float* out = blockIdx.y == 0 ? o.out[0] : blockIdx.y == 1 ? o.out[1] : o.out[2];
   float s = 0.f;
   if (c < cols)
+#pragma unroll 8
     for (int p = ty; p < parts; p += kRpGroups) s += src[(size_t)p * cols + c];
   part[ty][tx] = s;
   __syncthreads();
