@@ -63,7 +63,8 @@ def recorded_gemm_traffic(workload: str):
 
 def dispatch_bench(ctx, pwb, I, reps: int = 200):
     """Chained dispatch cost (Section 5.1 analogue on one GPU): chains of L trivial functions on a
-    128-float buffer.  host = time for the enqueue call to return; wall = until the result is ready."""
+    128-float buffer (additions: those of a chain share launches, op by op has one each).  host = time for the
+    enqueue call to return; wall = until the result is ready."""
     add1 = ctx.compile_scalar_fn(pwb.PW_FN_ADD_CONST, 128, 1.0)
     x = I.dispatch_input()
     out = {}
@@ -435,7 +436,7 @@ def measure(args, workload, steps, warmup, torch, pwb, I):
         "ms_per_step_device": {"median": round(per_step[len(per_step) // 2], 3), "min": round(per_step[0], 3),
                                "max": round(per_step[-1], 3)},
         loss_key: [round(losses[0], 4), round(losses[-1], 4)],
-        "roofline": {"bound": "mfma", "kernel": "bf16 MFMA GEMM (gemm_ring_kernel, gemm_ring_group_kernel, gemm_bf16_kernel; all layouts, general epilogues)", "achieved": round(gemm_tflops, 1),
+        "roofline": {"bound": "mfma", "kernel": "bf16 MFMA GEMM (gemm_ring_kernel, gemm_ring_group_kernel, gemm_tile_kernel; all layouts, general epilogues)", "achieved": round(gemm_tflops, 1),
                      "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s", "frac": round(gemm_tflops / PEAK_BF16_TFLOPS, 4),
                      "traffic": recorded_gemm_traffic(workload), "launches_per_step": n_gemm // max(1, profiled_steps), "steps_with_events": profiled_steps,
                      "avg_launch_ms": round(gemm_ms / max(1, n_gemm), 4),

@@ -105,9 +105,10 @@ int main(int argc, char** argv) {
     // For a kernel trace (rocprofv3 --kernel-trace -- dispatch_bench --gaps): the same chain of 128 trivial
     // computations dispatched four ways, 20 times each (then two pipelines, below), the phases 100 ms apart so that the trace can be cut at the
     // pauses.  The device-side launch gap of a mode is next.start - previous.end between consecutive kernels of a chain.
+    // (Busy functions of no duration: unlike plain additions they keep a launch each in every mode.)
     constexpr int L = 128, reps = 20;
     pw_future x = input();
-    pw_fn one = compile(PW_FN_ADD_CONST, 1.f, 0.f, 1);
+    pw_fn one = compile(PW_FN_BUSY, 1.f, 0.f, 1);
     std::vector<pw_fn> chain(L, one);
     const char* names[4] = {"chained_stream", "chained_graph", "sequential", "op_by_op"};
     for (int phase = 0; phase < 4; ++phase) {
