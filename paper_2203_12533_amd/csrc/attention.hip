@@ -211,13 +211,15 @@ __global__ __launch_bounds__(64 * kFWaves) void attention_fwd_f32_kernel(RowArgs
     float mx = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
     mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
     mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * c2;
-    const float m_new = fmaxf(m, mx), alpha = __builtin_amdgcn_exp2f(m - m_new);   // first tile: exp2(-inf) = 0
+    const float m_new = fmaxf(m, mx), alpha = m == m_new ? 1.f : __builtin_amdgcn_exp2f(m - m_new);   // (both -inf: see ref)
     m = m_new;
+    // A wave that has met nothing but scores of -inf so far holds zeros: exp2(-inf - (-inf)) would turn them into NaN.
+    const float ref = m == -INFINITY ? 0.f : m;
     f32x4 p;
     float sum = 0.f;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      p[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], c2, -m));
+      p[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], c2, -ref));
       sum += p[r];
     }
     l = l * alpha + sum;
@@ -247,7 +249,7 @@ __global__ __launch_bounds__(64 * kFWaves) void attention_fwd_f32_kernel(RowArgs
     float total = 0.f;
 #pragma unroll
     for (int w = 0; w < kFWaves; ++w) {
-      const float f = __builtin_amdgcn_exp2f(ms[w][row] - top);   // a wave without a tile: exp2(-inf) = 0
+      const float f = ms[w][row] == top ? 1.f : __builtin_amdgcn_exp2f(ms[w][row] - top);   // a wave without a tile: exp2(-inf) = 0
       total = __builtin_fmaf(ls[w][row], f, total);
       v += *reinterpret_cast<const f32x4*>(part + (w * kFT + row) * kPartLd<HD> + col) * f;
     }

@@ -608,6 +608,45 @@ def test_bf16_attention_with_scores_of_minus_infinity(ctx, orc, hd):
     assert_close(host(o), ro, 6e-3)
 
 
+# Keys that score -inf (an infinite key) and the finite ones between them, by the tiles and waves of each kernel.  Some key
+# of every query is finite: its output is what the finite keys alone give.
+def _minus_inf_case(ctx, orc, bf16, B, Tq, Tk, hd, off, lead=0):
+    """lead: elements in front of every array, so that rows of bf16 start off the 16-byte grid."""
+    q, k, v = _rand(81, (B * Tq, hd), 1.0), _rand(82, (B * Tk, hd), 1.0), _rand(83, (B * Tk, hd), 1.0)
+    q[:, 0] = 1.0
+    dt = torch.bfloat16 if bf16 else torch.float32
+
+    def place(x):
+        t = torch.zeros(lead + x.size, dtype=dt, device="cuda")
+        t[lead:] = torch.from_numpy(np.ascontiguousarray(x, np.float32)).cuda().reshape(-1).to(dt)
+        return t, t[lead:].float().cpu().numpy().reshape(x.shape).astype(np.float64)
+
+    (qt, qv), (kt, kv), (vt, vv) = place(q), place(k), place(v)
+    gone = torch.as_tensor(np.tile(off, B), device="cuda")
+    kt[lead:].view(B * Tk, hd)[gone] = 0.0
+    kt[lead:].view(B * Tk, hd)[gone, 0] = -torch.inf
+    o, lse = torch.full((lead + B * Tq * hd,), 7.0, dtype=dt, device="cuda"), torch.empty((B, 1, Tq), device="cuda")
+    at = lambda t: ptr(t) + lead * t.element_size()  # noqa: E731
+    ctx.mha_fwd(pwb.MhaArgs(DT[bf16], at(qt), at(kt), at(vt), hd, hd, B, Tq, Tk, 1, hd, 0), at(o), ptr(lse))
+    ctx.synchronize()
+    keep = ~np.tile(off, B)
+    ro = orc.mha_fwd(qv, np.ascontiguousarray(kv[keep]), np.ascontiguousarray(vv[keep]), B, Tq, int((~off).sum()), 1, hd, causal=False)
+    assert_close(host(o[lead:]).reshape(B * Tq, hd), ro, 6e-3 if bf16 else 1e-5)
+    s = np.einsum("bqd,bkd->bqk", qv.reshape(B, Tq, hd), kv.reshape(B, Tk, hd)[:, ~off]) / np.sqrt(hd)
+    assert np.abs(host(lse)[:, 0] - np.log(np.exp(s).sum(-1))).max() < 1e-4
+
+
+# the fp32 kernel's waves take every fourth tile of 16 keys: one wave's first tile, all of its tiles, all but one key; and the
+# same kernel for bf16 rows that are not 16-byte aligned
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("off", [range(16, 32), range(16, 20), [j for j in range(150) if j // 16 % 4 == 2], range(1, 150), range(149)])
+def test_fp32_attention_with_scores_of_minus_infinity(ctx, orc, off, hd, bf16):
+    mask = np.zeros(150, bool)
+    mask[list(off)] = True
+    _minus_inf_case(ctx, orc, bf16, 2, 35, 150, hd, mask, lead=4 if bf16 else 0)
+
+
 # one tile of 16 positions and one to either side, several tiles per wave; what a query may not see (or a key is not
 # seen by) must not matter even where it is not a number
 @pytest.mark.parametrize("hd", [64, 128])
