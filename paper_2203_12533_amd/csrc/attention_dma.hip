@@ -290,7 +290,7 @@ __global__ __launch_bounds__(kNT, 2) void attn_fwd_dma_kernel(MhaDev a, bf16* __
     // accumulators rescaled) only when some row's maximum grew by more than 2^8; otherwise exp2(s - m) <= 256.
     if (__builtin_amdgcn_ballot_w64(mx > m + 8.f) != 0) {
       const float m_new = fmaxf(m, mx);
-      const float alpha = PARTS > 1 && m == m_new ? 1.f : __builtin_amdgcn_exp2f(m - m_new);   // (both -inf: see ref)
+      const float alpha = m == m_new ? 1.f : __builtin_amdgcn_exp2f(m - m_new);   // (both -inf: see ref)
       m = m_new;
       l *= alpha;
 #pragma unroll
@@ -298,8 +298,8 @@ __global__ __launch_bounds__(kNT, 2) void attn_fwd_dma_kernel(MhaDev a, bf16* __
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[cb][r] *= alpha;
     }
-    // (a part that has met nothing but -inf so far takes its zeros to the other part)
-    const float ref = PARTS > 1 && m == -INFINITY ? 0.f : m;
+    // A row that has met nothing but scores of -inf so far holds zeros, which the tiles (or the part) to come add to.
+    const float ref = m == -INFINITY ? 0.f : m;
     float sum = 0.f;
 #pragma unroll
     for (int kb = 0; kb < kSub / 32; ++kb)

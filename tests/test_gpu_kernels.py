@@ -647,6 +647,15 @@ def test_fp32_attention_with_scores_of_minus_infinity(ctx, orc, off, hd, bf16):
     _minus_inf_case(ctx, orc, bf16, 2, 35, 150, hd, mask, lead=4 if bf16 else 0)
 
 
+# the bf16 kernel of 128-row blocks (enough of them for it), tiles of 64 keys: the first tile, a later one, all but one key
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("off", [range(64), range(64, 128), range(100), range(149), range(1, 150)])
+def test_bf16_attention_of_many_blocks_with_scores_of_minus_infinity(ctx, orc, off, hd):
+    mask = np.zeros(150, bool)
+    mask[list(off)] = True
+    _minus_inf_case(ctx, orc, True, 260, 20, 150, hd, mask)
+
+
 # one tile of 16 positions and one to either side, several tiles per wave; what a query may not see (or a key is not
 # seen by) must not matter even where it is not a number
 @pytest.mark.parametrize("hd", [64, 128])
