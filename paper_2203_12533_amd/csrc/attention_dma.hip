@@ -31,6 +31,11 @@
 // Rows past the end of a sequence are fetched from its last valid row (always in bounds); every use of such
 // a row is masked (causality, or the explicit key-index mask of the unmasked variant) or multiplied by an exact
 // zero (P = exp2(-inf)).
+// Values that are not finite.  A masked pair enters the second products with a probability of zero, and zero times infinity
+// is NaN; so is the sum of the two parts of a split probability, of either sign, times infinity.  With SPLIT these calls give
+// what a sum over the visible pairs alone gives: rows that did not come out finite are summed once more, pair by pair, at
+// the end (nothing in the loop).  Without it (head_dim 128, packed causal) a masked value that is not finite spoils rows of
+// its tile.
 // Queries, keys and values come with their own pointers, row strides and lengths (MhaDev), so one set of kernels
 // serves the packed causal self-attention of a decoder, the unmasked self-attention of an encoder and attention
 // of decoder queries over encoder keys; CAUSAL is a template parameter (it decides which tiles are visited).
@@ -177,6 +182,56 @@ __device__ __forceinline__ void second_product(const bf16* __restrict__ tile, in
     }
     mfma_frag<SPLIT>(u.v, frag, acc[cb]);
   }
+}
+
+// Sums over the visible pairs one by one, from global memory: slow and sparing of registers.
+template <int HD>
+__device__ __forceinline__ float row_dot(const bf16* __restrict__ a, const bf16* __restrict__ b) {
+  float s = 0.f;
+#pragma unroll 1
+  for (int c = 0; c < HD; c += 8) {
+    const bf16x8 x = *reinterpret_cast<const bf16x8*>(a + c), y = *reinterpret_cast<const bf16x8*>(b + c);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) s = fmaf((float)x[e], (float)y[e], s);
+  }
+  return s;
+}
+template <int HD>
+__device__ __forceinline__ void add_row(float w, const bf16* __restrict__ row, f32x16* acc) {
+  const int half = (threadIdx.x & 63) >> 5;
+#pragma unroll
+  for (int q = 0; q < HD / 8; ++q) {         // this lane's features 8 q + 4 half .. + 3
+    const bf16x4 t = *reinterpret_cast<const bf16x4*>(row + 8 * q + 4 * half);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[q / 4][4 * (q % 4) + e] = fmaf(w, (float)t[e], acc[q / 4][4 * (q % 4) + e]);
+  }
+}
+// Whether one of this lane's sums is NaN or infinite (zero times it is NaN).
+template <int HD> __device__ __forceinline__ bool not_finite(const f32x16* acc) {
+  float t[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int cb = 0; cb < HD / 32; ++cb)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) t[r & 3] = fmaf(acc[cb][r], 0.f, t[r & 3]);
+  const float u = (t[0] + t[1]) + (t[2] + t[3]);
+  return u != u;
+}
+template <int HD> __device__ __forceinline__ void clear(f32x16* acc) {
+#pragma unroll
+  for (int cb = 0; cb < HD / 32; ++cb)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[cb][r] = 0.f;
+}
+// Forward and dQ: acc = the sum of weight(key, q.k) x[key] over the keys that this lane's query sees.
+template <int HD, bool CAUSAL, class Weight>
+__device__ __forceinline__ void sum_again(const bf16* q, int64_t ldq, const bf16* k, const bf16* x, int64_t ldkv, int q0, int Tq, int Tk,
+                                          Weight weight, f32x16* acc) {
+  const int query = min(q0 + ((int)threadIdx.x & 31), Tq - 1);      // (rows past the end are not stored)
+  const bf16* mine = q + query * ldq;
+  clear<HD>(acc);
+#pragma unroll 1
+  for (int j = 0; j < (CAUSAL ? min(q0 + 32, Tk) : Tk); ++j)
+    if (!CAUSAL || j <= query) add_row<HD>(weight(j, row_dot<HD>(mine, k + j * ldkv)), x + j * ldkv, acc);
 }
 
 __device__ __forceinline__ void wait_and_sync() {
@@ -335,13 +390,23 @@ __global__ __launch_bounds__(kNT, 2) void attn_fwd_dma_kernel(MhaDev a, bf16* __
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[cb][r] = acc[cb][r] * w0 + box[(cb * 16 + r) * 64] * w1;
   }
-  if (query < Tq) {
+  auto store = [&](const f32x16* sum) {
+    if (query >= Tq) return;
     const int64_t row = ((int64_t)b * Tq + query) * d + h * HD;
     if (o_lo)
-      store_row_split<HD>(o + row, o_lo + row, acc, 1.f / l);
+      store_row_split<HD>(o + row, o_lo + row, sum, 1.f / l);
     else
-      store_row<HD>(o + row, acc, 1.f / l);
+      store_row<HD>(o + row, sum, 1.f / l);
     if (half == 0) lse[(int64_t)bh * Tq + query] = (m + __builtin_amdgcn_logf(l)) * kLn2;
+  };
+  // (Where l is NaN a visible score was, and the row is what it has to be.)
+  if (SPLIT && __builtin_amdgcn_ballot_w64(query < Tq && l == l && not_finite<HD>(acc)) != 0) {
+    f32x16 again[HD / 32];
+    sum_again<HD, CAUSAL>(qbase, a.ldq, kbase, vbase, ld, q0, Tq, Tk,
+                          [&](int, float s) { return __builtin_amdgcn_exp2f(fmaf(s, c2, m == -INFINITY ? 0.f : -m)); }, again);
+    store(again);
+  } else {
+    store(acc);
   }
 }
 
@@ -447,7 +512,17 @@ __global__ __launch_bounds__(kNT, 2) void attn_dq_dma_kernel(MhaDev a, const bf1
   }
   if constexpr (PARTS > 1)
     if (!sum_parts<HD>(reinterpret_cast<float*>(smem) + (wave & 1) * (HD / 2 * 64) + lane, part, acc)) return;
-  if (query < Tq) store_row<HD>(dq + ((int64_t)b * Tq + query) * lddq + h * HD, acc, scale);
+  bf16* const row = dq + ((int64_t)b * Tq + query) * lddq + h * HD;
+  if (SPLIT && __builtin_amdgcn_ballot_w64(query < Tq && lse2 == lse2 && dl == dl && not_finite<HD>(acc)) != 0) {
+    f32x16 again[HD / 32];
+    sum_again<HD, CAUSAL>(qbase, a.ldq, kbase, kbase, ld, q0, Tq, Tk, [&](int j, float s) {
+      const float dp = row_dot<HD>(dout + ((int64_t)b * Tq + min(query, Tq - 1)) * d + h * HD, vbase + j * ld);
+      return __builtin_amdgcn_exp2f(fmaf(s, c2, -lse2)) * (dp - dl);
+    }, again);
+    if (query < Tq) store_row<HD>(row, again, scale);
+  } else if (query < Tq) {
+    store_row<HD>(row, acc, scale);
+  }
 }
 
 // ===================================================================================================
@@ -572,6 +647,35 @@ __device__ __forceinline__ void dkv_back(const bf16* __restrict__ Qs, const bf16
     const int b2 = j / (2 * kBlocks), mat = (j / kBlocks) & 1, cb = j % kBlocks;
     mfma_frag<SPLIT>(fr[j % (kAhead + 1)], mat ? dsf[b2] : pf[b2], mat ? dk[cb] : dv[cb]);
     __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// A wave's 32 keys over again (see the head of the file).
+template <int HD, bool CAUSAL>
+__device__ __forceinline__ void dkv_again(const MhaDev& a, const bf16* dout, const float* lse, const float* delta, bf16* dk_out, bf16* dv_out,
+                                          int64_t lddkv, int bh, int k0) {
+  const int T = a.Tq, Tk = a.Tk, H = a.H, b = bh / H, h = bh - b * H, d = H * HD;
+  int key = k0 + ((int)threadIdx.x & 31);
+  asm volatile("" : "+v"(key));                // nothing of this is worked out before the loop and kept in registers over it
+  const bf16* q = a.q + (int64_t)b * T * a.ldq + h * HD;
+  const bf16* g = dout + (int64_t)b * T * d + h * HD;
+  const int64_t mine = ((int64_t)b * Tk + min(key, Tk - 1)) * a.ldkv + h * HD, row = ((int64_t)b * Tk + key) * lddkv + h * HD;
+  const float scale = 1.f / sqrtf((float)HD), c2 = kLog2e * scale;
+  lse += (int64_t)bh * T;
+  delta += (int64_t)bh * T;
+#pragma unroll 1
+  for (int which = 0; which < 2; ++which) {    // dV, then dK
+    f32x16 sum[HD / 32];
+    clear<HD>(sum);
+#pragma unroll 1
+    for (int i = CAUSAL ? k0 : 0; i < T; ++i)
+      if (!CAUSAL || i >= key) {
+        const bf16 *qi = q + i * a.ldq, *gi = g + (int64_t)i * d;
+        float w = __builtin_amdgcn_exp2f(fmaf(row_dot<HD>(qi, a.k + mine), c2, -lse[i] * kLog2e));
+        if (which) w *= row_dot<HD>(gi, a.v + mine) - delta[i];
+        add_row<HD>(w, which ? qi : gi, sum);
+      }
+    if (key < Tk) store_row<HD>((which ? dk_out : dv_out) + row, sum, which ? scale : 1.f);
   }
 }
 
@@ -753,6 +857,10 @@ __global__ __launch_bounds__(kNT, HD == 64 ? 2 : 1) void attn_dkv_dma_kernel(Mha
     float* const box = reinterpret_cast<float*>(smem) + (wave & 1) * (HD / 2 * 64) + lane;
     (void)sum_parts<HD>(box, part, dk);
     if (!sum_parts<HD>(box, part, dv)) return;
+  }
+  if (SPLIT && __builtin_amdgcn_ballot_w64(key < Tk && (not_finite<HD>(dk) || not_finite<HD>(dv))) != 0) {
+    dkv_again<HD, CAUSAL>(a, dout, lse, delta, dk_out, dv_out, lddkv, bh, k0);
+    return;
   }
   if (key < Tk) {
     const int64_t row = ((int64_t)b * Tk + key) * lddkv + h * HD;

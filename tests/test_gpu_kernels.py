@@ -699,6 +699,92 @@ def test_fp32_causal_attention_ignores_what_is_masked(ctx, T, hd):
     assert_close(g[:, 1:, 2 * d:], rv[:, 1:], 1e-5)
 
 
+# The same for the bf16 kernels at head width 64: 32-row blocks on the diagonal and one position to either side, in workgroups
+# of 64 rows (few) and of 128 (many), the hidden rows one and a third of all.
+@pytest.mark.parametrize("packed", [False])
+@pytest.mark.parametrize("B,T,H", [(2, 2, 2), (2, 31, 2), (2, 33, 2), (1, 64, 2), (1, 97, 2), (2, 200, 2), (33, 33, 4), (33, 100, 4), (17, 161, 4)])
+def test_bf16_causal_attention_at_head_width_64_ignores_what_is_masked(ctx, B, T, H, packed):
+    hd = 64
+    d = H * hd
+    qkv, dout = I.round_to_bf16(_rand(41, (B, T, 3 * d))), I.round_to_bf16(_rand(42, (B, T, d)))
+
+    def run(qkv, dout):
+        dev = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda().to(torch.bfloat16)  # noqa: E731
+        qd, gd = dev(qkv), dev(dout)
+        o, g, lse, delta = torch.empty_like(gd), torch.empty_like(qd), torch.empty((B, H, T), device="cuda"), torch.empty((B, H, T), device="cuda")
+        if packed:
+            ctx.op("attention_fwd", pwb.PW_BF16, ptr(qd), ptr(o), ptr(lse), B, T, H, hd)
+            ctx.op("attention_bwd", pwb.PW_BF16, ptr(qd), ptr(o), ptr(gd), ptr(lse), ptr(delta), ptr(g), B, T, H, hd)
+        else:
+            q, kv, o_lo = qd[..., :d].contiguous(), qd[..., d:].contiguous(), torch.empty_like(gd)
+            dq, dkv = torch.empty_like(q), torch.empty_like(kv)
+            a = pwb.MhaArgs(pwb.PW_BF16, ptr(q), ptr(kv), ptr(kv) + 2 * d, d, 2 * d, B, T, T, H, hd, 1)
+            ctx.mha_fwd(a, ptr(o), ptr(lse), ptr(o_lo))
+            ctx.mha_bwd(a, ptr(o), ptr(gd), ptr(lse), ptr(delta), ptr(dq), d, ptr(dkv), ptr(dkv) + 2 * d, 2 * d, ptr(o_lo))
+            ctx.synchronize()
+            g = torch.cat([dq, dkv], 2)
+        ctx.synchronize()
+        return host(o), host(g)
+
+    q, k, v = (np.moveaxis(t.reshape(B, T, H, hd), 2, 1).astype(np.float64) for t in np.split(qkv, 3, axis=2))
+    go = np.moveaxis(dout.reshape(B, T, H, hd), 2, 1).astype(np.float64)
+    s = np.where(np.tril(np.ones((T, T), bool)), q @ k.swapaxes(2, 3) / np.sqrt(hd), -np.inf)
+    p = np.exp(s - s.max(-1, keepdims=True))
+    p /= p.sum(-1, keepdims=True)
+    ro = p @ v
+    ds = p * (go @ v.swapaxes(2, 3) - (go * ro).sum(-1, keepdims=True)) / np.sqrt(hd)
+    flat = lambda t: np.moveaxis(t, 1, 2).reshape(B, T, d)  # noqa: E731
+    ro, rq, rk, rv = flat(ro), flat(ds @ k), flat(ds.swapaxes(2, 3) @ q), flat(p.swapaxes(2, 3) @ go)
+    for n in sorted({1, T // 3} - {0}):
+        bad = qkv.copy()
+        bad[:, T - n:, d:2 * d] = np.nan            # the last keys and values: no earlier query sees them
+        bad[:, T - n:, 2 * d:] = -np.inf
+        o, g = run(bad, dout)
+        end = (T - n) // 64 * 64 if packed else T - n
+        if end > 0:
+            assert_close(o[:, :end], ro[:, :end], 6e-3)
+        if end > 1:
+            assert_close(g[:, 1:end, :d], rq[:, 1:end], 1.5e-2)
+        bad, bad_g = qkv.copy(), dout.copy()
+        bad[:, :n, :d] = np.nan                     # the first queries and their output gradients: no later key is seen by them
+        bad_g[:, :n] = np.inf
+        o, g = run(bad, bad_g)
+        assert_close(o[:, n:], ro[:, n:], 6e-3)
+        first = (n + 31) // 32 * 32 if packed else n
+        if first < T:
+            assert_close(g[:, first:, d:2 * d], rk[:, first:], 1.5e-2)
+            assert_close(g[:, first:, 2 * d:], rv[:, first:], 1.5e-2)
+
+
+# infinities that are seen: they arrive as infinities, and once - not again for the rows behind the end of a sequence that ends
+# inside a tile, nor as the difference of two parts of a probability
+@pytest.mark.parametrize("hd", [64])
+@pytest.mark.parametrize("T", [5, 33, 70])
+@pytest.mark.parametrize("packed", [False])
+def test_bf16_attention_passes_infinite_values_on(ctx, T, hd, packed):
+    q, k, v, g = (_rand(s, (T, hd)) for s in (91, 92, 93, 94))
+    v[T - 1, 3], g[T - 1, 5] = np.inf, -np.inf
+    qkv, qkvv = dev_act(np.concatenate([q, k, v], 1), True)
+    gt, gv = dev_act(g, True)
+    o, o_lo, dqkv = empty_act((T, hd), True), empty_act((T, hd), True), empty_act((T, 3 * hd), True)
+    lse, delta = torch.empty((1, 1, T), device="cuda"), torch.empty((1, 1, T), device="cuda")
+    at = lambda t, i: ptr(t) + 2 * hd * i  # noqa: E731
+    a = pwb.MhaArgs(pwb.PW_BF16, at(qkv, 0), at(qkv, 1), at(qkv, 2), 3 * hd, 3 * hd, 1, T, T, 1, hd, int(packed))
+    ctx.mha_fwd(a, ptr(o), ptr(lse), ptr(o_lo))
+    ctx.mha_bwd(a, ptr(o), ptr(gt), ptr(lse), ptr(delta), at(dqkv, 0), 3 * hd, at(dqkv, 1), at(dqkv, 2), 3 * hd, ptr(o_lo))
+    ctx.synchronize()
+    qv, kv, vv = np.split(qkvv, 3, axis=1)
+    s = qv @ kv.T / np.sqrt(hd)
+    p = np.exp(np.where(np.tril(np.ones((T, T), bool)), s, -np.inf) if packed else s)
+    p /= p.sum(1, keepdims=True)
+    sees = slice(T - 1, T) if packed else slice(0, T)          # queries that see the last key; every key is seen by the last query
+    for got, ref, col, inf in ((host(o)[sees], (p @ np.where(np.isfinite(vv), vv, 0.0))[sees], 3, np.inf),
+                               (host(dqkv)[:, 2 * hd:], p.T @ np.where(np.isfinite(gv), gv, 0.0), 5, -np.inf)):
+        assert (got[:, col] == inf).all()
+        rest = np.arange(hd) != col
+        assert_close(got[:, rest], ref[:, rest], 1.5e-2)
+
+
 @pytest.mark.parametrize("bf16", [False, True])
 @pytest.mark.parametrize("B,T,V", [(3, 5, 1024), (2, 7, 4096), (1, 3, 32768), (2, 2, 8)])
 def test_softmax_xent(ctx, orc, B, T, V, bf16):
