@@ -489,6 +489,9 @@ pw_status pw_op_attention_bwd(pw_ctx* ctx, int dtype, const void* qkv, const voi
  * above.  q, k, v: device pointers to element (batch 0, row 0, feature 0) of arrays in `dtype`; rows are ldq
  * (q) and ldkv (k and v) elements apart, batch b starts at row b*Tq (q) or b*Tk (k, v), head h owns features
  * h*hd .. (h+1)*hd of a row; hd in {64, 128}.  causal = 1: query i sees keys j <= i and Tq must equal Tk.
+ * Values that are not finite in rows a causal mask hides make no difference to the rows they are hidden from in fp32,
+ * nor in bf16 at hd = 64 unless the call is packed ([Q|K|V] rows): there, and at hd = 128, such a value may spoil the
+ * results of the 64 positions of its tile.
  * Nothing is owned or kept; PW_ERR_INVALID on a rejected shape or null pointer. */
 typedef struct {
   int32_t dtype;

@@ -28,9 +28,8 @@
 // barrier one behind the other), so a launch that leaves units idle, or whose causal mask gives one block twice the average,
 // lasts as long as its longest chain of steps.  Blocks of 64 rows then, two waves to 32 of them that take the halves of every
 // tile in turn and add up through LDS at the end: half the steps, in the same fp32 sums.  The two above: 53 -> 43.5, 85 -> 73.8.
-// Rows past the end of a sequence are fetched from its last valid row (always in bounds); every use of such
-// a row is masked (causality, or the explicit key-index mask of the unmasked variant) or multiplied by an exact
-// zero (P = exp2(-inf)).
+// Rows past the end of a sequence are fetched from a block of zeros; every use of such a row is masked or multiplied by an
+// exact zero (P = exp2(-inf)).
 // Values that are not finite.  A masked pair enters the second products with a probability of zero, and zero times infinity
 // is NaN; so is the sum of the two parts of a split probability, of either sign, times infinity.  With SPLIT these calls give
 // what a sum over the visible pairs alone gives: rows that did not come out finite are summed once more, pair by pair, at
@@ -50,6 +49,7 @@ namespace pw {
 namespace {
 
 constexpr int kNT = 256;                 // 4 waves
+__device__ __attribute__((aligned(16))) const uint32_t kZeroRow[4] = {0, 0, 0, 0};
 typedef __attribute__((address_space(3))) void* lds_ptr;
 typedef short short4v __attribute__((ext_vector_type(4)));
 
@@ -95,8 +95,8 @@ struct TileOffsets {
     }
   }
 };
-// src: element (row 0 of the sequence, feature 0); tile rows row0 .. row0+ROWS-1; rows past `last` are fetched
-// from row `last` (the slow path, only for the one tile that straddles the end of the sequence).
+// src: element (row 0 of the sequence, feature 0); tile rows row0 .. row0+ROWS-1; rows past `last` read as zero (the slow
+// path, only for the one tile that straddles the end of the sequence).
 template <int ROWS, int HD>
 __device__ __forceinline__ void issue_tile(const bf16* __restrict__ src, int64_t ld, int row0, int last,
                                            const TileOffsets<ROWS, HD>& to, uint32_t lds_off, int wave, int lane) {
@@ -111,8 +111,9 @@ __device__ __forceinline__ void issue_tile(const bf16* __restrict__ src, int64_t
       const int instr = wave * kPerWave + j;
       const int r = instr * kRowsPerInstr<HD> + lane / (HD / 8);
       const int c = (lane % (HD / 8)) ^ swz<HD>(r);
-      const int row = min(row0 + r, last);
-      dma16(src + (int64_t)row * ld + c * 8, lds_off + instr * 1024);
+      const bf16* g = src + (int64_t)(row0 + r) * ld + c * 8;
+      if (row0 + r > last) g = reinterpret_cast<const bf16*>(kZeroRow);
+      dma16(g, lds_off + instr * 1024);
     }
   }
 }
@@ -743,7 +744,21 @@ __global__ __launch_bounds__(kNT, HD == 64 ? 2 : 1) void attn_dkv_dma_kernel(Mha
   // k0 / 32 on; it starts with the tile that holds that block (waves 2 and 3 of a workgroup one tile after waves 0
   // and 1) and from there on runs every block - an odd first block's even neighbour is computed fully masked, which
   // keeps the pipeline below free of per-wave branches.
-  auto tile_q = [&](int n) { return smem + ((n >> 1) % kStages) * (2 * kTile); };
+  // Without the sums over again (SPLIT) what that neighbour holds must not matter either: it is read as zeros.
+  constexpr bool kHides = HD == 64 && CAUSAL && !SPLIT;
+  constexpr int kZeros = kStages * 2 * kTile + 2 * kStages * BQ * 2;                // behind the statistics
+  auto tile_q = [&](int n) { return smem + (kHides && 32 * n + 31 < k0 ? kZeros : ((n >> 1) % kStages) * (2 * kTile)); };
+  auto first_stats = [&](int n, DkvStats& st) {
+    load_stats(Ls[(n >> 1) % kStages], Ds[(n >> 1) % kStages], n & 1, half, st);
+    if (kHides && 32 * n + 31 < k0) {                    // (every such wave writes the zeros for itself)
+#pragma unroll
+      for (int i = 0; i < 32 * HD / 512; ++i)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) reinterpret_cast<uint4*>(smem + kZeros + t * kTile)[64 * i + lane] = make_uint4(0, 0, 0, 0);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) st.dq[r] = 0.f;
+    }
+  };
   // What happens between the two blocks of tile t: tile t + 1 has to have landed, for every wave; behind the barrier
   // nobody reads tile t - 1 any more, so its stage takes tile t + 2.
   auto advance = [&](int t) {
@@ -826,7 +841,7 @@ __global__ __launch_bounds__(kNT, HD == 64 ? 2 : 1) void attn_dkv_dma_kernel(Mha
       t0 = first_tile + 1;
     }
     if (any) {
-      load_stats(Ls[t0 % kStages], Ds[t0 % kStages], 0, half, st);
+      first_stats(2 * t0, st);
       dkv_front<HD, SPLIT, true, false>(tile_q(2 * t0), tile_q(2 * t0) + kTile, 0, kf, vf, s0, dp0, s0, dp0, st, c2, pf, dsf);
       for (int t = t0; t + 1 < n_tiles; ++t) {
         step(2 * t, yes{}, s0, dp0, s1, dp1);
@@ -838,8 +853,8 @@ __global__ __launch_bounds__(kNT, HD == 64 ? 2 : 1) void attn_dkv_dma_kernel(Mha
     }
   } else {
     // One block per tile and wave, the next one in the next tile: every step is led by the wait for it.
-    load_stats(Ls[first_tile % kStages], Ds[first_tile % kStages], part, half, st);
-    dkv_front<HD, SPLIT, true, false>(tile_q(2 * first_tile), tile_q(2 * first_tile) + kTile, part * 32, kf, vf, s0, dp0, s0, dp0, st, c2, pf, dsf);
+    first_stats(2 * first_tile + part, st);
+    dkv_front<HD, SPLIT, true, false>(tile_q(2 * first_tile + part), tile_q(2 * first_tile + part) + kTile, part * 32, kf, vf, s0, dp0, s0, dp0, st, c2, pf, dsf);
     int t = first_tile;
     for (; t + 2 < n_tiles; t += 2) {
       advance(t);
@@ -873,14 +888,14 @@ __global__ __launch_bounds__(kNT, HD == 64 ? 2 : 1) void attn_dkv_dma_kernel(Mha
 
 // Dynamic LDS: two stages of two 64-row tiles (64 KiB at head_dim 128); dK/dV three stages and their statistics (97.5 KiB).
 template <int HD, int PARTS> constexpr int kSmemTiles = 2 * 2 * kSubRows<HD, PARTS> * PARTS * HD * 2;
-template <int HD> constexpr int kSmemDkv = 3 * 2 * 64 * HD * 2 + 6 * 64 * 4;
+template <int HD, bool HIDES> constexpr int kSmemDkv = 3 * 2 * 64 * HD * 2 + 6 * 64 * 4 + (HIDES ? (64 + 32) * HD * 2 : 0);   // (tile_q)
 
 template <int HD, bool CAUSAL, bool SPLIT, int PARTS>
 static hipError_t prepare_dma() {
   const struct { const void* fn; int bytes; } all[] = {
       {reinterpret_cast<const void*>(attn_fwd_dma_kernel<HD, CAUSAL, SPLIT, PARTS>), kSmemTiles<HD, PARTS>},
       {reinterpret_cast<const void*>(attn_dq_dma_kernel<HD, CAUSAL, SPLIT, PARTS>), kSmemTiles<HD, PARTS>},
-      {reinterpret_cast<const void*>(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, PARTS>), kSmemDkv<HD>}};
+      {reinterpret_cast<const void*>(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, PARTS>), kSmemDkv<HD, HD == 64 && CAUSAL && !SPLIT>}};
   for (const auto& k : all) {
     const hipError_t e = hipFuncSetAttribute(k.fn, hipFuncAttributeMaxDynamicSharedMemorySize, k.bytes);
     if (e != hipSuccess) return e;
@@ -960,7 +975,7 @@ static hipError_t bwd_dma(hipStream_t s, const MhaArgs& a, const MhaGrads& g) {
   if (two_parts(a, a.Tq, a.Tk, 128, HD == 64 ? 512 : 256)) run_q(attn_dq_dma_kernel<HD, CAUSAL, SPLIT, 2>, blocks_of<2>(a.Tq, a), kSmemTiles<HD, 2>);
   else run_q(attn_dq_dma_kernel<HD, CAUSAL, SPLIT, 1>, blocks_of<1>(a.Tq, a), kSmemTiles<HD, 1>);
   auto run_kv = [&](auto kernel, int grid) {
-    kernel<<<grid, kNT, kSmemDkv<HD>, s>>>(dev_of(a), (const bf16*)g.dout, g.lse, g.delta, (bf16*)g.dk, (bf16*)g.dv, g.lddkv);
+    kernel<<<grid, kNT, kSmemDkv<HD, HD == 64 && CAUSAL && !SPLIT>, s>>>(dev_of(a), (const bf16*)g.dout, g.lse, g.delta, (bf16*)g.dk, (bf16*)g.dv, g.lddkv);
   };
   if (two_parts(a, a.Tk, a.Tq, 128, HD == 64 ? 512 : 128)) run_kv(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, 2>, blocks_of<2>(a.Tk, a));
   else run_kv(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, 1>, blocks_of<1>(a.Tk, a));
