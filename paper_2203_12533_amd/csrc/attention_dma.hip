@@ -925,9 +925,12 @@ static MhaDev dev_of(const MhaArgs& a) {
   return MhaDev{(const bf16*)a.q, (const bf16*)a.k, (const bf16*)a.v, a.ldq, a.ldkv, a.Tq, a.Tk, a.H};
 }
 
-// Whether the kernels of this file take the problem: bf16, 16-byte aligned rows.
+// Whether the kernels of this file take the problem: bf16, 16-byte aligned rows, no farther apart than a lane's 32-bit byte
+// offset into a tile of up to 128 rows reaches (128 * 2^24 * 2 bytes = 2^32).
+constexpr int64_t kMaxLd = 1 << 24;
 bool mha_dma_supported(const MhaArgs& a) {
   if (a.dtype != kBF16 || (a.hd != 128 && a.hd != 64)) return false;
+  if (a.ldq > kMaxLd || a.ldkv > kMaxLd) return false;
   if (((uintptr_t)a.q | (uintptr_t)a.k | (uintptr_t)a.v) & 15) return false;
   return a.ldq % 8 == 0 && a.ldkv % 8 == 0;
 }

@@ -786,6 +786,36 @@ def test_bf16_attention_passes_infinite_values_on(ctx, T, hd, packed):
         assert_close(got[:, rest], ref[:, rest], 1.5e-2)
 
 
+# rows too far apart for 32-bit byte offsets into a tile: keys and values from 2^32 / (2 * 127) elements on (tiles of up to 128
+# rows), queries from 2^32 / (2 * 63) on (tiles of 64)
+@pytest.mark.parametrize("hd", [64, 128])
+def test_bf16_attention_with_rows_far_apart(ctx, orc, hd):
+    Tq, Tk, ldq, ldkv = 66, 130, (1 << 25) + (1 << 20), (1 << 24) + (1 << 18)
+    assert 63 * ldq * 2 >= 1 << 32 and 127 * ldkv * 2 >= 1 << 32
+
+    def far(x, ld):
+        t = torch.empty(((x.shape[0] - 1) * ld + x.shape[1],), dtype=torch.bfloat16, device="cuda")
+        rows = t.as_strided(x.shape, (ld, 1))
+        rows.copy_(torch.from_numpy(np.ascontiguousarray(x)).cuda().to(torch.bfloat16))
+        return t, rows
+
+    q, kv, g = (I.round_to_bf16(_rand(s, shp)) for s, shp in ((95, (Tq, hd)), (96, (Tk, 2 * hd)), (97, (Tq, hd))))
+    (qt, _), (kvt, _), (gt, _) = far(q, ldq), far(kv, ldkv), dev_act(g, True)
+    o, o_lo, dq, dkv = (empty_act(shp, True) for shp in ((Tq, hd), (Tq, hd), (Tq, hd), (Tk, 2 * hd)))
+    lse, delta = torch.empty((1, 1, Tq), device="cuda"), torch.empty((1, 1, Tq), device="cuda")
+    a = pwb.MhaArgs(pwb.PW_BF16, ptr(qt), ptr(kvt), ptr(kvt) + 2 * hd, ldq, ldkv, 1, Tq, Tk, 1, hd, 0)
+    ctx.mha_fwd(a, ptr(o), ptr(lse), ptr(o_lo))
+    ctx.mha_bwd(a, ptr(o), ptr(gt), ptr(lse), ptr(delta), ptr(dq), hd, ptr(dkv), ptr(dkv) + 2 * hd, 2 * hd, ptr(o_lo))
+    ctx.synchronize()
+    qv, kv_, gv = (np.ascontiguousarray(x, np.float64) for x in (q, kv, g))
+    k, v = np.ascontiguousarray(kv_[:, :hd]), np.ascontiguousarray(kv_[:, hd:])
+    assert_close(host(o), orc.mha_fwd(qv, k, v, 1, Tq, Tk, 1, hd), 6e-3)
+    for got, ref in zip((host(dq), host(dkv)[:, :hd], host(dkv)[:, hd:]), orc.mha_bwd(qv, k, v, gv, 1, Tq, Tk, 1, hd)):
+        assert_close(got, ref, 1.5e-2)
+    del qt, kvt
+    torch.cuda.empty_cache()                  # 13 GB
+
+
 @pytest.mark.parametrize("bf16", [False, True])
 @pytest.mark.parametrize("B,T,V", [(3, 5, 1024), (2, 7, 4096), (1, 3, 32768), (2, 2, 8)])
 def test_softmax_xent(ctx, orc, B, T, V, bf16):
