@@ -473,10 +473,10 @@ static bool is_packed_causal(const MhaArgs& a) {
 
 hipError_t launch_mha_fwd(hipStream_t s, const MhaArgs& a, void* o, void* o_lo, float* lse) {
   if (!mha_args_ok(a) || !o || !lse) return hipErrorInvalidValue;
-  const bool packed64 = a.dtype == kBF16 && a.hd == 64 && is_packed_causal(a);
-  if (packed64 && (((uintptr_t)a.q | (uintptr_t)o) & 15)) return hipErrorInvalidValue;
+  const bool packed = a.dtype == kBF16 && is_packed_causal(a);
+  if (packed && (((uintptr_t)a.q | (uintptr_t)o) & 15)) return hipErrorInvalidValue;
   if (use_dma_kernels() && mha_dma_supported(a) && !(((uintptr_t)o | (uintptr_t)o_lo) & 15))
-    return launch_mha_fwd_dma(s, a, o, o_lo, lse, !packed64);
+    return launch_mha_fwd_dma(s, a, o, o_lo, lse, a.hd == 64 && !packed);
   if (a.dtype == kF32) return a.hd == 64 ? fwd_f32<float, 64>(s, a, o, o_lo, lse) : fwd_f32<float, 128>(s, a, o, o_lo, lse);
   return a.hd == 64 ? fwd_f32<bf16, 64>(s, a, o, o_lo, lse) : fwd_f32<bf16, 128>(s, a, o, o_lo, lse);
 }
@@ -488,11 +488,12 @@ hipError_t launch_mha_bwd(hipStream_t s, const MhaArgs& a, const void* o, const 
   if (lddq < d || lddkv < d) return hipErrorInvalidValue;
   const size_t es = a.dtype == kBF16 ? 2 : 4;
   const bool packed_out = lddq == 3 * d && lddkv == 3 * d && (char*)dk == (char*)dq + d * es && (char*)dv == (char*)dq + 2 * d * es;
-  const bool packed64 = a.dtype == kBF16 && a.hd == 64 && is_packed_causal(a) && packed_out;
-  if (packed64 && (((uintptr_t)a.q | (uintptr_t)o | (uintptr_t)dout | (uintptr_t)dq) & 15)) return hipErrorInvalidValue;
-  if (use_dma_kernels() && mha_dma_supported(a) && !(((uintptr_t)o | (uintptr_t)o_lo | (uintptr_t)dout) & 15) &&
-      (a.hd == 128 || mha_dma_outputs_aligned(dq, lddq, dk, dv, lddkv)))
-    return launch_mha_dq_dkv_dma(s, a, o, o_lo, dout, lse, delta, dq, lddq, dk, dv, lddkv, !packed64);
+  const bool packed = a.dtype == kBF16 && is_packed_causal(a) && packed_out;
+  const bool dma = use_dma_kernels() && mha_dma_supported(a) && !(((uintptr_t)o | (uintptr_t)o_lo | (uintptr_t)dout) & 15) &&
+                   (a.hd == 128 || mha_dma_outputs_aligned(dq, lddq, dk, dv, lddkv));
+  // (at head_dim 128 the direct-to-LDS kernels have always taken gradients on 8-byte boundaries)
+  if (packed && !(dma && a.hd == 128) && (((uintptr_t)a.q | (uintptr_t)o | (uintptr_t)dout | (uintptr_t)dq) & 15)) return hipErrorInvalidValue;
+  if (dma) return launch_mha_dq_dkv_dma(s, a, o, o_lo, dout, lse, delta, dq, lddq, dk, dv, lddkv, a.hd == 64 && !packed);
   if (a.dtype == kF32)
     return a.hd == 64 ? bwd_f32<float, 64>(s, a, o, o_lo, dout, lse, delta, dq, lddq, dk, dv, lddkv)
                       : bwd_f32<float, 128>(s, a, o, o_lo, dout, lse, delta, dq, lddq, dk, dv, lddkv);

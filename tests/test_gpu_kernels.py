@@ -542,6 +542,38 @@ def test_general_attention_rejects_bad_arguments(ctx):
     ctx.synchronize()
 
 
+@pytest.mark.parametrize("hd", [64, 128])
+def test_packed_causal_bf16_attention_rejects_misaligned_arrays(ctx, hd):
+    B, T, H = 1, 40, 2
+    d = H * hd
+    t = lambda n: torch.zeros(n + 8, dtype=torch.bfloat16, device="cuda")  # noqa: E731
+    qkv, o, g, dqkv = t(B * T * 3 * d), t(B * T * d), t(B * T * d), t(B * T * 3 * d)
+    lse, delta = torch.zeros((B, H, T), device="cuda"), torch.zeros((B, H, T), device="cuda")
+
+    def fwd(i=0, j=0):
+        ctx.op("attention_fwd", pwb.PW_BF16, ptr(qkv) + i, ptr(o) + j, ptr(lse), B, T, H, hd)
+
+    def bwd(i=0, j=0, k=0, m=0):
+        ctx.op("attention_bwd", pwb.PW_BF16, ptr(qkv) + i, ptr(o) + j, ptr(g) + k, ptr(lse), ptr(delta), ptr(dqkv) + m, B, T, H, hd)
+    for off in (2, 8):
+        for bad in (dict(i=off), dict(j=off)):
+            with pytest.raises(pwb.PwError):
+                fwd(**bad)
+        for bad in (dict(i=off), dict(j=off), dict(k=off)):
+            with pytest.raises(pwb.PwError):
+                bwd(**bad)
+    with pytest.raises(pwb.PwError):
+        bwd(m=2)
+    if hd == 64:
+        with pytest.raises(pwb.PwError):
+            bwd(m=8)
+    else:
+        bwd(m=8)                              # taken at this head width
+    fwd()
+    bwd()
+    ctx.synchronize()
+
+
 # ---- softmax cross-entropy ----------------------------------------------------------------------------
 
 # query blocks of 128, key tiles of 64, 32-row MFMA blocks and one to either side of each; probabilities enter the products
