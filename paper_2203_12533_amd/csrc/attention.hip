@@ -22,10 +22,10 @@ namespace pw {
 
 bool mha_dma_supported(const MhaArgs& a);
 bool mha_dma_outputs_aligned(const void* dq, int64_t lddq, const void* dk, const void* dv, int64_t lddkv);
-hipError_t launch_mha_fwd_dma(hipStream_t s, const MhaArgs& a, void* o, void* o_lo, float* lse, bool exact);
+hipError_t launch_mha_fwd_dma(hipStream_t s, const MhaArgs& a, void* o, void* o_lo, float* lse, bool split);
 hipError_t launch_mha_dq_dkv_dma(hipStream_t s, const MhaArgs& a, const void* o, const void* o_lo, const void* dout,
                                  const float* lse, float* delta, void* dq, int64_t lddq, void* dk, void* dv, int64_t lddkv,
-                                 bool exact);
+                                 bool split);
 
 // ---- the fp32 matrix-core family -----------------------------------------------------------------------
 // v_mfma_f32_16x16x4_f32: A lane l = row l%16, k-slot l/16; B lane l = column l%16, the same k-slot; D lane l = column
@@ -463,7 +463,7 @@ static bool use_dma_kernels() {
 }
 
 // Packed causal self-attention: at head_dim 64 the one form whose probabilities are rounded to bf16 for the second
-// products (as at head_dim 128 throughout); the others keep them exact.
+// products (as at head_dim 128 throughout); the others split them.
 static bool is_packed_causal(const MhaArgs& a) {
   const int64_t d = (int64_t)a.H * a.hd;
   const size_t es = a.dtype == kBF16 ? 2 : 4;

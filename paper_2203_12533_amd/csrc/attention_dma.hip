@@ -19,19 +19,22 @@
 // then hit 16 distinct 16-byte bank groups, and the 4 rows touched by one transposing read fall into 4
 // different 64-byte windows.  At head_dim 64 a row is half of the 256 bytes all banks hold and its parity picks the half:
 // c ^ ((((r >> 1) & 1) << 2) | ((r >> 2) & 3)) does the same.
-// SPLIT (head_dim 64, all but packed causal self-attention): probabilities and dS enter the second products as two bf16
-// values each, what the first one's rounding left over in the second, i.e. as exactly as in fp32 - these calls have always
-// been computed in fp32.  Measured (us, forward and backward): 4 x 333 queries over 520 keys, 8 heads: 116 on the fp32
-// matrix pipe -> 53; 2 x 2014 over 1092, 9 heads: 189.  Packed causal, 4 x 1000, 12 heads: 131 with tiles staged through
-// registers and a transposed copy in LDS -> 85.
+// SPLIT (head_dim 64, all but packed causal self-attention): these calls have always been computed in fp32.  The forward's
+// probabilities enter the second product as three bf16 values, which together are the fp32 ones: O with its remainder o_lo is
+// as close to 64 bits as the fp32 kernels bring it (2.5e-6 in the norm, what the storage of the pair rounds off; with two
+// values 3.4e-6).  In the backward two values do, 2^-17 of P and dS left out: dQ, dK and dV are stored in 8 bits, and their
+// errors against 64 bits are those of the fp32 kernels to four digits (1.66e-3), also where keys and values share a component
+// 64 times their spread.  Measured (us, forward and backward): 4 x 333 queries over 520 keys, 8 heads: 116 on the fp32
+// matrix pipe -> 54; 2 x 2014 over 1092, 9 heads: 189.  The forward's third value: 10.3 -> 11.2 there, 8 x 700, 16 heads 40 -> 45.
+// Packed causal, 4 x 1000, 12 heads: 131 with tiles staged through registers and a transposed copy in LDS -> 86.
 // PARTS = 2, for few blocks: a wave alone takes 1.2 to 1.5 us per step whatever else the chip does (products, softmax and
 // barrier one behind the other), so a launch that leaves units idle, or whose causal mask gives one block twice the average,
 // lasts as long as its longest chain of steps.  Blocks of 64 rows then, two waves to 32 of them that take the halves of every
-// tile in turn and add up through LDS at the end: half the steps, in the same fp32 sums.  The two above: 53 -> 43.5, 85 -> 73.8.
+// tile in turn and add up through LDS at the end: half the steps, in the same fp32 sums.  The two above: 54 -> 44, 86 -> 75.
 // Rows past the end of a sequence are fetched from a block of zeros; every use of such a row is masked or multiplied by an
 // exact zero (P = exp2(-inf)).
 // Values that are not finite.  A masked pair enters the second products with a probability of zero, and zero times infinity
-// is NaN; so is the sum of the two parts of a split probability, of either sign, times infinity.  With SPLIT these calls give
+// is NaN; so is a split probability times infinity where a part of it is zero or negative.  With SPLIT these calls give
 // what a sum over the visible pairs alone gives: rows that did not come out finite are summed once more, pair by pair, at
 // the end (nothing in the loop).  Without it (head_dim 128, packed causal) a masked value that is not finite spoils rows of
 // its tile.
@@ -144,29 +147,48 @@ __device__ __forceinline__ f32x16 first_product(const bf16* __restrict__ tile, i
   return acc;
 }
 
-// The second operand of a second product: 8 probabilities (or dS) per lane in bf16, and - SPLIT - what their rounding left
-// over, so that the product is as exact as with fp32 probabilities (2^-17).
-template <bool SPLIT> struct Frag { bf16x8 hi, lo; };
-template <> struct Frag<false> { bf16x8 hi; };
-template <bool SPLIT>
-__device__ __forceinline__ Frag<SPLIT> pack_frag(const f32x16& v, int first) {
-  Frag<SPLIT> f;
-  f.hi = pack8(v, first);
-  if constexpr (SPLIT) {
+// The second operand of a second product: 8 probabilities (or dS) per lane as a sum of TERMS bf16 values.  Three, each the
+// upper half of what the ones before left over, are the fp32 value itself; two, rounded, leave 2^-17 of it.
+template <int TERMS> struct Frag { bf16x8 v[TERMS]; };
+template <int TERMS>
+__device__ __forceinline__ Frag<TERMS> pack_frag(const f32x16& v, int first) {
+  Frag<TERMS> f;
+  if constexpr (TERMS == 3) {
+    union { uint32_t w[4]; bf16x8 v; } u[3];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) f.lo[e] = (bf16)(v[first + e] - (float)f.hi[e]);
+    for (int e = 0; e < 8; e += 2) {
+      float x = v[first + e], y = v[first + e + 1];
+#pragma unroll
+      for (int t = 0; t < 3; ++t) {
+        u[t].w[e / 2] = __builtin_amdgcn_perm(__float_as_uint(y), __float_as_uint(x), 0x07060302u);   // both upper halves
+        x -= __uint_as_float(__float_as_uint(x) & 0xffff0000u);
+        y -= __uint_as_float(__float_as_uint(y) & 0xffff0000u);
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < 3; ++t) f.v[t] = u[t].v;
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      float left = v[first + e];
+#pragma unroll
+      for (int t = 0; t < TERMS; ++t) {
+        f.v[t][e] = (bf16)left;
+        left -= (float)f.v[t][e];
+      }
+    }
   }
   return f;
 }
-template <bool SPLIT>
-__device__ __forceinline__ void mfma_frag(const bf16x8& a, const Frag<SPLIT>& b, f32x16& acc) {
-  if constexpr (SPLIT) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b.lo, acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b.hi, acc, 0, 0, 0);
+template <int TERMS>
+__device__ __forceinline__ void mfma_frag(const bf16x8& a, const Frag<TERMS>& b, f32x16& acc) {
+#pragma unroll
+  for (int t = TERMS - 1; t >= 0; --t) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b.v[t], acc, 0, 0, 0);   // smallest first
 }
 
 // acc[cb] += Tile^T[features cb*32 ..][rows row_base .. row_base+15] . frag, the tile read transposed.
-template <int HD, bool SPLIT>
-__device__ __forceinline__ void second_product(const bf16* __restrict__ tile, int row_base, const Frag<SPLIT>& frag, f32x16* acc) {
+template <int HD, int TERMS>
+__device__ __forceinline__ void second_product(const bf16* __restrict__ tile, int row_base, const Frag<TERMS>& frag, f32x16* acc) {
   const int lane = threadIdx.x & 63;
   const int grp = lane >> 4, L = lane & 15;
   const int row0 = row_base + 8 * (grp >> 1) + (L >> 2);          // tile row this lane points at for t = 0
@@ -181,7 +203,7 @@ __device__ __forceinline__ void second_product(const bf16* __restrict__ tile, in
       const bf16* p = tile + row * HD + ((chunk ^ swz<HD>(row)) << 3) + (f0 & 7);
       u.h[t] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4v*)p);
     }
-    mfma_frag<SPLIT>(u.v, frag, acc[cb]);
+    mfma_frag<TERMS>(u.v, frag, acc[cb]);
   }
 }
 
@@ -273,7 +295,7 @@ template <int HD, int PARTS> constexpr int kSubRows = HD == 128 && PARTS == 2 ? 
 template <int HD, bool CAUSAL, bool SPLIT, int PARTS>
 __global__ __launch_bounds__(kNT, 2) void attn_fwd_dma_kernel(MhaDev a, bf16* __restrict__ o, bf16* __restrict__ o_lo,
                                                               float* __restrict__ lse) {
-  constexpr int kSub = kSubRows<HD, PARTS>, BKV = kSub * PARTS, kRows = 128 / PARTS;
+  constexpr int kSub = kSubRows<HD, PARTS>, BKV = kSub * PARTS, kRows = 128 / PARTS, kTerms = SPLIT ? 3 : 1;
   constexpr int kTile = BKV * HD;                       // elements per K (or V) tile
   extern __shared__ __attribute__((aligned(1024))) bf16 smem[];         // [stage][K | V]
   const int Tq = a.Tq, Tk = a.Tk, H = a.H;
@@ -369,7 +391,7 @@ __global__ __launch_bounds__(kNT, 2) void attn_fwd_dma_kernel(MhaDev a, bf16* __
 #pragma unroll
     for (int kb = 0; kb < kSub / 32; ++kb)
 #pragma unroll
-      for (int b2 = 0; b2 < 2; ++b2) second_product<HD, SPLIT>(Vs, kb * 32 + b2 * 16, pack_frag<SPLIT>(s[kb], b2 * 8), acc);
+      for (int b2 = 0; b2 < 2; ++b2) second_product<HD, kTerms>(Vs, kb * 32 + b2 * 16, pack_frag<kTerms>(s[kb], b2 * 8), acc);
   }
   l += __shfl_xor(l, 32, 64);
   if constexpr (PARTS > 1) {   // the second part hands its reference, sum and accumulators over through LDS
@@ -421,7 +443,7 @@ template <int HD, bool CAUSAL, bool SPLIT, int PARTS>
 __global__ __launch_bounds__(kNT, 2) void attn_dq_dma_kernel(MhaDev a, const bf16* __restrict__ o, const bf16* __restrict__ o_lo,
                                                              const bf16* __restrict__ dout, const float* __restrict__ lse,
                                                              float* __restrict__ delta, bf16* __restrict__ dq, int64_t lddq) {
-  constexpr int kSub = kSubRows<HD, PARTS>, BKV = kSub * PARTS, kRows = 128 / PARTS;
+  constexpr int kSub = kSubRows<HD, PARTS>, BKV = kSub * PARTS, kRows = 128 / PARTS, kTerms = SPLIT ? 2 : 1;
   constexpr int kTile = BKV * HD;
   extern __shared__ __attribute__((aligned(1024))) bf16 smem[];
   const int Tq = a.Tq, Tk = a.Tk, H = a.H;
@@ -508,7 +530,7 @@ __global__ __launch_bounds__(kNT, 2) void attn_dq_dma_kernel(MhaDev a, const bf1
 #pragma unroll
       for (int r = 0; r < 16; ++r) s[r] = __builtin_amdgcn_exp2f(fmaf(s[r], c2, -lse2)) * (dp[r] - dl);
 #pragma unroll
-      for (int b2 = 0; b2 < 2; ++b2) second_product<HD, SPLIT>(Ks, kb * 32 + b2 * 16, pack_frag<SPLIT>(s, b2 * 8), acc);   // dQ^T += K^T . dS^T
+      for (int b2 = 0; b2 < 2; ++b2) second_product<HD, kTerms>(Ks, kb * 32 + b2 * 16, pack_frag<kTerms>(s, b2 * 8), acc);   // dQ^T += K^T . dS^T
     }
   }
   if constexpr (PARTS > 1)
@@ -559,10 +581,10 @@ __device__ __forceinline__ void load_stats(const float* Ls, const float* Ds, int
 // First products of block `next` (sn = S, dpn = dP against the tile rows rbn .. rbn+31 of Qn / Gn), with - when
 // HAVE_CUR - the arithmetic of block `cur` between the MFMAs: s becomes P = exp2(S c2 - lse), ds = P (dP - delta).
 // (Masked scores are handled through the statistics: a log-sum-exp of +inf makes P an exact zero.)
-template <int HD, bool SPLIT, bool HAVE_NEXT, bool HAVE_CUR>
+template <int HD, int TERMS, bool HAVE_NEXT, bool HAVE_CUR>
 __device__ __forceinline__ void dkv_front(const bf16* __restrict__ Qn, const bf16* __restrict__ Gn, int rbn,
                                           const bf16x8* kf, const bf16x8* vf, f32x16& sn, f32x16& dpn, f32x16& s,
-                                          const f32x16& dp, const DkvStats& st, float c2, Frag<SPLIT>* pf, Frag<SPLIT>* dsf) {
+                                          const f32x16& dp, const DkvStats& st, float c2, Frag<TERMS>* pf, Frag<TERMS>* dsf) {
   constexpr int kDepth = 3, KK = HD / 16, kElems = 16 / (2 * KK);   // score elements per MFMA
   const int lane = threadIdx.x & 63;
   const int row = rbn + perm_row(lane & 31);
@@ -608,17 +630,17 @@ __device__ __forceinline__ void dkv_front(const bf16* __restrict__ Qn, const bf1
   if (HAVE_CUR) {
 #pragma unroll
     for (int b2 = 0; b2 < 2; ++b2) {
-      pf[b2] = pack_frag<SPLIT>(s, b2 * 8);
-      dsf[b2] = pack_frag<SPLIT>(ds, b2 * 8);
+      pf[b2] = pack_frag<TERMS>(s, b2 * 8);
+      dsf[b2] = pack_frag<TERMS>(ds, b2 * 8);
     }
   }
 }
 
 // Second products of a block: dv += Gs^T . P and dk += Qs^T . dS over the 32 queries at tile rows rb .. rb+31,
-// HD / 8 MFMAs (twice as many with SPLIT) whose transposed operand reads run kAhead steps ahead.
-template <int HD, bool SPLIT>
-__device__ __forceinline__ void dkv_back(const bf16* __restrict__ Qs, const bf16* __restrict__ Gs, int rb, const Frag<SPLIT>* pf,
-                                         const Frag<SPLIT>* dsf, f32x16* dk, f32x16* dv) {
+// TERMS * HD / 8 MFMAs whose transposed operand reads run kAhead steps ahead.
+template <int HD, int TERMS>
+__device__ __forceinline__ void dkv_back(const bf16* __restrict__ Qs, const bf16* __restrict__ Gs, int rb, const Frag<TERMS>* pf,
+                                         const Frag<TERMS>* dsf, f32x16* dk, f32x16* dv) {
   constexpr int kAhead = 2, kBlocks = HD / 32, kSteps = 4 * kBlocks;
   const int lane = threadIdx.x & 63;
   const int grp = lane >> 4, L = lane & 15;
@@ -646,7 +668,7 @@ __device__ __forceinline__ void dkv_back(const bf16* __restrict__ Qs, const bf16
   for (int j = 0; j < kSteps; ++j) {
     if (j + kAhead < kSteps) fr[(j + kAhead) % (kAhead + 1)] = read(j + kAhead);
     const int b2 = j / (2 * kBlocks), mat = (j / kBlocks) & 1, cb = j % kBlocks;
-    mfma_frag<SPLIT>(fr[j % (kAhead + 1)], mat ? dsf[b2] : pf[b2], mat ? dk[cb] : dv[cb]);
+    mfma_frag<TERMS>(fr[j % (kAhead + 1)], mat ? dsf[b2] : pf[b2], mat ? dk[cb] : dv[cb]);
     __builtin_amdgcn_sched_barrier(0);
   }
 }
@@ -684,7 +706,7 @@ template <int HD, bool CAUSAL, bool SPLIT, int PARTS>
 __global__ __launch_bounds__(kNT, HD == 64 ? 2 : 1) void attn_dkv_dma_kernel(MhaDev a, const bf16* __restrict__ dout,
                                                             const float* __restrict__ lse, const float* __restrict__ delta,
                                                             bf16* __restrict__ dk_out, bf16* __restrict__ dv_out, int64_t lddkv) {
-  constexpr int BQ = 64, kStages = 3, kRows = 128 / PARTS;
+  constexpr int BQ = 64, kStages = 3, kRows = 128 / PARTS, kTerms = SPLIT ? 2 : 1;
   constexpr int kTile = BQ * HD;
   extern __shared__ __attribute__((aligned(1024))) bf16 smem[];          // [stage][Q | dO], then the statistics
   float (*Ls)[BQ] = reinterpret_cast<float (*)[BQ]>(smem + kStages * 2 * kTile);
@@ -784,7 +806,7 @@ __global__ __launch_bounds__(kNT, HD == 64 ? 2 : 1) void attn_dkv_dma_kernel(Mha
   // Two sets of score registers: the even block of a tile lives in (s0, dp0), the odd one in (s1, dp1), so nothing is
   // ever copied from "next" to "current".
   f32x16 s0, dp0, s1, dp1;
-  Frag<SPLIT> pf[2], dsf[2];
+  Frag<kTerms> pf[2], dsf[2];
   DkvStats st;
   // One step of the pipeline: the arithmetic of block n (scores in s, dp) between the first products of block n + 1
   // (into sn, dpn; NEXT: there is one), then the second products of block n.
@@ -816,10 +838,10 @@ __global__ __launch_bounds__(kNT, HD == 64 ? 2 : 1) void attn_dkv_dma_kernel(Mha
         asm volatile("" : "+v"(st.lq[r]));
       }
     }
-    dkv_front<HD, SPLIT, NEXT, true>(Qn, Qn + kTile, (nn & 1) * 32, kf, vf, sn, dpn, s, dp, st, c2, pf, dsf);
+    dkv_front<HD, kTerms, NEXT, true>(Qn, Qn + kTile, (nn & 1) * 32, kf, vf, sn, dpn, s, dp, st, c2, pf, dsf);
     // the next block's statistics travel to registers under the second products (its tile is resident: see advance)
     if (NEXT) load_stats(Ls[(nn >> 1) % kStages], Ds[(nn >> 1) % kStages], nn & 1, half, st);
-    dkv_back<HD, SPLIT>(Qs, Qs + kTile, hb * 32, pf, dsf, dk, dv);
+    dkv_back<HD, kTerms>(Qs, Qs + kTile, hb * 32, pf, dsf, dk, dv);
     // Register classes: the output accumulators and the K / V fragments are only ever touched by MFMAs and live in
     // the accumulation registers; the scores are worked on by the vector ALU and stay in ordinary registers, so no
     // MFMA result has to be copied across (with the wait states that costs).
@@ -842,7 +864,7 @@ __global__ __launch_bounds__(kNT, HD == 64 ? 2 : 1) void attn_dkv_dma_kernel(Mha
     }
     if (any) {
       first_stats(2 * t0, st);
-      dkv_front<HD, SPLIT, true, false>(tile_q(2 * t0), tile_q(2 * t0) + kTile, 0, kf, vf, s0, dp0, s0, dp0, st, c2, pf, dsf);
+      dkv_front<HD, kTerms, true, false>(tile_q(2 * t0), tile_q(2 * t0) + kTile, 0, kf, vf, s0, dp0, s0, dp0, st, c2, pf, dsf);
       for (int t = t0; t + 1 < n_tiles; ++t) {
         step(2 * t, yes{}, s0, dp0, s1, dp1);
         advance(t);
@@ -854,7 +876,7 @@ __global__ __launch_bounds__(kNT, HD == 64 ? 2 : 1) void attn_dkv_dma_kernel(Mha
   } else {
     // One block per tile and wave, the next one in the next tile: every step is led by the wait for it.
     first_stats(2 * first_tile + part, st);
-    dkv_front<HD, SPLIT, true, false>(tile_q(2 * first_tile + part), tile_q(2 * first_tile + part) + kTile, part * 32, kf, vf, s0, dp0, s0, dp0, st, c2, pf, dsf);
+    dkv_front<HD, kTerms, true, false>(tile_q(2 * first_tile + part), tile_q(2 * first_tile + part) + kTile, part * 32, kf, vf, s0, dp0, s0, dp0, st, c2, pf, dsf);
     int t = first_tile;
     for (; t + 2 < n_tiles; t += 2) {
       advance(t);
@@ -960,13 +982,13 @@ static hipError_t fwd_dma(hipStream_t s, const MhaArgs& a, void* o, void* o_lo, 
   else run(attn_fwd_dma_kernel<HD, CAUSAL, SPLIT, 1>, blocks_of<1>(a.Tq, a), kSmemTiles<HD, 1>);
   return hipGetLastError();
 }
-// exact: probabilities enter the products with V, K, Q and dO as fp32 would (head_dim 64 only).
-hipError_t launch_mha_fwd_dma(hipStream_t s, const MhaArgs& a, void* o, void* o_lo, float* lse, bool exact) {
+// split: probabilities and dS enter the second products as sums of bf16 values (SPLIT; head_dim 64 only).
+hipError_t launch_mha_fwd_dma(hipStream_t s, const MhaArgs& a, void* o, void* o_lo, float* lse, bool split) {
   const hipError_t e = attention_dma_init();
   if (e != hipSuccess) return e;
   if (a.hd == 128) return a.causal ? fwd_dma<128, true, false>(s, a, o, o_lo, lse) : fwd_dma<128, false, false>(s, a, o, o_lo, lse);
   if (!a.causal) return fwd_dma<64, false, true>(s, a, o, o_lo, lse);
-  return exact ? fwd_dma<64, true, true>(s, a, o, o_lo, lse) : fwd_dma<64, true, false>(s, a, o, o_lo, lse);
+  return split ? fwd_dma<64, true, true>(s, a, o, o_lo, lse) : fwd_dma<64, true, false>(s, a, o, o_lo, lse);
 }
 
 struct MhaGrads { const void *o, *o_lo, *dout; const float* lse; float* delta; void* dq; int64_t lddq; void *dk, *dv; int64_t lddkv; };
@@ -989,14 +1011,14 @@ bool mha_dma_outputs_aligned(const void* dq, int64_t lddq, const void* dk, const
 }
 hipError_t launch_mha_dq_dkv_dma(hipStream_t s, const MhaArgs& a, const void* o, const void* o_lo, const void* dout,
                                  const float* lse, float* delta, void* dq, int64_t lddq, void* dk, void* dv, int64_t lddkv,
-                                 bool exact) {
+                                 bool split) {
   const hipError_t e = attention_dma_init();
   if (e != hipSuccess) return e;
   if (!mha_dma_outputs_aligned(dq, lddq, dk, dv, lddkv)) return hipErrorInvalidValue;
   const MhaGrads g{o, o_lo, dout, lse, delta, dq, lddq, dk, dv, lddkv};
   if (a.hd == 128) return a.causal ? bwd_dma<128, true, false>(s, a, g) : bwd_dma<128, false, false>(s, a, g);
   if (!a.causal) return bwd_dma<64, false, true>(s, a, g);
-  return exact ? bwd_dma<64, true, true>(s, a, g) : bwd_dma<64, true, false>(s, a, g);
+  return split ? bwd_dma<64, true, true>(s, a, g) : bwd_dma<64, true, false>(s, a, g);
 }
 
 }  // namespace pw
