@@ -46,8 +46,7 @@ hipError_t launch_embedding_fwd(hipStream_t s, const int32_t* tokens, const floa
 // dwte - a count and, as far as they fit, the positions in whatever order integer atomics deal the slots - which the last
 // kernel sorts and overwrites.  That kernel writes each row once: zeros for an unused id, else the sum of its rows.
 // HBM-bound by the write of dwte (268 of the 345 MB that 8192 positions, 32768 ids of 2048 columns cannot do without).
-// Measured there 85 us; a fill of dwte and a search through all tokens by the workgroup of every position took 143 (1024
-// ids: 32 against 60; 256 columns: 23 against 77).
+// A fill of dwte and a search through all tokens by the workgroup of every position took twice as long there.
 __device__ __forceinline__ int id_slots(int d) { return d - 1 < 2047 ? d - 1 : 2047; }   // positions that fit the row
 
 __global__ __launch_bounds__(256) void embedding_ids_reset_kernel(float* __restrict__ dwte, int d, int V) {
@@ -63,22 +62,32 @@ __global__ __launch_bounds__(256) void embedding_ids_gather_kernel(const int32_t
   if (slot < id_slots(d)) row[1 + slot] = p;
 }
 
-// VEC float4 per thread cover a row (d <= 1024 * VEC).  The first blocks take kEbRows rows of dwte each (what is known about
-// them is read in one go: with a row of its own a block spends as long waiting for it as writing), the last T blocks one
-// row of dwpe (the sum over the batch).
-// SCAN, for at most kEbScan positions: nothing has been gathered; every block looks through all tokens for its ids, which
-// takes less time than two more launches (512 positions, 5000 ids of 1012 columns, with the forward lookup: 9.4 us against
-// 17.8, and 15.8 with the fill and search).
-constexpr int kEbRows = 4;
+// A row of dwte or dwpe belongs to a group of TPR threads (16 to 256, VEC float4 each: d <= 4 * TPR * VEC); the 256 / TPR
+// groups of a block work side by side, so that narrow rows fill it too.  The first `id_blocks` blocks take kEbRows rows of dwte
+// each (what is known about them is read in one go: with a row of its own a block spends as long waiting for it as writing),
+// rows id_blocks apart: frequent ids are often neighbours, and a block adds its long rows one after the other.  The other
+// blocks take dwpe (sums over the batch).
+// SCAN, for at most kEbScan positions: nothing has been gathered; every block looks through all tokens for its ids.  That
+// takes a time that grows with positions x blocks, two more launches about 5 us.  Both ways, us, at 2048 | 3000 positions: 32768
+// ids of 64 columns 9.2 / 12.0 | 11.6 / 12.2, of 256 16 / 20 | 20 / 20, of 2048 46 / 47 | 55 / 56; 100000 ids of 128 33 / 31 | 44 / 31,
+// of 1024 73 / 167 | 96 / 173; 1024 ids of 512 9 / 14 | 11 / 16.
+// Order of an id's positions: up to three by comparison; up to kPart by counting for each how many are below, all rows of the
+// block at once; more of them the same way row by row (n^2 / 256 steps of a thread) as long as that takes less than a look
+// through all N tokens in order (a step for every 256).
+// Measured (us; before: d / 4 threads for four neighbouring rows; before that: fill and search): 2048 positions over 32768 ids of
+// 64 columns 7.7 (31.1; 12.6), of 2048 columns 43 (42; 54); 8192 over 32768 x 2048 64 (65; 123); drawn log-uniformly 156 (241; 430),
+// over 1024 x 256 90 (338; 219).
+template <int TPR> constexpr int kEbGroups = 256 / TPR;
+template <int TPR> constexpr int kEbRows = TPR >= 256 ? 4 : TPR >= 64 ? 8 : 16;
 constexpr int kEbScan = 2048;
-template <int VEC, bool SCAN>
+template <int TPR, int VEC, bool SCAN>
 __global__ __launch_bounds__(256) void embedding_bwd_kernel(const int32_t* __restrict__ tokens, const float* __restrict__ dx,
                                                             float* __restrict__ dwte, float* __restrict__ dwpe, int B, int T,
-                                                            int d, int V, int stride, int id_blocks) {
+                                                            int d, int V, int stride, int id_blocks, uint32_t id_magic) {
   constexpr int kAhead = VEC <= 2 ? 8 : 8 / VEC;          // rows of dx in flight
-  constexpr int kList = 2048;
-  __shared__ int list[kList], sorted[kList], wave_cnt[4];
-  const int d4 = d >> 2, nt = blockDim.x, N = B * T;
+  constexpr int kList = 2048, G = kEbGroups<TPR>, R = kEbRows<TPR>, kPart = kList / R;
+  __shared__ int list[kList], sorted[kList], count[R + 1], wave_cnt[4];
+  const int d4 = d >> 2, N = B * T, group = threadIdx.x / TPR, lane_in = threadIdx.x % TPR;
   float4 acc[VEC];
   auto clear = [&] {
 #pragma unroll
@@ -88,7 +97,7 @@ __global__ __launch_bounds__(256) void embedding_bwd_kernel(const int32_t* __res
     const float4* row = reinterpret_cast<const float4*>(dx + (size_t)p * d);
 #pragma unroll
     for (int i = 0; i < VEC; ++i)
-      if ((int)threadIdx.x + i * nt < d4) v[i] = row[threadIdx.x + i * nt];
+      if (lane_in + i * TPR < d4) v[i] = row[lane_in + i * TPR];
   };
   auto add = [&](const float4 (&v)[VEC]) {
 #pragma unroll
@@ -114,106 +123,184 @@ __global__ __launch_bounds__(256) void embedding_bwd_kernel(const int32_t* __res
   auto store = [&](float* out) {
 #pragma unroll
     for (int i = 0; i < VEC; ++i)
-      if ((int)threadIdx.x + i * nt < d4) reinterpret_cast<float4*>(out)[threadIdx.x + i * nt] = acc[i];
+      if (lane_in + i * TPR < d4) reinterpret_cast<float4*>(out)[lane_in + i * TPR] = acc[i];
   };
   clear();
   if ((int)blockIdx.x >= id_blocks) {
-    const int t = blockIdx.x - id_blocks;
+    const int t = (blockIdx.x - id_blocks) * G + group;
+    if (t >= T) return;
     add_all(B, [&](int b) { return b * T + t; });
     store(dwpe + (size_t)t * d);
     return;
   }
-  const int id0 = blockIdx.x * kEbRows;
-  auto sort = [&](int n) {                                // list -> sorted; elements differ: a place is how many are below
-    for (int i = threadIdx.x; i < n; i += nt) {
+  auto id_of = [&](int r) { return (int)blockIdx.x + r * id_blocks; };
+  // from -> to, by `threads` threads; elements differ: a place is how many are below
+  auto sort = [](const int* from, int* to, int n, int thread, int threads) {
+    for (int i = thread; i < n; i += threads) {
+      const int mine = from[i];
       int place = 0;
-      for (int j = 0; j < n; ++j) place += list[j] < list[i];
-      sorted[place] = list[i];
+      for (int j = 0; j < n; ++j) place += from[j] < mine;
+      to[place] = mine;
     }
-    __syncthreads();
+  };
+  // A look through all tokens in order for row r; its group adds and stores.  The whole block calls.
+  auto search = [&](int r) {
+    const int id = id_of(r);
+    const bool owner = group == r % G;
+    clear();
+    int have = 0;
+    for (int base = 0; base < N; base += 256) {
+      const int p = base + threadIdx.x;
+      const bool hit = p < N && token_at(tokens, p, T, stride, V) == id;
+      const uint64_t mask = __ballot(hit);
+      const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+      if (lane == 0) wave_cnt[w] = __popcll(mask);
+      __syncthreads();
+      int before = 0, total = 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if (i < w) before += wave_cnt[i];
+        total += wave_cnt[i];
+      }
+      if (hit) list[have + before + __popcll(mask & ((1ull << lane) - 1))] = p;
+      have += total;
+      __syncthreads();
+      if (have + 256 > kList || base + 256 >= N) {
+        if (owner) add_all(have, [&](int k) { return list[k]; });
+        have = 0;
+        __syncthreads();
+      }
+    }
+    if (owner) store(dwte + (size_t)id * d);
   };
   if constexpr (SCAN) {
-    __shared__ int found[kEbRows + 1];                    // per row, and altogether
-    if (threadIdx.x <= kEbRows) found[threadIdx.x] = 0;
+    if (threadIdx.x <= R) count[threadIdx.x] = 0;         // per row, and altogether
     __syncthreads();
-    for (int p = threadIdx.x; p < N; p += nt) {
-      const int r = token_at(tokens, p, T, stride, V) - id0;
-      if (r >= 0 && r < kEbRows) {
-        atomicAdd(&found[r], 1);
-        list[atomicAdd(&found[kEbRows], 1)] = r * kEbScan + p;
+    const int rows_on = 256 / T, on = 256 - rows_on * T;  // positions 256 apart, as (row, column) of the token array
+    int t = threadIdx.x % T;
+    const int32_t* tok = tokens + (size_t)(threadIdx.x / T) * stride;
+    for (int p = threadIdx.x; p < N; p += 256) {
+      const int id = min(max(tok[t], 0), V - 1);
+      tok += (size_t)rows_on * stride;
+      t += on;
+      if (t >= T) t -= T, tok += stride;
+      int r = (int)__umulhi((uint32_t)id, id_magic), rest = id - r * id_blocks;   // id / id_blocks, one off at most
+      if (rest < 0) rest += id_blocks, --r;
+      if (rest >= id_blocks) rest -= id_blocks, ++r;
+      if (rest == (int)blockIdx.x) {
+        atomicAdd(&count[r], 1);
+        const int slot = atomicAdd(&count[R], 1);
+        if (slot < kList) list[slot] = r * kEbScan + p;
       }
     }
     __syncthreads();
-    if (found[kEbRows] > 0) sort(found[kEbRows]);
+    const int all = count[R];                             // (those behind kList are not in the list)
+    if (all > 256) {
+      for (int r = 0; r < R && id_of(r) < V; ++r) {
+        if (count[r] > 0) search(r);
+        else if (group == r % G) clear(), store(dwte + (size_t)id_of(r) * d);
+      }
+      return;
+    }
+    if (all > 0) {
+      sort(list, sorted, all, threadIdx.x, 256);
+      __syncthreads();
+    }
     int from = 0;
 #pragma unroll
-    for (int r = 0; r < kEbRows; ++r) {
-      if (id0 + r >= V) break;
-      if (r > 0) clear();
-      add_all(found[r], [&](int k) { return sorted[from + k] & (kEbScan - 1); });
-      from += found[r];
-      store(dwte + (size_t)(id0 + r) * d);
+    for (int k = 0; k < R / G; ++k) {
+      const int r = group + k * G;
+      if (id_of(r) >= V) break;
+      for (int q = k == 0 ? 0 : r - G; q < r; ++q) from += count[q];
+      if (k > 0) clear();
+      add_all(count[r], [&](int j) { return sorted[from + j] & (kEbScan - 1); });
+      store(dwte + (size_t)id_of(r) * d);
     }
     return;
   }
-  int4 use[kEbRows];                                      // the count and the first three slots
+  int4 use[R / G];                                        // the count and the first three slots
 #pragma unroll
-  for (int r = 0; r < kEbRows; ++r)
-    if (id0 + r < V) use[r] = *reinterpret_cast<const int4*>(dwte + (size_t)(id0 + r) * d);
+  for (int k = 0; k < R / G; ++k) {
+    const int r = group + k * G;
+    use[k] = id_of(r) < V ? *reinterpret_cast<const int4*>(dwte + (size_t)id_of(r) * d) : make_int4(-1, 0, 0, 0);
+    if (lane_in == 0) count[r] = use[k].x;
+  }
   __syncthreads();                                        // every wave has read the first 16 bytes of the block's rows
 #pragma unroll
-  for (int r = 0; r < kEbRows; ++r) {
-    const int id = id0 + r;
-    if (id >= V) break;                                   // uniform, as everything that depends on a count
-    const int count = use[r].x;
-    if (r > 0) clear();
-    if (count <= 3) {
-      const int a = use[r].y, b = count > 1 ? use[r].z : 0x7fffffff, c = count > 2 ? use[r].w : 0x7fffffff;
-      const int lo = min(a, min(b, c)), hi = max(a, max(b, c));
-      const int mid = count == 2 ? max(a, b) : max(min(a, b), min(max(a, b), c));
-      add_all(count, [&](int k) { return k == 0 ? lo : k == 1 ? mid : hi; });
-    } else if (count <= id_slots(d)) {
-      const int* row = reinterpret_cast<const int*>(dwte + (size_t)id * d) + 1;
-      for (int i = threadIdx.x; i < count; i += nt) list[i] = row[i];
-      __syncthreads();
-      sort(count);
-      add_all(count, [&](int k) { return sorted[k]; });
-    } else {                                              // more than the row holds: look through all tokens, in order
-      int have = 0;
-      for (int base = 0; base < N; base += nt) {
-        const int p = base + threadIdx.x;
-        const bool hit = p < N && token_at(tokens, p, T, stride, V) == id;
-        const uint64_t mask = __ballot(hit);
-        const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-        if (lane == 0) wave_cnt[w] = __popcll(mask);
-        __syncthreads();
-        int before = 0, total = 0;
-        for (int i = 0; i < (nt >> 6); ++i) {
-          if (i < w) before += wave_cnt[i];
-          total += wave_cnt[i];
-        }
-        if (hit) list[have + before + __popcll(mask & ((1ull << lane) - 1))] = p;
-        have += total;
-        __syncthreads();
-        if (have + nt > kList || base + nt >= N) {
-          add_all(have, [&](int k) { return list[k]; });
-          have = 0;
-          __syncthreads();
-        }
-      }
+  for (int k = 0; k < R / G; ++k) {
+    const int n = use[k].x;
+    if (n < 0 || n > 3) continue;
+    const int a = use[k].y, b = n > 1 ? use[k].z : 0x7fffffff, c = n > 2 ? use[k].w : 0x7fffffff;
+    const int lo = min(a, min(b, c)), hi = max(a, max(b, c));
+    const int mid = n == 2 ? max(a, b) : max(min(a, b), min(max(a, b), c));
+    clear();
+    add_all(n, [&](int j) { return j == 0 ? lo : j == 1 ? mid : hi; });
+    store(dwte + (size_t)id_of(group + k * G) * d);
+  }
+  int longest = 0;
+#pragma unroll
+  for (int r = 0; r < R; ++r) longest = max(longest, count[r]);
+  if (longest <= 3) return;
+  // Rows whose positions fit a part of the list, all of them at once; then the others, the whole block row by row.
+  auto shared_part = [&](int n) { return n > 3 && n <= kPart && n <= id_slots(d); };
+#pragma unroll 1
+  for (int r = group; r < R; r += G)
+    if (shared_part(count[r]))
+      for (int i = lane_in; i < count[r]; i += TPR) list[r * kPart + i] = reinterpret_cast<const int*>(dwte + (size_t)id_of(r) * d)[1 + i];
+  __syncthreads();
+#pragma unroll 1
+  for (int r = group; r < R; r += G)
+    if (shared_part(count[r])) sort(list + r * kPart, sorted + r * kPart, count[r], lane_in, TPR);
+  __syncthreads();
+#pragma unroll 1
+  for (int r = group; r < R; r += G)
+    if (shared_part(count[r])) {
+      clear();
+      add_all(count[r], [&](int k) { return sorted[r * kPart + k]; });
+      store(dwte + (size_t)id_of(r) * d);
     }
-    store(dwte + (size_t)id * d);
+  __syncthreads();
+#pragma unroll 1
+  for (int r = 0; r < R; ++r) {
+    const int n = count[r];
+    if (n <= 3 || shared_part(n)) continue;
+    if (n > id_slots(d) || (int64_t)n * n > 128 * (int64_t)N) {
+      search(r);
+      continue;
+    }
+    float* const row = dwte + (size_t)id_of(r) * d;
+    for (int i = threadIdx.x; i < n; i += 256) list[i] = reinterpret_cast<const int*>(row)[1 + i];
+    __syncthreads();
+    sort(list, sorted, n, threadIdx.x, 256);
+    __syncthreads();
+    if (group == r % G) {
+      clear();
+      add_all(n, [&](int k) { return sorted[k]; });
+      store(row);
+    }
+    __syncthreads();
   }
 }
 
 template <bool SCAN>
-static void launch_embedding_bwd_rows(hipStream_t s, int block, const int32_t* tokens, const float* dx, float* dwte, float* dwpe,
-                                      int B, int T, int d, int V, int stride) {
-  const int id_blocks = (V + kEbRows - 1) / kEbRows, grid = id_blocks + T;
-  if (d <= 1024) embedding_bwd_kernel<1, SCAN><<<grid, block, 0, s>>>(tokens, dx, dwte, dwpe, B, T, d, V, stride, id_blocks);
-  else if (d <= 2048) embedding_bwd_kernel<2, SCAN><<<grid, block, 0, s>>>(tokens, dx, dwte, dwpe, B, T, d, V, stride, id_blocks);
-  else if (d <= 4096) embedding_bwd_kernel<4, SCAN><<<grid, block, 0, s>>>(tokens, dx, dwte, dwpe, B, T, d, V, stride, id_blocks);
-  else embedding_bwd_kernel<8, SCAN><<<grid, block, 0, s>>>(tokens, dx, dwte, dwpe, B, T, d, V, stride, id_blocks);
+static void launch_embedding_bwd_rows(hipStream_t s, const int32_t* tokens, const float* dx, float* dwte, float* dwpe, int B, int T,
+                                      int d, int V, int stride) {
+  auto run = [&](auto kernel, int rows, int groups) {
+    const int id_blocks = (V + rows - 1) / rows;
+    const uint64_t magic = (1ull << 32) / (uint64_t)id_blocks + 1;
+    kernel<<<id_blocks + (T + groups - 1) / groups, 256, 0, s>>>(tokens, dx, dwte, dwpe, B, T, d, V, stride, id_blocks,
+                                                                 (uint32_t)(magic < 0xffffffffull ? magic : 0xffffffffull));
+  };
+#define PW_EMBEDDING_BWD(TPR, VEC) run(embedding_bwd_kernel<TPR, VEC, SCAN>, kEbRows<TPR>, kEbGroups<TPR>)
+  if (d <= 64) PW_EMBEDDING_BWD(16, 1);
+  else if (d <= 128) PW_EMBEDDING_BWD(32, 1);
+  else if (d <= 256) PW_EMBEDDING_BWD(64, 1);
+  else if (d <= 512) PW_EMBEDDING_BWD(128, 1);
+  else if (d <= 1024) PW_EMBEDDING_BWD(256, 1);
+  else if (d <= 2048) PW_EMBEDDING_BWD(256, 2);
+  else if (d <= 4096) PW_EMBEDDING_BWD(256, 4);
+  else PW_EMBEDDING_BWD(256, 8);
+#undef PW_EMBEDDING_BWD
 }
 
 hipError_t launch_embedding_bwd(hipStream_t s, const int32_t* tokens, const float* dx, float* dwte, float* dwpe,
@@ -226,14 +313,12 @@ hipError_t launch_embedding_bwd(hipStream_t s, const int32_t* tokens, const floa
     const hipError_t e = launch_fill_f32(s, dwte, (int64_t)V * d, 0.f);
     return e != hipSuccess ? e : launch_fill_f32(s, dwpe, (int64_t)T * d, 0.f);
   }
-  int block = ((d >> 2) + 63) / 64 * 64;                  // one float4 per thread, whole waves, at most 256
-  if (block > 256) block = 256;
   if ((int64_t)B * T <= kEbScan) {
-    launch_embedding_bwd_rows<true>(s, block, tokens, dx, dwte, dwpe, B, T, d, V, stride);
+    launch_embedding_bwd_rows<true>(s, tokens, dx, dwte, dwpe, B, T, d, V, stride);
   } else {
     embedding_ids_reset_kernel<<<(V + 255) / 256, 256, 0, s>>>(dwte, d, V);
     embedding_ids_gather_kernel<<<(B * T + 255) / 256, 256, 0, s>>>(tokens, dwte, B * T, T, d, V, stride);
-    launch_embedding_bwd_rows<false>(s, block, tokens, dx, dwte, dwpe, B, T, d, V, stride);
+    launch_embedding_bwd_rows<false>(s, tokens, dx, dwte, dwpe, B, T, d, V, stride);
   }
   return hipGetLastError();
 }

@@ -957,6 +957,29 @@ def test_embedding_backward_adds_rows_in_order_of_position(ctx, B, T, d, V):
     assert np.array_equal(dwpe.cpu().numpy(), wpe)
 
 
+# rows of every width of a group of threads; few ids, so that every block has several long rows: as many positions as are
+# sorted side by side, row by row and looked up in order (by scan: 256 of a block and one more; gathered: what fits the row,
+# a part of the list, n^2 against 128 N), one block for all ids, the last position that is scanned for and one more
+@pytest.mark.parametrize("B,T,d,V", [(1, 256, 64, 5), (1, 257, 64, 5), (1, 300, 60, 1), (3, 600, 128, 40), (3, 701, 64, 33), (3, 701, 128, 9),
+                                     (3, 701, 512, 9), (3, 701, 516, 6), (3, 701, 1024, 3), (2, 1500, 1024, 5), (1, 2048, 256, 700), (1, 2049, 256, 700),
+                                     (2, 1100, 2052, 11), (1, 2300, 4, 3)])
+def test_embedding_backward_of_few_ids_adds_rows_in_order_of_position(ctx, B, T, d, V):
+    tok = I.tokens(9, 7, (B, T + 1), V)
+    tok[:, ::3] = V // 2                           # one of them a third of all
+    dx = _rand(55, (B, T, d))
+    td, xd = dev_i32(tok), dev_f32(dx)
+    dwte, dwpe = torch.full((V, d), 3.0, device="cuda"), torch.full((T, d), 3.0, device="cuda")
+    ctx.op("embedding_bwd", ptr(td), ptr(xd), ptr(dwte), ptr(dwpe), B, T, d, V)
+    ctx.synchronize()
+    want, wpe = np.zeros((V, d), np.float32), np.zeros((T, d), np.float32)
+    for b in range(B):
+        for t in range(T):                         # fp32 additions one after the other: the same bits
+            want[tok[b, t]] += dx[b, t]
+        wpe += dx[b]
+    assert np.array_equal(dwte.cpu().numpy(), want)
+    assert np.array_equal(dwpe.cpu().numpy(), wpe)
+
+
 # rows held in registers in 1, 2, 4 and 8 pieces per thread, one column past each, and rows read twice
 @pytest.mark.parametrize("bf16,V", [(True, 4096), (True, 4104), (True, 8200), (True, 16392), (True, 32776), (False, 2052),
                                     (False, 4100), (False, 8196), (False, 16388)])
