@@ -41,6 +41,7 @@
 // Queries, keys and values come with their own pointers, row strides and lengths (MhaDev), so one set of kernels
 // serves the packed causal self-attention of a decoder, the unmasked self-attention of an encoder and attention
 // of decoder queries over encoder keys; CAUSAL is a template parameter (it decides which tiles are visited).
+#include <algorithm>
 #include <type_traits>
 
 #include "attention_common.hpp"
@@ -961,24 +962,32 @@ bool mha_dma_supported(const MhaArgs& a) {
 template <int PARTS> static int blocks_of(int rows, const MhaArgs& a) { return (rows + 128 / PARTS - 1) / (128 / PARTS) * a.B * a.H; }
 // Whether two waves share 32 rows (PARTS = 2: blocks of 64 rows, half the steps each, every tile loaded twice as often).
 // It pays where the blocks of 128 leave compute units idle (twice as many still find one each: 128 of them), and under the
-// causal mask also up to a block per unit (two at head_dim 64, where units hold several), since the longest blocks, twice the
-// average, then decide - if those are long.  Both ways in us:
-//   forward: causal 2 x 1024, 16 x 128 28.4 -> 24.8; 4 x 1000, 12 x 64 23.8 -> 20.4; 4 x 2048, 8 x 64 42.1 -> 34.5; but 8 x 1000, 12 x 64
-//     (768 blocks) 31 -> 35, 16 x 256, 16 x 64 11.9 -> 14.6, 8 x 1024, 16 x 128 58 -> 74.  Unmasked, 4 x 1024, 8 x 64 (256) 26.9 -> 23.2, 4 x
-//     333 over 520 15.7 -> 11.0; but 16 x 512 (512) 25.3 -> 25.5, 4 x 1024, 16 x 64 40.2 -> 41.7.
-//   dQ (with dK/dV): causal 2 x 1024, 16 x 128 70.6 -> 66.0, 2 x 1024, 16 x 64 59.7 -> 54.7; 32 x 128, 12 x 64 23.5 -> 27.2.  Unmasked, 1 x 1000 over
-//     2000, 16 x 128 (128) 93 -> 81; 4 x 700 over 500, 8 x 128 (192) 50.0 -> 51.9.
-//   dK/dV (with dQ): causal 4 x 1000, 12 x 64 62.6 -> 53.4, 1 x 1024, 8 x 128 65.9 -> 53.9; 3 x 700, 12 x 128 (216) 53.8 -> 59.6.  Unmasked, 1 x 2048 over
-//     256, 16 x 128 (32) 83 -> 60.6, 4 x 700 over 500 (128) 50.0 -> 43.9; 4 x 333 over 520, 8 x 64 (160) 37.9 -> 39.8.
-static bool two_parts(const MhaArgs& a, int rows, int other, int unmasked_limit, int causal_limit) {
+// causal mask also up to a block per unit, at head_dim 64, where units hold several, up to one and a half, since the longest
+// blocks, twice the average, then decide - if those are long enough.  Both ways in us (one wave / two):
+//   forward: causal, T x 64: 64 (any number) 4.7 / 5.2; 128 blocks: 128 5.7 / 5.3, 192 6.2 / 6.3, 320 8.0 / 7.3; 256 blocks: 320 8.1 / 8.6, 384
+//     9.6 / 8.5, 448 9.9 / 10.0, 512 11.5 / 9.4; 384 blocks: 448 12.7 / 15.1, 512 15.3 / 14.0, 1024 23.7 / 19.7; 512 blocks: 512 13.6 / 14.8, 768
+//     17.8 / 23.7.  T x 128: 64 5.4 / 6.0; 256 blocks: 256 12.4 / 10.9, 320 11.9 / 13.0, 384 15.0 / 12.9, 448 14.9 / 15.4, 512 17.4 / 14.8, 1024
+//     28.2 / 22.0; 384 blocks: 512 22.9 / 22.3, 768 27.5 / 29.6.
+//     Unmasked, 192 blocks over keys of 64: 64 7.0 / 7.9, 100 8.7 / 8.1, 512 16.9 / 13.9; of 128: 128 10.8 / 11.7, 192 12.2 / 13.0, 256 13.8 / 14.2, 384
+//     18.3 / 17.4; 256 blocks, 1024 35.6 / 32.4; 512 blocks, 16 x 512 x 64 25.3 / 25.5.
+//   backward (dQ and dK/dV): causal, T x 64: 64 10.7 / 12.4; 128 blocks: 128 15.2 / 13.5; 256 blocks: 320 22.5 / 23.6, 384 25.7 / 24.7, 512 30.2 / 27.6;
+//     384 blocks: 448 36.2 / 39.4, 768 50.8 / 51.6, 1024 62.2 / 55.1; 512 blocks: 768 51.5 / 60.3, 1024 61.8 / 61.1.  T x 128: 64 15.4 / 17.9, 128
+//     blocks: 128 23.4 / 21.1, 1024 69 / 48.
+//   dQ alone: causal 2 x 1024, 16 x 128 (256) 70.6 / 66.0; unmasked 1 x 1000 over 2000, 16 x 128 (128) 93 / 81, 4 x 700 over 500, 8 x 128 (192) 50.0 / 51.9.
+//   dK/dV alone: causal 3 x 700, 12 x 128 (216) 53.8 / 59.6; unmasked 1 x 2048 over 256, 16 x 128 (32) 83 / 60.6, 4 x 333 over 520, 8 x 64 (160) 37.9 / 39.8.
+// most: the largest number of blocks, for rows whose other side is at least `from` long (where it is shorter, 128; under the
+// causal mask 256 between 384 and `from`, none up to 64: one tile has no halves worth sharing).
+static bool two_parts(const MhaArgs& a, int rows, int other, int from, int most) {
   const int blocks = blocks_of<1>(rows, a);
-  return blocks <= (a.causal ? (other >= 384 ? causal_limit : 128) : unmasked_limit);
+  if (a.causal && other <= 64) return false;
+  if (other >= from) return blocks <= most;
+  return blocks <= (a.causal && other >= 384 ? std::min(most, 256) : 128);
 }
 
 template <int HD, bool CAUSAL, bool SPLIT>
 static hipError_t fwd_dma(hipStream_t s, const MhaArgs& a, void* o, void* o_lo, float* lse) {
   auto run = [&](auto kernel, int grid, int lds) { kernel<<<grid, kNT, lds, s>>>(dev_of(a), (bf16*)o, (bf16*)o_lo, lse); };
-  if (two_parts(a, a.Tq, a.Tk, 256, HD == 64 ? 512 : 256)) run(attn_fwd_dma_kernel<HD, CAUSAL, SPLIT, 2>, blocks_of<2>(a.Tq, a), kSmemTiles<HD, 2>);
+  if (CAUSAL ? two_parts(a, a.Tq, a.Tk, 512, HD == 64 ? 384 : 256) : two_parts(a, a.Tq, a.Tk, HD == 64 ? 65 : 256, 256)) run(attn_fwd_dma_kernel<HD, CAUSAL, SPLIT, 2>, blocks_of<2>(a.Tq, a), kSmemTiles<HD, 2>);
   else run(attn_fwd_dma_kernel<HD, CAUSAL, SPLIT, 1>, blocks_of<1>(a.Tq, a), kSmemTiles<HD, 1>);
   return hipGetLastError();
 }
@@ -997,12 +1006,12 @@ static hipError_t bwd_dma(hipStream_t s, const MhaArgs& a, const MhaGrads& g) {
   auto run_q = [&](auto kernel, int grid, int lds) {
     kernel<<<grid, kNT, lds, s>>>(dev_of(a), (const bf16*)g.o, (const bf16*)g.o_lo, (const bf16*)g.dout, g.lse, g.delta, (bf16*)g.dq, g.lddq);
   };
-  if (two_parts(a, a.Tq, a.Tk, 128, HD == 64 ? 512 : 256)) run_q(attn_dq_dma_kernel<HD, CAUSAL, SPLIT, 2>, blocks_of<2>(a.Tq, a), kSmemTiles<HD, 2>);
+  if (CAUSAL ? two_parts(a, a.Tq, a.Tk, 768, HD == 64 ? 384 : 256) : two_parts(a, a.Tq, a.Tk, 0, 128)) run_q(attn_dq_dma_kernel<HD, CAUSAL, SPLIT, 2>, blocks_of<2>(a.Tq, a), kSmemTiles<HD, 2>);
   else run_q(attn_dq_dma_kernel<HD, CAUSAL, SPLIT, 1>, blocks_of<1>(a.Tq, a), kSmemTiles<HD, 1>);
   auto run_kv = [&](auto kernel, int grid) {
     kernel<<<grid, kNT, kSmemDkv<HD, HD == 64 && CAUSAL && !SPLIT>, s>>>(dev_of(a), (const bf16*)g.dout, g.lse, g.delta, (bf16*)g.dk, (bf16*)g.dv, g.lddkv);
   };
-  if (two_parts(a, a.Tk, a.Tq, 128, HD == 64 ? 512 : 128)) run_kv(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, 2>, blocks_of<2>(a.Tk, a));
+  if (CAUSAL ? two_parts(a, a.Tk, a.Tq, 768, HD == 64 ? 384 : 128) : two_parts(a, a.Tk, a.Tq, 0, 128)) run_kv(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, 2>, blocks_of<2>(a.Tk, a));
   else run_kv(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, 1>, blocks_of<1>(a.Tk, a));
   return hipGetLastError();
 }
