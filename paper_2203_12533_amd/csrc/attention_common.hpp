@@ -67,14 +67,6 @@ __device__ __forceinline__ void load_row_frags(const bf16* __restrict__ src, int
 }
 
 
-__device__ __forceinline__ bf16x8 pack8(const f32x16& v, int first) {
-  bf16x8 o;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) o[e] = (bf16)v[first + e];
-  return o;
-}
-
-
 // Tile-local row index that register r of this lane's D column stands for (see file header).
 __device__ __forceinline__ int reg_row(int r, int half) { return 16 * (r >> 3) + 8 * half + (r & 7); }
 

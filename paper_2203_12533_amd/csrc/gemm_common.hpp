@@ -277,28 +277,16 @@ struct GemmBf16Params {
   EpiParams epi;
 };
 
-// Epilogue of the MFMA kernels.  acc[i][j][r] is element m = 32 i + lane%32, n = 32 j + 8 (r/4) + 4 (lane/32) + r%4
-// of the wave tile (rows mw0.., columns nw0..): a lane owns one row fragment of 4 columns, so storing straight
-// from the accumulators would scatter 8-byte pieces over 32 rows per instruction.  Instead each wave parks one
+// Epilogue of the ring kernel.  acc[a][b][r] is element m = 16 a + lane%16, n = 16 b + 4 (lane/16) + r of the wave tile
+// (rows mw0.., columns nw0..): a lane owns one row fragment of 4 columns, so storing straight
+// from the accumulators would scatter 8-byte pieces over 16 rows per instruction.  Instead each wave parks one
 // 32 x 64 block at a time in its own slice of LDS (the operand tiles are dead by now) and reads it back
 // row-wise: 8 lanes cover the 64 columns of a row with 8 consecutive values each, so every global access of
 // the epilogue (output, residual, saved pre-activation) is a 16-byte vector and every row segment a full
 // 128-byte line or more.  What a segment needs from memory besides the accumulators is fetched one 32-row block
-// ahead.  All waves of the block must call (it synchronises the block).
-// Parks 32-row block i, 64-column half h of a wave tile in `stage` (rows of ld floats), from either accumulator
-// layout: 32 x 32 MFMA blocks (layout above) or 16 x 16 blocks, where acc[a][b][r] is element m = 16 a + lane%16,
-// n = 16 b + 4 (lane/16) + r.  Both write 16-byte pieces that tile the banks without conflicts at ld = 68.
-template <int FM, int FN>
-__device__ __forceinline__ void stage_block(float* stage, int ld, const f32x16 (&acc)[FM][FN], int i, int h, int lane) {
-  const int lrow = lane & 31, lhalf = lane >> 5;
-#pragma unroll
-  for (int j = 0; j < 2; ++j)
-#pragma unroll
-    for (int qq = 0; qq < 4; ++qq)
-      *reinterpret_cast<float4*>(stage + lrow * ld + j * 32 + qq * 8 + lhalf * 4) =
-          make_float4(acc[i][2 * h + j][qq * 4], acc[i][2 * h + j][qq * 4 + 1], acc[i][2 * h + j][qq * 4 + 2],
-                      acc[i][2 * h + j][qq * 4 + 3]);
-}
+// ahead.  All waves of the block must call (it synchronises the block).  Full tiles only.
+// Parks 32-row block i, 64-column half h of a wave tile in `stage` (rows of ld floats): 16-byte pieces that tile the
+// banks without conflicts at ld = 68.
 template <int FM16, int FN16>
 __device__ __forceinline__ void stage_block(float* stage, int ld, const f32x4 (&acc)[FM16][FN16], int i, int h, int lane) {
   const int lrow = lane & 15, lq = lane >> 4;
@@ -311,17 +299,16 @@ __device__ __forceinline__ void stage_block(float* stage, int ld, const f32x4 (&
                       acc[2 * i + a][4 * h + b][3]);
 }
 
-// FM, FN: the wave tile in units of 32 rows / 32 columns, whatever the accumulator layout.
-template <int FM, int FN, bool EDGE, int KIND, typename Acc>
-__device__ __forceinline__ void gemm_epilogue_staged_kind(bf16* smem, Acc& acc, const GemmBf16Params& p,
+// FM, FN: the wave tile in units of 32 rows / 32 columns.
+template <int FM, int FN, int KIND>
+__device__ __forceinline__ void gemm_epilogue_staged_kind(bf16* smem, const f32x4 (&acc)[2 * FM][2 * FN], const GemmBf16Params& p,
                                                           int64_t mw0, int64_t nw0, int wave, int lane) {
   static_assert(FN % 2 == 0, "epilogue staging works on 64-column halves of the wave tile");
   constexpr int kLdS = 64 + 4;   // floats; 272-byte rows keep the 16-byte LDS accesses conflict-free
-  static_assert(!EDGE || KIND <= kExtraOldC, "the dedicated epilogues exist for full tiles only");
   constexpr bool kAhead = KIND != kExtraNone && KIND != kExtraXentStats;
   const int r8 = lane >> 3, c8 = lane & 7;
   const void* const extra_src = epi_extra_src(p.epi, KIND);
-  const int64_t M = p.M, N = p.N, ldc = p.epi.ldc;
+  const int64_t ldc = p.epi.ldc;
   float ic1 = 0.f, ic2 = 0.f;   // Adam's bias corrections
   if (KIND == kExtraAdam) {
     ic1 = p.epi.ad_c ? p.epi.ad_c[0] : p.epi.ad_ic1;
@@ -338,7 +325,7 @@ __device__ __forceinline__ void gemm_epilogue_staged_kind(bf16* smem, Acc& acc, 
     } else if (KIND == kExtraXentGrad) {
       x.lo.x = __float_as_uint(p.epi.xe_lse[m]);
       x.lo.y = (uint32_t)xent_target(p.epi, m);
-    } else if (!EDGE || (m < M && n + 7 < N)) {
+    } else {
       epi_extra_load(KIND, extra_src, m * ldc + n, x);
     }
   };
@@ -392,11 +379,8 @@ __device__ __forceinline__ void gemm_epilogue_staged_kind(bf16* smem, Acc& acc, 
           epilogue8_xent_stats(p.epi, m, n, v, c8);
         } else if (KIND == kExtraXentGrad) {
           epilogue8_xent_grad(p.epi, m, n, v, x);
-        } else if (!EDGE || (m < M && n + 7 < N)) {
+        } else {
           epilogue8(p.epi, m, n, v, KIND, x);
-        } else if (m < M) {
-          for (int e = 0; e < 8; ++e)
-            if (n + e < N) epilogue1<true>(p.epi, m, n + e, v[e]);
         }
       };
       if (kAhead) {   // unrolled: each segment has its own registers for what was fetched ahead
@@ -415,22 +399,22 @@ __device__ __forceinline__ void gemm_epilogue_staged_kind(bf16* smem, Acc& acc, 
 // 1 the two of the LM head fused with the loss (statistics; gradient of the logits); 2 Adam on the product.  The
 // dedicated sets have kernel instantiations of their own so that the general kernels do not grow.
 constexpr int kEpiSetGeneral = 0, kEpiSetXent = 1, kEpiSetAdam = 2;
-template <int FM, int FN, bool EDGE, int EPISET = kEpiSetGeneral, typename Acc>
-__device__ __forceinline__ void gemm_epilogue_staged(bf16* smem, Acc& acc, const GemmBf16Params& p,
+template <int FM, int FN, int EPISET = kEpiSetGeneral>
+__device__ __forceinline__ void gemm_epilogue_staged(bf16* smem, const f32x4 (&acc)[2 * FM][2 * FN], const GemmBf16Params& p,
                                                      int64_t mw0, int64_t nw0, int wave, int lane) {
   if constexpr (EPISET == kEpiSetAdam) {
-    gemm_epilogue_staged_kind<FM, FN, EDGE, kExtraAdam>(smem, acc, p, mw0, nw0, wave, lane);
+    gemm_epilogue_staged_kind<FM, FN, kExtraAdam>(smem, acc, p, mw0, nw0, wave, lane);
     return;
   } else if constexpr (EPISET == kEpiSetXent) {
-    if (p.epi.mode == kEpiXentStats) gemm_epilogue_staged_kind<FM, FN, EDGE, kExtraXentStats>(smem, acc, p, mw0, nw0, wave, lane);
-    else gemm_epilogue_staged_kind<FM, FN, EDGE, kExtraXentGrad>(smem, acc, p, mw0, nw0, wave, lane);
+    if (p.epi.mode == kEpiXentStats) gemm_epilogue_staged_kind<FM, FN, kExtraXentStats>(smem, acc, p, mw0, nw0, wave, lane);
+    else gemm_epilogue_staged_kind<FM, FN, kExtraXentGrad>(smem, acc, p, mw0, nw0, wave, lane);
     return;
   }
   switch (epi_extra_kind(p.epi)) {   // uniform over the launch
-    case kExtraAuxBf16: gemm_epilogue_staged_kind<FM, FN, EDGE, kExtraAuxBf16>(smem, acc, p, mw0, nw0, wave, lane); break;
-    case kExtraAuxF32: gemm_epilogue_staged_kind<FM, FN, EDGE, kExtraAuxF32>(smem, acc, p, mw0, nw0, wave, lane); break;
-    case kExtraOldC: gemm_epilogue_staged_kind<FM, FN, EDGE, kExtraOldC>(smem, acc, p, mw0, nw0, wave, lane); break;
-    default: gemm_epilogue_staged_kind<FM, FN, EDGE, kExtraNone>(smem, acc, p, mw0, nw0, wave, lane); break;
+    case kExtraAuxBf16: gemm_epilogue_staged_kind<FM, FN, kExtraAuxBf16>(smem, acc, p, mw0, nw0, wave, lane); break;
+    case kExtraAuxF32: gemm_epilogue_staged_kind<FM, FN, kExtraAuxF32>(smem, acc, p, mw0, nw0, wave, lane); break;
+    case kExtraOldC: gemm_epilogue_staged_kind<FM, FN, kExtraOldC>(smem, acc, p, mw0, nw0, wave, lane); break;
+    default: gemm_epilogue_staged_kind<FM, FN, kExtraNone>(smem, acc, p, mw0, nw0, wave, lane); break;
   }
 }
 

@@ -258,7 +258,7 @@ __device__ __forceinline__ void ring_tile(const GemmBf16Params& p, int pid, bf16
       }
     }
   }
-  gemm_epilogue_staged<kWaveM / 32, kWaveN / 32, false, EPISET>(smem, acc, p, m0 + wm * kWaveM, n0 + wn * kWaveN, wave, lane);
+  gemm_epilogue_staged<kWaveM / 32, kWaveN / 32, EPISET>(smem, acc, p, m0 + wm * kWaveM, n0 + wn * kWaveN, wave, lane);
 }
 
 template <bool A_KMAJOR, bool B_KMAJOR, int NW, int EPISET = kEpiSetGeneral>
