@@ -19,11 +19,14 @@ def ctx():
     c.close()
 
 
+# Plain additions of a chain share a launch, so that a chain of up to 128 of them is one stream launch in either mode; busy
+# functions of no duration add as well and keep a launch each: from eight on PW_GRAPH captures and replays a graph.
+@pytest.mark.parametrize("kind", [pwb.PW_FN_ADD_CONST, pwb.PW_FN_BUSY])
 @pytest.mark.parametrize("mode", [pwb.PW_STREAM, pwb.PW_GRAPH, pwb.PW_SEQUENTIAL])
 @pytest.mark.parametrize("L", [1, 8, 32, 128])
-def test_chain_on_pending_input_is_exact(ctx, orc, L, mode):
+def test_chain_on_pending_input_is_exact(ctx, orc, L, mode, kind):
     x = I.dispatch_input()
-    add1 = ctx.compile_scalar_fn(pwb.PW_FN_ADD_CONST, 128, 1.0)
+    add1 = ctx.compile_scalar_fn(kind, 128, 1.0, busy_us=0.0 if kind == pwb.PW_FN_BUSY else None)
     want = orc.chain_add(x, L)
     for rep in range(3):                       # replays of a cached graph must stay right
         xin = x + np.float32(rep)
@@ -92,10 +95,11 @@ def test_readiness_through_the_completion_word_is_not_early_and_not_lost(ctx, or
     ctx.fn_release(big)
 
 
-def test_sequential_mode_is_not_given_a_pending_input(ctx):
+@pytest.mark.parametrize("kind", [pwb.PW_FN_ADD_CONST, pwb.PW_FN_BUSY])   # (additions share launches, see above)
+def test_sequential_mode_is_not_given_a_pending_input(ctx, kind):
     """PW_SEQUENTIAL synchronises after every link; with a ready input it must give the same bits."""
     x = I.dispatch_input()
-    add1 = ctx.compile_scalar_fn(pwb.PW_FN_ADD_CONST, 128, 1.0)
+    add1 = ctx.compile_scalar_fn(kind, 128, 1.0, busy_us=0.0 if kind == pwb.PW_FN_BUSY else None)
     f_in = ctx.future_from_host(x)
     outs = []
     for mode in (pwb.PW_STREAM, pwb.PW_GRAPH, pwb.PW_SEQUENTIAL):
