@@ -63,35 +63,42 @@ def recorded_gemm_traffic(workload: str):
 
 def dispatch_bench(ctx, pwb, I, reps: int = 200):
     """Chained dispatch cost (Section 5.1 analogue on one GPU): chains of L trivial functions on a
-    128-float buffer (additions: those of a chain share launches, op by op has one each).  host = time for the
-    enqueue call to return; wall = until the result is ready."""
+    128-float buffer.  host = time for the enqueue call to return; wall = until the result is ready.  Busy functions of no
+    duration keep a launch each in every mode, so these are costs per dispatched function; the additions of a chain share
+    launches, which "additions_stream" shows as a whole."""
+    busy = ctx.compile_scalar_fn(pwb.PW_FN_BUSY, 128, 1.0, busy_us=0.0)
     add1 = ctx.compile_scalar_fn(pwb.PW_FN_ADD_CONST, 128, 1.0)
     x = I.dispatch_input()
     out = {}
+
+    def chained(fn, L, mode):
+        f_in = ctx.future_from_host(x)
+        host_t, wall_t = [], []
+        for r in range(reps + 20):
+            ctx.synchronize()
+            t0 = time.perf_counter()
+            (f,) = ctx.chain([fn] * L, [f_in], 1, mode)
+            t1 = time.perf_counter()
+            ctx.await_(f, fetch=False)
+            t2 = time.perf_counter()
+            ctx.future_release(f)
+            if r >= 20:
+                host_t.append(t1 - t0)
+                wall_t.append(t2 - t0)
+        ctx.future_release(f_in)
+        return float(np.median(host_t)) * 1e6, float(np.median(wall_t)) * 1e6
+
     for L in (1, 8, 32, 128):
         for mode, mname in ((pwb.PW_STREAM, "stream"), (pwb.PW_GRAPH, "graph")):
-            f_in = ctx.future_from_host(x)
-            host_t, wall_t = [], []
-            for r in range(reps + 20):
-                ctx.synchronize()
-                t0 = time.perf_counter()
-                (f,) = ctx.chain([add1] * L, [f_in], 1, mode)
-                t1 = time.perf_counter()
-                ctx.await_(f, fetch=False)
-                t2 = time.perf_counter()
-                ctx.future_release(f)
-                if r >= 20:
-                    host_t.append(t1 - t0)
-                    wall_t.append(t2 - t0)
-            ctx.future_release(f_in)
-            out[f"L{L}_{mname}"] = {"host_us_per_fn": round(float(np.median(host_t)) * 1e6 / L, 3),
-                                    "wall_us_per_fn": round(float(np.median(wall_t)) * 1e6 / L, 3)}
+            host, wall = chained(busy, L, mode)
+            out[f"L{L}_{mname}"] = {"host_us_per_fn": round(host / L, 3), "wall_us_per_fn": round(wall / L, 3)}
+    out["additions_stream"] = {f"L{L}_wall_us_per_chain": round(chained(add1, L, pwb.PW_STREAM)[1], 2) for L in (1, 8, 32, 128)}
     # op-by-op: one client call per function, each awaited (the stress case of Section 5.1)
     f = ctx.future_from_host(x)
     ctx.synchronize()
     t0 = time.perf_counter()
     for _ in range(128):
-        (g,) = ctx.run_fn(add1, [f])
+        (g,) = ctx.run_fn(busy, [f])
         ctx.await_(g, fetch=False)
         ctx.future_release(f)
         f = g
