@@ -816,7 +816,7 @@ __global__ __launch_bounds__(kNT, HD == 64 ? 2 : 1) void attn_dkv_dma_kernel(Mha
     constexpr bool NEXT = decltype(next)::value;
     const int hb = n & 1, nn = n + PARTS;
     const bf16* Qs = tile_q(n);
-    const bf16* Qn = tile_q(nn);
+    const bf16* Qn = smem + ((nn >> 1) % kStages) * (2 * kTile);      // (a hidden block is a wave's first)
     // st holds the block's raw statistics, read from LDS during the previous step
 #pragma unroll
     for (int r = 0; r < 16; ++r) st.lq[r] *= kLog2e;
