@@ -263,13 +263,34 @@ static hipError_t launch_gemm_impl(hipStream_t s, const GemmArgs& a) {
     if ((a.M + 63) / 64 > 65535) return hipErrorInvalidValue;
     return launch_gemm_f32(s, a, epi_of(a));
   }
-  // Full 256 x 256 tiles in rounds of one per compute unit that are nearly full: the ring-buffered kernel.  (It needs 1.4
-  // times less of the chip per FLOP than 128 x 128 tiles, so it loses where more than a quarter of its rounds is idle:
-  // 4096 x 4352 x 2048, 272 tiles, 94 us against 75; 2048 x 6144 x 2048, 192 tiles, 51 against 50; 2048 x 8192 x 2048, 256
-  // tiles, 57 against 64.)
-  const int64_t tiles = (a.M / 256) * (a.N / 256), slots = (tiles + 255) / 256 * 256;
-  if (ring_eligible(a) && (a.b_colsum || (tiles >= 150 && 100 * tiles > 76 * slots)))
-    return launch_gemm_ring(s, bf16_params_of(a, 256), a.a_kmajor, a.b_kmajor);
+  // Full 256 x 256 tiles in rounds of one per compute unit: the ring-buffered kernel, which needs 1.4 times less of the chip
+  // per FLOP than 128 x 128 tiles, and so
+  //  * a single round from 150 tiles on if k is long (us, ring / tiles of 128: 2048 x 5120, 160 tiles, K 4096 79 / 92, K 2048 44 / 44,
+  //    k-major 55 / 49; 2048 x 6144, 192 tiles, K 8192 159 / 178, K 4096 84 / 95, K 2048 46 / 48, k-major 56 / 54);
+  //  * otherwise where at most a quarter of the rounds is idle (2048 x 8192 x 2048, 256 tiles, 57 / 64; 3072 x 6144 x 2048, 288 tiles,
+  //    91 / 73);
+  //  * and where the last round would be half full at most, the rounds before it, with that round's columns a problem of their
+  //    own (2048 x 12288, 384 tiles, ring / 128 / both: K 8192 393 / 410 / 327, row-major A 314 / 342 / 296, K 4096 162 / 162 / 153,
+  //    K 2048 87 / 92 / 86; K 1024 52 / 52 / 55; 8192 x 5120 x 2048, 640 tiles, 149 / - / 140).
+  if (ring_eligible(a)) {
+    const int64_t tm = a.M / 256, tiles = tm * (a.N / 256), slots = (tiles + 255) / 256 * 256, rest = tiles % 256;
+    if (!a.b_colsum && a.K >= 2048 && tiles > 256 && rest > 0 && rest <= 128 && rest % tm == 0) {
+      const int64_t n2 = rest / tm * 256, n1 = a.N - n2;
+      const int64_t out_size = a.out_dtype == kBF16 ? 2 : 4, aux_size = a.epilogue == kEpiBiasResidual ? 4 : 2;
+      GemmArgs head = a, tail = a;
+      head.N = n1;
+      tail.N = n2;
+      tail.B = (const char*)a.B + (a.b_kmajor ? n1 : n1 * a.ldb) * 2;
+      tail.C = (char*)a.C + n1 * out_size;
+      if (a.bias) tail.bias = a.bias + n1;
+      if (a.aux) tail.aux = (const char*)a.aux + n1 * aux_size;
+      if (a.C2) tail.C2 = (char*)a.C2 + n1 * out_size;
+      err = launch_gemm_impl(s, head);
+      return err != hipSuccess ? err : launch_gemm_impl(s, tail);
+    }
+    if (a.b_colsum || (tiles >= 150 && (100 * tiles > 76 * slots || (tiles < 256 && a.K > 2048))))
+      return launch_gemm_ring(s, bf16_params_of(a, 256), a.a_kmajor, a.b_kmajor);
+  }
   return launch_gemm_tile(s, bf16_params_of(a, 256), a.a_kmajor, a.b_kmajor);
 }
 

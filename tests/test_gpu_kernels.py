@@ -161,6 +161,39 @@ def test_gemm_bf16_any_shape_in_every_layout(ctx, M, N, K, pad, a_k, b_k):
     assert (got[:, N:] == 7.0).all()
 
 
+# 264 full tiles of 256 x 256, 2048 deep: a round of 256 on the ring kernel, the last columns (two tiles wide) on their own; and
+# 160 of them 2056 deep and more (any-shape kernel) or 2112 (ring).  Every operand and output that goes by columns takes part.
+@pytest.mark.parametrize("N,K", [(16896, 2048), (10240, 2056), (10240, 2112)])
+@pytest.mark.parametrize("b_k", [0, 1])
+def test_gemm_whose_last_columns_are_a_problem_of_their_own(ctx, N, K, b_k):
+    M = 1024
+    g = torch.Generator(device="cuda").manual_seed(N + K + b_k)
+    rn = lambda *s, std=1.0: torch.randn(*s, generator=g, device="cuda") * std  # noqa: E731
+    x, w = rn(M, K).bfloat16(), rn(*((K, N) if b_k else (N, K)), std=0.02).bfloat16()
+    bias, res, pre = rn(N), rn(M, N), rn(M, N).bfloat16()
+    lin = x.float() @ (w.float() if b_k else w.float().T.contiguous())
+    kw = dict(dtype=pwb.PW_BF16, a_kmajor=0, b_kmajor=b_k, M=M, N=N, K=K, lda=K, ldb=N if b_k else K, ldc=N, A=ptr(x), B=ptr(w))
+    u, h, du = (torch.empty((M, N), dtype=torch.bfloat16, device="cuda") for _ in range(3))
+    y, acc = torch.empty((M, N), device="cuda"), res.clone()
+    torch.cuda.synchronize()
+    ctx.gemm(epilogue=pwb.PW_EPI_BIAS_GELU, out_dtype=pwb.PW_BF16, accumulate=0, bias=ptr(bias), C=ptr(u), C2=ptr(h), **kw)
+    ctx.gemm(epilogue=pwb.PW_EPI_BIAS_RESIDUAL, out_dtype=pwb.PW_F32, accumulate=0, bias=ptr(bias), aux=ptr(res), C=ptr(y), **kw)
+    ctx.gemm(epilogue=pwb.PW_EPI_GELU_BWD, out_dtype=pwb.PW_BF16, accumulate=0, aux=ptr(pre), C=ptr(du), **kw)
+    ctx.gemm(epilogue=pwb.PW_EPI_STORE, out_dtype=pwb.PW_F32, accumulate=1, C=ptr(acc), **kw)
+    dw = torch.empty((K, N), device="cuda")          # both operands k-major: 1024 rows of k, K x N outputs
+    ctx.gemm(dtype=pwb.PW_BF16, a_kmajor=1, b_kmajor=1, M=K, N=N, K=M, lda=K, ldb=N, ldc=N, epilogue=pwb.PW_EPI_STORE, out_dtype=pwb.PW_F32,
+             accumulate=0, A=ptr(x), B=ptr(pre), C=ptr(dw))
+    ctx.synchronize()
+    leaf = pre.float().requires_grad_(True)
+    (slope,) = torch.autograd.grad(torch.nn.functional.gelu(leaf, approximate="tanh").sum(), leaf)
+    z = lin + bias
+    # column by column, so that no part of the product can hide behind the rest: bf16 storage 2^-9, fp32 sums of K products
+    for got, ref, tol in ((u, z, 4e-3), (h, torch.nn.functional.gelu(z, approximate="tanh"), 6e-3), (y, z + res, 1e-5), (du, lin * slope, 4e-3),
+                          (acc, lin + res, 1e-5), (dw, x.float().T.contiguous() @ pre.float(), 1e-5)):
+        err = (got.float() - ref).norm(dim=0) / ref.norm(dim=0)
+        assert err.max().item() < tol
+
+
 @pytest.mark.parametrize("bf16", [False, True])
 def test_gemm_pair_small_problems_and_rejection(ctx, orc, bf16):
     """Two problems that do not qualify for a shared launch still give both results; one bad argument set
