@@ -148,8 +148,8 @@ def test_fused_update_switch_where_it_cannot_apply(ctx):
 
 @pytest.mark.parametrize("bf16", [False, True])
 def test_head_dim_64_and_single_position_sequences(ctx, orc, bf16):
-    """head_dim 64 (in bf16: the causal self-attention runs on the head_dim-64 MFMA kernels, the other two
-    attention roles on the row kernels) and the degenerate lengths: one source position, then one target position."""
+    """head_dim 64 (in bf16: the decoder's packed self-attention and the two roles whose probabilities are kept in several
+    terms, on the kernels of that width) and the degenerate lengths: one source position, then one target position."""
     for src_len, tgt_len in ((1, 9), (70, 1)):
         # (bf16 operands need token counts that are multiples of 8: batch 8 there, 3 in fp32)
         cfg = I.EncDecConfig(1, 2, 128, 2, 256, 64, src_len, tgt_len, 8 if bf16 else 3, bf16=bf16, optimizer="sgd", lr=1e-2)

@@ -410,8 +410,6 @@ def test_layernorm_forward_backward(ctx, orc, N, d, bf16):
         assert_close(host(dxlp), rdx + dres, 4e-3)
 
 
-# ---- attention ----------------------------------------------------------------------------------------
-
 # the block kernel's widths (256, 512 and 1024 threads, one and two pieces each), one column group past each, and row counts
 # that make a block go round twice and end inside its last group of rows; every optional argument left out as well
 @pytest.mark.parametrize("bf16", [False, True])
@@ -441,6 +439,8 @@ def test_layernorm_backward_in_blocks_of_rows(ctx, bf16, N, d):
             assert_close(host(lp), want, 4e-3 if bf16 else 1e-5)
             assert_close(host(ds), want.sum(0) + 2.0, 1e-5)
 
+
+# ---- attention ----------------------------------------------------------------------------------------
 
 @pytest.mark.parametrize("bf16", [False, True])
 @pytest.mark.parametrize("B,T,H,hd", [(2, 200, 2, 64), (1, 130, 3, 128), (2, 1, 1, 64), (1, 384, 2, 128)])
@@ -606,8 +606,6 @@ def test_packed_causal_bf16_attention_rejects_misaligned_arrays(ctx, hd):
     bwd()
     ctx.synchronize()
 
-
-# ---- softmax cross-entropy ----------------------------------------------------------------------------
 
 # query blocks of 128, key tiles of 64, 32-row MFMA blocks and one to either side of each; what the split of the
 # probabilities leaves out at this head width (nothing forward, 2^-17 backward) is far below the rounding of the stored results
@@ -903,6 +901,8 @@ def test_bf16_attention_with_rows_far_apart(ctx, orc, hd):
     torch.cuda.empty_cache()                  # 13 GB
 
 
+# ---- softmax cross-entropy ----------------------------------------------------------------------------
+
 @pytest.mark.parametrize("bf16", [False, True])
 @pytest.mark.parametrize("B,T,V", [(3, 5, 1024), (2, 7, 4096), (1, 3, 32768), (2, 2, 8)])
 def test_softmax_xent(ctx, orc, B, T, V, bf16):
@@ -918,6 +918,27 @@ def test_softmax_xent(ctx, orc, B, T, V, bf16):
     assert_close(host(z), rdz, 6e-3 if bf16 else 1e-5)
     if not bf16:
         assert np.abs(host(z).sum(axis=1)).max() < 1e-6     # rows of dlogits sum to 0
+
+
+# rows held in registers in 1, 2, 4 and 8 pieces per thread, one column past each, and rows read twice
+@pytest.mark.parametrize("bf16,V", [(True, 4096), (True, 4104), (True, 8200), (True, 16392), (True, 32776), (False, 2052),
+                                    (False, 4100), (False, 8196), (False, 16388)])
+def test_softmax_xent_at_every_row_length(ctx, orc, bf16, V):
+    B, T = 2, 3
+    z, zv = dev_act(_rand(61, (B * T, V), 2.0), bf16)
+    tok = I.tokens(8, 6, (B, T + 1), V)
+    tok[0, 1], tok[1, 3] = V - 1, 0
+    td, loss, rows = dev_i32(tok), torch.empty(1, device="cuda"), torch.empty(B * T, device="cuda")
+    ctx.op("softmax_xent", DT[bf16], ptr(z), ptr(td), ptr(loss), ptr(rows), B, T, V)
+    ctx.synchronize()
+    tgt = tok[:, 1:].reshape(-1)
+    lse = np.log(np.exp(zv - zv.max(1, keepdims=True)).sum(1)) + zv.max(1)
+    want = lse - zv[np.arange(B * T), tgt]
+    dz = np.exp(zv - lse[:, None])
+    dz[np.arange(B * T), tgt] -= 1.0
+    assert np.abs(host(rows) - want).max() < 1e-5 * np.abs(want).max()
+    assert abs(host(loss)[0] - want.mean()) < 1e-5 * want.mean()
+    assert_close(host(z), dz / (B * T), 4e-3 if bf16 else 1e-5)
 
 
 # ---- embedding ----------------------------------------------------------------------------------------
@@ -968,8 +989,6 @@ def test_embedding_backward_handles_one_id_everywhere(ctx, orc):
     assert_close(host(dwte), rwte, 1e-5)
 
 
-# ---- column sums and optimisers -----------------------------------------------------------------------
-
 # positions that fit an id's row of dwte and that do not (4 columns hold three), more of them than the list of one pass
 # (2048), rows of one to eight pieces per thread, the smallest and a large table
 @pytest.mark.parametrize("B,T,d,V", [(1, 1, 4, 1), (4, 1024, 4, 1), (2, 700, 8, 3), (3, 50, 1028, 40), (2, 300, 2048, 60),
@@ -1013,26 +1032,7 @@ def test_embedding_backward_of_few_ids_adds_rows_in_order_of_position(ctx, B, T,
     assert np.array_equal(dwpe.cpu().numpy(), wpe)
 
 
-# rows held in registers in 1, 2, 4 and 8 pieces per thread, one column past each, and rows read twice
-@pytest.mark.parametrize("bf16,V", [(True, 4096), (True, 4104), (True, 8200), (True, 16392), (True, 32776), (False, 2052),
-                                    (False, 4100), (False, 8196), (False, 16388)])
-def test_softmax_xent_at_every_row_length(ctx, orc, bf16, V):
-    B, T = 2, 3
-    z, zv = dev_act(_rand(61, (B * T, V), 2.0), bf16)
-    tok = I.tokens(8, 6, (B, T + 1), V)
-    tok[0, 1], tok[1, 3] = V - 1, 0
-    td, loss, rows = dev_i32(tok), torch.empty(1, device="cuda"), torch.empty(B * T, device="cuda")
-    ctx.op("softmax_xent", DT[bf16], ptr(z), ptr(td), ptr(loss), ptr(rows), B, T, V)
-    ctx.synchronize()
-    tgt = tok[:, 1:].reshape(-1)
-    lse = np.log(np.exp(zv - zv.max(1, keepdims=True)).sum(1)) + zv.max(1)
-    want = lse - zv[np.arange(B * T), tgt]
-    dz = np.exp(zv - lse[:, None])
-    dz[np.arange(B * T), tgt] -= 1.0
-    assert np.abs(host(rows) - want).max() < 1e-5 * np.abs(want).max()
-    assert abs(host(loss)[0] - want.mean()) < 1e-5 * want.mean()
-    assert_close(host(z), dz / (B * T), 4e-3 if bf16 else 1e-5)
-
+# ---- column sums and optimisers -----------------------------------------------------------------------
 
 @pytest.mark.parametrize("bf16", [False, True])
 @pytest.mark.parametrize("rows,cols", [(513, 768), (8, 64), (2048, 8192), (1, 12)])
