@@ -75,7 +75,7 @@ __global__ __launch_bounds__(256) void embedding_ids_gather_kernel(const int32_t
 // block at once; more of them the same way row by row (n^2 / 256 steps of a thread) as long as that takes less than a look
 // through all N tokens in order (a step for every 256).
 // Measured (us; before: d / 4 threads for four neighbouring rows; before that: fill and search): 2048 positions over 32768 ids of
-// 64 columns 7.7 (31.1; 12.6), of 2048 columns 43 (42; 54); 8192 over 32768 x 2048 64 (65; 123); drawn log-uniformly 156 (241; 430),
+// 64 columns 7.3 (31.1; 12.6), of 2048 columns 43 (42; 54); 8192 over 32768 x 2048 64 (65; 123); drawn log-uniformly 156 (241; 430),
 // over 1024 x 256 90 (338; 219).
 template <int TPR> constexpr int kEbGroups = 256 / TPR;
 template <int TPR> constexpr int kEbRows = TPR >= 256 ? 4 : TPR >= 64 ? 8 : 16;
@@ -179,18 +179,28 @@ __global__ __launch_bounds__(256) void embedding_bwd_kernel(const int32_t* __res
     const int rows_on = 256 / T, on = 256 - rows_on * T;  // positions 256 apart, as (row, column) of the token array
     int t = threadIdx.x % T;
     const int32_t* tok = tokens + (size_t)(threadIdx.x / T) * stride;
-    for (int p = threadIdx.x; p < N; p += 256) {
-      const int id = min(max(tok[t], 0), V - 1);
-      tok += (size_t)rows_on * stride;
-      t += on;
-      if (t >= T) t -= T, tok += stride;
-      int r = (int)__umulhi((uint32_t)id, id_magic), rest = id - r * id_blocks;   // id / id_blocks, one off at most
-      if (rest < 0) rest += id_blocks, --r;
-      if (rest >= id_blocks) rest -= id_blocks, ++r;
-      if (rest == (int)blockIdx.x) {
-        atomicAdd(&count[r], 1);
-        const int slot = atomicAdd(&count[R], 1);
-        if (slot < kList) list[slot] = r * kEbScan + p;
+    constexpr int kLook = 4;                              // tokens in flight (one: 2046 positions x 5000 ids x 512 6.4 us, four: 6.1)
+    for (int p = threadIdx.x; p < N; p += kLook * 256) {
+      int ids[kLook];
+#pragma unroll
+      for (int j = 0; j < kLook; ++j) {
+        if (p + j * 256 < N) ids[j] = tok[t];
+        tok += (size_t)rows_on * stride;
+        t += on;
+        if (t >= T) t -= T, tok += stride;
+      }
+#pragma unroll
+      for (int j = 0; j < kLook; ++j) {
+        if (p + j * 256 >= N) break;
+        const int id = min(max(ids[j], 0), V - 1);
+        int r = (int)__umulhi((uint32_t)id, id_magic), rest = id - r * id_blocks;   // id / id_blocks, one off at most
+        if (rest < 0) rest += id_blocks, --r;
+        if (rest >= id_blocks) rest -= id_blocks, ++r;
+        if (rest == (int)blockIdx.x) {
+          atomicAdd(&count[r], 1);
+          const int slot = atomicAdd(&count[R], 1);
+          if (slot < kList) list[slot] = r * kEbScan + p + j * 256;
+        }
       }
     }
     __syncthreads();
