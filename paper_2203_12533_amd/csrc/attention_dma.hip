@@ -82,14 +82,14 @@ __device__ __forceinline__ void dma16_s(const bf16* base, uint32_t voff, uint32_
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(voff), "s"(base), "s"(lds_off) : "memory", "m0");
 }
 
-// Direct loads of a ROWS x HD tile, instructions of 1 KiB (512 / HD rows), ROWS * HD / 2048 per wave (4 waves).  Lane l
+// Direct loads of a ROWS x HD tile, instructions of 1 KiB (512 / HD rows), dealt to WAVES waves.  Lane l
 // fetches chunk (l % (HD/8)) ^ swz<HD>(row) of row l / (HD/8) of an instruction's rows.
 // TileOffsets holds this lane's byte offsets inside a tile whose first row is row 0 (they do not depend on the
 // tile), so a tile that lies fully inside the sequence costs no vector arithmetic: base + rows*ld is scalar.
 template <int HD> constexpr int kRowsPerInstr = 512 / HD;
-template <int ROWS, int HD>
+template <int ROWS, int HD, int WAVES = 4>
 struct TileOffsets {
-  static constexpr int kPerWave = ROWS * HD / 2048;
+  static constexpr int kPerWave = ROWS * HD / (512 * WAVES);
   uint32_t off[kPerWave];
   __device__ __forceinline__ void init(int64_t ld, int wave, int lane) {
 #pragma unroll
@@ -101,10 +101,10 @@ struct TileOffsets {
 };
 // src: element (row 0 of the sequence, feature 0); tile rows row0 .. row0+ROWS-1; rows past `last` read as zero (the slow
 // path, only for the one tile that straddles the end of the sequence).
-template <int ROWS, int HD>
+template <int ROWS, int HD, int WAVES>
 __device__ __forceinline__ void issue_tile(const bf16* __restrict__ src, int64_t ld, int row0, int last,
-                                           const TileOffsets<ROWS, HD>& to, uint32_t lds_off, int wave, int lane) {
-  constexpr int kPerWave = TileOffsets<ROWS, HD>::kPerWave;
+                                           const TileOffsets<ROWS, HD, WAVES>& to, uint32_t lds_off, int wave, int lane) {
+  constexpr int kPerWave = TileOffsets<ROWS, HD, WAVES>::kPerWave;
   if (row0 + ROWS - 1 <= last) {
     const bf16* base = src + (int64_t)row0 * ld;
 #pragma unroll
@@ -332,8 +332,8 @@ __global__ __launch_bounds__(kNT, 2) void attn_fwd_dma_kernel(MhaDev a, bf16* __
   to.init(ld, wave, lane);
   auto issue = [&](int t) {
     const uint32_t st = smem_off + (uint32_t)(t & 1) * (2 * kTile * 2);
-    issue_tile<BKV, HD>(kbase, ld, t * BKV, Tk - 1, to, st, wave, lane);
-    issue_tile<BKV, HD>(vbase, ld, t * BKV, Tk - 1, to, st + kTile * 2, wave, lane);
+    issue_tile(kbase, ld, t * BKV, Tk - 1, to, st, wave, lane);
+    issue_tile(vbase, ld, t * BKV, Tk - 1, to, st + kTile * 2, wave, lane);
   };
   issue(0);
   for (int t = 0; t < n_tiles; ++t) {
@@ -507,8 +507,8 @@ __global__ __launch_bounds__(kNT, 2) void attn_dq_dma_kernel(MhaDev a, const bf1
   to.init(ld, wave, lane);
   auto issue = [&](int t) {
     const uint32_t st = smem_off + (uint32_t)(t & 1) * (2 * kTile * 2);
-    issue_tile<BKV, HD>(kbase, ld, t * BKV, Tk - 1, to, st, wave, lane);
-    issue_tile<BKV, HD>(vbase, ld, t * BKV, Tk - 1, to, st + kTile * 2, wave, lane);
+    issue_tile(kbase, ld, t * BKV, Tk - 1, to, st, wave, lane);
+    issue_tile(vbase, ld, t * BKV, Tk - 1, to, st + kTile * 2, wave, lane);
   };
   issue(0);
   for (int t = 0; t < n_tiles; ++t) {
@@ -755,8 +755,8 @@ __global__ __launch_bounds__(kNT, HD == 64 ? 2 : 1) void attn_dkv_dma_kernel(Mha
   const uint32_t stats_off = smem_off + kStages * 2 * kTile * 2;
   auto issue = [&](int t) {
     const uint32_t st = smem_off + (uint32_t)(t % kStages) * (2 * kTile * 2);
-    issue_tile<BQ, HD>(qbase, ld, t * BQ, T - 1, to_q, st, wave, lane);
-    issue_tile<BQ, HD>(gbase, d, t * BQ, T - 1, to_g, st + kTile * 2, wave, lane);
+    issue_tile(qbase, ld, t * BQ, T - 1, to_q, st, wave, lane);
+    issue_tile(gbase, d, t * BQ, T - 1, to_g, st + kTile * 2, wave, lane);
     if (wave == 0) {
       const int i = min(t * BQ + lane, T - 1);
       dma4(lse_bh + i, stats_off + (uint32_t)(t % kStages) * (BQ * 4));
@@ -907,6 +907,162 @@ __global__ __launch_bounds__(kNT, HD == 64 ? 2 : 1) void attn_dkv_dma_kernel(Mha
   }
 }
 
+// ===================================================================================================
+// dK, dV at head_dim 128 where blocks of 128 keys fill the chip and there is more than one tile of queries: 8 waves, two to a
+// SIMD, each pair with the same 32 keys; of every tile of 64 queries one wave takes the first 32, the other the rest, and their
+// sums meet in LDS at the end (in a fixed order).
+// What bounds the kernel above is that a SIMD has one wave: products, exponentials and LDS round trips of a block follow one
+// another (3200 clocks for 1024 of matrix work).  A second wave needs each of them within 256 registers: K and V stay in LDS
+// next to a ring of two tiles (129 KiB, one workgroup per compute unit) instead of in 64 registers, the addresses of LDS
+// reads are worked out from one register each, the statistics come in under the last first products.  Half as many
+// LDS bytes again per block is the price; two roles per pair (P and dV | dP, dS and dK over 64 keys each, P handed over through LDS:
+// half the reads), halves of a pair one phase apart, and V in registers were all slower or the same, wave priorities no different.
+// Measured (us, this kernel alone, before / now): causal 8 x 1024, 16 heads 126 / 109; unmasked 4 x 1000, 16 heads 95.7 / 80.3.  Forward
+// and backward: causal 4 x 1000, 8 heads 89.1 / 84.3; 8 x 300, 12 heads 59.8 / 58.1; 2048, 16 heads 150.7 / 137.7; 4 x 333 queries over 520
+// keys, 16 heads 80.7 / 76.9.  One tile has nothing to overlap: 8 x 60 queries over 1500 keys 122.4 / 125.4, left to the kernel above.
+// ===================================================================================================
+constexpr int kPairWaves = 8, kPairBQ = 64, kPairTile = kPairBQ * 128;
+constexpr int kSmemPair = (2 * 128 * 128 + 2 * 2 * kPairTile) * 2 + 2 * 2 * kPairBQ * 4;
+template <bool CAUSAL>
+__global__ __launch_bounds__(64 * kPairWaves, 2) void attn_dkv_pair_kernel(MhaDev a, const bf16* __restrict__ dout,
+                                                                           const float* __restrict__ lse, const float* __restrict__ delta,
+                                                                           bf16* __restrict__ dk_out, bf16* __restrict__ dv_out, int64_t lddkv) {
+  constexpr int HD = 128, KK = HD / 16, kRows = 128, kDepth = 2;
+  extern __shared__ __attribute__((aligned(1024))) bf16 smem[];          // K | V | [stage][Q | dO] | statistics
+  bf16* const ring = smem + 2 * kRows * HD;
+  float (*Ls)[kPairBQ] = reinterpret_cast<float (*)[kPairBQ]>(ring + 2 * 2 * kPairTile);
+  float (*Ds)[kPairBQ] = Ls + 2;
+  const int T = a.Tq, Tk = a.Tk, H = a.H, d = H * HD;
+  const int64_t ld = a.ldq;
+  int bh, kblk;
+  const int nk = (Tk + kRows - 1) / kRows;
+  xcd_block_map(blockIdx.x, gridDim.x, nk, CAUSAL ? causal_group(nk, 32) : 1, bh, kblk);
+  const int b = bh / H, h = bh - b * H;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, half = lane >> 5;
+  const int part = wave >> 2, kw = (wave & 3) * 32;
+  const int k0 = kblk * kRows + kw, key = k0 + (lane & 31);
+  const bf16* qbase = a.q + (int64_t)b * T * ld + h * HD;
+  const bf16* gbase = dout + (int64_t)b * T * d + h * HD;
+  const float scale = 1.f / sqrtf((float)HD), c2 = kLog2e * scale;
+  const uint32_t smem_off = (uint32_t)(uintptr_t)(lds_ptr)smem;
+  const uint32_t ring_off = smem_off + 2 * kRows * HD * 2, stats_off = ring_off + 2 * 2 * kPairTile * 2;
+  const float* lse_bh = lse + (int64_t)bh * T;
+  const float* delta_bh = delta + (int64_t)bh * T;
+  {
+    TileOffsets<kRows, HD, kPairWaves> to;
+    to.init(a.ldkv, wave, lane);
+    issue_tile(a.k + (int64_t)b * Tk * a.ldkv + h * HD, a.ldkv, kblk * kRows, Tk - 1, to, smem_off, wave, lane);
+    issue_tile(a.v + (int64_t)b * Tk * a.ldkv + h * HD, a.ldkv, kblk * kRows, Tk - 1, to, smem_off + kRows * HD * 2, wave, lane);
+  }
+  TileOffsets<kPairBQ, HD, kPairWaves> to_q, to_g;
+  to_q.init(ld, wave, lane);
+  to_g.init(d, wave, lane);
+  auto issue = [&](int t) {
+    const uint32_t st = ring_off + (uint32_t)(t & 1) * (2 * kPairTile * 2);
+    issue_tile(qbase, ld, t * kPairBQ, T - 1, to_q, st, wave, lane);
+    issue_tile(gbase, d, t * kPairBQ, T - 1, to_g, st + kPairTile * 2, wave, lane);
+    if (wave < 2) {                            // statistics of rows past the end: the last row's, masked where they are used
+      const int i = min(t * kPairBQ + lane, T - 1);
+      dma4((wave ? delta_bh : lse_bh) + i, stats_off + (uint32_t)(2 * wave + (t & 1)) * (kPairBQ * 4));
+    }
+  };
+  f32x16 dk[HD / 32], dv[HD / 32];
+  clear<HD>(dk);
+  clear<HD>(dv);
+  const int first_tile = CAUSAL ? (kblk * kRows) / kPairBQ : 0, n_tiles = (T + kPairBQ - 1) / kPairBQ;
+  // Where this lane's row of a first operand starts in LDS: features 16 kk + 8 half .. are at that address ^ (kk << 5).
+  const int qrow = part * 32 + perm_row(lane & 31), krow = kw + (lane & 31);
+  const uint32_t q_at = ring_off + qrow * (HD * 2) + ((half ^ swz<HD>(qrow)) << 4);
+  uint32_t k_at = smem_off + krow * (HD * 2) + ((half ^ swz<HD>(krow)) << 4);
+  // ... and of the second ones, read transposed: features 32 cb .. of queries 16 b2 .. at that address ^ (cb << 6), + 4096 b2.
+  const int trow = part * 32 + 8 * (lane >> 5) + ((lane & 15) >> 2);
+  const uint32_t back_at = ring_off + trow * (HD * 2) + (((2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) ^ swz<HD>(trow)) << 4) + 8 * (lane & 1);
+  issue(first_tile);
+  for (int t = first_tile; t < n_tiles; ++t) {
+    wait_and_sync();
+    if (t + 1 < n_tiles) issue(t + 1);
+    const int ib = t * kPairBQ + part * 32;    // first query of this wave's block
+    if ((CAUSAL && ib + 31 < k0) || ib >= T) continue;
+    uint32_t qa = q_at + (uint32_t)(t & 1) * (2 * kPairTile * 2);
+    asm volatile("" : "+v"(qa), "+v"(k_at));   // (the addresses below are worked out anew: 16 registers kept for them spill)
+    f32x16 s, dp;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] = dp[r] = 0.f;
+    bf16x8 fq[kDepth], fk[kDepth], fg[kDepth], fv[kDepth];
+    auto fetch = [&](int kk) {
+      typedef __attribute__((address_space(3))) const bf16x8* chunk;
+      const uint32_t aq = qa ^ (kk << 5), ak = k_at ^ (kk << 5);
+      fq[kk % kDepth] = *(chunk)(uintptr_t)aq;
+      fk[kk % kDepth] = *(chunk)(uintptr_t)ak;
+      fg[kk % kDepth] = *(chunk)(uintptr_t)(aq + kPairTile * 2);
+      fv[kk % kDepth] = *(chunk)(uintptr_t)(ak + kRows * HD * 2);
+    };
+#pragma unroll
+    for (int kk = 0; kk < kDepth; ++kk) fetch(kk);
+    __builtin_amdgcn_sched_barrier(0);
+    DkvStats st;
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) {
+      if (kk == KK - 1) load_stats(Ls[t & 1], Ds[t & 1], part, half, st);
+      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fq[kk % kDepth], fk[kk % kDepth], s, 0, 0, 0);
+      dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fg[kk % kDepth], fv[kk % kDepth], dp, 0, 0, 0);
+      if (kk + kDepth < KK) fetch(kk + kDepth);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) st.lq[r] *= kLog2e;
+    if ((CAUSAL && ib < k0 + 31) || ib + 31 >= T) {   // the diagonal, or the end of the queries
+      const int from = CAUSAL ? key - ib : -1, to = T - ib;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        if (reg_row(r, half) < from || reg_row(r, half) >= to) st.lq[r] = INFINITY;   // no such pair: P = 0
+        asm volatile("" : "+v"(st.lq[r]));
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      s[r] = __builtin_amdgcn_exp2f(fmaf(s[r], c2, -st.lq[r]));
+      dp[r] = s[r] * (dp[r] - st.dq[r]);
+    }
+    uint32_t ba = back_at + (uint32_t)(t & 1) * (2 * kPairTile * 2);
+    asm volatile("" : "+v"(ba));
+    auto read = [&](int j) {                   // j: 8 b2 + 4 (0: dO -> dV, 1: Q -> dK) + cb
+      typedef __attribute__((address_space(3))) short4v* piece;
+      union { bf16x8 v; short4v h[2]; } u;
+#pragma unroll
+      for (int e = 0; e < 2; ++e)
+        u.h[e] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+            (piece)(uintptr_t)((ba ^ ((j & 3) << 6) ^ (e << 4)) + 1024 * e + 4096 * (j >> 3) + ((j & 4) ? 0 : kPairTile * 2)));
+      return u.v;
+    };
+    constexpr int kAhead = 2;
+    bf16x8 fr[kAhead + 1];
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j) fr[j] = read(j);
+    Frag<1> w[2][2];
+#pragma unroll
+    for (int b2 = 0; b2 < 2; ++b2) {
+      w[b2][0] = pack_frag<1>(s, b2 * 8);
+      w[b2][1] = pack_frag<1>(dp, b2 * 8);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      if (j + kAhead < 16) fr[(j + kAhead) % (kAhead + 1)] = read(j + kAhead);
+      mfma_frag<1>(fr[j % (kAhead + 1)], w[j >> 3][(j >> 2) & 1], (j & 4) ? dk[j & 3] : dv[j & 3]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  float* const box = reinterpret_cast<float*>(smem) + (wave & 3) * (HD / 2 * 64) + lane;
+  (void)sum_parts<HD>(box, part, dk);          // (its barriers: every wave is done with the tiles)
+  if (!sum_parts<HD>(box, part, dv)) return;
+  if (key < Tk) {
+    const int64_t row = ((int64_t)b * Tk + key) * lddkv + h * HD;
+    store_row<HD>(dk_out + row, dk, scale);
+    store_row<HD>(dv_out + row, dv, 1.f);
+  }
+}
+
 }  // namespace
 
 // Dynamic LDS: two stages of two 64-row tiles (64 KiB at head_dim 128); dK/dV three stages and their statistics (97.5 KiB).
@@ -940,6 +1096,8 @@ hipError_t attention_dma_init() {
   if (e == hipSuccess) e = prepare_parts<64, true, false>();
   if (e == hipSuccess) e = prepare_parts<64, true, true>();
   if (e == hipSuccess) e = prepare_parts<64, false, true>();
+  for (const void* fn : {reinterpret_cast<const void*>(attn_dkv_pair_kernel<true>), reinterpret_cast<const void*>(attn_dkv_pair_kernel<false>)})
+    if (e == hipSuccess) e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kSmemPair);
   if (e == hipSuccess) done = true;
   return e;
 }
@@ -1012,6 +1170,9 @@ static hipError_t bwd_dma(hipStream_t s, const MhaArgs& a, const MhaGrads& g) {
     kernel<<<grid, kNT, kSmemDkv<HD, HD == 64 && CAUSAL && !SPLIT>, s>>>(dev_of(a), (const bf16*)g.dout, g.lse, g.delta, (bf16*)g.dk, (bf16*)g.dv, g.lddkv);
   };
   if (CAUSAL ? two_parts(a, a.Tk, a.Tq, 768, HD == 64 ? 384 : 128) : two_parts(a, a.Tk, a.Tq, 0, 128)) run_kv(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, 2>, blocks_of<2>(a.Tk, a));
+  else if (HD == 128 && a.Tq > kPairBQ)
+    attn_dkv_pair_kernel<CAUSAL><<<blocks_of<1>(a.Tk, a), 64 * kPairWaves, kSmemPair, s>>>(
+        dev_of(a), (const bf16*)g.dout, g.lse, g.delta, (bf16*)g.dk, (bf16*)g.dv, g.lddkv);
   else run_kv(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, 1>, blocks_of<1>(a.Tk, a));
   return hipGetLastError();
 }

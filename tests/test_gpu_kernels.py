@@ -677,6 +677,14 @@ def test_bf16_attention_blocks_of_64_and_of_128_rows(ctx, orc, B, Tq, Tk, H, hd,
 
 
 # keys that no query attends to (scores of -inf) in every tile of one wave's part, and all but the first of the other's
+@pytest.mark.parametrize("B,Tq,Tk,H,causal", [(13, 65, 129, 5, 0), (13, 128, 130, 5, 0), (26, 97, 33, 5, 0), (13, 129, 129, 5, 1), (11, 300, 300, 4, 1),
+                                              (26, 66, 66, 5, 1), (13, 192, 192, 5, 1)])
+def test_bf16_attention_at_head_width_128_with_a_chip_full_of_key_blocks(ctx, orc, B, Tq, Tk, H, causal):
+    """More than 128 blocks of 128 keys and more than one tile of 64 queries: two waves share 32 keys in dK/dV, each with its own
+    half of every tile - whole and ragged tiles, a last tile with nothing in its second half, keys that fill no block."""
+    _mha_case(ctx, orc, True, B, Tq, Tk, H, 128, causal=bool(causal), packed_kv=True)
+
+
 @pytest.mark.parametrize("hd", [64, 128])
 def test_bf16_attention_with_scores_of_minus_infinity(ctx, orc, hd):
     B, Tq, Tk, H = 1, 50, 160, 1
