@@ -7,7 +7,7 @@
 // k-loop and how few compute units take part in it, so the k-range of an output tile is cut into slices, one wave
 // each, whose partial tiles meet in LDS and are added in slice order (the same bits on every run).  The shorter sums
 // also round less: against 64 bits 1.5e-7 ... 2.9e-7 where one long sum has 2.9e-7 ... 5.7e-7.
-// Measured (us per launch, MI355X; before: 64 x 64 tiles on the vector ALU, one k-loop): 512 x 256 x 1024 133 -> 10,
+// Measured (us per launch, MI355X; before: 64 x 64 tiles on the vector ALU, one k-loop): 512 x 256 x 1024 133 -> 6.9,
 // 512 x 1024 x 256 36 -> 7.6, 1024 x 256 x 512 (weight gradient) 72 -> 7.1, 1000 x 512 x 2048 360 -> 30,
 // 2048^3 451 -> 156 (110 TFLOP/s of the 157 the fp32 matrix pipe has at 2.4 GHz), 4096 x 4096 x 1024 646 -> 289.
 //
@@ -31,6 +31,7 @@ namespace {
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 typedef float f32x2u __attribute__((ext_vector_type(2), aligned(4)));
 template <int F> struct PieceOf;
+template <> struct PieceOf<1> { typedef float type __attribute__((ext_vector_type(1), aligned(4))); };
 template <> struct PieceOf<2> { typedef f32x2u type; };
 template <> struct PieceOf<4> { typedef f32x4u type; };
 
@@ -115,27 +116,27 @@ struct GemmF32Params {
   EpiParams epi;
 };
 
-// One 16 F x 16 F output tile per workgroup; its kWK waves take one slice of k each.
+// One 16 FM x 16 F output tile per workgroup; its kWK waves take one slice of k each.
 constexpr int kWK = 4;
-template <int F, bool AK, bool BK_>
+template <int FM, int F, bool AK, bool BK_>
 __global__ __launch_bounds__(64 * kWK) void gemm_f32_kernel(GemmF32Params p) {
-  constexpr int T = 16 * F;
-  constexpr int kDepth = F == 2 ? 3 : 2;      // steps in flight per wave
+  constexpr int TM = 16 * FM, T = 16 * F;
+  constexpr int kDepth = F == 2 ? 5 - FM : 2; // steps in flight per wave
   int tm, tn;
   tile_of_block(blockIdx.x, p.tiles_m * p.tiles_n, p.tiles_m, p.tiles_n, tm, tn);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t m0 = (int64_t)tm * T, n0 = (int64_t)tn * T;
+  const int64_t m0 = (int64_t)tm * TM, n0 = (int64_t)tn * T;
 
-  f32x4 acc[F][F];
+  f32x4 acc[FM][F];
 #pragma unroll
-  for (int i = 0; i < F; ++i)
+  for (int i = 0; i < FM; ++i)
 #pragma unroll
     for (int j = 0; j < F; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  auto multiply = [&](const float (&a)[4][F], const float (&b)[4][F]) {
+  auto multiply = [&](const float (&a)[4][FM], const float (&b)[4][F]) {
 #pragma unroll
     for (int k = 0; k < 4; ++k)
 #pragma unroll
-      for (int i = 0; i < F; ++i)
+      for (int i = 0; i < FM; ++i)
 #pragma unroll
         for (int j = 0; j < F; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[k][j], a[k][i], acc[i][j], 0, 0, 0);
   };
@@ -144,16 +145,16 @@ __global__ __launch_bounds__(64 * kWK) void gemm_f32_kernel(GemmF32Params p) {
   const int64_t per = (steps + kWK - 1) / kWK;
   const int64_t s0 = wave * per, s1 = (s0 + per < steps ? s0 + per : steps);
   if (s0 < s1) {
-    F32Operand<F, AK> oa;
+    F32Operand<FM, AK> oa;
     F32Operand<F, BK_> ob;
     oa.init(p.A, p.lda, m0, p.M, lane);
     ob.init(p.B, p.ldb, n0, p.N, lane);
-    const bool tiny = p.M < F || p.N < F;
-    const bool edge = m0 + T > p.M || n0 + T > p.N;
+    const bool tiny = p.M < FM || p.N < F;
+    const bool edge = m0 + TM > p.M || n0 + T > p.N;
     const int64_t sw = tiny ? s0 : (s1 < whole ? s1 : whole);   // steps s0 .. sw-1 load whole pieces
     auto stream = [&](auto e) {
       constexpr bool EDGE = decltype(e)::value;
-      float fa[kDepth][4][F], fb[kDepth][4][F];
+      float fa[kDepth][4][FM], fb[kDepth][4][F];
       int64_t s = s0;
 #pragma unroll
       for (int d = 0; d < kDepth; ++d)
@@ -184,7 +185,7 @@ __global__ __launch_bounds__(64 * kWK) void gemm_f32_kernel(GemmF32Params p) {
     if (edge) stream(std::integral_constant<bool, true>{});
     else stream(std::integral_constant<bool, false>{});
     for (int64_t s = sw; s < s1; ++s) {
-      float fa[4][F], fb[4][F];
+      float fa[4][FM], fb[4][F];
       oa.load_guarded(s * kStepK, p.K, lane, fa);
       ob.load_guarded(s * kStepK, p.K, lane, fb);
       multiply(fa, fb);
@@ -202,45 +203,45 @@ __global__ __launch_bounds__(64 * kWK) void gemm_f32_kernel(GemmF32Params p) {
         if (n + e < p.N) epilogue1<false>(p.epi, m, n + e, v[e]);
     }
   };
-  // acc[i][j][r]: row F (lane%16) + i, column 4 F (lane/16) + F r + j of the wave tile
+  // acc[i][j][r]: row FM (lane%16) + i, column 4 F (lane/16) + F r + j of the wave tile
   const int c = lane & 15, q = lane >> 4;
   auto value = [&](int i, int col) { return acc[i][col % F][col / F]; };   // col: 0 .. 4F-1 of this lane's columns
   // Partial tiles meet in LDS, [slice][row][column], rows padded by 4 floats: the 16 rows that the 16-byte
   // stores of one instruction touch then start in 8 different bank groups of 8 banks.
   constexpr int kLd = T + 4;
-  __shared__ __attribute__((aligned(16))) float part[kWK * T * kLd];
-  float* mine = part + wave * (T * kLd);
+  __shared__ __attribute__((aligned(16))) float part[kWK * TM * kLd];
+  float* mine = part + wave * (TM * kLd);
 #pragma unroll
-  for (int i = 0; i < F; ++i)
+  for (int i = 0; i < FM; ++i)
 #pragma unroll
     for (int g = 0; g < F; ++g)
-      *reinterpret_cast<float4*>(mine + (F * c + i) * kLd + 4 * F * q + 4 * g) =
+      *reinterpret_cast<float4*>(mine + (FM * c + i) * kLd + 4 * F * q + 4 * g) =
           make_float4(value(i, 4 * g), value(i, 4 * g + 1), value(i, 4 * g + 2), value(i, 4 * g + 3));
   __syncthreads();
-  for (int piece = threadIdx.x; piece < T * T / 4; piece += 64 * kWK) {
+  for (int piece = threadIdx.x; piece < TM * T / 4; piece += 64 * kWK) {
     const int row = piece / (T / 4), col = piece % (T / 4) * 4;
     const float* src = part + row * kLd + col;
     float4 t = *reinterpret_cast<const float4*>(src);
 #pragma unroll
     for (int k = 1; k < kWK; ++k) {
-      const float4 u = *reinterpret_cast<const float4*>(src + k * (T * kLd));
+      const float4 u = *reinterpret_cast<const float4*>(src + k * (TM * kLd));
       t.x += u.x; t.y += u.y; t.z += u.z; t.w += u.w;
     }
     put4(m0 + row, n0 + col, t.x, t.y, t.z, t.w);
   }
 }
 
-template <int F>
+template <int FM, int F>
 hipError_t launch_tile(hipStream_t s, GemmF32Params p, bool ak, bool bk) {
-  const int64_t tm = (p.M + 16 * F - 1) / (16 * F), tn = (p.N + 16 * F - 1) / (16 * F);
+  const int64_t tm = (p.M + 16 * FM - 1) / (16 * FM), tn = (p.N + 16 * F - 1) / (16 * F);
   if (tm * tn > (1LL << 30)) return hipErrorInvalidValue;
   p.tiles_m = (int)tm;
   p.tiles_n = (int)tn;
   const int grid = (int)(tm * tn), block = 64 * kWK;
-  if (!ak && !bk) gemm_f32_kernel<F, false, false><<<grid, block, 0, s>>>(p);
-  else if (!ak) gemm_f32_kernel<F, false, true><<<grid, block, 0, s>>>(p);
-  else if (!bk) gemm_f32_kernel<F, true, false><<<grid, block, 0, s>>>(p);
-  else gemm_f32_kernel<F, true, true><<<grid, block, 0, s>>>(p);
+  if (!ak && !bk) gemm_f32_kernel<FM, F, false, false><<<grid, block, 0, s>>>(p);
+  else if (!ak) gemm_f32_kernel<FM, F, false, true><<<grid, block, 0, s>>>(p);
+  else if (!bk) gemm_f32_kernel<FM, F, true, false><<<grid, block, 0, s>>>(p);
+  else gemm_f32_kernel<FM, F, true, true><<<grid, block, 0, s>>>(p);
   return hipGetLastError();
 }
 
@@ -250,10 +251,16 @@ hipError_t launch_tile(hipStream_t s, GemmF32Params p, bool ak, bool bk) {
 // 23 us against 34 with 32 x 32; 1000 x 2048 x 512: 33 against 36); below that the smaller tiles occupy more of the
 // chip (1000 x 512 x 2048, 128 tiles of 64 x 64: 30 us against 44; 512 x 256 x 1024: 10 against 22).  8 or 16 slices
 // of k instead of 4 measured the same or slower at every size.
+// 16 x 32 tiles where those of 32 x 32 leave half the compute units without one: the serial chain of a wave is half as long and
+// twice as many units take part (us, 32 x 32 / 16 x 32: 512 x 256 x 1024, 128 tiles of 32 x 32, 9.3 / 6.9; 64 x 256 x 1024, 16 tiles,
+// 9.2 / 6.6; 256 x 256 x 512 k-major, 64, 6.2 / 5.2; 512 x 256 x 256, 128, 4.9 / 5.0; beyond 128 tiles no gain: 300 x 448 x 704, 140,
+// 7.9 / 9.0; 512 x 512 x 512, 256, 6.9 / 8.3).
 hipError_t launch_gemm_f32(hipStream_t s, const GemmArgs& a, const EpiParams& epi) {
   const GemmF32Params p{(const float*)a.A, (const float*)a.B, a.M, a.N, a.K, a.lda, a.ldb, 0, 0, epi};
   const int64_t t64 = ((a.M + 63) / 64) * ((a.N + 63) / 64);
-  return t64 >= 256 ? launch_tile<4>(s, p, a.a_kmajor, a.b_kmajor) : launch_tile<2>(s, p, a.a_kmajor, a.b_kmajor);
+  const int64_t t32 = ((a.M + 31) / 32) * ((a.N + 31) / 32);
+  if (t64 >= 256) return launch_tile<4, 4>(s, p, a.a_kmajor, a.b_kmajor);
+  return t32 > 128 ? launch_tile<2, 2>(s, p, a.a_kmajor, a.b_kmajor) : launch_tile<1, 2>(s, p, a.a_kmajor, a.b_kmajor);
 }
 
 }  // namespace pw

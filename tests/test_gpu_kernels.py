@@ -131,6 +131,13 @@ def test_gemm_fp32_edges_in_every_layout(ctx, M, N, K, a_k, b_k):
     assert (got[:, N:] == 7.0).all()
 
 
+# tiles of 16 x 32 up to 128 tiles of 32 x 32 (the third shape: exactly; the fourth: a row of tiles more), edges of the lower tile
+@pytest.mark.parametrize("a_k,b_k", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("M,N,K", [(16, 32, 64), (17, 31, 129), (512, 256, 83), (513, 256, 83), (47, 33, 1000)])
+def test_gemm_fp32_low_tiles_in_every_layout(ctx, M, N, K, a_k, b_k):
+    test_gemm_fp32_edges_in_every_layout(ctx, M, N, K, a_k, b_k)
+
+
 # one size per tile shape of the any-shape kernel (64 x 64 and 128 x 64 tiles with k split over waves, 128 x 128 in both
 # loop forms), ragged in every dimension, k from one partial step on; what lies behind the last k of a row is no number, and
 # the last size has rows too far apart for 32-bit offsets
