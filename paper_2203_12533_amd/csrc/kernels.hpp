@@ -72,6 +72,9 @@ hipError_t launch_add2(hipStream_t s, const float* a, const float* b, float* y, 
 hipError_t launch_fill_f32(hipStream_t s, float* p, int64_t n, float v);
 hipError_t launch_f32_to_bf16(hipStream_t s, const float* src, void* dst, int64_t n);
 hipError_t launch_bf16_to_f32(hipStream_t s, const void* src, float* dst, int64_t n);
+// src (16-byte aligned) to pinned host memory; words[i] receives token when piece i of kReadBackPiece bytes has arrived.
+constexpr int64_t kReadBackPiece = 16384;
+hipError_t launch_read_back(hipStream_t s, const void* src, void* dst, int64_t bytes, uint32_t* words, uint32_t token);
 hipError_t launch_copy_bytes(hipStream_t s, const void* src, void* dst, int64_t bytes);
 // Spins (bounded by timeout_ticks of the 100 MHz wall clock) until *flag != 0.  *flag == 1 means
 // "resolved"; any other value, or a timeout, writes 1 to *poison.  Both words live in pinned host memory.

@@ -277,6 +277,47 @@ void stop_executors(pw_ctx* c) {
 
 }  // namespace
 
+namespace pw {
+namespace rt {
+hipError_t read_back(pw_ctx* c, hipStream_t s, const void* src, void* dst, size_t bytes) {
+  if (!c->rb_stage) {
+    if (hipHostMalloc((void**)&c->rb_stage, kReadBackBytes, hipHostMallocDefault) != hipSuccess) c->rb_stage = nullptr;
+    const size_t words = kReadBackBytes / kReadBackPiece * sizeof(uint32_t);
+    if (c->rb_stage && !c->rb_words) {
+      if (hipHostMalloc((void**)&c->rb_words, words, hipHostMallocDefault) != hipSuccess) {
+        (void)hipHostFree(c->rb_stage);
+        c->rb_stage = nullptr, c->rb_words = nullptr;
+      } else {
+        memset(c->rb_words, 0, words);
+      }
+    }
+    if (!c->rb_stage) (void)hipGetLastError();
+  }
+  if (!c->rb_stage || bytes > kReadBackBytes || ((uintptr_t)src & 15)) {
+    const hipError_t e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s);
+    return e != hipSuccess ? e : hipStreamSynchronize(s);
+  }
+  if (bytes == 0) return hipStreamSynchronize(s);
+  if (++c->rb_seq == 0) ++c->rb_seq;
+  hipError_t e = launch_read_back(s, src, c->rb_stage, (int64_t)bytes, c->rb_words, c->rb_seq);
+  if (e != hipSuccess) return e;
+  // The words are polled for a while; a stream that is still busy then is waited for, which reports its errors too.
+  bool drained = false;
+  const auto t0 = std::chrono::steady_clock::now();
+  for (size_t piece = 0; piece * kReadBackPiece < bytes; ++piece) {
+    for (int spin = 0; !drained && __atomic_load_n(&c->rb_words[piece], __ATOMIC_ACQUIRE) != c->rb_seq; ++spin)
+      if ((spin & 255) == 255 && std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(2)) {
+        if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
+        drained = true;
+      }
+    const size_t from = piece * kReadBackPiece;
+    memcpy((char*)dst + from, c->rb_stage + from, std::min(bytes - from, (size_t)kReadBackPiece));
+  }
+  return hipSuccess;
+}
+}  // namespace rt
+}  // namespace pw
+
 // =====================================================================================================
 extern "C" {
 
@@ -346,6 +387,8 @@ pw_status pw_ctx_destroy(pw_ctx* c) {
   for (hipEvent_t e : c->event_pool) (void)hipEventDestroy(e);
   c->futures.clear();
   for (uint32_t* s : c->word_slabs) (void)hipHostFree(s);
+  if (c->rb_stage) (void)hipHostFree(c->rb_stage);
+  if (c->rb_words) (void)hipHostFree(c->rb_words);
   (void)hipStreamDestroy(c->gate);
   (void)hipStreamDestroy(c->io);
   if (c->own_exec) (void)hipStreamDestroy(c->exec);
@@ -1113,9 +1156,9 @@ pw_status pw_await(pw_ctx* c, pw_future h, void* host_dst, size_t bytes) {
   f->refcount++;
   hipEvent_t ev = f->event;
   hipStream_t exec = c->exec;
-  // Readiness alone (nothing to copy out) of a future with a completion word: poll the word for a while - it arrives
-  // microseconds before the stream's event does - and fall back to the event if it does not show up.
-  const std::shared_ptr<GateWords> done = (host_dst && bytes) ? nullptr : f->done;
+  // A future with a completion word: poll the word for a while - it arrives microseconds before the stream's event does - and
+  // fall back to the event if it does not show up.
+  const std::shared_ptr<GateWords> done = f->done;
   const uint32_t done_token = f->done_token;
   api_lk_.unlock();
   bool signalled = false;
@@ -1137,8 +1180,11 @@ pw_status pw_await(pw_ctx* c, pw_future h, void* host_dst, size_t bytes) {
     for (auto& p : f->poison)
       if (__atomic_load_n(&p->words[1], __ATOMIC_ACQUIRE)) { st = fail(c, PW_ERR_POISONED, "a pending input was poisoned or timed out"); break; }
   if (st == PW_OK && host_dst && bytes) {
-    if (hipMemcpyAsync(host_dst, f->buf, bytes, hipMemcpyDeviceToHost, c->io) != hipSuccess || hipStreamSynchronize(c->io) != hipSuccess)
-      st = fail(c, PW_ERR_DEVICE, "copy to the host failed");
+    // memory of the caller's (wrapped) may be any that the runtime can copy from
+    hipError_t copied = hipSuccess;
+    if (f->owns) copied = read_back(c, c->io, f->buf, host_dst, bytes);
+    else if ((copied = hipMemcpyAsync(host_dst, f->buf, bytes, hipMemcpyDeviceToHost, c->io)) == hipSuccess) copied = hipStreamSynchronize(c->io);
+    if (copied != hipSuccess) st = fail(c, PW_ERR_DEVICE, "copy to the host failed");
   }
   future_drop(c, h);
   return st;

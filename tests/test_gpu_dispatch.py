@@ -198,6 +198,20 @@ def test_figure2_program_with_fan_out(ctx):
         ctx.future_release(f)
 
 
+# one element, the edges of a 16-byte store, of a piece (4096 floats) and of the staging (16384 floats)
+@pytest.mark.parametrize("n", [1, 3, 4, 5, 4095, 4096, 4097, 8195, 16383, 16384, 16385, 100003])
+def test_values_come_back_whole(ctx, n):
+    add = ctx.compile_scalar_fn(pwb.PW_FN_ADD_CONST, n, 1.0)
+    for seed in (1, 2):                       # the second through staging that holds the first
+        x = np.random.default_rng(seed).standard_normal(n).astype(np.float32)
+        f = ctx.future_from_host(x)
+        (g,) = ctx.run_fn(add, [f], 1)
+        assert np.array_equal(ctx.await_(g), x + np.float32(1.0))
+        assert np.array_equal(ctx.await_(f), x)
+        ctx.future_release(f)
+        ctx.future_release(g)
+
+
 def test_signature_mismatch_is_rejected_before_any_launch(ctx):
     add128 = ctx.compile_scalar_fn(pwb.PW_FN_ADD_CONST, 128, 1.0)
     add64 = ctx.compile_scalar_fn(pwb.PW_FN_ADD_CONST, 64, 1.0)
