@@ -249,18 +249,24 @@ hipError_t launch_tile(hipStream_t s, GemmF32Params p, bool ak, bool bk) {
 
 // 64 x 64 tiles, which read half as much per FLOP, once there is one of them for every compute unit (2048 x 512 x 1000:
 // 23 us against 34 with 32 x 32; 1000 x 2048 x 512: 33 against 36); below that the smaller tiles occupy more of the
-// chip (1000 x 512 x 2048, 128 tiles of 64 x 64: 30 us against 44; 512 x 256 x 1024: 10 against 22).  8 or 16 slices
+// chip (1000 x 512 x 2048, 128 tiles of 64 x 64: 30 us against 44).  8 or 16 slices
 // of k instead of 4 measured the same or slower at every size.
 // 16 x 32 tiles where those of 32 x 32 leave half the compute units without one: the serial chain of a wave is half as long and
-// twice as many units take part (us, 32 x 32 / 16 x 32: 512 x 256 x 1024, 128 tiles of 32 x 32, 9.3 / 6.9; 64 x 256 x 1024, 16 tiles,
-// 9.2 / 6.6; 256 x 256 x 512 k-major, 64, 6.2 / 5.2; 512 x 256 x 256, 128, 4.9 / 5.0; beyond 128 tiles no gain: 300 x 448 x 704, 140,
-// 7.9 / 9.0; 512 x 512 x 512, 256, 6.9 / 8.3).
+// twice as many units take part (us per launch, median of a kernel trace, 32 x 32 / 16 x 32: 512 x 256 x 1024, 128 tiles of 32 x 32,
+// 9.7 / 7.1; 64 x 256 x 1024, 16 tiles, 10.0 / 6.9; 256 x 256 x 512 k-major, 64, 6.6 / 5.6; 512 x 256 x 256, 128, 4.9 / 4.2; beyond 128
+// tiles no gain: 300 x 448 x 704, 140, 7.9 / 9.0; 512 x 512 x 512, 256, 6.8 / 7.6).
+// Not for up to four tiles and a short k: more workgroups end later than these few waves compute (32 x 32 x 64 2.8 / 3.3, x 256 4.1 /
+// 4.1; 64 x 64 x 16 3.1 / 3.5, x 160 4.1 / 4.0; from five tiles on no difference is left: 160 x 32 x 16 3.5 / 3.5).
+static bool low_tiles(const GemmArgs& a, int64_t t32) {
+  if (t32 > 128) return false;
+  return t32 > 4 || a.K > (t32 == 1 ? 256 : 160);
+}
 hipError_t launch_gemm_f32(hipStream_t s, const GemmArgs& a, const EpiParams& epi) {
   const GemmF32Params p{(const float*)a.A, (const float*)a.B, a.M, a.N, a.K, a.lda, a.ldb, 0, 0, epi};
   const int64_t t64 = ((a.M + 63) / 64) * ((a.N + 63) / 64);
   const int64_t t32 = ((a.M + 31) / 32) * ((a.N + 31) / 32);
   if (t64 >= 256) return launch_tile<4, 4>(s, p, a.a_kmajor, a.b_kmajor);
-  return t32 > 128 ? launch_tile<2, 2>(s, p, a.a_kmajor, a.b_kmajor) : launch_tile<1, 2>(s, p, a.a_kmajor, a.b_kmajor);
+  return low_tiles(a, t32) ? launch_tile<1, 2>(s, p, a.a_kmajor, a.b_kmajor) : launch_tile<2, 2>(s, p, a.a_kmajor, a.b_kmajor);
 }
 
 }  // namespace pw

@@ -138,6 +138,13 @@ def test_gemm_fp32_low_tiles_in_every_layout(ctx, M, N, K, a_k, b_k):
     test_gemm_fp32_edges_in_every_layout(ctx, M, N, K, a_k, b_k)
 
 
+# up to four tiles of 32 x 32 and a short k: on those tiles (one k later on 16 x 32), rows and columns that end inside them
+@pytest.mark.parametrize("a_k,b_k", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("M,N,K", [(1, 1, 1), (17, 20, 31), (32, 32, 256), (31, 32, 257), (33, 64, 160), (64, 35, 161), (97, 30, 100), (130, 31, 64)])
+def test_gemm_fp32_of_a_few_tiles_in_every_layout(ctx, M, N, K, a_k, b_k):
+    test_gemm_fp32_edges_in_every_layout(ctx, M, N, K, a_k, b_k)
+
+
 # one size per tile shape of the any-shape kernel (64 x 64 and 128 x 64 tiles with k split over waves, 128 x 128 in both
 # loop forms), ragged in every dimension, k from one partial step on; what lies behind the last k of a row is no number, and
 # the last size has rows too far apart for 32-bit offsets
