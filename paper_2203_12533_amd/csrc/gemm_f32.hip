@@ -257,9 +257,17 @@ hipError_t launch_tile(hipStream_t s, GemmF32Params p, bool ak, bool bk) {
 // tiles no gain: 300 x 448 x 704, 140, 7.9 / 9.0; 512 x 512 x 512, 256, 6.8 / 7.6).
 // Not for up to four tiles and a short k: more workgroups end later than these few waves compute (32 x 32 x 64 2.8 / 3.3, x 256 4.1 /
 // 4.1; 64 x 64 x 16 3.1 / 3.5, x 160 4.1 / 4.0; from five tiles on no difference is left: 160 x 32 x 16 3.5 / 3.5).
+// Nor where both operands are k-major, their rows straddle cache lines (a piece of one k is 64 bytes of A and 128 of B, and then comes
+// from two lines) and they are more than an XCD's L2 of 4 MiB holds: the lower tile fetches each line of B twice as often (32 x 32 /
+// 16 x 32: 130 x 620 x 2048 18.3 / 28.0, 160 x 590 x 3072 27.3 / 40.2, 480 x 250 x 4096 47.4 / 53.3, 41 x 151 x 6144 43.6 / 54.7).  A long k or
+// few tiles move that further out: 300 x 300 x 1024 11.2 / 9.8, x 1280 13.2 / 11.1, 16 x 1000 x 4096 36.4 / 27.6, 558 x 32 x 4096 29.8 / 27.0.
+// Whole lines have no such limit (496 x 256 x 8192 87.7 / 37.0), nor has one k-major operand (480 x 250 x 8192 79.8 / 37.8).
 static bool low_tiles(const GemmArgs& a, int64_t t32) {
   if (t32 > 128) return false;
-  return t32 > 4 || a.K > (t32 == 1 ? 256 : 160);
+  if (t32 <= 4 && a.K <= (t32 == 1 ? 256 : 160)) return false;
+  const bool straddles = a.a_kmajor && a.b_kmajor &&
+                         (((uintptr_t)a.A | (uint64_t)a.lda * 4) % 64 != 0 || ((uintptr_t)a.B | (uint64_t)a.ldb * 4) % 128 != 0);
+  return !straddles || (a.M + a.N) * a.K < (1 << 20) || a.K * t32 < (a.K > 4096 ? 60000 : 140000);
 }
 hipError_t launch_gemm_f32(hipStream_t s, const GemmArgs& a, const EpiParams& epi) {
   const GemmF32Params p{(const float*)a.A, (const float*)a.B, a.M, a.N, a.K, a.lda, a.ldb, 0, 0, epi};

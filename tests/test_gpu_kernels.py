@@ -145,6 +145,13 @@ def test_gemm_fp32_of_a_few_tiles_in_every_layout(ctx, M, N, K, a_k, b_k):
     test_gemm_fp32_edges_in_every_layout(ctx, M, N, K, a_k, b_k)
 
 
+# both operands k-major, rows that straddle cache lines, more than 2^20 values of both: tiles of 16 x 32 up to 140000 / (tiles of
+# 32 x 32) steps of k (1400 here), from there on 32 x 32; 60000 / tiles past k = 4096
+@pytest.mark.parametrize("M,N,K", [(130, 620, 1399), (130, 620, 1401), (41, 151, 5999), (41, 151, 6001)])
+def test_gemm_fp32_of_long_kmajor_rows_that_straddle_lines(ctx, M, N, K):
+    test_gemm_fp32_edges_in_every_layout(ctx, M, N, K, 1, 1)
+
+
 # one size per tile shape of the any-shape kernel (64 x 64 and 128 x 64 tiles with k split over waves, 128 x 128 in both
 # loop forms), ragged in every dimension, k from one partial step on; what lies behind the last k of a row is no number, and
 # the last size has rows too far apart for 32-bit offsets
