@@ -275,29 +275,30 @@ void stop_executors(pw_ctx* c) {
   c->executors.clear();
 }
 
-}  // namespace
+// Copies out (pw_await): up to kReadBackBytes through pinned staging, by a kernel that signals piece by piece.
+constexpr size_t kReadBackBytes = 64u << 10;   // above, the runtime's own copy is no slower (128 KiB, us: 16.4 / 17.1)
 
-namespace pw {
-namespace rt {
+// The staging and a word per piece of it, from the first use on; false: none to be had.
+bool read_back_staging(pw_ctx* c) {
+  if (c->rb_stage) return true;
+  const size_t words = kReadBackBytes / kReadBackPiece * sizeof(uint32_t);
+  char* stage = nullptr;
+  uint32_t* w = nullptr;
+  if (hipHostMalloc((void**)&stage, kReadBackBytes, hipHostMallocDefault) != hipSuccess ||
+      hipHostMalloc((void**)&w, words, hipHostMallocDefault) != hipSuccess) {
+    if (stage) (void)hipHostFree(stage);
+    (void)hipGetLastError();
+    return false;
+  }
+  memset(w, 0, words);
+  c->rb_stage = stage;
+  c->rb_words = w;
+  return true;
+}
+
+// 1 .. kReadBackBytes bytes from a pool buffer to pageable host memory behind what stream s holds, waited for.  The caller holds
+// the context's lock (the staging is the context's).
 hipError_t read_back(pw_ctx* c, hipStream_t s, const void* src, void* dst, size_t bytes) {
-  if (!c->rb_stage) {
-    if (hipHostMalloc((void**)&c->rb_stage, kReadBackBytes, hipHostMallocDefault) != hipSuccess) c->rb_stage = nullptr;
-    const size_t words = kReadBackBytes / kReadBackPiece * sizeof(uint32_t);
-    if (c->rb_stage && !c->rb_words) {
-      if (hipHostMalloc((void**)&c->rb_words, words, hipHostMallocDefault) != hipSuccess) {
-        (void)hipHostFree(c->rb_stage);
-        c->rb_stage = nullptr, c->rb_words = nullptr;
-      } else {
-        memset(c->rb_words, 0, words);
-      }
-    }
-    if (!c->rb_stage) (void)hipGetLastError();
-  }
-  if (!c->rb_stage || bytes > kReadBackBytes || ((uintptr_t)src & 15)) {
-    const hipError_t e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s);
-    return e != hipSuccess ? e : hipStreamSynchronize(s);
-  }
-  if (bytes == 0) return hipStreamSynchronize(s);
   if (++c->rb_seq == 0) ++c->rb_seq;
   hipError_t e = launch_read_back(s, src, c->rb_stage, (int64_t)bytes, c->rb_words, c->rb_seq);
   if (e != hipSuccess) return e;
@@ -315,8 +316,8 @@ hipError_t read_back(pw_ctx* c, hipStream_t s, const void* src, void* dst, size_
   }
   return hipSuccess;
 }
-}  // namespace rt
-}  // namespace pw
+
+}  // namespace
 
 // =====================================================================================================
 extern "C" {
@@ -1181,8 +1182,8 @@ pw_status pw_await(pw_ctx* c, pw_future h, void* host_dst, size_t bytes) {
       if (__atomic_load_n(&p->words[1], __ATOMIC_ACQUIRE)) { st = fail(c, PW_ERR_POISONED, "a pending input was poisoned or timed out"); break; }
   if (st == PW_OK && host_dst && bytes) {
     // memory of the caller's (wrapped) may be any that the runtime can copy from
-    hipError_t copied = hipSuccess;
-    if (f->owns) copied = read_back(c, c->io, f->buf, host_dst, bytes);
+    hipError_t copied;
+    if (f->owns && bytes <= kReadBackBytes && read_back_staging(c)) copied = read_back(c, c->io, f->buf, host_dst, bytes);
     else if ((copied = hipMemcpyAsync(host_dst, f->buf, bytes, hipMemcpyDeviceToHost, c->io)) == hipSuccess) copied = hipStreamSynchronize(c->io);
     if (copied != hipSuccess) st = fail(c, PW_ERR_DEVICE, "copy to the host failed");
   }

@@ -134,7 +134,6 @@ using namespace pw;
 using namespace pw::rt;
 
 struct pw_sched;
-constexpr size_t kReadBackBytes = 64u << 10;   // above, the runtime's own copy is no slower (128 KiB, us: 16.4 / 17.1)
 
 struct pw_ctx {
   int device = 0;
@@ -167,7 +166,7 @@ struct pw_ctx {
   std::vector<uint32_t*> free_done_words;
   uint32_t done_seq = 0;
   std::map<size_t, std::vector<void*>> staging_pool;
-  // copies out (read_back): kReadBackBytes of pinned staging and a word per piece of it, from the first use on
+  // copies out (pw_await): pinned staging and a word per piece of it
   char* rb_stage = nullptr;
   uint32_t* rb_words = nullptr;
   uint32_t rb_seq = 0;
@@ -298,10 +297,6 @@ inline pw_status fail(pw_ctx* c, pw_status st, const char* fmt, ...) {
     if (e_ != hipSuccess) return fail(c, e_ == hipErrorOutOfMemory ? PW_ERR_OOM : PW_ERR_DEVICE, \
                                       "%s: %s", #expr, hipGetErrorString(e_));                   \
   } while (0)
-
-// Copies `bytes` from device memory to pageable host memory behind what stream s holds, and waits for it.  The caller holds the
-// context's lock (the staging is the context's).
-hipError_t read_back(pw_ctx* c, hipStream_t s, const void* src, void* dst, size_t bytes);
 
 // Handles are (generation << 32) | (slot + 1): a stale handle finds a different generation and gives null.
 inline FutureRec* future_get(pw_ctx* c, pw_future h) {
