@@ -112,8 +112,9 @@ def test_gemm_fused_epilogues(ctx, orc, bf16, shape):
     assert_close(host(du), orc.gelu_bwd(prev, nobias), tol)
 
 
-# tiles of 32 x 32 and (from 256 tiles of 64 x 64 on) 64 x 64; fewer rows than a fragment piece, one past a tile, k not a
-# multiple of the 16-deep step and shorter than the four slices of it; rows of odd length (no alignment anywhere)
+# tiles of 32 x 32 (one of them, short k), 16 x 32 (the second shape) and, from 256 tiles of 64 x 64 on, 64 x 64; fewer rows than a
+# fragment piece, one past a tile, k not a multiple of the 16-deep step and shorter than the four slices of it; rows of odd length
+# (no alignment anywhere)
 @pytest.mark.parametrize("a_k,b_k", [(0, 0), (0, 1), (1, 0), (1, 1)])
 @pytest.mark.parametrize("M,N,K", [(1, 3, 5), (33, 65, 16), (31, 32, 130), (1025, 1021, 67), (3, 20000, 33)])
 def test_gemm_fp32_edges_in_every_layout(ctx, M, N, K, a_k, b_k):
@@ -135,6 +136,13 @@ def test_gemm_fp32_edges_in_every_layout(ctx, M, N, K, a_k, b_k):
 @pytest.mark.parametrize("a_k,b_k", [(0, 0), (0, 1), (1, 0), (1, 1)])
 @pytest.mark.parametrize("M,N,K", [(16, 32, 64), (17, 31, 129), (512, 256, 83), (513, 256, 83), (47, 33, 1000)])
 def test_gemm_fp32_low_tiles_in_every_layout(ctx, M, N, K, a_k, b_k):
+    test_gemm_fp32_edges_in_every_layout(ctx, M, N, K, a_k, b_k)
+
+
+# from 129 tiles of 32 x 32 on these: ragged rows and columns, k of less than one step, of one and of four and a bit, one row or column
+@pytest.mark.parametrize("a_k,b_k", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("M,N,K", [(417, 389, 67), (417, 389, 5), (417, 389, 16), (1, 6000, 33), (6000, 1, 33)])
+def test_gemm_fp32_square_tiles_in_every_layout(ctx, M, N, K, a_k, b_k):
     test_gemm_fp32_edges_in_every_layout(ctx, M, N, K, a_k, b_k)
 
 
@@ -697,7 +705,6 @@ def test_bf16_attention_blocks_of_64_and_of_128_rows(ctx, orc, B, Tq, Tk, H, hd,
     _mha_case(ctx, orc, True, B, Tq, Tk, H, hd, causal, packed_kv=True)
 
 
-# keys that no query attends to (scores of -inf) in every tile of one wave's part, and all but the first of the other's
 @pytest.mark.parametrize("B,Tq,Tk,H,causal", [(13, 65, 129, 5, 0), (13, 128, 130, 5, 0), (26, 97, 33, 5, 0), (13, 129, 129, 5, 1), (11, 300, 300, 4, 1),
                                               (26, 66, 66, 5, 1), (13, 192, 192, 5, 1)])
 def test_bf16_attention_at_head_width_128_with_a_chip_full_of_key_blocks(ctx, orc, B, Tq, Tk, H, causal):
@@ -706,6 +713,39 @@ def test_bf16_attention_at_head_width_128_with_a_chip_full_of_key_blocks(ctx, or
     _mha_case(ctx, orc, True, B, Tq, Tk, H, 128, causal=bool(causal), packed_kv=True)
 
 
+# more than 128 blocks of 128 keys and a single tile of queries: four waves to 128 keys in dK/dV, at both ends of that tile
+@pytest.mark.parametrize("B,Tq,Tk,H,causal", [(40, 60, 100, 4, 0), (33, 64, 130, 8, 0), (33, 64, 64, 8, 1), (140, 1, 20, 1, 0)])
+def test_bf16_attention_at_head_width_128_with_one_tile_of_queries(ctx, orc, B, Tq, Tk, H, causal):
+    _mha_case(ctx, orc, True, B, Tq, Tk, H, 128, causal=bool(causal), packed_kv=True)
+
+
+# dK/dV where two waves share 32 keys, with keys that no query attends to (an infinite key): all of a wave's, some of it, all but one
+# of a block's.  The gradients of the finite keys are what these alone give.
+@pytest.mark.parametrize("off", [range(32), range(40, 50), range(127), range(100, 150), range(1, 150)])
+def test_bf16_attention_gradients_beside_keys_at_minus_infinity(ctx, orc, off):
+    B, Tq, Tk, hd = 70, 70, 150, 128
+    q, k, v, g = (_rand(s, (B * t, hd)) for s, t in ((81, Tq), (82, Tk), (83, Tk), (84, Tq)))
+    q[:, 0], gone = 1.0, np.zeros(Tk, bool)
+    gone[list(off)] = True
+    gone = np.tile(gone, B)
+    (qt, qv), (kt, kv), (vt, vv), (gt, gv) = (dev_act(x, True) for x in (q, k, v, g))
+    kt[torch.as_tensor(gone, device="cuda")] = 0.0
+    kt[torch.as_tensor(gone, device="cuda"), 0] = -torch.inf
+    o, dq, dk, dv = (empty_act(x.shape, True) for x in (q, q, k, v))
+    lse, delta = torch.empty((B, 1, Tq), device="cuda"), torch.empty((B, 1, Tq), device="cuda")
+    torch.cuda.synchronize()
+    a = pwb.MhaArgs(pwb.PW_BF16, ptr(qt), ptr(kt), ptr(vt), hd, hd, B, Tq, Tk, 1, hd, 0)
+    ctx.mha_fwd(a, ptr(o), ptr(lse))
+    ctx.mha_bwd(a, ptr(o), ptr(gt), ptr(lse), ptr(delta), ptr(dq), hd, ptr(dk), ptr(dv), hd)
+    ctx.synchronize()
+    kept, n = (np.ascontiguousarray(x[~gone]) for x in (kv, vv)), int((~gone).sum()) // B
+    _, rk, rv = orc.mha_bwd(qv, *kept, gv, B, Tq, n, 1, hd, causal=False)
+    if n > 1:                                 # (one key: its score gradients are zero in exact arithmetic)
+        assert_close(host(dk)[~gone], rk, 1.5e-2)
+    assert_close(host(dv)[~gone], rv, 1.5e-2)
+
+
+# keys that no query attends to (scores of -inf) in every tile of one wave's part, and all but the first of the other's
 @pytest.mark.parametrize("hd", [64, 128])
 def test_bf16_attention_with_scores_of_minus_infinity(ctx, orc, hd):
     B, Tq, Tk, H = 1, 50, 160, 1
@@ -898,6 +938,60 @@ def test_bf16_attention_passes_infinite_values_on(ctx, T, hd, packed):
         assert (got[:, col] == inf).all()
         rest = np.arange(hd) != col
         assert_close(got[:, rest], ref[:, rest], 1.5e-2)
+
+
+# the same where two waves share 32 keys in dK/dV: queries that end inside a tile, in its first half and in its second
+@pytest.mark.parametrize("T", [70, 100])
+@pytest.mark.parametrize("packed", [True, False])
+def test_bf16_attention_of_many_blocks_passes_infinite_values_on(ctx, T, packed):
+    B, hd = 130, 128
+    q, k, v, g = (_rand(s, (T, hd)) for s in (91, 92, 93, 94))
+    v[T - 1, 3], g[T - 1, 5] = np.inf, -np.inf
+    qkv, qkvv = dev_act(np.tile(np.concatenate([q, k, v], 1), (B, 1)), True)
+    gt, gv = dev_act(np.tile(g, (B, 1)), True)
+    o, o_lo, dqkv = empty_act((B * T, hd), True), empty_act((B * T, hd), True), empty_act((B * T, 3 * hd), True)
+    lse, delta = torch.empty((B, 1, T), device="cuda"), torch.empty((B, 1, T), device="cuda")
+    at = lambda t, i: ptr(t) + 2 * hd * i  # noqa: E731
+    a = pwb.MhaArgs(pwb.PW_BF16, at(qkv, 0), at(qkv, 1), at(qkv, 2), 3 * hd, 3 * hd, B, T, T, 1, hd, int(packed))
+    ctx.mha_fwd(a, ptr(o), ptr(lse), ptr(o_lo))
+    ctx.mha_bwd(a, ptr(o), ptr(gt), ptr(lse), ptr(delta), at(dqkv, 0), 3 * hd, at(dqkv, 1), at(dqkv, 2), 3 * hd, ptr(o_lo))
+    ctx.synchronize()
+    qv, kv, _ = np.split(qkvv[:T], 3, axis=1)
+    s = qv @ kv.T / np.sqrt(hd)
+    p = np.exp(np.where(np.tril(np.ones((T, T), bool)), s, -np.inf) if packed else s)
+    p /= p.sum(1, keepdims=True)
+    got, ref = host(dqkv)[:, 2 * hd:], np.tile(p.T @ np.where(np.isfinite(gv[:T]), gv[:T], 0.0), (B, 1))
+    assert (got[:, 5] == -np.inf).all()
+    rest = np.arange(hd) != 5
+    assert_close(got[:, rest], ref[:, rest], 1.5e-2)
+
+
+# the widest rows that 32-bit offsets into tiles of 128 keys take, with a chip full of key blocks at head width 128
+def test_bf16_attention_with_the_widest_rows_of_many_key_blocks(ctx, orc):
+    Tq, Tk, H, hd, ld = 66, 130, 65, 128, 1 << 24
+    d = H * hd
+
+    def far(x):
+        t = torch.empty(((x.shape[0] - 1) * ld + x.shape[1],), dtype=torch.bfloat16, device="cuda")
+        t.as_strided(x.shape, (ld, 1)).copy_(torch.from_numpy(x).cuda().to(torch.bfloat16))
+        return t
+
+    q, kv, g = (I.round_to_bf16(_rand(s, shp)) for s, shp in ((95, (Tq, d)), (96, (Tk, 2 * d)), (97, (Tq, d))))
+    qt, kvt, (gt, _) = far(q), far(kv), dev_act(g, True)
+    o, o_lo, dq, dkv = (empty_act(shp, True) for shp in ((Tq, d), (Tq, d), (Tq, d), (Tk, 2 * d)))
+    lse, delta = torch.empty((1, H, Tq), device="cuda"), torch.empty((1, H, Tq), device="cuda")
+    a = pwb.MhaArgs(pwb.PW_BF16, ptr(qt), ptr(kvt), ptr(kvt) + 2 * d, ld, ld, 1, Tq, Tk, H, hd, 0)
+    torch.cuda.synchronize()
+    ctx.mha_fwd(a, ptr(o), ptr(lse), ptr(o_lo))
+    ctx.mha_bwd(a, ptr(o), ptr(gt), ptr(lse), ptr(delta), ptr(dq), d, ptr(dkv), ptr(dkv) + 2 * d, 2 * d, ptr(o_lo))
+    ctx.synchronize()
+    qv, kv_, gv = (np.ascontiguousarray(x, np.float64) for x in (q, kv, g))
+    k, v = np.ascontiguousarray(kv_[:, :d]), np.ascontiguousarray(kv_[:, d:])
+    assert_close(host(o), orc.mha_fwd(qv, k, v, 1, Tq, Tk, H, hd), 6e-3)
+    for got, ref in zip((host(dq), host(dkv)[:, :d], host(dkv)[:, d:]), orc.mha_bwd(qv, k, v, gv, 1, Tq, Tk, H, hd)):
+        assert_close(got, ref, 1.5e-2)
+    del qt, kvt
+    torch.cuda.empty_cache()                  # 6.6 GB
 
 
 # rows too far apart for 32-bit byte offsets into a tile: keys and values from 2^32 / (2 * 127) elements on (tiles of up to 128
