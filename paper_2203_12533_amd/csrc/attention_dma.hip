@@ -552,13 +552,15 @@ __global__ __launch_bounds__(kNT, 2) void attn_dq_dma_kernel(MhaDev a, const bf1
 // ===================================================================================================
 // dK, dV: block = 128 keys of one (batch, head); wave = 32 keys; query tiles of 64 as two 32-query blocks.
 // Software-pipelined: the four phases of a block - first products S and dP, softmax / dS arithmetic on the
-// vector ALU, second products into dV and dK - no longer run one after the other.  A wave has one SIMD to itself
-// here (its two output accumulators, the K / V fragments and the scores leave no room for a second wave), so
+// vector ALU, second products into dV and dK - no longer run one after the other.  At width 128 a wave has one SIMD to
+// itself here (its two output accumulators, the K / V fragments and the scores leave no room for a second wave), so
 // nothing else hides the latencies: the first products of block n+1 are issued between the vector instructions
 // of block n (one score element per MFMA: about as many vector cycles as the MFMA occupies the matrix pipe), and
 // the transposed LDS reads of the second products run two MFMAs ahead.  Three tiles are resident (ring of
 // three stages): the first products of the next tile start while the second products of the current one still
 // read theirs.
+// At width 128 these are the launches of few key blocks (PARTS = 2) and those of a single tile of queries (PARTS = 1, no next tile);
+// attn_dkv_pair_kernel below has the others.
 // ===================================================================================================
 struct DkvStats { float lq[16], dq[16]; };
 
@@ -908,18 +910,22 @@ __global__ __launch_bounds__(kNT, HD == 64 ? 2 : 1) void attn_dkv_dma_kernel(Mha
 }
 
 // ===================================================================================================
-// dK, dV at head_dim 128 where blocks of 128 keys fill the chip and there is more than one tile of queries: 8 waves, two to a
-// SIMD, each pair with the same 32 keys; of every tile of 64 queries one wave takes the first 32, the other the rest, and their
-// sums meet in LDS at the end (in a fixed order).
+// dK, dV at head_dim 128 for more than 128 blocks of 128 keys and more than one tile of queries: 8 waves, two to a SIMD, each pair
+// with the same 32 keys; of every tile of 64 queries one wave takes the first 32, the other the rest, and their sums meet in LDS
+// at the end (in a fixed order).
 // What bounds the kernel above is that a SIMD has one wave: products, exponentials and LDS round trips of a block follow one
 // another (3200 clocks for 1024 of matrix work).  A second wave needs each of them within 256 registers: K and V stay in LDS
 // next to a ring of two tiles (129 KiB, one workgroup per compute unit) instead of in 64 registers, the addresses of LDS
 // reads are worked out from one register each, the statistics come in under the last first products.  Half as many
 // LDS bytes again per block is the price; two roles per pair (P and dV | dP, dS and dK over 64 keys each, P handed over through LDS:
 // half the reads), halves of a pair one phase apart, and V in registers were all slower or the same, wave priorities no different.
-// Measured (us, this kernel alone, before / now): causal 8 x 1024, 16 heads 126 / 109; unmasked 4 x 1000, 16 heads 95.7 / 80.3.  Forward
-// and backward: causal 4 x 1000, 8 heads 89.1 / 84.3; 8 x 300, 12 heads 59.8 / 58.1; 2048, 16 heads 150.7 / 137.7; 4 x 333 queries over 520
-// keys, 16 heads 80.7 / 76.9.  One tile has nothing to overlap: 8 x 60 queries over 1500 keys 122.4 / 125.4, left to the kernel above.
+// What bounds it: no unit is full (causal 8 x 1024, 16 heads, counters: matrix pipe 28 % of the time, before 24 %; LDS reads 28 %, no
+// conflicts; vector issue 31 % of a SIMD); a wave waits on counters 37 % and to issue 32 % of its time, the barrier per tile keeps both
+// waves of a SIMD in the same phase.
+// Measured (us, this kernel alone, kernel traces, before / now): in train steps causal 8 x 1024, 16 heads 123 / 101, 2 x 1024, 32 heads
+// 97.8 / 79.2, unmasked 8 x 1024, 16 heads 179 / 153; by itself causal 2 x 1024, 16 heads 41.0 / 33.2, 16 x 128, 16 heads 16.4 / 14.6.
+// Forward and backward: causal 4 x 1000, 8 heads 89.1 / 84.3; 8 x 300, 12 heads 59.8 / 58.1; 4 x 333 queries over 520 keys, 16 heads
+// 80.7 / 76.9.  The dispatch (bwd_dma) has both limits' figures.
 // ===================================================================================================
 constexpr int kPairWaves = 8, kPairBQ = 64, kPairTile = kPairBQ * 128;
 constexpr int kSmemPair = (2 * 128 * 128 + 2 * 2 * kPairTile) * 2 + 2 * 2 * kPairBQ * 4;
@@ -1065,7 +1071,8 @@ __global__ __launch_bounds__(64 * kPairWaves, 2) void attn_dkv_pair_kernel(MhaDe
 
 }  // namespace
 
-// Dynamic LDS: two stages of two 64-row tiles (64 KiB at head_dim 128); dK/dV three stages and their statistics (97.5 KiB).
+// Dynamic LDS: two stages of two 64-row tiles (64 KiB at head_dim 128); dK/dV three stages and their statistics (97.5 KiB;
+// attn_dkv_pair_kernel has kSmemPair, 129 KiB).
 template <int HD, int PARTS> constexpr int kSmemTiles = 2 * 2 * kSubRows<HD, PARTS> * PARTS * HD * 2;
 template <int HD, bool HIDES> constexpr int kSmemDkv = 3 * 2 * 64 * HD * 2 + 6 * 64 * 4 + (HIDES ? (64 + 32) * HD * 2 : 0);   // (tile_q)
 
@@ -1132,7 +1139,8 @@ template <int PARTS> static int blocks_of(int rows, const MhaArgs& a) { return (
 //     384 blocks: 448 36.2 / 39.4, 768 50.8 / 51.6, 1024 62.2 / 55.1; 512 blocks: 768 51.5 / 60.3, 1024 61.8 / 61.1.  T x 128: 64 15.4 / 17.9, 128
 //     blocks: 128 23.4 / 21.1, 1024 69 / 48.
 //   dQ alone: causal 2 x 1024, 16 x 128 (256) 70.6 / 66.0; unmasked 1 x 1000 over 2000, 16 x 128 (128) 93 / 81, 4 x 700 over 500, 8 x 128 (192) 50.0 / 51.9.
-//   dK/dV alone: causal 3 x 700, 12 x 128 (216) 53.8 / 59.6; unmasked 1 x 2048 over 256, 16 x 128 (32) 83 / 60.6, 4 x 333 over 520, 8 x 64 (160) 37.9 / 39.8.
+//   dK/dV alone: unmasked 1 x 2048 over 256, 16 x 128 (32) 83 / 60.6, 4 x 333 over 520, 8 x 64 (160) 37.9 / 39.8.  At head_dim 128 the other
+//   side of the 128 blocks is attn_dkv_pair_kernel, see bwd_dma.
 // most: the largest number of blocks, for rows whose other side is at least `from` long (where it is shorter, 128; under the
 // causal mask 256 between 384 and `from`, none up to 64: one tile has no halves worth sharing).
 static bool two_parts(const MhaArgs& a, int rows, int other, int from, int most) {
@@ -1169,6 +1177,13 @@ static hipError_t bwd_dma(hipStream_t s, const MhaArgs& a, const MhaGrads& g) {
   auto run_kv = [&](auto kernel, int grid) {
     kernel<<<grid, kNT, kSmemDkv<HD, HD == 64 && CAUSAL && !SPLIT>, s>>>(dev_of(a), (const bf16*)g.dout, g.lse, g.delta, (bf16*)g.dk, (bf16*)g.dv, g.lddkv);
   };
+  // Width 128, dK/dV alone (us, kernel traces, attn_dkv_dma_kernel of one wave / of two parts / attn_dkv_pair_kernel): causal 112 blocks,
+  // T 192 15.7 / 12.9 / 13.6, 512 24.9 / 18.6 / 20.4, 1024 38.9 / 27.6 / 30.9; 136, T 100 12.7 / 18.3 / 12.8, 192 15.9 / 13.3 / 13.4, 512 24.9 / 26.7 / 20.6,
+  // 1024 39.0 / 35.8 / 31.3; 216, 700 31.4 / 37.7 / 25.7; 256, 65 12.2 / 17.1 / 11.7, 2048 70.0 / 58.0 / 56.4; 512, 256 33.8 / 45.5 / 30.8.  Unmasked 128
+  // blocks, 256 queries over 500 keys 16.5 / 14.9 / 14.8, 1000 38.3 / 28.6 / 30.9; 136, 256 16.3 / 25.2 / 14.6, 1000 38.2 / 52.9 / 31.0.  Past 128 blocks
+  // two parts win only where their blocks of 64 still find a unit each (138 blocks of T 700 are 253 of 64: 30.0 / 22.3 / 24.4).  One
+  // tile of queries gives pairs nothing to overlap and more waves to start: 64 over 100 keys, 256 blocks 11.2 / 18.0 / 12.5, over 500 13.3
+  // / 19.0 / 13.2.
   if (CAUSAL ? two_parts(a, a.Tk, a.Tq, 768, HD == 64 ? 384 : 128) : two_parts(a, a.Tk, a.Tq, 0, 128)) run_kv(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, 2>, blocks_of<2>(a.Tk, a));
   else if (HD == 128 && a.Tq > kPairBQ)
     attn_dkv_pair_kernel<CAUSAL><<<blocks_of<1>(a.Tk, a), 64 * kPairWaves, kSmemPair, s>>>(

@@ -7,9 +7,10 @@
 // k-loop and how few compute units take part in it, so the k-range of an output tile is cut into slices, one wave
 // each, whose partial tiles meet in LDS and are added in slice order (the same bits on every run).  The shorter sums
 // also round less: against 64 bits 1.5e-7 ... 2.9e-7 where one long sum has 2.9e-7 ... 5.7e-7.
-// Measured (us per launch, MI355X; before: 64 x 64 tiles on the vector ALU, one k-loop): 512 x 256 x 1024 133 -> 6.9,
-// 512 x 1024 x 256 36 -> 7.6, 1024 x 256 x 512 (weight gradient) 72 -> 7.1, 1000 x 512 x 2048 360 -> 30,
-// 2048^3 451 -> 156 (110 TFLOP/s of the 157 the fp32 matrix pipe has at 2.4 GHz), 4096 x 4096 x 1024 646 -> 289.
+// Measured (us per launch, MI355X, the same operands again and again; before: 64 x 64 tiles on the vector ALU, one k-loop):
+// 512 x 256 x 1024 133 -> 7.1, 512 x 1024 x 256 36 -> 7.6, 1024 x 256 x 512 (weight gradient) 72 -> 7.0, 1000 x 512 x 2048 360 -> 30,
+// 2048^3 451 -> 156 (110 TFLOP/s of the 157 the fp32 matrix pipe has at 2.4 GHz), 4096 x 4096 x 1024 646 -> 289.  Behind other kernels,
+// in a feed-forward block of 512 x 256 x 1024, the first three take 8.7, 9.1 (with the GELU epilogue) and 7.0.
 //
 // Fragments.  The instruction takes one value per lane and operand: row lane%16, k-slot lane/16.  Which k a slot stands
 // for and which tile row a fragment row stands for is free as long as both operands (and the epilogue) agree:
@@ -121,7 +122,9 @@ constexpr int kWK = 4;
 template <int FM, int F, bool AK, bool BK_>
 __global__ __launch_bounds__(64 * kWK) void gemm_f32_kernel(GemmF32Params p) {
   constexpr int TM = 16 * FM, T = 16 * F;
-  constexpr int kDepth = F == 2 ? 5 - FM : 2; // steps in flight per wave
+  // Steps in flight per wave.  Four or three on 16 x 32 tiles (us, 512 x 256 x 1024): A row-major and B k-major 7.3 / 7.7, both
+  // k-major 7.5 / 7.5, both row-major 8.7 / 8.5, A k-major and B row-major 8.4 / 7.6.
+  constexpr int kDepth = F == 2 ? 5 - FM : 2;
   int tm, tn;
   tile_of_block(blockIdx.x, p.tiles_m * p.tiles_n, p.tiles_m, p.tiles_n, tm, tn);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
