@@ -1183,7 +1183,8 @@ static hipError_t bwd_dma(hipStream_t s, const MhaArgs& a, const MhaGrads& g) {
   // blocks, 256 queries over 500 keys 16.5 / 14.9 / 14.8, 1000 38.3 / 28.6 / 30.9; 136, 256 16.3 / 25.2 / 14.6, 1000 38.2 / 52.9 / 31.0.  Past 128 blocks
   // two parts win only where their blocks of 64 still find a unit each (138 blocks of T 700 are 253 of 64: 30.0 / 22.3 / 24.4).  One
   // tile of queries gives pairs nothing to overlap and more waves to start: 64 over 100 keys, 256 blocks 11.2 / 18.0 / 12.5, over 500 13.3
-  // / 19.0 / 13.2.
+  // / 19.0 / 13.2.  Of what pairs have, 128 queries (two whole tiles) over up to 48 keys lose on 130 to 224 blocks: 160, 32 keys 8.4 / - / 8.7;
+  // 96 queries 8.8 / - / 8.7, 160 10.8 / - / 10.5, and all of these on 256 blocks and more gain, so no line is drawn for them.
   if (CAUSAL ? two_parts(a, a.Tk, a.Tq, 768, HD == 64 ? 384 : 128) : two_parts(a, a.Tk, a.Tq, 0, 128)) run_kv(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, 2>, blocks_of<2>(a.Tk, a));
   else if (HD == 128 && a.Tq > kPairBQ)
     attn_dkv_pair_kernel<CAUSAL><<<blocks_of<1>(a.Tk, a), 64 * kPairWaves, kSmemPair, s>>>(
