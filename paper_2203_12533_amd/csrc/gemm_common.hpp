@@ -134,9 +134,11 @@ __device__ __forceinline__ void add8(float* v, const uint4& lo, const uint4& hi)
 
 // Epilogue on 8 consecutive columns n0..n0+7 of row m (bf16-activation kernels; all accesses 16-byte vectors).
 // x holds what epi_extra_load(kind, epi_extra_src(e, kind), m * ldc + n0, x) fetched, kind = epi_extra_kind(e).
+// BIAS: false where v has the bias already.
+template <bool BIAS = true>
 __device__ __forceinline__ void epilogue8(const EpiParams& e, int64_t m, int64_t n0, float* v, int kind, const EpiExtra& x) {
   const int64_t off = m * e.ldc + n0;
-  if (epi_has_bias(e.mode) && e.bias) {
+  if (BIAS && epi_has_bias(e.mode) && e.bias) {
     const float4 b0 = *reinterpret_cast<const float4*>(e.bias + n0), b1 = *reinterpret_cast<const float4*>(e.bias + n0 + 4);
     v[0] += b0.x; v[1] += b0.y; v[2] += b0.z; v[3] += b0.w; v[4] += b1.x; v[5] += b1.y; v[6] += b1.z; v[7] += b1.w;
   }

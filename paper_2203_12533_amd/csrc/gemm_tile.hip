@@ -150,7 +150,9 @@ template <int WM_, int WN_, int WK_, bool DEEP_>
 struct Shape {
   static constexpr int WM = WM_, WN = WN_, WK = WK_;
   static constexpr bool DEEP = DEEP_;
+  static constexpr bool kSkew = WK > 1 && WM * WN > 1;               // the second group runs half a tile behind the first
   static constexpr int BM = 64 * WM, BN = 64 * WN, G = WM * WN, kThreads = 64 * G * WK;
+  static constexpr int kWavesPerSimd = WK == 1 || kThreads == 512 ? 2 : 1;
   static constexpr int kStage = (BM + BN) * kTBK;                    // elements
   static constexpr int kLdP = BN + 4;                                // floats per row of a partial tile
   static constexpr size_t kRing = (size_t)WK * NS * kStage * 2, kParts = (size_t)WK * BM * kLdP * 4;
@@ -183,21 +185,23 @@ __device__ __forceinline__ void finish(const float* parts, const GemmBf16Params&
 #pragma unroll
       for (int i = 0; i < kSteps; ++i) epi_extra_load(KIND, src, (m0 + row0 + i * kRows) * p.epi.ldc + n, x[i]);
     }
-    __syncthreads();                          // every partial tile is in LDS
-    if (KIND != kExtraNone) {
+    float bias[8] = {};                       // (the same columns in every step)
+    if (epi_has_bias(p.epi.mode) && p.epi.bias) {
+      const f32x4 a = *reinterpret_cast<const f32x4*>(p.epi.bias + n), b = *reinterpret_cast<const f32x4*>(p.epi.bias + n + 4);
 #pragma unroll
-      for (int i = 0; i < kSteps; ++i) {
-        float v[8];
-        sum(row0 + i * kRows, v);
-        epilogue8(p.epi, m0 + row0 + i * kRows, n, v, KIND, x[i]);
+      for (int e = 0; e < 4; ++e) {
+        bias[e] = a[e];
+        bias[e + 4] = b[e];
       }
-    } else {
-#pragma unroll 1
-      for (int i = 0; i < kSteps; ++i) {
-        float v[8];
-        sum(row0 + i * kRows, v);
-        epilogue8(p.epi, m0 + row0 + i * kRows, n, v, KIND, x[0]);
-      }
+    }
+    __syncthreads();                          // every partial tile is in LDS
+#pragma unroll
+    for (int i = 0; i < kSteps; ++i) {
+      float v[8];
+      sum(row0 + i * kRows, v);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] += bias[e];
+      epilogue8<false>(p.epi, m0 + row0 + i * kRows, n, v, KIND, x[i]);
     }
     return;
   }
@@ -219,7 +223,7 @@ __device__ __forceinline__ void finish(const float* parts, const GemmBf16Params&
 }
 
 template <class S, bool AK, bool BK_, bool WIDE = false>
-__global__ __launch_bounds__(S::kThreads, S::WK == 1 ? 2 : 1) void gemm_tile_kernel(GemmBf16Params p) {
+__global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_tile_kernel(GemmBf16Params p) {
   constexpr int G = S::G, WN = S::WN, WK = S::WK;
   constexpr bool kShared = G > 1;             // several waves read one operand tile: barriers; else every wave is on its own
   using OpA = Operand<S::BM, G, AK, WIDE>;
@@ -378,6 +382,11 @@ __global__ __launch_bounds__(S::kThreads, S::WK == 1 ? 2 : 1) void gemm_tile_ker
   static_assert(S::DEEP ? kPer <= 16 : kPer == 8, "one direct load at most in front of each MFMA of a half");
   static_assert(NS == 2, "two stages: the waits leave at most one tile in flight, the loop goes two tiles a round");
   constexpr int kAhead = S::DEEP ? NS + 1 : NS;   // tile i loads tile i + kAhead
+  // Two groups of several waves: one of them reads its operand tiles from LDS while the other multiplies.  In step, LDS and matrix
+  // pipe take turns (us, 128 x 128 tiles, four waves alone / two groups in step / half a tile apart, profiles of one launch: the main
+  // loop of 1000 x 3072 x 768 5.3 / 5.5 / 4.2, of 2048 x 2048 x 2048 13.8 / 14.3 / 11.6).  Apart, the LDS bounds it: 96 KiB in
+  // and out of it per 128 x 128 x 64, 0.32 us at 2.4 GHz, take 0.36.  Each group passes as many barriers as the other.
+  if (S::kSkew && g == 1) meet();
   int i = 0;
   for (; i + NS - 1 + kAhead < n - 1; i += NS) {  // NS tiles, none of which loads the last one
     tile(i, std::integral_constant<int, 0>{}, std::true_type{});
@@ -389,6 +398,7 @@ __global__ __launch_bounds__(S::kThreads, S::WK == 1 ? 2 : 1) void gemm_tile_ker
     if (i + 1 < rounds) tile(i + 1, std::integral_constant<int, 1>{}, std::false_type{});
   }
 
+  if (S::kSkew && g == 0) meet();
   __syncthreads();                            // nobody reads operand tiles any more
   float* const parts = reinterpret_cast<float*>(smem);
   float* mine = parts + (g * S::BM + wm * 64 + (lane & 15)) * S::kLdP + wn * 64 + 4 * (lane >> 4);
@@ -433,6 +443,7 @@ hipError_t launch(hipStream_t s, GemmBf16Params p, bool ak, bool bk) {
 
 using Split = Shape<1, 1, 4, true>;     // 64 x 64 tiles, k over four waves of their own (one per SIMD: 300 registers)
 using Half = Shape<2, 1, 2, true>;      // 128 x 64 tiles, k over two pairs of waves (likewise)
+using Duo = Shape<2, 2, 2, true>;       // 128 x 128 tiles, k over two groups of four waves (two per SIMD)
 using One = Shape<2, 2, 1, true>;       // 128 x 128 tiles, two workgroups per compute unit
 using Two = Shape<2, 2, 1, false>;      // the same with the leaner loop
 
@@ -442,6 +453,7 @@ hipError_t gemm_tile_init() {
   hipError_t e = prepare<Split>();
   if (e == hipSuccess) e = prepare<Split, true>();
   if (e == hipSuccess) e = prepare<Half>();
+  if (e == hipSuccess) e = prepare<Duo>();
   if (e == hipSuccess) e = prepare<One>();
   if (e == hipSuccess) e = prepare<Two>();
   return e;
@@ -449,8 +461,10 @@ hipError_t gemm_tile_init() {
 
 // Which shape (us per launch before: 128 x 128 tiles staged through registers, or full ring tiles on half the chip).
 // The fewer tiles of 128 x 128 there are, the smaller the tile and the more waves share its k: 1000 x 768 x 3072 (48
-// tiles) 51 -> 13 with Split (Half 20, One 24); 1280 x 1280 x 4096 (100) 72 -> 25 with Half (Split 30, One 30); up to one
-// tile per compute unit One: 3072 x 768 x 1000 (144) 22 -> 12.5, 2048 x 2048 x 8192 (256) 104 -> 69 (Two 82).  Beyond that
+// tiles) 51 -> 13 with Split (Half 20, One 24); 1280 x 1280 x 4096 (100) 72 -> 23 with Half (Split 30, One 30, Duo 28); up to one
+// tile per compute unit Duo from k = 256 on (us, One / Duo: 1000 x 3072 x 768 with GELU 13.4 / 12.9, as a GELU' data gradient 13.8 /
+// 12.6, stored 10.7 / 10.3; 768 x 3072 x 1000 k-major 13.0 / 12.8; 1792 x 2048 x 320 10.3 / 10.1; 2000 x 2000 x 4096 39.2 / 38.3;
+// 2048 x 2048 x 8192 59 / 58, Two 82), where k is shorter One (2048 x 1152 x 128 7.1 / 7.7).  Beyond that
 // two workgroups share a compute unit and hide each other's waits; with a long k the leaner loop is ahead (2048 x 8000 x
 // 8000: 216 against 251), with a short one it is not (4568 x 2240 x 1152: 32 against 29; 4096 x 4352 x 2048: 79 / 75).
 hipError_t launch_gemm_tile(hipStream_t s, const GemmBf16Params& p, bool ak, bool bk) {
@@ -458,7 +472,8 @@ hipError_t launch_gemm_tile(hipStream_t s, const GemmBf16Params& p, bool ak, boo
   const int64_t t128 = ((p.M + 127) / 128) * ((p.N + 127) / 128);
   if (t128 <= 64) return launch<Split>(s, p, ak, bk);
   if (t128 <= 128) return launch<Half>(s, p, ak, bk);
-  if (t128 <= 256 || p.K <= 2048) return launch<One>(s, p, ak, bk);
+  if (t128 <= 256 && p.K >= 256) return launch<Duo>(s, p, ak, bk);
+  if (p.K <= 2048) return launch<One>(s, p, ak, bk);
   return launch<Two>(s, p, ak, bk);
 }
 

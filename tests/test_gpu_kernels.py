@@ -190,6 +190,14 @@ def test_gemm_bf16_any_shape_in_every_layout(ctx, M, N, K, pad, a_k, b_k):
     assert (got[:, N:] == 7.0).all()
 
 
+# 210 tiles of 128 x 128 from k = 256 on, k over two groups of four waves half a tile apart: equally many k tiles each, a partial last one,
+# one more in the first group than in the second, and enough of them for the streaming loop, in an even and in an odd number
+@pytest.mark.parametrize("a_k,b_k", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("K", [248, 256, 264, 328, 448, 832, 904, 1096])
+def test_gemm_bf16_two_groups_of_waves_in_every_layout(ctx, K, a_k, b_k):
+    test_gemm_bf16_any_shape_in_every_layout(ctx, 1672, 1800, K, 8, a_k, b_k)
+
+
 # 264 full tiles of 256 x 256, 2048 deep: a round of 256 on the ring kernel, the last columns (two tiles wide) on their own; and
 # 160 of them 2056 deep and more (any-shape kernel) or 2112 (ring).  Every operand and output that goes by columns takes part.
 @pytest.mark.parametrize("N,K", [(16896, 2048), (10240, 2056), (10240, 2112)])
