@@ -587,7 +587,7 @@ __device__ __forceinline__ void load_stats(const float* Ls, const float* Ds, int
 template <int HD, int TERMS, bool HAVE_NEXT, bool HAVE_CUR>
 __device__ __forceinline__ void dkv_front(const bf16* __restrict__ Qn, const bf16* __restrict__ Gn, int rbn,
                                           const bf16x8* kf, const bf16x8* vf, f32x16& sn, f32x16& dpn, f32x16& s,
-                                          const f32x16& dp, const DkvStats& st, float c2, Frag<TERMS>* pf, Frag<TERMS>* dsf) {
+                                          f32x16& dp, const DkvStats& st, float c2, Frag<TERMS>* pf, Frag<TERMS>* dsf) {
   constexpr int kDepth = 3, KK = HD / 16, kElems = 16 / (2 * KK);   // score elements per MFMA
   const int lane = threadIdx.x & 63;
   const int row = rbn + perm_row(lane & 31);
@@ -604,12 +604,10 @@ __device__ __forceinline__ void dkv_front(const bf16* __restrict__ Qn, const bf1
       fg[kk] = *reinterpret_cast<const bf16x8*>(ag + ((2 * kk) ^ t) * 8);
     }
   }
-  f32x16 ds;
   auto element = [&](int r) {
     if (HAVE_CUR) {
-      const float p = __builtin_amdgcn_exp2f(fmaf(s[r], c2, -st.lq[r]));
-      s[r] = p;
-      ds[r] = p * (dp[r] - st.dq[r]);
+      s[r] = __builtin_amdgcn_exp2f(fmaf(s[r], c2, -st.lq[r]));
+      dp[r] = s[r] * (dp[r] - st.dq[r]);
     }
   };
   __builtin_amdgcn_sched_barrier(0);
@@ -634,7 +632,7 @@ __device__ __forceinline__ void dkv_front(const bf16* __restrict__ Qn, const bf1
 #pragma unroll
     for (int b2 = 0; b2 < 2; ++b2) {
       pf[b2] = pack_frag<TERMS>(s, b2 * 8);
-      dsf[b2] = pack_frag<TERMS>(ds, b2 * 8);
+      dsf[b2] = pack_frag<TERMS>(dp, b2 * 8);
     }
   }
 }
@@ -705,8 +703,10 @@ __device__ __forceinline__ void dkv_again(const MhaDev& a, const bf16* dout, con
   }
 }
 
-template <int HD, bool CAUSAL, bool SPLIT, int PARTS>
-__global__ __launch_bounds__(kNT, HD == 64 ? 2 : 1) void attn_dkv_dma_kernel(MhaDev a, const bf16* __restrict__ dout,
+// ALONE: a compute unit has one workgroup at most, so a wave may have 512 registers.  In 256, which two workgroups need, head width 64
+// spills (8 to 64 registers): reloads in the loop, and each waits for the tiles in flight as well.
+template <int HD, bool CAUSAL, bool SPLIT, int PARTS, bool ALONE = HD == 128>
+__global__ __launch_bounds__(kNT, ALONE ? 1 : 2) void attn_dkv_dma_kernel(MhaDev a, const bf16* __restrict__ dout,
                                                             const float* __restrict__ lse, const float* __restrict__ delta,
                                                             bf16* __restrict__ dk_out, bf16* __restrict__ dv_out, int64_t lddkv) {
   constexpr int BQ = 64, kStages = 3, kRows = 128 / PARTS, kTerms = SPLIT ? 2 : 1;
@@ -1079,6 +1079,7 @@ template <int HD, bool HIDES> constexpr int kSmemDkv = 3 * 2 * 64 * HD * 2 + 6 *
 template <int HD, bool CAUSAL, bool SPLIT, int PARTS>
 static hipError_t prepare_dma() {
   const struct { const void* fn; int bytes; } all[] = {
+      {reinterpret_cast<const void*>(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, PARTS, true>), kSmemDkv<HD, HD == 64 && CAUSAL && !SPLIT>},
       {reinterpret_cast<const void*>(attn_fwd_dma_kernel<HD, CAUSAL, SPLIT, PARTS>), kSmemTiles<HD, PARTS>},
       {reinterpret_cast<const void*>(attn_dq_dma_kernel<HD, CAUSAL, SPLIT, PARTS>), kSmemTiles<HD, PARTS>},
       {reinterpret_cast<const void*>(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, PARTS>), kSmemDkv<HD, HD == 64 && CAUSAL && !SPLIT>}};
@@ -1185,10 +1186,16 @@ static hipError_t bwd_dma(hipStream_t s, const MhaArgs& a, const MhaGrads& g) {
   // tile of queries gives pairs nothing to overlap and more waves to start: 64 over 100 keys, 256 blocks 11.2 / 18.0 / 12.5, over 500 13.3
   // / 19.0 / 13.2.  Of what pairs have, 128 queries (two whole tiles) over up to 48 keys lose on 130 to 224 blocks: 160, 32 keys 8.4 / - / 8.7;
   // 96 queries 8.8 / - / 8.7, 160 10.8 / - / 10.5, and all of these on 256 blocks and more gain, so no line is drawn for them.
-  if (CAUSAL ? two_parts(a, a.Tk, a.Tq, 768, HD == 64 ? 384 : 128) : two_parts(a, a.Tk, a.Tq, 0, 128)) run_kv(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, 2>, blocks_of<2>(a.Tk, a));
+  // Width 64: up to a block per unit the registers of two are this one's (us, kernel traces, 256 registers / 512: 4 x 333 over 520, 8 heads,
+  // 160 blocks, 22.4 / 19.0).
+  if (CAUSAL ? two_parts(a, a.Tk, a.Tq, 768, HD == 64 ? 384 : 128) : two_parts(a, a.Tk, a.Tq, 0, 128)) {
+    if (HD == 64 && blocks_of<2>(a.Tk, a) <= 256) run_kv(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, 2, true>, blocks_of<2>(a.Tk, a));
+    else run_kv(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, 2>, blocks_of<2>(a.Tk, a));
+  }
   else if (HD == 128 && a.Tq > kPairBQ)
     attn_dkv_pair_kernel<CAUSAL><<<blocks_of<1>(a.Tk, a), 64 * kPairWaves, kSmemPair, s>>>(
         dev_of(a), (const bf16*)g.dout, g.lse, g.delta, (bf16*)g.dk, (bf16*)g.dv, g.lddkv);
+  else if (HD == 64 && blocks_of<1>(a.Tk, a) <= 256) run_kv(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, 1, true>, blocks_of<1>(a.Tk, a));
   else run_kv(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, 1>, blocks_of<1>(a.Tk, a));
   return hipGetLastError();
 }

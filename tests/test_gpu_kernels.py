@@ -721,6 +721,12 @@ def test_bf16_attention_at_head_width_128_with_a_chip_full_of_key_blocks(ctx, or
     _mha_case(ctx, orc, True, B, Tq, Tk, H, 128, causal=bool(causal), packed_kv=True)
 
 
+# dK/dV at head width 64 with a block per compute unit at most and with one more: of 128 keys, and of 64 that two waves share
+@pytest.mark.parametrize("B,Tq,Tk,H,causal", [(64, 70, 40, 4, 0), (65, 200, 40, 4, 0), (65, 130, 130, 2, 1), (8, 775, 775, 2, 1), (10, 770, 770, 2, 1)])
+def test_bf16_attention_gradients_at_head_width_64_around_a_block_per_unit(ctx, orc, B, Tq, Tk, H, causal):
+    _mha_case(ctx, orc, True, B, Tq, Tk, H, 64, causal=bool(causal), packed_kv=True)
+
+
 # more than 128 blocks of 128 keys and a single tile of queries: four waves to 128 keys in dK/dV, at both ends of that tile
 @pytest.mark.parametrize("B,Tq,Tk,H,causal", [(40, 60, 100, 4, 0), (33, 64, 130, 8, 0), (33, 64, 64, 8, 1), (140, 1, 20, 1, 0)])
 def test_bf16_attention_at_head_width_128_with_one_tile_of_queries(ctx, orc, B, Tq, Tk, H, causal):
