@@ -48,24 +48,31 @@ __device__ __forceinline__ int perm_row(int i) {   // [0-3, 8-11, 4-7, 12-15] wi
 }
 
 
+// A row of zeros, as long as the widest head.
+static __device__ __attribute__((aligned(16))) const uint32_t kZeroRow[64] = {};
+
 // Fragments of 32 rows x HD features held in registers as the B operand of a first product:
-// lane l holds row (row0 + l%32), features kk*16 + 8*(l/32) .. +7 for every kk.  Rows >= limit read as zero.
+// lane l holds row (row0 + l%32), features kk*16 + 8*(l/32) .. +7 for every kk.  Rows >= limit read as zero - from kZeroRow, so
+// that no branch stands between the loads: all of a kernel's prologue are in flight together.
 template <int HD>
 __device__ __forceinline__ void load_row_frags(const bf16* __restrict__ src, int64_t ld, int row0, int limit, bf16x8* frag) {
+  static_assert(HD * 2 <= sizeof(kZeroRow), "kZeroRow stands for a row");
   const int lane = threadIdx.x & 63;
   const int row = row0 + (lane & 31);
-  const bf16* p = src + (int64_t)row * ld + (lane >> 5) * 8;
+  typedef __attribute__((address_space(1))) const bf16x8* global_ptr;     // (a choice of two pointers is a generic one else)
+  const uint64_t mine = (uint64_t)(src + (int64_t)row * ld), zeros = (uint64_t)(uintptr_t)kZeroRow;
+  const uint64_t p = (row < limit ? mine : zeros) + (lane >> 5) * 16;
 #pragma unroll
-  for (int kk = 0; kk < HD / 16; ++kk) {
-    if (row < limit) {
-      frag[kk] = *reinterpret_cast<const bf16x8*>(p + kk * 16);
-    } else {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) frag[kk][e] = (bf16)0.f;
-    }
-  }
+  for (int kk = 0; kk < HD / 16; ++kk) frag[kk] = *(global_ptr)(p + kk * 32);
 }
 
+
+// Makes the compiler wait for fragments here, in front of a loop, and not at their first use inside it, on every round and behind
+// the loads of the next tile.
+template <int HD> __device__ __forceinline__ void arrived(bf16x8* frag) {
+#pragma unroll
+  for (int kk = 0; kk < HD / 16; ++kk) asm volatile("" : "+v"(frag[kk]));
+}
 
 // Tile-local row index that register r of this lane's D column stands for (see file header).
 __device__ __forceinline__ int reg_row(int r, int half) { return 16 * (r >> 3) + 8 * half + (r & 7); }

@@ -53,7 +53,6 @@ namespace pw {
 namespace {
 
 constexpr int kNT = 256;                 // 4 waves
-__device__ __attribute__((aligned(16))) const uint32_t kZeroRow[4] = {0, 0, 0, 0};
 typedef __attribute__((address_space(3))) void* lds_ptr;
 typedef short short4v __attribute__((ext_vector_type(4)));
 
@@ -120,6 +119,23 @@ __device__ __forceinline__ void issue_tile(const bf16* __restrict__ src, int64_t
       dma16(g, lds_off + instr * 1024);
     }
   }
+}
+
+// A wave's own 32 rows of an operand that stays in registers (fragments as load_row_frags has them), by way of LDS: read from global
+// memory row by row, 16 bytes per lane, an instruction touches 32 lines for 32 bytes of each (about 64 clocks; Q, dO and O of the dQ
+// kernel at width 128 took 4.8 us in front of its loop), direct loads touch whole rows.  tile: 32 * HD elements of the wave's.
+template <int HD>
+__device__ __forceinline__ void stage_rows(const bf16* src, int64_t ld, int row0, int limit, uint32_t lds_off, int lane) {
+  TileOffsets<32, HD, 1> to;
+  to.init(ld, 0, lane);
+  issue_tile(src, ld, row0, limit - 1, to, lds_off, 0, lane);
+}
+template <int HD>
+__device__ __forceinline__ void staged_frags(const bf16* __restrict__ tile, bf16x8* frag) {
+  const int lane = threadIdx.x & 63, row = lane & 31, t = (lane >> 5) ^ swz<HD>(row);
+#pragma unroll
+  for (int kk = 0; kk < HD / 16; ++kk) frag[kk] = *reinterpret_cast<const bf16x8*>(tile + row * HD + ((2 * kk) ^ t) * 8);
+  arrived<HD>(frag);
 }
 
 // 32x32 block of a first product: A rows (permuted) from a swizzled natural LDS tile, B from register fragments.
@@ -317,15 +333,6 @@ __global__ __launch_bounds__(kNT, 2) void attn_fwd_dma_kernel(MhaDev a, bf16* __
   const float c2 = kLog2e / sqrtf((float)HD);
   const uint32_t smem_off = (uint32_t)(uintptr_t)(lds_ptr)smem;
 
-  bf16x8 qf[HD / 16];
-  load_row_frags<HD>(qbase, a.ldq, q0, Tq, qf);
-  f32x16 acc[HD / 32];
-#pragma unroll
-  for (int cb = 0; cb < HD / 32; ++cb)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[cb][r] = 0.f;
-  float m = -INFINITY, l = 0.f;
-
   const int last_q = min(Tq, (qblk + 1) * kRows) - 1;
   const int n_tiles = CAUSAL ? last_q / BKV + 1 : (Tk + BKV - 1) / BKV;
   TileOffsets<BKV, HD> to;
@@ -335,7 +342,17 @@ __global__ __launch_bounds__(kNT, 2) void attn_fwd_dma_kernel(MhaDev a, bf16* __
     issue_tile(kbase, ld, t * BKV, Tk - 1, to, st, wave, lane);
     issue_tile(vbase, ld, t * BKV, Tk - 1, to, st + kTile * 2, wave, lane);
   };
+  // The queries pass through the stage of tile 1, which is asked for behind the first barrier.
+  static_assert(4 * 32 <= 2 * BKV, "a stage holds 32 rows for each wave");
+  constexpr int kMine = 2 * kTile, kTileLoads = 2 * TileOffsets<BKV, HD>::kPerWave;
+  stage_rows<HD>(qbase, a.ldq, q0, Tq, smem_off + (kMine + wave * 32 * HD) * 2, lane);
   issue(0);
+  f32x16 acc[HD / 32];
+  clear<HD>(acc);
+  float m = -INFINITY, l = 0.f;
+  bf16x8 qf[HD / 16];
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kTileLoads) : "memory");
+  staged_frags<HD>(smem + kMine + wave * 32 * HD, qf);
   for (int t = 0; t < n_tiles; ++t) {
     const int j0 = t * BKV + part * kSub;
     wait_and_sync();
@@ -466,40 +483,6 @@ __global__ __launch_bounds__(kNT, 2) void attn_dq_dma_kernel(MhaDev a, const bf1
   const float c2 = kLog2e * scale;
   const uint32_t smem_off = (uint32_t)(uintptr_t)(lds_ptr)smem;
 
-  bf16x8 qf[HD / 16], gf[HD / 16];
-  load_row_frags<HD>(qbase, a.ldq, q0, Tq, qf);
-  load_row_frags<HD>(dout + (int64_t)b * Tq * d + h * HD, d, q0, Tq, gf);
-  const float lse2 = query < Tq ? lse[(int64_t)bh * Tq + query] * kLog2e : INFINITY;   // +inf: P = 0 for rows past the end
-  float dl;
-  {
-    bf16x8 of[HD / 16];
-    load_row_frags<HD>(o + (int64_t)b * Tq * d + h * HD, d, q0, Tq, of);
-    // The diagonal of O . dO^T, from the same instructions as dP: where a query sees one key only, O is V and dP - delta
-    // comes out as the exact zero that it is.
-    f32x16 od;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) od[r] = 0.f;
-#pragma unroll
-    for (int kk = 0; kk < HD / 16; ++kk) od = __builtin_amdgcn_mfma_f32_32x32x16_bf16(of[kk], gf[kk], od, 0, 0, 0);
-    if (o_lo) {
-      load_row_frags<HD>(o_lo + (int64_t)b * Tq * d + h * HD, d, q0, Tq, of);
-#pragma unroll
-      for (int kk = 0; kk < HD / 16; ++kk) od = __builtin_amdgcn_mfma_f32_32x32x16_bf16(of[kk], gf[kk], od, 0, 0, 0);
-    }
-    // register r of half h holds row 8 (r/4) + 4 h + r%4: this column's own row is i = lane % 32
-    const int i = lane & 31, reg = 4 * (i >> 3) + (i & 3);
-    dl = od[0];
-#pragma unroll
-    for (int r = 1; r < 16; ++r) dl = reg == r ? od[r] : dl;
-    dl = __shfl(dl, i + 32 * ((i >> 2) & 1), 64);
-    if (half == 0 && part == 0 && query < Tq) delta[(int64_t)bh * Tq + query] = dl;
-  }
-  f32x16 acc[HD / 32];
-#pragma unroll
-  for (int cb = 0; cb < HD / 32; ++cb)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[cb][r] = 0.f;
-
   const int last_q = min(Tq, (qblk + 1) * kRows) - 1;
   const int n_tiles = CAUSAL ? last_q / BKV + 1 : (Tk + BKV - 1) / BKV;
   const int last_key = CAUSAL ? query : Tk - 1;
@@ -510,7 +493,48 @@ __global__ __launch_bounds__(kNT, 2) void attn_dq_dma_kernel(MhaDev a, const bf1
     issue_tile(kbase, ld, t * BKV, Tk - 1, to, st, wave, lane);
     issue_tile(vbase, ld, t * BKV, Tk - 1, to, st + kTile * 2, wave, lane);
   };
-  issue(0);
+  const float lse_in = lse[(int64_t)bh * Tq + min(query, Tq - 1)];
+  // O and dO come through both stages, Q through that of tile 1 behind O; tile 0 follows when no wave reads its dO any more.
+  static_assert(4 * 32 <= 2 * BKV, "a stage holds 32 rows for each wave");
+  constexpr int kTileLoads = 2 * TileOffsets<BKV, HD>::kPerWave;
+  const int mine = wave * 32 * HD, mine1 = 2 * kTile + mine;
+  stage_rows<HD>(o + (int64_t)b * Tq * d + h * HD, d, q0, Tq, smem_off + mine1 * 2, lane);
+  stage_rows<HD>(dout + (int64_t)b * Tq * d + h * HD, d, q0, Tq, smem_off + mine * 2, lane);
+  bf16x8 qf[HD / 16], gf[HD / 16];
+  float dl;
+  {
+    f32x16 od;
+    bf16x8 of[HD / 16], lf[HD / 16];
+    if (o_lo) load_row_frags<HD>(o_lo + (int64_t)b * Tq * d + h * HD, d, q0, Tq, lf);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    staged_frags<HD>(smem + mine1, of);
+    staged_frags<HD>(smem + mine, gf);
+    stage_rows<HD>(qbase, a.ldq, q0, Tq, smem_off + mine1 * 2, lane);
+    __builtin_amdgcn_s_barrier();
+    issue(0);
+    // The diagonal of O . dO^T, from the same instructions as dP: where a query sees one key only, O is V and dP - delta
+    // comes out as the exact zero that it is.
+#pragma unroll
+    for (int r = 0; r < 16; ++r) od[r] = 0.f;
+#pragma unroll
+    for (int kk = 0; kk < HD / 16; ++kk) od = __builtin_amdgcn_mfma_f32_32x32x16_bf16(of[kk], gf[kk], od, 0, 0, 0);
+    if (o_lo) {
+#pragma unroll
+      for (int kk = 0; kk < HD / 16; ++kk) od = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lf[kk], gf[kk], od, 0, 0, 0);
+    }
+    // register r of half h holds row 8 (r/4) + 4 h + r%4: this column's own row is i = lane % 32
+    const int i = lane & 31, reg = 4 * (i >> 3) + (i & 3);
+    dl = od[0];
+#pragma unroll
+    for (int r = 1; r < 16; ++r) dl = reg == r ? od[r] : dl;
+    dl = __shfl(dl, i + 32 * ((i >> 2) & 1), 64);
+    if (half == 0 && part == 0 && query < Tq) delta[(int64_t)bh * Tq + query] = dl;
+  }
+  f32x16 acc[HD / 32];
+  clear<HD>(acc);
+  const float lse2 = query < Tq ? lse_in * kLog2e : INFINITY;   // +inf: P = 0 for rows past the end
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kTileLoads) : "memory");
+  staged_frags<HD>(smem + mine1, qf);
   for (int t = 0; t < n_tiles; ++t) {
     const int j0 = t * BKV + part * kSub;
     wait_and_sync();
