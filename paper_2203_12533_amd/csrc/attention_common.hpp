@@ -33,6 +33,25 @@ __device__ __forceinline__ void xcd_block_map(int pid, int nblk, int n_inner, in
 // an XCD holds at once (32 compute units x workgroups per unit).
 __device__ __forceinline__ int causal_group(int n_inner, int resident) { return (resident + n_inner - 1) / n_inner; }
 
+// The map of the bf16 kernels under a causal mask: all blocks of rank 0 first, then all of rank 1, ..., so that the launch ends with its
+// shortest blocks however the number of problems divides; a problem stays on one XCD but for the up to seven that a rank's end carries
+// over.  Groups, which start their longest blocks one group after the other, lose where an XCD's share is no whole number of
+// them (us, forward / backward, groups -> this: 8 x 1400, 16 heads of 64, 57 / 168.5 -> 49 / 144; 4 x 1000, 12 of 64, 21.4 / 52.5 -> 18.4 /
+// 48; 8 x 2048, 16 of 64, 97.5 / 298.5 -> 89.3 / 276; 8 x 700, 8 of 128, 24.0 / 70 -> 21.0 / 57; 3 x 1024, 16 of 128, 30.4 / 82.5 -> 27.6 / 74.7).
+// `stream`: bytes that the blocks of a problem read from its other side.  At width 128 they have to fit an XCD's L2 of 4 MiB for all its
+// problems together, which are in flight at the same time (8 x 1024, 16 heads, 8 MiB: 51 / 163 -> 54.6 / 168; 4 x 1024, 4 MiB: 30.8 / 85.8 -> 30.6 /
+// 87.6).  Fewer problems than XCDs leave most of them without one of their own (1 x 1500, 3 heads of 64, forward 15.3 -> 15.5).
+template <int HD>
+__device__ __forceinline__ void causal_block_map(int pid, int nblk, int n_inner, int64_t stream, int resident, int& problem, int& inner) {
+  const int problems = nblk / n_inner;
+  if (problems < 8 || (HD == 128 && problems * stream >= 8 * (4 << 20))) {
+    xcd_block_map(pid, nblk, n_inner, causal_group(n_inner, resident), problem, inner);
+  } else {
+    inner = pid / problems;
+    problem = (pid - inner * problems + inner * problems % 8) % problems;
+  }
+}
+
 // max of three in one instruction.  (Scores are never signalling NaNs, so the quieting pass the compiler puts
 // in front of every fmaxf on values it cannot trace is not needed.)
 __device__ __forceinline__ float max3(float a, float b, float c) {

@@ -320,7 +320,8 @@ __global__ __launch_bounds__(kNT, 2) void attn_fwd_dma_kernel(MhaDev a, bf16* __
   const int64_t ld = a.ldkv;
   const int nq = (Tq + kRows - 1) / kRows;
   int bh, qi;
-  xcd_block_map(blockIdx.x, gridDim.x, nq, CAUSAL ? causal_group(nq, 64) : 1, bh, qi);
+  if (CAUSAL) causal_block_map<HD>(blockIdx.x, gridDim.x, nq, (int64_t)Tk * (2 * HD * 2), 64, bh, qi);
+  else xcd_block_map(blockIdx.x, gridDim.x, nq, 1, bh, qi);
   const int b = bh / H, h = bh - b * H;
   const int qblk = CAUSAL ? nq - 1 - qi : qi;           // causal: longest blocks of a problem first
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, half = lane >> 5;
@@ -469,7 +470,8 @@ __global__ __launch_bounds__(kNT, 2) void attn_dq_dma_kernel(MhaDev a, const bf1
   const int64_t ld = a.ldkv;
   const int nq = (Tq + kRows - 1) / kRows;
   int bh, qi;
-  xcd_block_map(blockIdx.x, gridDim.x, nq, CAUSAL ? causal_group(nq, 64) : 1, bh, qi);
+  if (CAUSAL) causal_block_map<HD>(blockIdx.x, gridDim.x, nq, (int64_t)Tk * (2 * HD * 2), 64, bh, qi);
+  else xcd_block_map(blockIdx.x, gridDim.x, nq, 1, bh, qi);
   const int b = bh / H, h = bh - b * H;
   const int qblk = CAUSAL ? nq - 1 - qi : qi;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, half = lane >> 5;
@@ -743,7 +745,8 @@ __global__ __launch_bounds__(kNT, ALONE ? 1 : 2) void attn_dkv_dma_kernel(MhaDev
   const int64_t ld = a.ldq;
   int bh, kblk;                                         // causal: first key blocks see the most queries, they come first
   const int nk = (Tk + kRows - 1) / kRows;
-  xcd_block_map(blockIdx.x, gridDim.x, nk, CAUSAL ? causal_group(nk, 32) : 1, bh, kblk);
+  if (CAUSAL) causal_block_map<HD>(blockIdx.x, gridDim.x, nk, (int64_t)T * (2 * HD * 2), 32, bh, kblk);
+  else xcd_block_map(blockIdx.x, gridDim.x, nk, 1, bh, kblk);
   const int b = bh / H, h = bh - b * H;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, half = lane >> 5;
   const int part = PARTS == 1 ? 0 : wave >> 1;          // which 32 rows of every tile are this wave's (PARTS = 1: all 64)
@@ -966,7 +969,8 @@ __global__ __launch_bounds__(64 * kPairWaves, 2) void attn_dkv_pair_kernel(MhaDe
   const int64_t ld = a.ldq;
   int bh, kblk;
   const int nk = (Tk + kRows - 1) / kRows;
-  xcd_block_map(blockIdx.x, gridDim.x, nk, CAUSAL ? causal_group(nk, 32) : 1, bh, kblk);
+  if (CAUSAL) causal_block_map<HD>(blockIdx.x, gridDim.x, nk, (int64_t)T * (2 * HD * 2), 32, bh, kblk);
+  else xcd_block_map(blockIdx.x, gridDim.x, nk, 1, bh, kblk);
   const int b = bh / H, h = bh - b * H;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, half = lane >> 5;
   const int part = wave >> 2, kw = (wave & 3) * 32;

@@ -721,6 +721,15 @@ def test_bf16_attention_at_head_width_128_with_a_chip_full_of_key_blocks(ctx, or
     _mha_case(ctx, orc, True, B, Tq, Tk, H, 128, causal=bool(causal), packed_kv=True)
 
 
+# the order of a causal launch's blocks: by rank over all problems, with eight of them and one to either side, and numbers that eight does
+# not divide; problem groups where fewer than eight are, or more than an L2 holds (at width 128 from 65536 rows of keys on, which
+# 1008 problems of 65 stay below)
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("B,T,H", [(1, 260, 7), (2, 200, 4), (3, 200, 3), (11, 140, 3), (1, 513, 13), (63, 65, 16), (64, 65, 16)])
+def test_bf16_causal_attention_block_orders(ctx, orc, B, T, H, hd):
+    _mha_case(ctx, orc, True, B, T, T, H, hd, causal=True, packed_kv=True)
+
+
 # dK/dV at head width 64 with a block per compute unit at most and with one more: of 128 keys, and of 64 that two waves share
 @pytest.mark.parametrize("B,Tq,Tk,H,causal", [(64, 70, 40, 4, 0), (65, 200, 40, 4, 0), (65, 130, 130, 2, 1), (8, 775, 775, 2, 1), (10, 770, 770, 2, 1)])
 def test_bf16_attention_gradients_at_head_width_64_around_a_block_per_unit(ctx, orc, B, Tq, Tk, H, causal):
