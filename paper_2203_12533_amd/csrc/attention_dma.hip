@@ -43,6 +43,7 @@
 // of decoder queries over encoder keys; CAUSAL is a template parameter (it decides which tiles are visited).
 #include <algorithm>
 #include <type_traits>
+#include <vector>
 
 #include "attention_common.hpp"
 #include "common.hpp"
@@ -731,7 +732,7 @@ __device__ __forceinline__ void dkv_again(const MhaDev& a, const bf16* dout, con
 
 // ALONE: a compute unit has one workgroup at most, so a wave may have 512 registers.  In 256, which two workgroups need, head width 64
 // spills (8 to 64 registers): reloads in the loop, and each waits for the tiles in flight as well.
-template <int HD, bool CAUSAL, bool SPLIT, int PARTS, bool ALONE = HD == 128>
+template <int HD, bool CAUSAL, bool SPLIT, int PARTS, bool ALONE>
 __global__ __launch_bounds__(kNT, ALONE ? 1 : 2) void attn_dkv_dma_kernel(MhaDev a, const bf16* __restrict__ dout,
                                                             const float* __restrict__ lse, const float* __restrict__ delta,
                                                             bf16* __restrict__ dk_out, bf16* __restrict__ dv_out, int64_t lddkv) {
@@ -937,7 +938,7 @@ __global__ __launch_bounds__(kNT, ALONE ? 1 : 2) void attn_dkv_dma_kernel(MhaDev
 }
 
 // ===================================================================================================
-// dK, dV at head_dim 128 for more than 128 blocks of 128 keys and more than one tile of queries: 8 waves, two to a SIMD, each pair
+// dK, dV for more than 128 blocks of 128 keys at head_dim 128 (more than one tile of queries) and, unmasked, at 64: 8 waves, two to a SIMD, each pair
 // with the same 32 keys; of every tile of 64 queries one wave takes the first 32, the other the rest, and their sums meet in LDS
 // at the end (in a fixed order).
 // What bounds the kernel above is that a SIMD has one wave: products, exponentials and LDS round trips of a block follow one
@@ -954,13 +955,13 @@ __global__ __launch_bounds__(kNT, ALONE ? 1 : 2) void attn_dkv_dma_kernel(MhaDev
 // Forward and backward: causal 4 x 1000, 8 heads 89.1 / 84.3; 8 x 300, 12 heads 59.8 / 58.1; 4 x 333 queries over 520 keys, 16 heads
 // 80.7 / 76.9.  The dispatch (bwd_dma) has both limits' figures.
 // ===================================================================================================
-constexpr int kPairWaves = 8, kPairBQ = 64, kPairTile = kPairBQ * 128;
-constexpr int kSmemPair = (2 * 128 * 128 + 2 * 2 * kPairTile) * 2 + 2 * 2 * kPairBQ * 4;
-template <bool CAUSAL>
+constexpr int kPairWaves = 8, kPairBQ = 64;
+template <int HD> constexpr int kSmemPair = (2 * 128 * HD + 2 * 2 * kPairBQ * HD) * 2 + 2 * 2 * kPairBQ * 4;
+template <int HD, bool CAUSAL, bool SPLIT>
 __global__ __launch_bounds__(64 * kPairWaves, 2) void attn_dkv_pair_kernel(MhaDev a, const bf16* __restrict__ dout,
                                                                            const float* __restrict__ lse, const float* __restrict__ delta,
                                                                            bf16* __restrict__ dk_out, bf16* __restrict__ dv_out, int64_t lddkv) {
-  constexpr int HD = 128, KK = HD / 16, kRows = 128, kDepth = 2;
+  constexpr int KK = HD / 16, kRows = 128, kDepth = 2, kPairTile = kPairBQ * HD, kTerms = SPLIT ? 2 : 1;
   extern __shared__ __attribute__((aligned(1024))) bf16 smem[];          // K | V | [stage][Q | dO] | statistics
   bf16* const ring = smem + 2 * kRows * HD;
   float (*Ls)[kPairBQ] = reinterpret_cast<float (*)[kPairBQ]>(ring + 2 * 2 * kPairTile);
@@ -1008,7 +1009,7 @@ __global__ __launch_bounds__(64 * kPairWaves, 2) void attn_dkv_pair_kernel(MhaDe
   const int qrow = part * 32 + perm_row(lane & 31), krow = kw + (lane & 31);
   const uint32_t q_at = ring_off + qrow * (HD * 2) + ((half ^ swz<HD>(qrow)) << 4);
   uint32_t k_at = smem_off + krow * (HD * 2) + ((half ^ swz<HD>(krow)) << 4);
-  // ... and of the second ones, read transposed: features 32 cb .. of queries 16 b2 .. at that address ^ (cb << 6), + 4096 b2.
+  // ... and of the second ones, read transposed: features 32 cb .. of queries 16 b2 .. at that address ^ (cb << 6), + 32 HD b2.
   const int trow = part * 32 + 8 * (lane >> 5) + ((lane & 15) >> 2);
   const uint32_t back_at = ring_off + trow * (HD * 2) + (((2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) ^ swz<HD>(trow)) << 4) + 8 * (lane & 1);
   issue(first_tile);
@@ -1060,36 +1061,42 @@ __global__ __launch_bounds__(64 * kPairWaves, 2) void attn_dkv_pair_kernel(MhaDe
     }
     uint32_t ba = back_at + (uint32_t)(t & 1) * (2 * kPairTile * 2);
     asm volatile("" : "+v"(ba));
-    auto read = [&](int j) {                   // j: 8 b2 + 4 (0: dO -> dV, 1: Q -> dK) + cb
+    auto read = [&](int j) {                   // j: (2 b2 + (0: dO -> dV, 1: Q -> dK)) * HD / 32 + cb
+      const int cb = j % (HD / 32), mat = j / (HD / 32) & 1, b2 = j / (HD / 16);
       typedef __attribute__((address_space(3))) short4v* piece;
       union { bf16x8 v; short4v h[2]; } u;
 #pragma unroll
       for (int e = 0; e < 2; ++e)
         u.h[e] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-            (piece)(uintptr_t)((ba ^ ((j & 3) << 6) ^ (e << 4)) + 1024 * e + 4096 * (j >> 3) + ((j & 4) ? 0 : kPairTile * 2)));
+            (piece)(uintptr_t)((ba ^ (cb << 6) ^ (e << 4)) + 8 * HD * e + 32 * HD * b2 + (mat ? 0 : kPairTile * 2)));
       return u.v;
     };
-    constexpr int kAhead = 2;
+    constexpr int kAhead = 2, kBlocks = HD / 32, kSteps = 4 * kBlocks;
     bf16x8 fr[kAhead + 1];
 #pragma unroll
     for (int j = 0; j < kAhead; ++j) fr[j] = read(j);
-    Frag<1> w[2][2];
+    Frag<kTerms> w[2][2];
 #pragma unroll
     for (int b2 = 0; b2 < 2; ++b2) {
-      w[b2][0] = pack_frag<1>(s, b2 * 8);
-      w[b2][1] = pack_frag<1>(dp, b2 * 8);
+      w[b2][0] = pack_frag<kTerms>(s, b2 * 8);
+      w[b2][1] = pack_frag<kTerms>(dp, b2 * 8);
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      if (j + kAhead < 16) fr[(j + kAhead) % (kAhead + 1)] = read(j + kAhead);
-      mfma_frag<1>(fr[j % (kAhead + 1)], w[j >> 3][(j >> 2) & 1], (j & 4) ? dk[j & 3] : dv[j & 3]);
+    for (int j = 0; j < kSteps; ++j) {
+      if (j + kAhead < kSteps) fr[(j + kAhead) % (kAhead + 1)] = read(j + kAhead);
+      const int cb = j % kBlocks, mat = j / kBlocks & 1;
+      mfma_frag<kTerms>(fr[j % (kAhead + 1)], w[j / (2 * kBlocks)][mat], mat ? dk[cb] : dv[cb]);
       __builtin_amdgcn_sched_barrier(0);
     }
   }
   float* const box = reinterpret_cast<float*>(smem) + (wave & 3) * (HD / 2 * 64) + lane;
   (void)sum_parts<HD>(box, part, dk);          // (its barriers: every wave is done with the tiles)
   if (!sum_parts<HD>(box, part, dv)) return;
+  if (SPLIT && __builtin_amdgcn_ballot_w64(key < Tk && (not_finite<HD>(dk) || not_finite<HD>(dv))) != 0) {
+    dkv_again<HD, CAUSAL>(a, dout, lse, delta, dk_out, dv_out, lddkv, bh, k0);
+    return;
+  }
   if (key < Tk) {
     const int64_t row = ((int64_t)b * Tk + key) * lddkv + h * HD;
     store_row<HD>(dk_out + row, dk, scale);
@@ -1100,17 +1107,19 @@ __global__ __launch_bounds__(64 * kPairWaves, 2) void attn_dkv_pair_kernel(MhaDe
 }  // namespace
 
 // Dynamic LDS: two stages of two 64-row tiles (64 KiB at head_dim 128); dK/dV three stages and their statistics (97.5 KiB;
-// attn_dkv_pair_kernel has kSmemPair, 129 KiB).
+// attn_dkv_pair_kernel has kSmemPair, 129 KiB, at width 64 65).
 template <int HD, int PARTS> constexpr int kSmemTiles = 2 * 2 * kSubRows<HD, PARTS> * PARTS * HD * 2;
 template <int HD, bool HIDES> constexpr int kSmemDkv = 3 * 2 * 64 * HD * 2 + 6 * 64 * 4 + (HIDES ? (64 + 32) * HD * 2 : 0);   // (tile_q)
 
 template <int HD, bool CAUSAL, bool SPLIT, int PARTS>
 static hipError_t prepare_dma() {
-  const struct { const void* fn; int bytes; } all[] = {
-      {reinterpret_cast<const void*>(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, PARTS, true>), kSmemDkv<HD, HD == 64 && CAUSAL && !SPLIT>},
-      {reinterpret_cast<const void*>(attn_fwd_dma_kernel<HD, CAUSAL, SPLIT, PARTS>), kSmemTiles<HD, PARTS>},
-      {reinterpret_cast<const void*>(attn_dq_dma_kernel<HD, CAUSAL, SPLIT, PARTS>), kSmemTiles<HD, PARTS>},
-      {reinterpret_cast<const void*>(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, PARTS>), kSmemDkv<HD, HD == 64 && CAUSAL && !SPLIT>}};
+  struct Kernel { const void* fn; int bytes; };
+  std::vector<Kernel> all = {{reinterpret_cast<const void*>(attn_fwd_dma_kernel<HD, CAUSAL, SPLIT, PARTS>), kSmemTiles<HD, PARTS>},
+                             {reinterpret_cast<const void*>(attn_dq_dma_kernel<HD, CAUSAL, SPLIT, PARTS>), kSmemTiles<HD, PARTS>}};
+  constexpr int kDkv = kSmemDkv<HD, HD == 64 && CAUSAL && !SPLIT>;
+  if constexpr (HD == 128 || CAUSAL || PARTS == 2) all.push_back({reinterpret_cast<const void*>(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, PARTS, true>), kDkv});
+  if constexpr (HD == 64 && CAUSAL) all.push_back({reinterpret_cast<const void*>(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, PARTS, false>), kDkv});
+  if constexpr (HD == 128 || !CAUSAL) all.push_back({reinterpret_cast<const void*>(attn_dkv_pair_kernel<HD, CAUSAL, SPLIT>), kSmemPair<HD>});
   for (const auto& k : all) {
     const hipError_t e = hipFuncSetAttribute(k.fn, hipFuncAttributeMaxDynamicSharedMemorySize, k.bytes);
     if (e != hipSuccess) return e;
@@ -1132,8 +1141,6 @@ hipError_t attention_dma_init() {
   if (e == hipSuccess) e = prepare_parts<64, true, false>();
   if (e == hipSuccess) e = prepare_parts<64, true, true>();
   if (e == hipSuccess) e = prepare_parts<64, false, true>();
-  for (const void* fn : {reinterpret_cast<const void*>(attn_dkv_pair_kernel<true>), reinterpret_cast<const void*>(attn_dkv_pair_kernel<false>)})
-    if (e == hipSuccess) e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kSmemPair);
   if (e == hipSuccess) done = true;
   return e;
 }
@@ -1214,17 +1221,24 @@ static hipError_t bwd_dma(hipStream_t s, const MhaArgs& a, const MhaGrads& g) {
   // tile of queries gives pairs nothing to overlap and more waves to start: 64 over 100 keys, 256 blocks 11.2 / 18.0 / 12.5, over 500 13.3
   // / 19.0 / 13.2.  Of what pairs have, 128 queries (two whole tiles) over up to 48 keys lose on 130 to 224 blocks: 160, 32 keys 8.4 / - / 8.7;
   // 96 queries 8.8 / - / 8.7, 160 10.8 / - / 10.5, and all of these on 256 blocks and more gain, so no line is drawn for them.
-  // Width 64: up to a block per unit the registers of two are this one's (us, kernel traces, 256 registers / 512: 4 x 333 over 520, 8 heads,
-  // 160 blocks, 22.4 / 19.0).
+  // Width 64, unmasked (one wave with the registers of two / pairs): 4 x 333 over 520, 8 heads, 160 blocks 16.1 / 12.2; 8 x 512, 16 heads, 512 blocks
+  // 40.3 / 33.4; 2 x 2014 over 1092, 9 heads, 162 blocks 65.7 / 49.6; one tile, 2 x 64 over 1000, 8 heads, 128 blocks 5.4 / 5.5.  Two parts up to 128
+  // blocks: 1 x 700, 6 heads 16.7 / 19.8; 4 x 600 over 60, 12 heads 15.5 / 17.7.  Packed causal pairs gain and lose: 1 x 2048, 16 heads 37.5 / 35.1, 8 x
+  // 1024 52.9 / 56.3, 4 x 1000, 12 heads 26.8 / 27.1.
+  // There, up to a block per unit, a block has the registers of two (4 x 333 over 520, before pairs: 22.4 with spills / 19.0).
+  constexpr bool kShares = HD == 64 && CAUSAL;               // kernels for two workgroups on a unit
+  auto two = [&](int blocks) { return kShares && blocks > 256; };
   if (CAUSAL ? two_parts(a, a.Tk, a.Tq, 768, HD == 64 ? 384 : 128) : two_parts(a, a.Tk, a.Tq, 0, 128)) {
-    if (HD == 64 && blocks_of<2>(a.Tk, a) <= 256) run_kv(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, 2, true>, blocks_of<2>(a.Tk, a));
-    else run_kv(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, 2>, blocks_of<2>(a.Tk, a));
-  }
-  else if (HD == 128 && a.Tq > kPairBQ)
-    attn_dkv_pair_kernel<CAUSAL><<<blocks_of<1>(a.Tk, a), 64 * kPairWaves, kSmemPair, s>>>(
+    const int blocks = blocks_of<2>(a.Tk, a);
+    run_kv(two(blocks) ? attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, 2, !kShares> : attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, 2, true>, blocks);
+  } else if (kShares || (HD == 128 && a.Tq <= kPairBQ)) {
+    const int blocks = blocks_of<1>(a.Tk, a);
+    if constexpr (HD == 128 || CAUSAL)
+      run_kv(two(blocks) ? attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, 1, !kShares> : attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, 1, true>, blocks);
+  } else if constexpr (!kShares) {
+    attn_dkv_pair_kernel<HD, CAUSAL, SPLIT><<<blocks_of<1>(a.Tk, a), 64 * kPairWaves, kSmemPair<HD>, s>>>(
         dev_of(a), (const bf16*)g.dout, g.lse, g.delta, (bf16*)g.dk, (bf16*)g.dv, g.lddkv);
-  else if (HD == 64 && blocks_of<1>(a.Tk, a) <= 256) run_kv(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, 1, true>, blocks_of<1>(a.Tk, a));
-  else run_kv(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, 1>, blocks_of<1>(a.Tk, a));
+  }
   return hipGetLastError();
 }
 bool mha_dma_outputs_aligned(const void* dq, int64_t lddq, const void* dk, const void* dv, int64_t lddkv) {
