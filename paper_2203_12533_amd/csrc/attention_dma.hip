@@ -42,7 +42,6 @@
 // serves the packed causal self-attention of a decoder, the unmasked self-attention of an encoder and attention
 // of decoder queries over encoder keys; CAUSAL is a template parameter (it decides which tiles are visited).
 #include <algorithm>
-#include <cstdlib>
 #include <type_traits>
 #include <vector>
 
@@ -282,8 +281,8 @@ __device__ __forceinline__ void wait_and_sync() {
   asm volatile("" ::: "memory");
 }
 
-// Where several waves hold partial sums of the same rows (PARTS > 1): the others' go through LDS to the first.
-// box: this lane's word of a [HD / 2][64] array that the waves with those rows share.
+// Where two waves hold partial sums of the same rows (PARTS = 2): the second one's go through LDS to the first.
+// box: this lane's word of a [HD / 2][64] array that both waves of a pair share.
 template <int HD>
 __device__ __forceinline__ void put_acc(float* box, const f32x16* acc) {
 #pragma unroll
@@ -291,36 +290,30 @@ __device__ __forceinline__ void put_acc(float* box, const f32x16* acc) {
 #pragma unroll
     for (int r = 0; r < 16; ++r) box[(cb * 16 + r) * 64] = acc[cb][r];
 }
-// acc of part 0 += those of the other parts, in their order; true in the waves that hold the result.  Called by the whole workgroup.
-// box: of part 1; those of later parts two boxes further on each.
-template <int HD, int PARTS = 2>
+// acc of part 0 += acc of part 1; true in the waves that hold the result.  Called by the whole workgroup.
+template <int HD>
 __device__ __forceinline__ bool sum_parts(float* box, int part, f32x16* acc) {
-  constexpr int kNext = 2 * (HD / 2) * 64;
   __syncthreads();
-  if (part > 0) put_acc<HD>(box + (part - 1) * kNext, acc);
+  if (part == 1) put_acc<HD>(box, acc);
   __syncthreads();
-  if (part > 0) return false;
+  if (part == 1) return false;
 #pragma unroll
-  for (int p = 0; p < PARTS - 1; ++p)
+  for (int cb = 0; cb < HD / 32; ++cb)
 #pragma unroll
-    for (int cb = 0; cb < HD / 32; ++cb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[cb][r] += box[p * kNext + (cb * 16 + r) * 64];
+    for (int r = 0; r < 16; ++r) acc[cb][r] += box[(cb * 16 + r) * 64];
   return true;
 }
 
 // Tile rows per wave and iteration in the forward and dQ kernels.
-template <int HD, int PARTS> constexpr int kSubRows = HD == 128 && PARTS > 1 ? 32 : 64;
-// Their waves: two for each part of 64 rows, four for 128.
-template <int PARTS> constexpr int kWavesOf = PARTS == 4 ? 8 : 4;
+template <int HD, int PARTS> constexpr int kSubRows = HD == 128 && PARTS == 2 ? 32 : 64;
 
 // ===================================================================================================
 // forward: block = 128 queries of one (batch, head); wave = 32 queries; key/value tiles of 64
 // ===================================================================================================
 template <int HD, bool CAUSAL, bool SPLIT, int PARTS>
-__global__ __launch_bounds__(64 * kWavesOf<PARTS>, 2) void attn_fwd_dma_kernel(MhaDev a, bf16* __restrict__ o, bf16* __restrict__ o_lo,
+__global__ __launch_bounds__(kNT, 2) void attn_fwd_dma_kernel(MhaDev a, bf16* __restrict__ o, bf16* __restrict__ o_lo,
                                                               float* __restrict__ lse) {
-  constexpr int kSub = kSubRows<HD, PARTS>, BKV = kSub * PARTS, kRows = PARTS == 1 ? 128 : 64, kWaves = kWavesOf<PARTS>, kTerms = SPLIT ? 3 : 1;
+  constexpr int kSub = kSubRows<HD, PARTS>, BKV = kSub * PARTS, kRows = 128 / PARTS, kTerms = SPLIT ? 3 : 1;
   constexpr int kTile = BKV * HD;                       // elements per K (or V) tile
   extern __shared__ __attribute__((aligned(1024))) bf16 smem[];         // [stage][K | V]
   const int Tq = a.Tq, Tk = a.Tk, H = a.H;
@@ -344,7 +337,7 @@ __global__ __launch_bounds__(64 * kWavesOf<PARTS>, 2) void attn_fwd_dma_kernel(M
 
   const int last_q = min(Tq, (qblk + 1) * kRows) - 1;
   const int n_tiles = CAUSAL ? last_q / BKV + 1 : (Tk + BKV - 1) / BKV;
-  TileOffsets<BKV, HD, kWaves> to;
+  TileOffsets<BKV, HD> to;
   to.init(ld, wave, lane);
   auto issue = [&](int t) {
     const uint32_t st = smem_off + (uint32_t)(t & 1) * (2 * kTile * 2);
@@ -352,8 +345,8 @@ __global__ __launch_bounds__(64 * kWavesOf<PARTS>, 2) void attn_fwd_dma_kernel(M
     issue_tile(vbase, ld, t * BKV, Tk - 1, to, st + kTile * 2, wave, lane);
   };
   // The queries pass through the stage of tile 1, which is asked for behind the first barrier.
-  static_assert(kWaves * 32 <= 2 * BKV, "a stage holds 32 rows for each wave");
-  constexpr int kMine = 2 * kTile, kTileLoads = 2 * TileOffsets<BKV, HD, kWaves>::kPerWave;
+  static_assert(4 * 32 <= 2 * BKV, "a stage holds 32 rows for each wave");
+  constexpr int kMine = 2 * kTile, kTileLoads = 2 * TileOffsets<BKV, HD>::kPerWave;
   stage_rows<HD>(qbase, a.ldq, q0, Tq, smem_off + (kMine + wave * 32 * HD) * 2, lane);
   issue(0);
   f32x16 acc[HD / 32];
@@ -421,30 +414,24 @@ __global__ __launch_bounds__(64 * kWavesOf<PARTS>, 2) void attn_fwd_dma_kernel(M
       for (int b2 = 0; b2 < 2; ++b2) second_product<HD, kTerms>(Vs, kb * 32 + b2 * 16, pack_frag<kTerms>(s[kb], b2 * 8), acc);
   }
   l += __shfl_xor(l, 32, 64);
-  if constexpr (PARTS > 1) {   // the other parts hand their reference, sum and accumulators over through LDS
-    constexpr int kBox = (HD / 2 + 2) * 64;
-    float* const box = reinterpret_cast<float*>(smem) + (wave & 1) * kBox + lane;     // of part 1; two further on, of the next
+  if constexpr (PARTS > 1) {   // the second part hands its reference, sum and accumulators over through LDS
+    float* const box = reinterpret_cast<float*>(smem) + (wave & 1) * ((HD / 2 + 2) * 64) + lane;
     __syncthreads();
-    if (part > 0) {
-      float* const mine = box + (part - 1) * 2 * kBox;
-      put_acc<HD>(mine, acc);
-      mine[(HD / 2) * 64] = m;
-      mine[(HD / 2 + 1) * 64] = l;
+    if (part == 1) {
+      put_acc<HD>(box, acc);
+      box[(HD / 2) * 64] = m;
+      box[(HD / 2 + 1) * 64] = l;
     }
     __syncthreads();
-    if (part > 0) return;
+    if (part == 1) return;
+    const float m1 = box[(HD / 2) * 64], top = fmaxf(m, m1);
+    const float w0 = m == top ? 1.f : __builtin_amdgcn_exp2f(m - top), w1 = m1 == top ? 1.f : __builtin_amdgcn_exp2f(m1 - top);
+    m = top;
+    l = l * w0 + box[(HD / 2 + 1) * 64] * w1;
 #pragma unroll
-    for (int p = 0; p < PARTS - 1; ++p) {
-      const float* const theirs = box + p * 2 * kBox;
-      const float m1 = theirs[(HD / 2) * 64], top = fmaxf(m, m1);
-      const float w0 = m == top ? 1.f : __builtin_amdgcn_exp2f(m - top), w1 = m1 == top ? 1.f : __builtin_amdgcn_exp2f(m1 - top);
-      m = top;
-      l = l * w0 + theirs[(HD / 2 + 1) * 64] * w1;
+    for (int cb = 0; cb < HD / 32; ++cb)
 #pragma unroll
-      for (int cb = 0; cb < HD / 32; ++cb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[cb][r] = acc[cb][r] * w0 + theirs[(cb * 16 + r) * 64] * w1;
-    }
+      for (int r = 0; r < 16; ++r) acc[cb][r] = acc[cb][r] * w0 + box[(cb * 16 + r) * 64] * w1;
   }
   auto store = [&](const f32x16* sum) {
     if (query >= Tq) return;
@@ -473,10 +460,10 @@ __global__ __launch_bounds__(64 * kWavesOf<PARTS>, 2) void attn_fwd_dma_kernel(M
 // registers anyway; O, plus the optional rounding remainder o_lo, is read the same way once) and leaves it in
 // `delta` for the dK/dV kernel, which is launched behind this one.
 template <int HD, bool CAUSAL, bool SPLIT, int PARTS>
-__global__ __launch_bounds__(64 * kWavesOf<PARTS>, 2) void attn_dq_dma_kernel(MhaDev a, const bf16* __restrict__ o, const bf16* __restrict__ o_lo,
+__global__ __launch_bounds__(kNT, 2) void attn_dq_dma_kernel(MhaDev a, const bf16* __restrict__ o, const bf16* __restrict__ o_lo,
                                                              const bf16* __restrict__ dout, const float* __restrict__ lse,
                                                              float* __restrict__ delta, bf16* __restrict__ dq, int64_t lddq) {
-  constexpr int kSub = kSubRows<HD, PARTS>, BKV = kSub * PARTS, kRows = PARTS == 1 ? 128 : 64, kWaves = kWavesOf<PARTS>, kTerms = SPLIT ? 2 : 1;
+  constexpr int kSub = kSubRows<HD, PARTS>, BKV = kSub * PARTS, kRows = 128 / PARTS, kTerms = SPLIT ? 2 : 1;
   constexpr int kTile = BKV * HD;
   extern __shared__ __attribute__((aligned(1024))) bf16 smem[];
   const int Tq = a.Tq, Tk = a.Tk, H = a.H;
@@ -502,7 +489,7 @@ __global__ __launch_bounds__(64 * kWavesOf<PARTS>, 2) void attn_dq_dma_kernel(Mh
   const int last_q = min(Tq, (qblk + 1) * kRows) - 1;
   const int n_tiles = CAUSAL ? last_q / BKV + 1 : (Tk + BKV - 1) / BKV;
   const int last_key = CAUSAL ? query : Tk - 1;
-  TileOffsets<BKV, HD, kWaves> to;
+  TileOffsets<BKV, HD> to;
   to.init(ld, wave, lane);
   auto issue = [&](int t) {
     const uint32_t st = smem_off + (uint32_t)(t & 1) * (2 * kTile * 2);
@@ -511,8 +498,8 @@ __global__ __launch_bounds__(64 * kWavesOf<PARTS>, 2) void attn_dq_dma_kernel(Mh
   };
   const float lse_in = lse[(int64_t)bh * Tq + min(query, Tq - 1)];
   // O and dO come through both stages, Q through that of tile 1 behind O; tile 0 follows when no wave reads its dO any more.
-  static_assert(kWaves * 32 <= 2 * BKV, "a stage holds 32 rows for each wave");
-  constexpr int kTileLoads = 2 * TileOffsets<BKV, HD, kWaves>::kPerWave;
+  static_assert(4 * 32 <= 2 * BKV, "a stage holds 32 rows for each wave");
+  constexpr int kTileLoads = 2 * TileOffsets<BKV, HD>::kPerWave;
   const int mine = wave * 32 * HD, mine1 = 2 * kTile + mine;
   stage_rows<HD>(o + (int64_t)b * Tq * d + h * HD, d, q0, Tq, smem_off + mine1 * 2, lane);
   stage_rows<HD>(dout + (int64_t)b * Tq * d + h * HD, d, q0, Tq, smem_off + mine * 2, lane);
@@ -575,7 +562,7 @@ __global__ __launch_bounds__(64 * kWavesOf<PARTS>, 2) void attn_dq_dma_kernel(Mh
     }
   }
   if constexpr (PARTS > 1)
-    if (!sum_parts<HD, PARTS>(reinterpret_cast<float*>(smem) + (wave & 1) * (HD / 2 * 64) + lane, part, acc)) return;
+    if (!sum_parts<HD>(reinterpret_cast<float*>(smem) + (wave & 1) * (HD / 2 * 64) + lane, part, acc)) return;
   bf16* const row = dq + ((int64_t)b * Tq + query) * lddq + h * HD;
   if (SPLIT && __builtin_amdgcn_ballot_w64(query < Tq && lse2 == lse2 && dl == dl && not_finite<HD>(acc)) != 0) {
     f32x16 again[HD / 32];
@@ -1130,10 +1117,6 @@ static hipError_t prepare_dma() {
   std::vector<Kernel> all = {{reinterpret_cast<const void*>(attn_fwd_dma_kernel<HD, CAUSAL, SPLIT, PARTS>), kSmemTiles<HD, PARTS>},
                              {reinterpret_cast<const void*>(attn_dq_dma_kernel<HD, CAUSAL, SPLIT, PARTS>), kSmemTiles<HD, PARTS>}};
   constexpr int kDkv = kSmemDkv<HD, HD == 64 && CAUSAL && !SPLIT>;
-  if constexpr (PARTS == 1) {
-    all.push_back({reinterpret_cast<const void*>(attn_fwd_dma_kernel<HD, CAUSAL, SPLIT, 4>), kSmemTiles<HD, 4>});
-    all.push_back({reinterpret_cast<const void*>(attn_dq_dma_kernel<HD, CAUSAL, SPLIT, 4>), kSmemTiles<HD, 4>});
-  }
   if constexpr (HD == 128 || CAUSAL || PARTS == 2) all.push_back({reinterpret_cast<const void*>(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, PARTS, true>), kDkv});
   if constexpr (HD == 64 && CAUSAL) all.push_back({reinterpret_cast<const void*>(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, PARTS, false>), kDkv});
   if constexpr (HD == 128 || !CAUSAL) all.push_back({reinterpret_cast<const void*>(attn_dkv_pair_kernel<HD, CAUSAL, SPLIT>), kSmemPair<HD>});
@@ -1203,20 +1186,10 @@ static bool two_parts(const MhaArgs& a, int rows, int other, int from, int most)
   return blocks <= (a.causal && other >= 384 ? std::min(most, 256) : 128);
 }
 
-static bool four_parts(int blocks, const MhaArgs& a) {
-  static const char* env = getenv("FOUR");
-  return env && env[0] == '1' && blocks <= 256;
-}
-
 template <int HD, bool CAUSAL, bool SPLIT>
 static hipError_t fwd_dma(hipStream_t s, const MhaArgs& a, void* o, void* o_lo, float* lse) {
-  auto run = [&](auto kernel, int grid, int lds, int threads = kNT) { kernel<<<grid, threads, lds, s>>>(dev_of(a), (bf16*)o, (bf16*)o_lo, lse); };
-  if (CAUSAL ? two_parts(a, a.Tq, a.Tk, 512, HD == 64 ? 384 : 256) : two_parts(a, a.Tq, a.Tk, HD == 64 ? 65 : 256, 256)) {
-    const int blocks = blocks_of<2>(a.Tq, a);
-    if (four_parts(blocks, a)) run(attn_fwd_dma_kernel<HD, CAUSAL, SPLIT, 4>, blocks, kSmemTiles<HD, 4>, 512);
-    else run(attn_fwd_dma_kernel<HD, CAUSAL, SPLIT, 2>, blocks, kSmemTiles<HD, 2>);
-  }
-
+  auto run = [&](auto kernel, int grid, int lds) { kernel<<<grid, kNT, lds, s>>>(dev_of(a), (bf16*)o, (bf16*)o_lo, lse); };
+  if (CAUSAL ? two_parts(a, a.Tq, a.Tk, 512, HD == 64 ? 384 : 256) : two_parts(a, a.Tq, a.Tk, HD == 64 ? 65 : 256, 256)) run(attn_fwd_dma_kernel<HD, CAUSAL, SPLIT, 2>, blocks_of<2>(a.Tq, a), kSmemTiles<HD, 2>);
   else run(attn_fwd_dma_kernel<HD, CAUSAL, SPLIT, 1>, blocks_of<1>(a.Tq, a), kSmemTiles<HD, 1>);
   return hipGetLastError();
 }
@@ -1232,15 +1205,10 @@ hipError_t launch_mha_fwd_dma(hipStream_t s, const MhaArgs& a, void* o, void* o_
 struct MhaGrads { const void *o, *o_lo, *dout; const float* lse; float* delta; void* dq; int64_t lddq; void *dk, *dv; int64_t lddkv; };
 template <int HD, bool CAUSAL, bool SPLIT>
 static hipError_t bwd_dma(hipStream_t s, const MhaArgs& a, const MhaGrads& g) {
-  auto run_q = [&](auto kernel, int grid, int lds, int threads = kNT) {
-    kernel<<<grid, threads, lds, s>>>(dev_of(a), (const bf16*)g.o, (const bf16*)g.o_lo, (const bf16*)g.dout, g.lse, g.delta, (bf16*)g.dq, g.lddq);
+  auto run_q = [&](auto kernel, int grid, int lds) {
+    kernel<<<grid, kNT, lds, s>>>(dev_of(a), (const bf16*)g.o, (const bf16*)g.o_lo, (const bf16*)g.dout, g.lse, g.delta, (bf16*)g.dq, g.lddq);
   };
-  if (CAUSAL ? two_parts(a, a.Tq, a.Tk, 768, HD == 64 ? 384 : 256) : two_parts(a, a.Tq, a.Tk, 0, 128)) {
-    const int blocks = blocks_of<2>(a.Tq, a);
-    if (four_parts(blocks, a)) run_q(attn_dq_dma_kernel<HD, CAUSAL, SPLIT, 4>, blocks, kSmemTiles<HD, 4>, 512);
-    else run_q(attn_dq_dma_kernel<HD, CAUSAL, SPLIT, 2>, blocks, kSmemTiles<HD, 2>);
-  }
-
+  if (CAUSAL ? two_parts(a, a.Tq, a.Tk, 768, HD == 64 ? 384 : 256) : two_parts(a, a.Tq, a.Tk, 0, 128)) run_q(attn_dq_dma_kernel<HD, CAUSAL, SPLIT, 2>, blocks_of<2>(a.Tq, a), kSmemTiles<HD, 2>);
   else run_q(attn_dq_dma_kernel<HD, CAUSAL, SPLIT, 1>, blocks_of<1>(a.Tq, a), kSmemTiles<HD, 1>);
   auto run_kv = [&](auto kernel, int grid) {
     kernel<<<grid, kNT, kSmemDkv<HD, HD == 64 && CAUSAL && !SPLIT>, s>>>(dev_of(a), (const bf16*)g.dout, g.lse, g.delta, (bf16*)g.dk, (bf16*)g.dv, g.lddkv);

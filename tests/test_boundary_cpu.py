@@ -56,6 +56,15 @@ def test_struct_layouts_match_the_header(tmp_path):
         assert getattr(ct, py_last).offset == off, (cname, last)
 
 
+def test_environment_variables_of_the_library_carry_its_prefix():
+    """A switch without the prefix takes another program's variable for its own."""
+    csrc, read = os.path.join(os.path.dirname(pwb.LIB_PATH), "csrc"), set()
+    for name in os.listdir(csrc):
+        with open(os.path.join(csrc, name)) as f:
+            read |= set(re.findall(r"getenv\(\s*([^)]*?)\s*\)", f.read()))
+    assert read and all(re.fullmatch(r'"PW_[A-Z0-9_]+"', v) for v in read), read
+
+
 def test_no_gpu_means_a_loud_failure_not_a_fallback():
     import torch
     if torch.cuda.is_available():
