@@ -203,7 +203,10 @@ def test_gemm_bf16_two_groups_of_waves_in_every_layout(ctx, K, a_k, b_k):
 @pytest.mark.parametrize("N,K", [(16896, 2048), (10240, 2056), (10240, 2112)])
 @pytest.mark.parametrize("b_k", [0, 1])
 def test_gemm_whose_last_columns_are_a_problem_of_their_own(ctx, N, K, b_k):
-    M = 1024
+    _bf16_epilogues(ctx, 1024, N, K, b_k)
+
+
+def _bf16_epilogues(ctx, M, N, K, b_k):
     g = torch.Generator(device="cuda").manual_seed(N + K + b_k)
     rn = lambda *s, std=1.0: torch.randn(*s, generator=g, device="cuda") * std  # noqa: E731
     x, w = rn(M, K).bfloat16(), rn(*((K, N) if b_k else (N, K)), std=0.02).bfloat16()
@@ -217,7 +220,7 @@ def test_gemm_whose_last_columns_are_a_problem_of_their_own(ctx, N, K, b_k):
     ctx.gemm(epilogue=pwb.PW_EPI_BIAS_RESIDUAL, out_dtype=pwb.PW_F32, accumulate=0, bias=ptr(bias), aux=ptr(res), C=ptr(y), **kw)
     ctx.gemm(epilogue=pwb.PW_EPI_GELU_BWD, out_dtype=pwb.PW_BF16, accumulate=0, aux=ptr(pre), C=ptr(du), **kw)
     ctx.gemm(epilogue=pwb.PW_EPI_STORE, out_dtype=pwb.PW_F32, accumulate=1, C=ptr(acc), **kw)
-    dw = torch.empty((K, N), device="cuda")          # both operands k-major: 1024 rows of k, K x N outputs
+    dw = torch.empty((K, N), device="cuda")          # both operands k-major: M rows of k, K x N outputs
     ctx.gemm(dtype=pwb.PW_BF16, a_kmajor=1, b_kmajor=1, M=K, N=N, K=M, lda=K, ldb=N, ldc=N, epilogue=pwb.PW_EPI_STORE, out_dtype=pwb.PW_F32,
              accumulate=0, A=ptr(x), B=ptr(pre), C=ptr(dw))
     ctx.synchronize()
@@ -229,6 +232,15 @@ def test_gemm_whose_last_columns_are_a_problem_of_their_own(ctx, N, K, b_k):
                           (acc, lin + res, 1e-5), (dw, x.float().T.contiguous() @ pre.float(), 1e-5)):
         err = (got.float() - ref).norm(dim=0) / ref.norm(dim=0)
         assert err.max().item() < tol
+
+
+# every epilogue of the any-shape kernel, by tile shape (64 x 64, 128 x 64, 128 x 128), whole tiles and ragged rows and columns: a bias
+# held over a tile's steps, old values and aux rows fetched ahead, a last vector of columns, fewer rows than a step covers
+@pytest.mark.parametrize("M,N,K", [(256, 512, 128), (200, 264, 520), (1024, 1536, 264), (1000, 1112, 776), (1024, 3072, 1024), (1000, 3080, 264),
+                                   (1672, 1800, 328), (1664, 2048, 2048), (2304, 2432, 128), (2312, 2440, 136)])
+@pytest.mark.parametrize("b_k", [0, 1])
+def test_gemm_bf16_epilogues_of_every_tile_shape(ctx, M, N, K, b_k):
+    _bf16_epilogues(ctx, M, N, K, b_k)
 
 
 @pytest.mark.parametrize("bf16", [False, True])
