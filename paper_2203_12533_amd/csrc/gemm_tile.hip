@@ -150,7 +150,8 @@ template <int WM_, int WN_, int WK_, bool DEEP_>
 struct Shape {
   static constexpr int WM = WM_, WN = WN_, WK = WK_;
   static constexpr bool DEEP = DEEP_;
-  static constexpr bool kSkew = WK > 1 && WM * WN > 1;               // the second group runs half a tile behind the first
+  static constexpr bool kSkew = WK > 1 && WM * WN > 1;               // the second group runs half a tile behind the first,
+  static constexpr int kApartFrom = WM * WN == 4 ? 0 : 13;           // from this many k tiles on
   static constexpr int BM = 64 * WM, BN = 64 * WN, G = WM * WN, kThreads = 64 * G * WK;
   static constexpr int kWavesPerSimd = WK == 1 || kThreads == 512 ? 2 : 1;
   static constexpr int kStage = (BM + BN) * kTBK;                    // elements
@@ -390,7 +391,11 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_tile_kerne
   // pipe take turns (us, 128 x 128 tiles, four waves alone / two groups in step / half a tile apart, profiles of one launch: the main
   // loop of 1000 x 3072 x 768 5.3 / 5.5 / 4.2, of 2048 x 2048 x 2048 13.8 / 14.3 / 11.6).  Apart, the LDS bounds it: 96 KiB in
   // and out of it per 128 x 128 x 64, 0.32 us at 2.4 GHz, take 0.36.  Each group passes as many barriers as the other.
-  if (S::kSkew && g == 1) meet();
+  // The half tile at either end has to be earned back: two pairs of waves need 13 k tiles (128 x 64 tiles, in step / apart: 1280 x 1280 x
+  // 256 6.7 / 6.9, 768 9.2 / 9.2, 1536 13.1 / 12.4; 1024 x 1536 x 832 8.9 / 8.8, 960 9.6 / 9.2), two groups of four waves none
+  // (1536 x 1536 x 256, row-major, 7.1 / 7.0, 768 10.4 / 9.6).
+  const bool apart = S::kSkew && total >= S::kApartFrom;
+  if (apart && g == 1) meet();
   int i = 0;
   for (; i + NS - 1 + kAhead < n - 1; i += NS) {  // NS tiles, none of which loads the last one
     tile(i, std::integral_constant<int, 0>{}, std::true_type{});
@@ -402,7 +407,7 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_tile_kerne
     if (i + 1 < rounds) tile(i + 1, std::integral_constant<int, 1>{}, std::false_type{});
   }
 
-  if (S::kSkew && g == 0) meet();
+  if (apart && g == 0) meet();
   __syncthreads();                            // nobody reads operand tiles any more
   float* const parts = reinterpret_cast<float*>(smem);
   float* mine = parts + (g * S::BM + wm * 64 + (lane & 15)) * S::kLdP + wn * 64 + 4 * (lane >> 4);

@@ -198,6 +198,13 @@ def test_gemm_bf16_two_groups_of_waves_in_every_layout(ctx, K, a_k, b_k):
     test_gemm_bf16_any_shape_in_every_layout(ctx, 1672, 1800, K, 8, a_k, b_k)
 
 
+# 128 x 64 tiles, k over two pairs of waves: in step up to twelve k tiles (the last of them partial or not), half a tile apart from there on
+@pytest.mark.parametrize("a_k,b_k", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("K", [8, 64, 136, 712, 768, 776, 832, 896, 904])
+def test_gemm_bf16_two_pairs_of_waves_in_every_layout(ctx, K, a_k, b_k):
+    test_gemm_bf16_any_shape_in_every_layout(ctx, 1000, 1112, K, 8, a_k, b_k)
+
+
 # 264 full tiles of 256 x 256, 2048 deep: a round of 256 on the ring kernel, the last columns (two tiles wide) on their own; and
 # 160 of them 2056 deep and more (any-shape kernel) or 2112 (ring).  Every operand and output that goes by columns takes part.
 @pytest.mark.parametrize("N,K", [(16896, 2048), (10240, 2056), (10240, 2112)])
