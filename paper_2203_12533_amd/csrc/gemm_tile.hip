@@ -471,18 +471,35 @@ hipError_t gemm_tile_init() {
 // Which shape (us per launch before: 128 x 128 tiles staged through registers, or full ring tiles on half the chip).
 // The fewer tiles of 128 x 128 there are, the smaller the tile and the more waves share its k: 1000 x 768 x 3072 (48
 // tiles) 51 -> 13 with Split (Half 20, One 24); 1280 x 1280 x 4096 (100) 72 -> 23 with Half (Split 30, One 30, Duo 28); up to one
-// tile per compute unit Duo from k = 256 on (us, One / Duo: 1000 x 3072 x 768 with GELU 13.4 / 12.9, as a GELU' data gradient 13.8 /
-// 12.6, stored 10.7 / 10.3; 768 x 3072 x 1000 k-major 13.0 / 12.8; 1792 x 2048 x 320 10.3 / 10.1; 2000 x 2000 x 4096 39.2 / 38.3;
-// 2048 x 2048 x 8192 59 / 58, Two 82), where k is shorter One (2048 x 1152 x 128 7.1 / 7.7).  Beyond that
+// tile per compute unit One, or Duo where that wins (duo_pays).  Beyond that
 // two workgroups share a compute unit and hide each other's waits; with a long k the leaner loop is ahead (2048 x 8000 x
 // 8000: 216 against 251), with a short one it is not (4568 x 2240 x 1152: 32 against 29; 4096 x 4352 x 2048: 79 / 75).
+//
+// Duo saves a fifth of the main loop and pays with a second tile of partial sums through LDS (0.3 to 0.5 us).  One / Duo, us:
+//   both operands row-major (without spills), from k = 1024 on: bf16 out 1536 x 1536 x 640 8.9 / 9.3, 768 9.6 / 9.5, 1024 10.9 / 10.6, 2048 17.4 /
+//     16.3; residual 1024 x 3072 x 768 12.6 / 12.7, 1024 14.5 / 14.2; GELU 768 11.7 / 11.8, 1024 13.1 / 12.8;
+//   ragged ones, whose rows wait for their old values or aux step by step and have half as many steps in Duo, from 256: 1000 x 3000 x 256 bf16
+//     out 7.7 / 7.5, GELU' 9.7 / 8.8, residual 10.4 / 10.0; 768 GELU' 13.1 / 12.0; 192 residual 9.7 / 9.9;
+//   plain fp32 out, where the stores come on top, from 1536: 1000 x 3000 x 768 12.1 / 12.2, 2000 x 2000 x 1024 14.2 / 14.4, 1536 x 1536 x 1536 15.6 /
+//     15.6, 2048 18.6 / 17.9;
+//   other layouts (a few registers spill, or transposing reads of both), whole tiles, from 2048: 2048 x 2048 x 1024, fp32 15.8 / 15.9, GELU
+//     14.5 / 14.8, 1536 19.5 / 19.2, 18.6 / 18.5, 2048 22.9 / 22.3, 22.4 / 22.0, k-major 23.2 / 21.8;
+//   ragged, from 4096: 2000 x 2000 x 2048 22.8 / 23.0, k-major 22.8 / 23.4, 1672 x 1800 x 3072 bf16 out 26.3 / 26.3, 4096 33.1 / 32.5, k-major
+//     36.5 / 36.8, 1000 x 3000 x 4096 with a residual 35.9 / 34.5; but GELU' as above: x 256 9.7 / 9.1, 1024 15.8 / 14.8, 2048 22.9 / 21.2.
+static bool duo_pays(const GemmBf16Params& p, bool ak, bool bk) {
+  const bool whole = p.M % 128 == 0 && p.N % 128 == 0, rows = !ak && !bk;
+  const bool plain = p.epi.mode == kEpiStore && !p.epi.out_bf16 && !p.epi.accumulate;
+  if (!whole && (p.epi.mode == kEpiGeluBwd || (rows && !plain))) return p.K >= 256;
+  if (rows) return p.K >= (plain ? 1536 : 1024);
+  return p.K >= (whole ? 2048 : 4096);
+}
 hipError_t launch_gemm_tile(hipStream_t s, const GemmBf16Params& p, bool ak, bool bk) {
   if (p.lda > kMaxLd || p.ldb > kMaxLd) return launch<Split, true>(s, p, ak, bk);
   const int64_t t128 = ((p.M + 127) / 128) * ((p.N + 127) / 128);
   if (t128 <= 64) return launch<Split>(s, p, ak, bk);
   if (t128 <= 128) return launch<Half>(s, p, ak, bk);
-  if (t128 <= 256 && p.K >= 256) return launch<Duo>(s, p, ak, bk);
-  if (p.K <= 2048) return launch<One>(s, p, ak, bk);
+  if (t128 <= 256 && duo_pays(p, ak, bk)) return launch<Duo>(s, p, ak, bk);
+  if (t128 <= 256 || p.K <= 2048) return launch<One>(s, p, ak, bk);
   return launch<Two>(s, p, ak, bk);
 }
 

@@ -190,12 +190,20 @@ def test_gemm_bf16_any_shape_in_every_layout(ctx, M, N, K, pad, a_k, b_k):
     assert (got[:, N:] == 7.0).all()
 
 
-# 210 tiles of 128 x 128 from k = 256 on, k over two groups of four waves half a tile apart: equally many k tiles each, a partial last one,
-# one more in the first group than in the second, and enough of them for the streaming loop, in an even and in an odd number
+# 210 ragged tiles of 128 x 128, four waves to each (with row-major operands and a plain output k goes over two groups from 1536 on)
 @pytest.mark.parametrize("a_k,b_k", [(0, 0), (0, 1), (1, 0), (1, 1)])
 @pytest.mark.parametrize("K", [248, 256, 264, 328, 448, 832, 904, 1096])
 def test_gemm_bf16_two_groups_of_waves_in_every_layout(ctx, K, a_k, b_k):
     test_gemm_bf16_any_shape_in_every_layout(ctx, 1672, 1800, K, 8, a_k, b_k)
+
+
+# the same tiles with k over two groups of four waves half a tile apart, whole tiles and (both operands row-major) ragged ones: one k tile
+# more in the first group than in the second or as many, an even and an odd number of them, a partial last one; one k below the limit
+@pytest.mark.parametrize("M,N,K,a_k,b_k", [(1664, 1792, K, a_k, b_k) for K in (2040, 2048, 2056, 2112, 2120, 2176, 2240) for a_k in (0, 1) for b_k in (0, 1)] +
+                         [(1672, 1800, K, 0, 0) for K in (1528, 1536, 1544, 1600, 1664, 1672)] +
+                         [(1672, 1800, K, a_k, b_k) for K in (4088, 4096, 4104) for a_k, b_k in ((0, 1), (1, 0), (1, 1))])
+def test_gemm_bf16_two_groups_of_waves_with_a_long_k(ctx, M, N, K, a_k, b_k):
+    test_gemm_bf16_any_shape_in_every_layout(ctx, M, N, K, 8, a_k, b_k)
 
 
 # 128 x 64 tiles, k over two pairs of waves: in step up to twelve k tiles (the last of them partial or not), half a tile apart from there on
@@ -231,11 +239,13 @@ def _bf16_epilogues(ctx, M, N, K, b_k):
     ctx.gemm(dtype=pwb.PW_BF16, a_kmajor=1, b_kmajor=1, M=K, N=N, K=M, lda=K, ldb=N, ldc=N, epilogue=pwb.PW_EPI_STORE, out_dtype=pwb.PW_F32,
              accumulate=0, A=ptr(x), B=ptr(pre), C=ptr(dw))
     ctx.synchronize()
-    leaf = pre.float().requires_grad_(True)
-    (slope,) = torch.autograd.grad(torch.nn.functional.gelu(leaf, approximate="tanh").sum(), leaf)
+    # (GELU and its slope in 64 bits: 1 + tanh cancels in 32, which is 1.7e-3 of a column of arguments around -4.6, 1.2e-2 around -5)
+    leaf = pre.double().requires_grad_(True)
+    slope = torch.autograd.grad(torch.nn.functional.gelu(leaf, approximate="tanh").sum(), leaf)[0].float()
     z = lin + bias
+    gelu = torch.nn.functional.gelu(z.double(), approximate="tanh").float()
     # column by column, so that no part of the product can hide behind the rest: bf16 storage 2^-9, fp32 sums of K products
-    for got, ref, tol in ((u, z, 4e-3), (h, torch.nn.functional.gelu(z, approximate="tanh"), 6e-3), (y, z + res, 1e-5), (du, lin * slope, 4e-3),
+    for got, ref, tol in ((u, z, 4e-3), (h, gelu, 6e-3), (y, z + res, 1e-5), (du, lin * slope, 4e-3),
                           (acc, lin + res, 1e-5), (dw, x.float().T.contiguous() @ pre.float(), 1e-5)):
         err = (got.float() - ref).norm(dim=0) / ref.norm(dim=0)
         assert err.max().item() < tol
@@ -243,8 +253,10 @@ def _bf16_epilogues(ctx, M, N, K, b_k):
 
 # every epilogue of the any-shape kernel, by tile shape (64 x 64, 128 x 64, 128 x 128), whole tiles and ragged rows and columns: a bias
 # held over a tile's steps, old values and aux rows fetched ahead, a last vector of columns, fewer rows than a step covers
-@pytest.mark.parametrize("M,N,K", [(256, 512, 128), (200, 264, 520), (1024, 1536, 264), (1000, 1112, 776), (1024, 3072, 1024), (1000, 3080, 264),
-                                   (1672, 1800, 328), (1664, 2048, 2048), (2304, 2432, 128), (2312, 2440, 136)])
+# (128 x 128 row-major ones of k over two groups from k = 256 on, ragged, and 1024, whole: one k on either side of both)
+@pytest.mark.parametrize("M,N,K", [(256, 512, 128), (200, 264, 520), (1024, 1536, 264), (1000, 1112, 776), (1024, 3072, 1016), (1024, 3072, 1024),
+                                   (1000, 3080, 248), (1000, 3080, 256), (1000, 3080, 264), (1672, 1800, 328), (1664, 2048, 2048),
+                                   (2304, 2432, 128), (2312, 2440, 136)])
 @pytest.mark.parametrize("b_k", [0, 1])
 def test_gemm_bf16_epilogues_of_every_tile_shape(ctx, M, N, K, b_k):
     _bf16_epilogues(ctx, M, N, K, b_k)
