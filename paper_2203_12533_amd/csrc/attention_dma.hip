@@ -43,7 +43,6 @@
 // of decoder queries over encoder keys; CAUSAL is a template parameter (it decides which tiles are visited).
 #include <algorithm>
 #include <type_traits>
-#include <vector>
 
 #include "attention_common.hpp"
 #include "common.hpp"
@@ -731,7 +730,8 @@ __device__ __forceinline__ void dkv_again(const MhaDev& a, const bf16* dout, con
 }
 
 // ALONE: a compute unit has one workgroup at most, so a wave may have 512 registers.  In 256, which two workgroups need, head width 64
-// spills (8 to 64 registers): reloads in the loop, and each waits for the tiles in flight as well.
+// spills (6 to 25 registers, unmasked 60): reloads in the loop, and each waits for the tiles in flight as well.  A few spills cost less than
+// the wider form's moves between the two register files; bwd_dma has the figures.
 template <int HD, bool CAUSAL, bool SPLIT, int PARTS, bool ALONE>
 __global__ __launch_bounds__(kNT, ALONE ? 1 : 2) void attn_dkv_dma_kernel(MhaDev a, const bf16* __restrict__ dout,
                                                             const float* __restrict__ lse, const float* __restrict__ delta,
@@ -1111,36 +1111,34 @@ __global__ __launch_bounds__(64 * kPairWaves, 2) void attn_dkv_pair_kernel(MhaDe
 template <int HD, int PARTS> constexpr int kSmemTiles = 2 * 2 * kSubRows<HD, PARTS> * PARTS * HD * 2;
 template <int HD, bool HIDES> constexpr int kSmemDkv = 3 * 2 * 64 * HD * 2 + 6 * 64 * 4 + (HIDES ? (64 + 32) * HD * 2 : 0);   // (tile_q)
 
-template <int HD, bool CAUSAL, bool SPLIT, int PARTS>
-static hipError_t prepare_dma() {
-  struct Kernel { const void* fn; int bytes; };
-  std::vector<Kernel> all = {{reinterpret_cast<const void*>(attn_fwd_dma_kernel<HD, CAUSAL, SPLIT, PARTS>), kSmemTiles<HD, PARTS>},
-                             {reinterpret_cast<const void*>(attn_dq_dma_kernel<HD, CAUSAL, SPLIT, PARTS>), kSmemTiles<HD, PARTS>}};
-  constexpr int kDkv = kSmemDkv<HD, HD == 64 && CAUSAL && !SPLIT>;
-  if constexpr (HD == 128 || CAUSAL || PARTS == 2) all.push_back({reinterpret_cast<const void*>(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, PARTS, true>), kDkv});
-  if constexpr (HD == 64 && CAUSAL) all.push_back({reinterpret_cast<const void*>(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, PARTS, false>), kDkv});
-  if constexpr (HD == 128 || !CAUSAL) all.push_back({reinterpret_cast<const void*>(attn_dkv_pair_kernel<HD, CAUSAL, SPLIT>), kSmemPair<HD>});
-  for (const auto& k : all) {
-    const hipError_t e = hipFuncSetAttribute(k.fn, hipFuncAttributeMaxDynamicSharedMemorySize, k.bytes);
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
-}
 template <int HD, bool CAUSAL, bool SPLIT>
-static hipError_t prepare_parts() {
-  const hipError_t e = prepare_dma<HD, CAUSAL, SPLIT, 1>();
-  return e != hipSuccess ? e : prepare_dma<HD, CAUSAL, SPLIT, 2>();
+static hipError_t prepare_dma() {
+  hipError_t e = hipSuccess;
+  auto raise = [&](auto kernel, int bytes) {
+    if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  };
+  raise(attn_fwd_dma_kernel<HD, CAUSAL, SPLIT, 1>, kSmemTiles<HD, 1>);
+  raise(attn_fwd_dma_kernel<HD, CAUSAL, SPLIT, 2>, kSmemTiles<HD, 2>);
+  raise(attn_dq_dma_kernel<HD, CAUSAL, SPLIT, 1>, kSmemTiles<HD, 1>);
+  raise(attn_dq_dma_kernel<HD, CAUSAL, SPLIT, 2>, kSmemTiles<HD, 2>);
+  constexpr int kDkv = kSmemDkv<HD, HD == 64 && CAUSAL && !SPLIT>;       // (which of these there are: bwd_dma)
+  if constexpr (HD == 128) raise(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, 1, true>, kDkv);
+  if constexpr (HD == 64 && CAUSAL) raise(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, 1, false>, kDkv);
+  if constexpr (HD == 128 || SPLIT) raise(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, 2, true>, kDkv);
+  if constexpr (HD == 64 && CAUSAL) raise(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, 2, false>, kDkv);
+  if constexpr (HD == 128 || !CAUSAL) raise(attn_dkv_pair_kernel<HD, CAUSAL, SPLIT>, kSmemPair<HD>);
+  return e;
 }
 
 // Raises the dynamic-LDS limit of the kernels (once; called at context creation, never inside a capture).
 hipError_t attention_dma_init() {
   static bool done = false;
   if (done) return hipSuccess;
-  hipError_t e = prepare_parts<128, true, false>();
-  if (e == hipSuccess) e = prepare_parts<128, false, false>();
-  if (e == hipSuccess) e = prepare_parts<64, true, false>();
-  if (e == hipSuccess) e = prepare_parts<64, true, true>();
-  if (e == hipSuccess) e = prepare_parts<64, false, true>();
+  hipError_t e = prepare_dma<128, true, false>();
+  if (e == hipSuccess) e = prepare_dma<128, false, false>();
+  if (e == hipSuccess) e = prepare_dma<64, true, false>();
+  if (e == hipSuccess) e = prepare_dma<64, true, true>();
+  if (e == hipSuccess) e = prepare_dma<64, false, true>();
   if (e == hipSuccess) done = true;
   return e;
 }
@@ -1225,18 +1223,28 @@ static hipError_t bwd_dma(hipStream_t s, const MhaArgs& a, const MhaGrads& g) {
   // 40.3 / 33.4; 2 x 2014 over 1092, 9 heads, 162 blocks 65.7 / 49.6; one tile, 2 x 64 over 1000, 8 heads, 128 blocks 5.4 / 5.5.  Two parts up to 128
   // blocks: 1 x 700, 6 heads 16.7 / 19.8; 4 x 600 over 60, 12 heads 15.5 / 17.7.  Packed causal pairs gain and lose: 1 x 2048, 16 heads 37.5 / 35.1, 8 x
   // 1024 52.9 / 56.3, 4 x 1000, 12 heads 26.8 / 27.1.
-  // There, up to a block per unit, a block has the registers of two (4 x 333 over 520, before pairs: 22.4 with spills / 19.0).
-  constexpr bool kShares = HD == 64 && CAUSAL;               // kernels for two workgroups on a unit
-  auto two = [&](int blocks) { return kShares && blocks > 256; };
+  // Two parts of width 64, registers of one workgroup of two on a unit / of both: 1 x 700, 6 heads, unmasked 27.0 / 17.8; 4 x 600 over 60, 12 heads
+  // 25.5 / 16.4; causal with split dS (25 registers spill) 1 x 2048, 8 heads 47.8 / 42.4, 8 x 300, 4 heads 12.3 / 11.4, 1 x 1024, 16 heads 27.6 / 24.5;
+  // packed causal (10 spill) 1 x 2048, 8 heads 31.8 / 33.4, 1 x 1024, 16 heads 18.8 / 20.1, 8 x 775, 2 heads 16.2 / 17.1.  One wave per 32 keys
+  // gains nothing: 16 x 128, 16 heads 10.3 / 10.7, with split dS forward and backward 17.6 / 17.8, 40 x 64, 6 heads 12.1 / 12.4.
+  constexpr bool kManyParts = HD == 64 && CAUSAL;            // more than 256 blocks of two parts occur
   if (CAUSAL ? two_parts(a, a.Tk, a.Tq, 768, HD == 64 ? 384 : 128) : two_parts(a, a.Tk, a.Tq, 0, 128)) {
     const int blocks = blocks_of<2>(a.Tk, a);
-    run_kv(two(blocks) ? attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, 2, !kShares> : attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, 2, true>, blocks);
-  } else if (kShares || (HD == 128 && a.Tq <= kPairBQ)) {
-    const int blocks = blocks_of<1>(a.Tk, a);
-    if constexpr (HD == 128 || CAUSAL)
-      run_kv(two(blocks) ? attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, 1, !kShares> : attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, 1, true>, blocks);
-  } else if constexpr (!kShares) {
-    attn_dkv_pair_kernel<HD, CAUSAL, SPLIT><<<blocks_of<1>(a.Tk, a), 64 * kPairWaves, kSmemPair<HD>, s>>>(
+    if constexpr (!kManyParts) run_kv(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, 2, true>, blocks);
+    else if constexpr (!SPLIT) run_kv(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, 2, false>, blocks);
+    else run_kv(blocks <= 256 ? attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, 2, true> : attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, 2, false>, blocks);
+    return hipGetLastError();
+  }
+  const int blocks = blocks_of<1>(a.Tk, a);
+  if constexpr (HD == 64 && CAUSAL) {
+    run_kv(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, 1, false>, blocks);
+  } else {
+    if constexpr (HD == 128)
+      if (a.Tq <= kPairBQ) {
+        run_kv(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, 1, true>, blocks);
+        return hipGetLastError();
+      }
+    attn_dkv_pair_kernel<HD, CAUSAL, SPLIT><<<blocks, 64 * kPairWaves, kSmemPair<HD>, s>>>(
         dev_of(a), (const bf16*)g.dout, g.lse, g.delta, (bf16*)g.dk, (bf16*)g.dv, g.lddkv);
   }
   return hipGetLastError();

@@ -761,10 +761,18 @@ def test_bf16_causal_attention_block_orders(ctx, orc, B, T, H, hd):
     _mha_case(ctx, orc, True, B, T, T, H, hd, causal=True, packed_kv=True)
 
 
-# dK/dV at head width 64 with a block per compute unit at most and with one more: of 128 keys, and of 64 that two waves share
-@pytest.mark.parametrize("B,Tq,Tk,H,causal", [(64, 70, 40, 4, 0), (65, 200, 40, 4, 0), (65, 130, 130, 2, 1), (8, 775, 775, 2, 1), (10, 770, 770, 2, 1)])
+# dK/dV at head width 64, by blocks of 128 keys: unmasked two waves share 32 keys up to 128 of them, from 129 on in workgroups of eight
+# waves; causal, with blocks of 64 that two waves share, a block per compute unit at most (208) and more (260), and one wave to 32 keys
+@pytest.mark.parametrize("B,Tq,Tk,H,causal", [(32, 70, 40, 4, 0), (43, 200, 40, 3, 0), (64, 70, 40, 4, 0), (65, 200, 40, 4, 0),
+                                              (65, 130, 130, 2, 1), (8, 775, 775, 2, 1), (10, 770, 770, 2, 1)])
 def test_bf16_attention_gradients_at_head_width_64_around_a_block_per_unit(ctx, orc, B, Tq, Tk, H, causal):
     _mha_case(ctx, orc, True, B, Tq, Tk, H, 64, causal=bool(causal), packed_kv=True)
+
+
+# the same for packed causal calls, whose probabilities and dS are rounded: two parts on 208 and 260 blocks, one wave to 32 keys on 136 and 260
+@pytest.mark.parametrize("B,T,H", [(8, 775, 2), (10, 770, 2), (34, 130, 2), (65, 130, 2)])
+def test_bf16_packed_causal_attention_at_head_width_64_around_a_block_per_unit(ctx, orc, B, T, H):
+    test_attention_forward_backward(ctx, orc, B, T, H, 64, True)
 
 
 # more than 128 blocks of 128 keys and a single tile of queries: four waves to 128 keys in dK/dV, at both ends of that tile
@@ -911,7 +919,8 @@ def test_fp32_causal_attention_ignores_what_is_masked(ctx, T, hd):
 # of 64 rows (few) and of 128 (many), the hidden rows one and a third of all.  Packed calls, whose probabilities are rounded to
 # bf16, hide such rows from other tiles (64 keys; in the dK/dV kernel 32 queries) only.
 @pytest.mark.parametrize("packed", [True, False])
-@pytest.mark.parametrize("B,T,H", [(2, 2, 2), (2, 31, 2), (2, 33, 2), (1, 64, 2), (1, 97, 2), (2, 200, 2), (33, 33, 4), (33, 100, 4), (17, 161, 4)])
+@pytest.mark.parametrize("B,T,H", [(2, 2, 2), (2, 31, 2), (2, 33, 2), (1, 64, 2), (1, 97, 2), (2, 200, 2), (33, 33, 4), (33, 100, 4), (17, 161, 4),
+                                   (33, 161, 4), (10, 770, 2)])
 def test_bf16_causal_attention_at_head_width_64_ignores_what_is_masked(ctx, B, T, H, packed):
     hd = 64
     d = H * hd
