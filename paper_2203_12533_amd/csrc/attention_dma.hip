@@ -1122,8 +1122,7 @@ static hipError_t prepare_dma() {
   raise(attn_dq_dma_kernel<HD, CAUSAL, SPLIT, 1>, kSmemTiles<HD, 1>);
   raise(attn_dq_dma_kernel<HD, CAUSAL, SPLIT, 2>, kSmemTiles<HD, 2>);
   constexpr int kDkv = kSmemDkv<HD, HD == 64 && CAUSAL && !SPLIT>;       // (which of these there are: bwd_dma)
-  if constexpr (HD == 128) raise(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, 1, true>, kDkv);
-  if constexpr (HD == 64 && CAUSAL) raise(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, 1, false>, kDkv);
+  raise(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, 1, HD == 128>, kDkv);
   if constexpr (HD == 128 || SPLIT) raise(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, 2, true>, kDkv);
   if constexpr (HD == 64 && CAUSAL) raise(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, 2, false>, kDkv);
   if constexpr (HD == 128 || !CAUSAL) raise(attn_dkv_pair_kernel<HD, CAUSAL, SPLIT>, kSmemPair<HD>);
@@ -1220,7 +1219,9 @@ static hipError_t bwd_dma(hipStream_t s, const MhaArgs& a, const MhaGrads& g) {
   // / 19.0 / 13.2.  Of what pairs have, 128 queries (two whole tiles) over up to 48 keys lose on 130 to 224 blocks: 160, 32 keys 8.4 / - / 8.7;
   // 96 queries 8.8 / - / 8.7, 160 10.8 / - / 10.5, and all of these on 256 blocks and more gain, so no line is drawn for them.
   // Width 64, unmasked (one wave with the registers of two / pairs): 4 x 333 over 520, 8 heads, 160 blocks 16.1 / 12.2; 8 x 512, 16 heads, 512 blocks
-  // 40.3 / 33.4; 2 x 2014 over 1092, 9 heads, 162 blocks 65.7 / 49.6; one tile, 2 x 64 over 1000, 8 heads, 128 blocks 5.4 / 5.5.  Two parts up to 128
+  // 40.3 / 33.4; 2 x 2014 over 1092, 9 heads, 162 blocks 65.7 / 49.6.  One tile of queries loses where a second round of workgroups of eight waves starts, past
+  // 256 blocks (backward, registers of one workgroup of two / pairs: 70 x 1 over 100, 4 heads, 280 blocks 18.2 / 21.0, 64 queries 18.9 / 22.0, 65 25.1 / 24.7; 16
+  // x 33 over 500, 8 heads, 512 blocks 24.0 / 25.5; 5 x 33 over 500, 8 heads, 160 blocks 17.3 / 17.4, 1 query 17.2 / 16.8).  Two parts up to 128
   // blocks: 1 x 700, 6 heads 16.7 / 19.8; 4 x 600 over 60, 12 heads 15.5 / 17.7.  Packed causal pairs gain and lose: 1 x 2048, 16 heads 37.5 / 35.1, 8 x
   // 1024 52.9 / 56.3, 4 x 1000, 12 heads 26.8 / 27.1.
   // Two parts of width 64, registers of one workgroup of two on a unit / of both: 1 x 700, 6 heads, unmasked 27.0 / 17.8; 4 x 600 over 60, 12 heads
@@ -1236,17 +1237,11 @@ static hipError_t bwd_dma(hipStream_t s, const MhaArgs& a, const MhaGrads& g) {
     return hipGetLastError();
   }
   const int blocks = blocks_of<1>(a.Tk, a);
-  if constexpr (HD == 64 && CAUSAL) {
-    run_kv(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, 1, false>, blocks);
-  } else {
-    if constexpr (HD == 128)
-      if (a.Tq <= kPairBQ) {
-        run_kv(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, 1, true>, blocks);
-        return hipGetLastError();
-      }
+  if ((HD == 64 && CAUSAL) || (a.Tq <= kPairBQ && (HD == 128 || blocks > 256)))
+    run_kv(attn_dkv_dma_kernel<HD, CAUSAL, SPLIT, 1, HD == 128>, blocks);
+  else if constexpr (HD == 128 || !CAUSAL)
     attn_dkv_pair_kernel<HD, CAUSAL, SPLIT><<<blocks, 64 * kPairWaves, kSmemPair<HD>, s>>>(
         dev_of(a), (const bf16*)g.dout, g.lse, g.delta, (bf16*)g.dk, (bf16*)g.dv, g.lddkv);
-  }
   return hipGetLastError();
 }
 bool mha_dma_outputs_aligned(const void* dq, int64_t lddq, const void* dk, const void* dv, int64_t lddkv) {

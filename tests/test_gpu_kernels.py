@@ -775,10 +775,17 @@ def test_bf16_packed_causal_attention_at_head_width_64_around_a_block_per_unit(c
     test_attention_forward_backward(ctx, orc, B, T, H, 64, True)
 
 
-# more than 128 blocks of 128 keys and a single tile of queries: four waves to 128 keys in dK/dV, at both ends of that tile
+# more than 128 blocks of 128 keys and a single tile of queries: four waves to 128 keys in dK/dV, at both ends of that tile (at head width
+# 64 from 257 blocks on, one block to either side; up to there eight waves, half of them without queries up to 32)
 @pytest.mark.parametrize("B,Tq,Tk,H,causal", [(40, 60, 100, 4, 0), (33, 64, 130, 8, 0), (33, 64, 64, 8, 1), (140, 1, 20, 1, 0)])
 def test_bf16_attention_at_head_width_128_with_one_tile_of_queries(ctx, orc, B, Tq, Tk, H, causal):
     _mha_case(ctx, orc, True, B, Tq, Tk, H, 128, causal=bool(causal), packed_kv=True)
+
+
+@pytest.mark.parametrize("B,Tq,Tk,H", [(40, 60, 100, 4), (140, 1, 20, 1), (43, 32, 130, 2), (43, 33, 130, 2), (64, 64, 100, 4), (257, 64, 100, 1),
+                                       (257, 1, 30, 1), (70, 33, 130, 2), (257, 65, 100, 1)])
+def test_bf16_attention_at_head_width_64_with_one_tile_of_queries(ctx, orc, B, Tq, Tk, H):
+    _mha_case(ctx, orc, True, B, Tq, Tk, H, 64, causal=False, packed_kv=True)
 
 
 # dK/dV where two waves share 32 keys, with keys that no query attends to (an infinite key): all of a wave's, some of it, all but one
