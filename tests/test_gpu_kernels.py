@@ -587,9 +587,8 @@ def test_unmasked_attention_with_separate_lengths(ctx, orc, B, Tq, Tk, H, hd, bf
 
 
 def test_causal_attention_block_order_with_partial_problem_groups(ctx, orc):
-    """Under the causal mask the workgroups of several problems are interleaved, longest blocks first, in groups
-    sized from the number of 128-row blocks per problem: 9 problems of 5 blocks give one group of 9 in the forward
-    and dQ kernels and groups of 7 and 2 in the dK/dV kernel, with a ragged last block."""
+    """Under the causal mask the workgroups of several problems are interleaved, longest blocks first: 9 problems of 5 blocks of 128
+    rows, the last of them ragged, one more than there are XCDs (which orders there are: ..._block_orders)."""
     _mha_case(ctx, orc, True, 3, 520, 520, 3, 128, causal=True, packed_kv=False)
 
 
@@ -753,10 +752,12 @@ def test_bf16_attention_at_head_width_128_with_a_chip_full_of_key_blocks(ctx, or
 
 
 # the order of a causal launch's blocks: by rank over all problems, with eight of them and one to either side, and numbers that eight does
-# not divide; problem groups where fewer than eight are, or more than an L2 holds (at width 128 from 65536 rows of keys on, which
-# 1008 problems of 65 stay below)
+# not divide; problem groups where fewer than eight are (7 of 16 blocks: groups of 4 and 3, in dK/dV of 2 and a last one of 1), or more than
+# an L2 holds (at width 128 from 65536 rows of keys on, which 1008 problems of 65 stay below; 254 of 3 blocks: groups of 22 and a last one
+# of 12, in dK/dV of 11 and a last one of 1)
 @pytest.mark.parametrize("hd", [64, 128])
-@pytest.mark.parametrize("B,T,H", [(1, 260, 7), (2, 200, 4), (3, 200, 3), (11, 140, 3), (1, 513, 13), (63, 65, 16), (64, 65, 16)])
+@pytest.mark.parametrize("B,T,H", [(1, 260, 7), (2, 200, 4), (3, 200, 3), (11, 140, 3), (1, 513, 13), (63, 65, 16), (64, 65, 16), (1, 1000, 7),
+                                   (127, 260, 2)])
 def test_bf16_causal_attention_block_orders(ctx, orc, B, T, H, hd):
     _mha_case(ctx, orc, True, B, T, T, H, hd, causal=True, packed_kv=True)
 
@@ -790,9 +791,10 @@ def test_bf16_attention_at_head_width_64_with_one_tile_of_queries(ctx, orc, B, T
 
 # dK/dV where two waves share 32 keys, with keys that no query attends to (an infinite key): all of a wave's, some of it, all but one
 # of a block's.  The gradients of the finite keys are what these alone give.
+@pytest.mark.parametrize("hd", [64, 128])
 @pytest.mark.parametrize("off", [range(32), range(40, 50), range(127), range(100, 150), range(1, 150)])
-def test_bf16_attention_gradients_beside_keys_at_minus_infinity(ctx, orc, off):
-    B, Tq, Tk, hd = 70, 70, 150, 128
+def test_bf16_attention_gradients_beside_keys_at_minus_infinity(ctx, orc, off, hd):
+    B, Tq, Tk = 70, 70, 150
     q, k, v, g = (_rand(s, (B * t, hd)) for s, t in ((81, Tq), (82, Tk), (83, Tk), (84, Tq)))
     q[:, 0], gone = 1.0, np.zeros(Tk, bool)
     gone[list(off)] = True
@@ -1010,11 +1012,13 @@ def test_bf16_attention_passes_infinite_values_on(ctx, T, hd, packed):
         assert_close(got[:, rest], ref[:, rest], 1.5e-2)
 
 
-# the same where two waves share 32 keys in dK/dV: queries that end inside a tile, in its first half and in its second
+# the same on more than 128 blocks of keys (where two waves of eight share 32 keys in dK/dV: all but causal calls of width 64): queries that
+# end inside a tile, in its first half and in its second
+@pytest.mark.parametrize("hd", [64, 128])
 @pytest.mark.parametrize("T", [70, 100])
 @pytest.mark.parametrize("packed", [True, False])
-def test_bf16_attention_of_many_blocks_passes_infinite_values_on(ctx, T, packed):
-    B, hd = 130, 128
+def test_bf16_attention_of_many_blocks_passes_infinite_values_on(ctx, T, packed, hd):
+    B = 130
     q, k, v, g = (_rand(s, (T, hd)) for s in (91, 92, 93, 94))
     v[T - 1, 3], g[T - 1, 5] = np.inf, -np.inf
     qkv, qkvv = dev_act(np.tile(np.concatenate([q, k, v], 1), (B, 1)), True)
@@ -1036,9 +1040,10 @@ def test_bf16_attention_of_many_blocks_passes_infinite_values_on(ctx, T, packed)
     assert_close(got[:, rest], ref[:, rest], 1.5e-2)
 
 
-# the widest rows that 32-bit offsets into tiles of 128 keys take, with a chip full of key blocks at head width 128
-def test_bf16_attention_with_the_widest_rows_of_many_key_blocks(ctx, orc):
-    Tq, Tk, H, hd, ld = 66, 130, 65, 128, 1 << 24
+# the widest rows that 32-bit offsets into tiles of 128 keys take, with a chip full of key blocks
+@pytest.mark.parametrize("hd", [64, 128])
+def test_bf16_attention_with_the_widest_rows_of_many_key_blocks(ctx, orc, hd):
+    Tq, Tk, H, ld = 66, 130, 65, 1 << 24
     d = H * hd
 
     def far(x):
