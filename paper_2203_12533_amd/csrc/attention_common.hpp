@@ -40,7 +40,8 @@ __device__ __forceinline__ int causal_group(int n_inner, int resident) { return 
 // 48; 8 x 2048, 16 of 64, 97.5 / 298.5 -> 89.3 / 276; 8 x 700, 8 of 128, 24.0 / 70 -> 21.0 / 57; 3 x 1024, 16 of 128, 30.4 / 82.5 -> 27.6 / 74.7).
 // `stream`: bytes that the blocks of a problem read from its other side.  At width 128 they have to fit an XCD's L2 of 4 MiB for all its
 // problems together, which are in flight at the same time (8 x 1024, 16 heads, 8 MiB: 51 / 163 -> 54.6 / 168; 4 x 1024, 4 MiB: 30.8 / 85.8 -> 30.6 /
-// 87.6).  Fewer problems than XCDs leave most of them without one of their own (1 x 1500, 3 heads of 64, forward 15.3 -> 15.5).
+// 87.6).  At width 64 this order is ahead at every length (8 x 4096, 16 heads, 16 MiB: 344 / 1100 -> 324 / 1037; 1 x 8192, 16 heads 211 / 561 ->
+// 172 / 523; 1 x 16384, 16 heads, 8 MiB 693 / 1971 -> 600 / 1899).  Fewer problems than XCDs leave most of them without one of their own (1 x 1500, 3 heads of 64, forward 15.3 -> 15.5).
 template <int HD>
 __device__ __forceinline__ void causal_block_map(int pid, int nblk, int n_inner, int64_t stream, int resident, int& problem, int& inner) {
   const int problems = nblk / n_inner;

@@ -25,12 +25,13 @@
 // values 3.4e-6).  In the backward two values do, 2^-17 of P and dS left out: dQ, dK and dV are stored in 8 bits, and their
 // errors against 64 bits are those of the fp32 kernels to four digits (1.66e-3), also where keys and values share a component
 // 64 times their spread.  Measured (us, forward and backward): 4 x 333 queries over 520 keys, 8 heads: 116 on the fp32
-// matrix pipe -> 54; 2 x 2014 over 1092, 9 heads: 189.  The forward's third value: 10.3 -> 11.2 there, 8 x 700, 16 heads 40 -> 45.
-// Packed causal, 4 x 1000, 12 heads: 131 with tiles staged through registers and a transposed copy in LDS -> 86.
+// matrix pipe -> 37; 2 x 2014 over 1092, 9 heads: 132.  The forward's third value: 10.3 -> 11.2 of the first, 8 x 700, 16 heads 40 -> 45.
+// Packed causal, 4 x 1000, 12 heads: 131 with tiles staged through registers and a transposed copy in LDS -> 65.
 // PARTS = 2, for few blocks: a wave alone takes 1.2 to 1.5 us per step whatever else the chip does (products, softmax and
 // barrier one behind the other), so a launch that leaves units idle, or whose causal mask gives one block twice the average,
 // lasts as long as its longest chain of steps.  Blocks of 64 rows then, two waves to 32 of them that take the halves of every
-// tile in turn and add up through LDS at the end: half the steps, in the same fp32 sums.  The two above: 54 -> 44, 86 -> 75.
+// tile in turn and add up through LDS at the end: half the steps, in the same fp32 sums.  The first above, whose dK/dV have too many
+// blocks for it: forward 16.9 -> 10.8, backward 29.8 -> 25.8; the causal one 19.1 -> 17.2, 49.5 -> 48.1.
 // Rows past the end of a sequence are fetched from a block of zeros; every use of such a row is masked or multiplied by an
 // exact zero (P = exp2(-inf)).
 // Values that are not finite.  A masked pair enters the second products with a probability of zero, and zero times infinity
@@ -938,9 +939,9 @@ __global__ __launch_bounds__(kNT, ALONE ? 1 : 2) void attn_dkv_dma_kernel(MhaDev
 }
 
 // ===================================================================================================
-// dK, dV for more than 128 blocks of 128 keys at head_dim 128 (more than one tile of queries) and, unmasked, at 64: 8 waves, two to a SIMD, each pair
-// with the same 32 keys; of every tile of 64 queries one wave takes the first 32, the other the rest, and their sums meet in LDS
-// at the end (in a fixed order).
+// dK, dV for more than 128 blocks of 128 keys, at head_dim 128 and, unmasked, at 64 (but for a single tile of queries: bwd_dma): 8 waves,
+// two to a SIMD, each pair with the same 32 keys; of every tile of 64 queries one wave takes the first 32, the other the rest, and
+// their sums meet in LDS at the end (in a fixed order).
 // What bounds the kernel above is that a SIMD has one wave: products, exponentials and LDS round trips of a block follow one
 // another (3200 clocks for 1024 of matrix work).  A second wave needs each of them within 256 registers: K and V stay in LDS
 // next to a ring of two tiles (129 KiB, one workgroup per compute unit) instead of in 64 registers, the addresses of LDS
@@ -949,7 +950,8 @@ __global__ __launch_bounds__(kNT, ALONE ? 1 : 2) void attn_dkv_dma_kernel(MhaDev
 // half the reads), halves of a pair one phase apart, and V in registers were all slower or the same, wave priorities no different.
 // What bounds it: no unit is full (causal 8 x 1024, 16 heads, counters: matrix pipe 28 % of the time, before 24 %; LDS reads 28 %, no
 // conflicts; vector issue 31 % of a SIMD); a wave waits on counters 37 % and to issue 32 % of its time, the barrier per tile keeps both
-// waves of a SIMD in the same phase.
+// waves of a SIMD in the same phase.  At width 64 (65 KiB, 175 registers; 4 x 333 over 520, 8 heads) the matrix pipe is busy 10 % and a wave
+// waits on counters 38 %: six tiles between a prologue and the meeting of the sums.
 // Measured (us, this kernel alone, kernel traces, before / now): in train steps causal 8 x 1024, 16 heads 123 / 101, 2 x 1024, 32 heads
 // 97.8 / 79.2, unmasked 8 x 1024, 16 heads 179 / 153; by itself causal 2 x 1024, 16 heads 41.0 / 33.2, 16 x 128, 16 heads 16.4 / 14.6.
 // Forward and backward: causal 4 x 1000, 8 heads 89.1 / 84.3; 8 x 300, 12 heads 59.8 / 58.1; 4 x 333 queries over 520 keys, 16 heads
@@ -1172,8 +1174,9 @@ template <int PARTS> static int blocks_of(int rows, const MhaArgs& a) { return (
 //     384 blocks: 448 36.2 / 39.4, 768 50.8 / 51.6, 1024 62.2 / 55.1; 512 blocks: 768 51.5 / 60.3, 1024 61.8 / 61.1.  T x 128: 64 15.4 / 17.9, 128
 //     blocks: 128 23.4 / 21.1, 1024 69 / 48.
 //   dQ alone: causal 2 x 1024, 16 x 128 (256) 70.6 / 66.0; unmasked 1 x 1000 over 2000, 16 x 128 (128) 93 / 81, 4 x 700 over 500, 8 x 128 (192) 50.0 / 51.9.
-//   dK/dV alone: unmasked 1 x 2048 over 256, 16 x 128 (32) 83 / 60.6, 4 x 333 over 520, 8 x 64 (160) 37.9 / 39.8.  At head_dim 128 the other
-//   side of the 128 blocks is attn_dkv_pair_kernel, see bwd_dma.
+//   dK/dV alone: unmasked 1 x 2048 over 256, 16 x 128 (32) 83 / 60.6.  At head_dim 128, and unmasked at 64, the other side of the 128
+//   blocks is attn_dkv_pair_kernel, see bwd_dma.
+// (Forward and dQ have since lost 0.5 to 5 us in front of their loops, with one wave and with two.)
 // most: the largest number of blocks, for rows whose other side is at least `from` long (where it is shorter, 128; under the
 // causal mask 256 between 384 and `from`, none up to 64: one tile has no halves worth sharing).
 static bool two_parts(const MhaArgs& a, int rows, int other, int from, int most) {
@@ -1222,7 +1225,7 @@ static hipError_t bwd_dma(hipStream_t s, const MhaArgs& a, const MhaGrads& g) {
   // 40.3 / 33.4; 2 x 2014 over 1092, 9 heads, 162 blocks 65.7 / 49.6.  One tile of queries loses where a second round of workgroups of eight waves starts, past
   // 256 blocks (backward, registers of one workgroup of two / pairs: 70 x 1 over 100, 4 heads, 280 blocks 18.2 / 21.0, 64 queries 18.9 / 22.0, 65 25.1 / 24.7; 16
   // x 33 over 500, 8 heads, 512 blocks 24.0 / 25.5; 5 x 33 over 500, 8 heads, 160 blocks 17.3 / 17.4, 1 query 17.2 / 16.8).  Two parts up to 128
-  // blocks: 1 x 700, 6 heads 16.7 / 19.8; 4 x 600 over 60, 12 heads 15.5 / 17.7.  Packed causal pairs gain and lose: 1 x 2048, 16 heads 37.5 / 35.1, 8 x
+  // blocks (those / pairs): 1 x 700, 6 heads 16.7 / 19.8; 4 x 600 over 60, 12 heads 15.5 / 17.7.  Packed causal pairs gain and lose: 1 x 2048, 16 heads 37.5 / 35.1, 8 x
   // 1024 52.9 / 56.3, 4 x 1000, 12 heads 26.8 / 27.1.
   // Two parts of width 64, registers of one workgroup of two on a unit / of both: 1 x 700, 6 heads, unmasked 27.0 / 17.8; 4 x 600 over 60, 12 heads
   // 25.5 / 16.4; causal with split dS (25 registers spill) 1 x 2048, 8 heads 47.8 / 42.4, 8 x 300, 4 heads 12.3 / 11.4, 1 x 1024, 16 heads 27.6 / 24.5;

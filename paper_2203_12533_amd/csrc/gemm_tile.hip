@@ -389,8 +389,10 @@ __global__ __launch_bounds__(S::kThreads, S::kWavesPerSimd) void gemm_tile_kerne
   constexpr int kAhead = S::DEEP ? NS + 1 : NS;   // tile i loads tile i + kAhead
   // Two groups of several waves: one of them reads its operand tiles from LDS while the other multiplies.  In step, LDS and matrix
   // pipe take turns (us, 128 x 128 tiles, four waves alone / two groups in step / half a tile apart, profiles of one launch: the main
-  // loop of 1000 x 3072 x 768 5.3 / 5.5 / 4.2, of 2048 x 2048 x 2048 13.8 / 14.3 / 11.6).  Apart, the LDS bounds it: 96 KiB in
-  // and out of it per 128 x 128 x 64, 0.32 us at 2.4 GHz, take 0.36.  Each group passes as many barriers as the other.
+  // loop of 1000 x 3072 x 768 5.3 / 5.5 / 4.2, of 2048 x 2048 x 2048 13.8 / 14.3 / 11.6).  Apart, no unit is full: in 2048 x 2048 products
+  // with k from 2048 to 6144, row-major, the matrix pipe is busy 34 % of a launch, LDS reads of the waves 18 %, and a wave waits to issue
+  // 45 % of its time and on counters 39 % (with a transposing read and its spills 26, 14, 46 and 41 %).  Each group passes as many
+  // barriers as the other.
   // The half tile at either end has to be earned back: two pairs of waves need 13 k tiles (128 x 64 tiles, in step / apart: 1280 x 1280 x
   // 256 6.7 / 6.9, 768 9.2 / 9.2, 1536 13.1 / 12.4; 1024 x 1536 x 832 8.9 / 8.8, 960 9.6 / 9.2), two groups of four waves none
   // (1536 x 1536 x 256, row-major, 7.1 / 7.0, 768 10.4 / 9.6).
